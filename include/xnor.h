@@ -325,6 +325,25 @@ int xnor_conv2d_fp32_fwd(const float *I, const float *Wt, const xnor_shape *s, f
 int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape *s, float *out, int algo,
                               void *stream);
 
+/*
+ * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
+ * both operands split exactly into three bf16 terms and the six products of them that reach the last
+ * bit of an fp32 product summed in fp32 by the bf16 matrix instruction.  Results are as close to the
+ * exact sum as those of the fp32 matrix instruction; infinities and NaN come out as fp32 arithmetic
+ * gives them, and an output so small that values below the bf16 instruction's normal range could
+ * matter to it is formed by the plain fp32 sum.
+ *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
+ *              call writes the split filters into it, its contents mean nothing afterwards.
+ * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes
+ * bytes are given, else what xnor_conv2d_fp32_fwd takes.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_UNSUPPORTED for
+ * kh*kw > 49 or a window whose input rows exceed 512 staged positions, XNOR_E_WORKSPACE for a workspace
+ * that is missing or too small.  Other values as in xnor_conv2d_fp32_fwd_algo.
+ *   xnor_conv2d_fp32_workspace_bytes   host only; 0 where no workspace would be used by XNOR_ALGO_AUTO.
+ */
+int xnor_conv2d_fp32_workspace_bytes(const xnor_shape *s, size_t *bytes);
+int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,
+                            size_t workspace_bytes, int algo, void *stream);
+
 /* Same as xnor_conv2d_fwd, with the kernel chosen by the caller (tests and measurements run every
  * variant).  Returns XNOR_E_UNSUPPORTED if `algo` cannot run this shape, XNOR_E_WORKSPACE if it
  * needs more workspace than given; XNOR_ALGO_DIRECT runs every shape without workspace. */

@@ -106,6 +106,8 @@ def _load() -> ctypes.CDLL:
     L.xnor_bwn_conv2d_fwd_algo.argtypes = [vp, vp, vp, sp, vp, ci, vp]
     L.xnor_conv2d_fp32_fwd.argtypes = [vp, vp, sp, vp, vp]
     L.xnor_conv2d_fp32_fwd_algo.argtypes = [vp, vp, sp, vp, ci, vp]
+    L.xnor_conv2d_fp32_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
+    L.xnor_conv2d_fp32_fwd_ws.argtypes = [vp, vp, sp, vp, vp, sz, ci, vp]
     L.xnor_conv2d_pick_algo.argtypes = [sp, sz]
     L.xnor_bwn_pick_algo.argtypes = [sp]
     L.xnor_bwn_split_plan.argtypes = [sp, ci, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(sz),
@@ -120,7 +122,8 @@ def _load() -> ctypes.CDLL:
                  "xnor_bwn_conv2d_fwd", "xnor_bwn_conv2d_fwd_algo",
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
-                 "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo"):
+                 "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
+                 "xnor_conv2d_fp32_workspace_bytes"):
         getattr(L, name).restype = ci
     return L
 
@@ -464,16 +467,34 @@ def xnor_bwn_conv2d_fwd(I: torch.Tensor, Wpk: torch.Tensor, alpha: torch.Tensor,
     return out
 
 
+def xnor_conv2d_fp32_workspace_bytes(s: Shape) -> int:
+    nbytes = s.__dict__.get("_fp32_ws")     # asked on every call: remembered per Shape
+    if nbytes is None:
+        n = ctypes.c_size_t()
+        _ok(lib.xnor_conv2d_fp32_workspace_bytes(ctypes.byref(s.c()), ctypes.byref(n)), "xnor_conv2d_fp32_workspace_bytes")
+        nbytes = n.value
+        object.__setattr__(s, "_fp32_ws", nbytes)
+    return nbytes
+
+
 def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch.Tensor | None = None,
-                         algo: int = ALGO_AUTO) -> torch.Tensor:
-    """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out."""
+                         algo: int = ALGO_AUTO, workspace: torch.Tensor | None | str = "auto") -> torch.Tensor:
+    """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out.
+
+    ``workspace``: a uint8 GPU tensor, None (run a kernel that needs none), or "auto" (allocate what
+    xnor_conv2d_fp32_workspace_bytes asks for, where the algorithm uses one)."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
         out = torch.empty(oshape, dtype=torch.float32, device=I.device)
-    _ok(lib.xnor_conv2d_fp32_fwd_algo(
+    if isinstance(workspace, str):
+        nbytes = xnor_conv2d_fp32_workspace_bytes(s) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
+        workspace = torch.empty((nbytes,), dtype=torch.uint8, device=I.device) if nbytes else None
+    _ok(lib.xnor_conv2d_fp32_fwd_ws(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
-        ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"), algo, _stream()),
+        ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),
+        _dev(workspace, torch.uint8, name="workspace") if workspace is not None else None,
+        workspace.numel() if workspace is not None else 0, algo, _stream()),
         f"xnor_conv2d_fp32_fwd[{ALGO_NAMES.get(algo, algo)}]")
     return out
 

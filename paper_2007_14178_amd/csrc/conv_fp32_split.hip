@@ -1,0 +1,696 @@
+// Real-valued fp32 convolution (the float comparison of Sec. IV, Table I) on the bf16 matrix
+// instruction.  Both operands are split into three bf16 terms, x = hi + mid + lo, each the nearest
+// bf16 to what the terms before it left over (3 x 8 significand bits hold all 24 of an fp32, both
+// differences are exact), and six of the nine products are summed in fp32:
+//     x*w ~ hi*hi + hi*mid + mid*hi + mid*mid + hi*lo + lo*hi.
+// The three left out are below 2^-25 of |x*w| and of either sign, less than the rounding of the
+// product to fp32.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each) do the work of eight
+// v_mfma_f32_32x32x2_f32 (64 cycles each), and the accumulator is rounded six times per sixteen
+// channels instead of eight: measured against 64-bit sums the result is no further off (see the
+// dispatch rule in xnor_api.hip for both kernels' figures).
+//
+//   split_filters_kernel: filters -> the A operands of the convolution in its order, into the
+//   caller's workspace, 6 bytes per weight: [filter tile of 32][chunk of 16 channels][tap][term]
+//   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7).
+//   conv_fp32_split_kernel: workgroup = 4 waves = 128 filters x up to 6 tiles of 32 output pixels of
+//   one image (64 filters x up to 12 tiles for layers of at most 64 filters); wave = 64 filters x up
+//   to three tiles.  Per chunk of 16 channels the input under the pixels is fetched a chunk ahead,
+//   split and staged in LDS as [position][term][16 channels] (112 bytes a position: sixteen lanes'
+//   16-byte reads at consecutive positions touch distinct banks), zero outside the image; a B
+//   operand is one 16-byte LDS read per lane and feeds four matrix instructions on average, an A operand is
+//   one 16-byte load per lane from the L2, a tap ahead, and feeds six.
+//
+// FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
+// chains, a long chain of matrix instructions would be the less exact of the two.  This form keeps two
+// accumulators per output: the matrix instructions sum four taps of a chunk (24 instructions), then that
+// sum is added to the other accumulator and what the addition rounded off is where the next four taps
+// start from.
+//
+// What the bf16 instruction does differently from the fp32 one is put right at the end: an output
+// that came out infinite or NaN (an input that is not finite, a term that overflowed, or a sum that
+// really does) is computed again by the plain fp32 sum, and so is one that is so small that terms
+// flushed to zero below 2^-126 could matter to it (only where an input or weight below 2^-50 was
+// seen, see `doubtful`).
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+#include "xnor_internal.hpp"
+
+namespace xnor {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kThreads = 256;
+constexpr int kChan = 16;              // channels per chunk = the reduction length of one matrix instruction
+constexpr int kPosBytes = 112;         // 3 terms x 32 bytes + 16: see above
+// granules (8 channels of one position) a thread fetches ahead per chunk; pixel tiles per wave.  The form
+// with short chains (see FLUSH) holds two accumulators per output and has fewer registers for both.
+constexpr int gran(bool flush) { return flush ? 3 : 4; }
+constexpr int wave_tiles(bool flush) { return flush ? 2 : 3; }
+constexpr int max_pos(bool flush) { return gran(flush) * 128; }   // staged positions of a workgroup
+constexpr int kFlushTaps = 4;
+constexpr int kMaxTaps = 49;           // 7 x 7; the filter pass holds 32 x 8 channels x taps in LDS
+constexpr int kOperandBytes = 3 * 1024;   // the three A operands of a (filter tile, chunk, tap)
+constexpr size_t kLdsShared = 80 * 1024;  // two workgroups per compute unit
+
+struct Fp32SplitParams {
+    const float *I;
+    const float *Wt;
+    const unsigned char *Wx;       // split filters, then one word per (filter tile, 8 channels): kTinyBit | max
+    float *out;
+    int N, C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW;
+    int nchunks, ftiles;
+    int fwaves;                    // waves along the filters: 2 or 1 (64 filters each)
+    int fgroups, groups;           // workgroups along the filters, along the pixels of an image
+    int tiles;                     // pixel tiles per workgroup (tw == 0), or tx * ty
+    int tw;                        // 0: a tile is 32 consecutive pixels; else tiles of tw x 32 / tw pixels
+    int tx, ty, gx;                // tw > 0: tiles of a workgroup along x and y, workgroups along x
+    int pitch, npos;               // staged positions per row, in all
+    uint32_t inv_pitch;
+};
+
+constexpr uint32_t kTinyBit = 0x80000000u;
+constexpr float kTiny = 8.8817841970012523e-16f;          // 2^-50
+constexpr float kDoubt = 2.5243548967072378e-29f;         // 2^-95
+
+__device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
+uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
+
+// two fp32 -> two bf16 in one dword, to nearest even (one v_cvt_pk_bf16_f32)
+__device__ inline uint32_t pack_bf16(float a, float b)
+{
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// what the bf16 pair `t` leaves of (a, b); exact
+__device__ inline void subtract_pair(float &a, float &b, uint32_t t)
+{
+    a -= __uint_as_float(t << 16);
+    b -= __uint_as_float(t & 0xffff0000u);
+}
+
+// 32 filters x 8 channels x all taps per workgroup: a coalesced read into LDS (a filter's channels are
+// one run in memory), then per (tap, filter) eight values from LDS, split, and three 16-byte writes of
+// 32 lanes side by side.  HBM-bound: 4 bytes read and 6 written per weight.
+__global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__restrict__ Wt, int F, int C, int taps,
+                                                                 int nchunks, int ftiles, unsigned char *__restrict__ Wx)
+{
+    extern __shared__ float wl[];
+    __shared__ uint32_t stat[2];
+    const int octs = 2 * nchunks;
+    const int ft = blockIdx.x / octs, oc = blockIdx.x - ft * octs;
+    const int run = 8 * taps, pitch = run | 1;                     // (odd: filters fall into distinct banks)
+    const int live = max(0, min(8, C - 8 * oc)) * taps;            // values of the run that exist
+    if (threadIdx.x < 2) stat[threadIdx.x] = threadIdx.x ? 0xffffffffu : 0u;
+    __syncthreads();
+    uint32_t top = 0, low = 0xffffffffu;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int f = wave; f < 32; f += kThreads / 64) {
+        const int fg = 32 * ft + f;
+        const float *src = Wt + ((size_t)min(fg, F - 1) * C + 8 * oc) * taps;
+        for (int i = lane; i < run; i += 64) {
+            const float v = fg < F && i < live ? src[i] : 0.f;
+            wl[f * pitch + i] = v;
+            const uint32_t twice = __float_as_uint(v) << 1;        // magnitude; 0 - 1 wraps to the top
+            top = max(top, twice);
+            low = min(low, twice - 1u);
+        }
+    }
+    atomicMax(&stat[0], top);
+    atomicMin(&stat[1], low);
+    __syncthreads();
+    unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * kOperandBytes + (oc & 1) * 512;
+    for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
+        const int f = i & 31, t = i >> 5;
+        uint32_t h[4], m[4], l[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float a = wl[f * pitch + (2 * k) * taps + t], b = wl[f * pitch + (2 * k + 1) * taps + t];
+            h[k] = pack_bf16(a, b);
+            subtract_pair(a, b, h[k]);
+            m[k] = pack_bf16(a, b);
+            subtract_pair(a, b, m[k]);
+            l[k] = pack_bf16(a, b);
+        }
+        uint4 *o = reinterpret_cast<uint4 *>(dst + (size_t)t * kOperandBytes + f * 16);
+        o[0] = make_uint4(h[0], h[1], h[2], h[3]);
+        o[64] = make_uint4(m[0], m[1], m[2], m[3]);
+        o[128] = make_uint4(l[0], l[1], l[2], l[3]);
+    }
+    if (threadIdx.x == 0) {
+        uint32_t *stats = reinterpret_cast<uint32_t *>(Wx + (size_t)ftiles * nchunks * taps * kOperandBytes);
+        stats[blockIdx.x] = (stat[0] >> 1) | (stat[1] < (__float_as_uint(kTiny) << 1) - 1u ? kTinyBit : 0u);
+    }
+}
+
+// One output by the plain sum: fp32 products, per tap over the channels, then over the taps.
+__device__ float plain_output(const Fp32SplitParams &p, int n, int f, int oy, int ox)
+{
+    const size_t HW = (size_t)p.H * p.W;
+    const int taps = p.kh * p.kw;
+    const float *img = p.I + (size_t)n * p.C * HW;
+    const float *flt = p.Wt + (size_t)f * p.C * taps;
+    float acc = 0.f;
+    for (int t = 0; t < taps; ++t) {
+        const int ky = t / p.kw, iy = oy * p.sh - p.ph + ky, ix = ox * p.sw - p.pw + t - ky * p.kw;
+        if ((unsigned)iy >= (unsigned)p.H || (unsigned)ix >= (unsigned)p.W) continue;
+        const float *src = img + (size_t)iy * p.W + ix;
+        float tap = 0.f;
+        for (int c0 = 0; c0 < p.C; c0 += 32) {
+            const int cn = min(32, p.C - c0);
+            float part = 0.f;
+            for (int j = 0; j < cn; ++j) part += src[(size_t)(c0 + j) * HW] * flt[(size_t)(c0 + j) * taps + t];
+            tap += part;
+        }
+        acc += tap;
+    }
+    return acc;
+}
+
+// The work of one wave with NT pixel tiles (0: it only takes part in the staging).  X0, Y0: the output
+// pixel of the workgroup's first tile (tw > 0); ix0, iy0: the input position of the staged block's corner.
+template <int NT, bool FLUSH>
+__device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams &p, int n, int f0, int t0, int X0, int Y0,
+                                                          int oy0, int iy0, int ix0, int rows, int tile0)
+{
+    // LDS: two input buffers, taken in turn by the chunks, each [npos][3][16] bf16 at a 112-byte pitch
+    extern __shared__ unsigned char lds_raw[];
+    const int tile_bytes = p.npos * kPosBytes;
+    const int lane = threadIdx.x & 63;
+    const int col = lane & 31, half = lane >> 5;
+    const int OHW = p.OH * p.OW;
+    const int taps = p.kh * p.kw;
+    const int HW = p.H * p.W;
+    // the pixel of lane `col` in tile j of the workgroup (clamped to the image for the reads) and
+    // whether it exists
+    const int tw_shift = p.tw ? 31 - __builtin_clz((unsigned)p.tw) : 5;
+    auto pixel_of = [&](int j, int &oy, int &ox) -> bool {
+        if (p.tw == 0) {
+            const int px = (t0 + j) * 32 + col, pxc = min(px, OHW - 1);
+            oy = pxc / p.OW;
+            ox = pxc - oy * p.OW;
+            return px < OHW;
+        }
+        const int jy = j / p.tx, jx = j - jy * p.tx;
+        oy = Y0 + jy * (32 >> tw_shift) + (col >> tw_shift);
+        ox = X0 + jx * p.tw + (col & (p.tw - 1));
+        const bool in = oy < p.OH && ox < p.OW;
+        oy = min(oy, p.OH - 1);
+        ox = min(ox, p.OW - 1);
+        return in;
+    };
+    int base[NT > 0 ? NT : 1];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int oy, ox;
+        pixel_of(tile0 + j, oy, ox);
+        base[j] = ((oy - oy0) * p.sh * p.pitch + (ox * p.sw - p.pw - ix0)) * kPosBytes + half * 16;
+    }
+
+    floatx16 acc[2][NT > 0 ? NT : 1], sum[2][FLUSH && NT > 0 ? NT : 1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[i][j][r] = 0.f;
+                if (FLUSH) sum[i][j][r] = 0.f;
+            }
+    int chain = kFlushTaps;                      // taps until the next flush
+    auto flush = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float s = sum[i][j][r] + acc[i][j][r];
+                    acc[i][j][r] -= s - sum[i][j][r];
+                    sum[i][j][r] = s;
+                }
+    };
+    constexpr int kGran = gran(FLUSH);
+
+    const float *img = p.I + (size_t)n * p.C * HW;
+
+    // Staging.  A granule is eight channels of one staged position: thread t takes the positions
+    // q * 128 + t % 128 (q < kGran) of channel octet t / 128, the same for a whole wave, so the address
+    // of a value is a scalar base (the channel's plane) plus a lane offset kept in registers.  A
+    // position past the last one repeats the last one (the same bytes to the same place), one outside
+    // the image loads offset 0 and becomes zero at the commit: no branch, and nothing waits for a
+    // load before the next is issued.
+    const int tl = threadIdx.x & 127;
+    const int oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);
+    uint32_t voff[kGran];
+    int wr_off[kGran];
+    uint32_t okbits = 0;
+#pragma unroll
+    for (int q = 0; q < kGran; ++q) {
+        const int pos = min(q * 128 + tl, p.npos - 1);
+        wr_off[q] = pos * kPosBytes + oct * 16;
+        const uint32_t r = quot((uint32_t)pos, p.inv_pitch);
+        const int xw = (int)((uint32_t)pos - r * (uint32_t)p.pitch);
+        const int iy = iy0 + (int)r, ix = ix0 + xw;
+        const bool ok = (int)r < rows && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
+        voff[q] = ok ? (uint32_t)(iy * p.W + ix) * 4u : 0u;
+        okbits |= ok ? 1u << q : 0u;
+    }
+    float nxt[kGran][8];
+    auto prefetch = [&](int ch) __attribute__((always_inline)) {
+        const int c0 = ch * kChan + 8 * oct;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int c = c0 + k < p.C ? c0 + k : 0;                             // (scalar)
+            const char *plane_c = reinterpret_cast<const char *>(img + (size_t)c * HW);
+#pragma unroll
+            for (int q = 0; q < kGran; ++q) {
+                nxt[q][k] = *reinterpret_cast<const float *>(plane_c + voff[q]);
+            }
+        }
+    };
+    // The commit of chunk `ch` into buffer ch % 2 comes in pieces, each laid among the matrix
+    // instructions of one step of the chunk before, in units small enough to fit behind one
+    // instruction: piece s < 2 * kGran splits and writes one half (four channels) of granule s / 2, the
+    // last one issues the loads of chunk ch + 1 into the registers just freed.
+    constexpr int kPieces = 2 * kGran + 1;
+    float pv[4];
+    uint32_t ph[2], pm[2], pl[2];
+    uint32_t xtop = 0, xlow = 0xffffffffu;     // largest and smallest non-zero magnitude seen (doubled bits, less one)
+    auto commit_unit = [&](auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
+        constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
+        if constexpr (S < 2 * kGran) {
+            constexpr int q = S >> 1, hf = S & 1;
+            if constexpr (U == 0 || U == 3) {
+                constexpr int k = U ? 2 : 0;
+                const int c0 = ch * kChan + 8 * oct + 4 * hf + k;
+                const bool ok = (okbits >> q) & 1u;
+                pv[k] = (ok && c0 < p.C) ? nxt[q][4 * hf + k] : 0.f;
+                pv[k + 1] = (ok && c0 + 1 < p.C) ? nxt[q][4 * hf + k + 1] : 0.f;
+                const uint32_t a = __float_as_uint(pv[k]) << 1, b = __float_as_uint(pv[k + 1]) << 1;
+                xtop = max(max(xtop, a), b);
+                xlow = min(min(xlow, a - 1u), b - 1u);
+            } else if constexpr (U == 1 || U == 4) {
+                constexpr int e = U == 4;
+                ph[e] = pack_bf16(pv[2 * e], pv[2 * e + 1]);
+                subtract_pair(pv[2 * e], pv[2 * e + 1], ph[e]);
+            } else if constexpr (U == 2 || U == 5) {
+                constexpr int e = U == 5;
+                pm[e] = pack_bf16(pv[2 * e], pv[2 * e + 1]);
+                subtract_pair(pv[2 * e], pv[2 * e + 1], pm[e]);
+                pl[e] = pack_bf16(pv[2 * e], pv[2 * e + 1]);
+            } else if constexpr (U == 6) {
+                uint2 *dst = reinterpret_cast<uint2 *>(lds_raw + (ch & 1) * tile_bytes + wr_off[q] + hf * 8);
+                dst[0] = make_uint2(ph[0], ph[1]);
+                dst[4] = make_uint2(pm[0], pm[1]);
+                dst[8] = make_uint2(pl[0], pl[1]);
+            }
+        } else if constexpr (U == 0) {
+            if (ch + 1 < p.nchunks) prefetch(ch + 1);
+        }
+    };
+    auto commit_piece = [&](auto piece_c, int ch) __attribute__((always_inline)) {
+        commit_unit(piece_c, std::integral_constant<int, 0>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 1>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 2>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 3>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 4>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 5>{}, ch);
+        commit_unit(piece_c, std::integral_constant<int, 6>{}, ch);
+    };
+    // pieces `from` .. kPieces - 1 of chunk ch, one after the other (granules without a position of their own: none)
+    auto commit_rest = [&](int from, int ch) __attribute__((always_inline)) {
+        if (from <= 0) commit_piece(std::integral_constant<int, 0>{}, ch);
+        if (from <= 1) commit_piece(std::integral_constant<int, 1>{}, ch);
+        if (from <= 2 && p.npos > 128) commit_piece(std::integral_constant<int, 2>{}, ch);
+        if (from <= 3 && p.npos > 128) commit_piece(std::integral_constant<int, 3>{}, ch);
+        if (from <= 4 && p.npos > 256) commit_piece(std::integral_constant<int, 4>{}, ch);
+        if (from <= 5 && p.npos > 256) commit_piece(std::integral_constant<int, 5>{}, ch);
+        if constexpr (kGran > 3) {
+            if (from <= 6 && p.npos > 384) commit_piece(std::integral_constant<int, 6>{}, ch);
+            if (from <= 7 && p.npos > 384) commit_piece(std::integral_constant<int, 7>{}, ch);
+        }
+        if (from < kPieces) commit_piece(std::integral_constant<int, kPieces - 1>{}, ch);
+        static_assert(kPieces <= 9, "one line per piece");
+    };
+
+    // The A operands of both filter tiles walk linearly through the workspace, chunk by chunk and tap by
+    // tap; those of the next tap are loaded at the head of a tap.
+    const int ft0 = f0 >> 5, ft1 = min(ft0 + 1, p.ftiles - 1);
+    const size_t per_tile = (size_t)p.nchunks * taps * kOperandBytes;
+    const unsigned char *wx0 = p.Wx + ft0 * per_tile, *wx1 = p.Wx + ft1 * per_tile;
+    int steps_left = p.nchunks * taps - 1;       // taps still to be fetched
+    uint4 a[2][3], an[2][3];
+    auto load_next = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            an[0][t] = reinterpret_cast<const uint4 *>(wx0)[t * 64 + lane];
+            an[1][t] = reinterpret_cast<const uint4 *>(wx1)[t * 64 + lane];
+        }
+        const int d = steps_left > 0 ? kOperandBytes : 0;          // (the last one is fetched again, unused)
+        wx0 += d; wx1 += d; --steps_left;
+    };
+
+    prefetch(0);
+    if constexpr (NT > 0) load_next();
+    commit_rest(0, 0);
+    __syncthreads();
+    for (int ch = 0; ch < p.nchunks; ++ch) {
+        const bool more = ch + 1 < p.nchunks;
+        int pc = more ? 0 : kPieces;                     // the next piece of chunk ch + 1 to commit
+        if constexpr (NT > 0) {
+            // The flat sequence of (tap, pixel tile) steps, twelve matrix instructions each; a step's
+            // three B operands are read one step ahead, and the chunk's first steps carry one piece
+            // of the next chunk's commit each.
+            const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
+            auto read3 = [&](uint4 (&b)[3], int byte_off) __attribute__((always_inline)) {
+                const uint4 *src = reinterpret_cast<const uint4 *>(tile_r + byte_off);
+                b[0] = src[0];
+                b[1] = src[2];
+                b[2] = src[4];
+            };
+            const int row_step = (p.pitch - p.kw + 1) * kPosBytes;
+            int off = 0, kx = 0;                         // byte offset and window column of the current tap
+            uint4 bc[3], bn[3];
+            read3(bc, base[0]);
+            auto step = [&](auto piece_c, int j, int next_off) __attribute__((always_inline)) {
+                constexpr int S = decltype(piece_c)::value;
+                read3(bn, next_off);
+                __builtin_amdgcn_sched_barrier(0);
+                auto unit = [&](auto m_c) __attribute__((always_inline)) {
+                    constexpr int M = decltype(m_c)::value, P = M >> 1;
+                    // hi*hi, mid*hi, hi*mid, lo*hi, mid*mid, hi*lo
+                    constexpr int ta = P == 0 ? 0 : P == 1 ? 1 : P == 2 ? 0 : P == 3 ? 2 : P == 4 ? 1 : 0;
+                    constexpr int tb = P == 0 ? 0 : P == 1 ? 0 : P == 2 ? 1 : P == 3 ? 0 : P == 4 ? 1 : 2;
+                    acc[M & 1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, a[M & 1][ta]), __builtin_bit_cast(bf16x8, bc[tb]), acc[M & 1][j], 0, 0, 0);
+                    if constexpr (S >= 0) commit_unit(piece_c, m_c, ch + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                unit(std::integral_constant<int, 0>{});
+                unit(std::integral_constant<int, 1>{});
+                unit(std::integral_constant<int, 2>{});
+                unit(std::integral_constant<int, 3>{});
+                unit(std::integral_constant<int, 4>{});
+                unit(std::integral_constant<int, 5>{});
+                unit(std::integral_constant<int, 6>{});
+                unit(std::integral_constant<int, 7>{});
+                unit(std::integral_constant<int, 8>{});
+                unit(std::integral_constant<int, 9>{});
+                unit(std::integral_constant<int, 10>{});
+                unit(std::integral_constant<int, 11>{});
+#pragma unroll
+                for (int t = 0; t < 3; ++t) bc[t] = bn[t];
+            };
+            // one tap: its NT steps, the first of them with piece FIRST of the commit (-1: no pieces)
+            auto tap_body = [&](auto first_c, int tap) __attribute__((always_inline)) {
+                constexpr int FIRST = decltype(first_c)::value;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) { a[0][t] = an[0][t]; a[1][t] = an[1][t]; }
+                load_next();
+                const bool wrap = kx + 1 == p.kw, further = tap + 1 < taps;
+                const int off_n = further ? off + (wrap ? row_step : kPosBytes) : off;
+                kx = wrap ? 0 : kx + 1;
+                step(std::integral_constant<int, (FIRST >= 0 && FIRST < kPieces) ? FIRST : -1>{}, 0, NT > 1 ? base[NT > 1 ? 1 : 0] + off : base[0] + off_n);
+                if constexpr (NT > 1) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 1 < kPieces) ? FIRST + 1 : -1>{}, 1, NT > 2 ? base[NT > 2 ? 2 : 0] + off : base[0] + off_n);
+                if constexpr (NT > 2) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 2 < kPieces) ? FIRST + 2 : -1>{}, 2, base[0] + off_n);
+                static_assert(NT <= 3, "one line per step");
+                off = off_n;
+                if constexpr (FLUSH)
+                    if (--chain == 0) { flush(); chain = kFlushTaps; }
+            };
+            int tap = 0;
+            if (more) {
+                if (tap < taps) { tap_body(std::integral_constant<int, 0>{}, tap); ++tap; }
+                if constexpr (1 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 1 * NT>{}, tap); ++tap; }
+                if constexpr (2 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 2 * NT>{}, tap); ++tap; }
+                if constexpr (3 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 3 * NT>{}, tap); ++tap; }
+                if constexpr (4 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 4 * NT>{}, tap); ++tap; }
+                if constexpr (5 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 5 * NT>{}, tap); ++tap; }
+                if constexpr (6 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 6 * NT>{}, tap); ++tap; }
+                if constexpr (7 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 7 * NT>{}, tap); ++tap; }
+                if constexpr (8 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 8 * NT>{}, tap); ++tap; }
+                static_assert(kPieces <= 9, "one line per tap that carries pieces");
+                pc = min(tap * NT, kPieces);
+            }
+            for (; tap < taps; ++tap) tap_body(std::integral_constant<int, -1>{}, tap);
+        }
+        if (pc < kPieces) commit_rest(pc, ch + 1);       // what the chunk's steps did not carry
+        __syncthreads();                                 // chunk ch has been read, chunk ch + 1 is written
+    }
+
+    // Below which magnitude an output is doubtful.  A term below 2^-126 is flushed: with nothing staged
+    // or weighted below 2^-50 that takes a product below 2^-116, no concern.  Otherwise the flushed terms
+    // add up to at most 2^-125 * Nred * (max |x| + max |w| + 1), and an output of 2^30 times that is
+    // not touched by them.
+    uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (everything staged has been read)
+#pragma unroll
+    for (int s = 1; s < 64; s *= 2) {
+        xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, s));
+        xlow = min(xlow, (uint32_t)__shfl_xor((int)xlow, s));
+    }
+    if (lane == 0) { wgstat[2 * (threadIdx.x >> 6)] = xtop; wgstat[2 * (threadIdx.x >> 6) + 1] = xlow; }
+    __syncthreads();
+    if constexpr (NT == 0) return;
+    xtop = max(max(wgstat[0], wgstat[2]), max(wgstat[4], wgstat[6]));
+    xlow = min(min(wgstat[1], wgstat[3]), min(wgstat[5], wgstat[7]));
+    const uint32_t *stats = reinterpret_cast<const uint32_t *>(p.Wx + (size_t)p.ftiles * per_tile);
+    uint32_t wstat = 0, wtiny = 0;
+    for (int i = lane; i < 2 * p.nchunks; i += 64) {
+        const uint32_t s0 = stats[ft0 * 2 * p.nchunks + i], s1 = stats[ft1 * 2 * p.nchunks + i];
+        wstat = max(wstat, max(s0 & ~kTinyBit, s1 & ~kTinyBit));
+        wtiny |= s0 | s1;
+    }
+    float doubtful = 0.f;
+    if (xlow < (__float_as_uint(kTiny) << 1) - 1u || __any((wtiny & kTinyBit) != 0)) {
+#pragma unroll
+        for (int s = 1; s < 64; s *= 2) wstat = max(wstat, (uint32_t)__shfl_xor((int)wstat, s));
+        doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wstat) + 1.f);
+    }
+
+    // accumulator register r of a lane: filter row 8*(r/4) + 4*half + r%4 of the filter tile,
+    // pixel column `col`
+    float *dst = p.out + (size_t)n * p.F * OHW;
+    uint32_t again[NT > 0 ? NT : 1];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        again[j] = 0;
+        int oy, ox;
+        if (pixel_of(tile0 + j, oy, ox)) {
+            const int px = oy * p.OW + ox;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                    const float v = FLUSH ? sum[i][j][r] + acc[i][j][r] : acc[i][j][r];
+                    if (f < p.F) {
+                        dst[(size_t)f * OHW + px] = v;
+                        if (!(fabsf(v) >= doubtful && fabsf(v) <= 3.402823466e38f)) again[j] |= 1u << (16 * i + r);
+                    }
+                }
+        }
+    }
+#pragma unroll 1
+    for (int j = 0; j < NT; ++j) {
+        uint32_t bits = j == 0 ? again[0] : j == 1 ? again[NT > 1 ? 1 : 0] : again[NT > 2 ? 2 : 0];
+        while (bits) {
+            const int b = __builtin_ctz(bits);
+            bits &= bits - 1;
+            int oy, ox;
+            pixel_of(tile0 + j, oy, ox);
+            const int f = f0 + (b >> 4) * 32 + 8 * ((b >> 2) & 3) + 4 * half + (b & 3);
+            dst[(size_t)f * OHW + oy * p.OW + ox] = plain_output(p, n, f, oy, ox);
+        }
+    }
+}
+
+template <bool FLUSH>
+__global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitParams p)
+{
+    int b = blockIdx.x;
+    const int h = b % p.fgroups; b /= p.fgroups;
+    const int g = b % p.groups;
+    const int n = b / p.groups;
+    const int OHW = p.OH * p.OW;
+    int nt, t0 = 0, X0 = 0, Y0 = 0, oy0, oy1, ix0;
+    if (p.tw == 0) {
+        const int total = (OHW + 31) >> 5;
+        t0 = g * p.tiles;
+        const int t1 = min(total, t0 + p.tiles);
+        nt = t1 - t0;
+        oy0 = (t0 * 32) / p.OW;
+        oy1 = (min(OHW, t1 * 32) - 1) / p.OW;
+        ix0 = -p.pw;
+    } else {
+        const int gy = g / p.gx;
+        X0 = (g - gy * p.gx) * p.tx * p.tw;
+        Y0 = gy * p.ty * (32 / p.tw);
+        const int rows_left = p.OH - Y0;                 // (tile rows below the image: none; columns beyond it stay)
+        nt = p.tx * min(p.ty, (rows_left * p.tw + 31) / 32);
+        oy0 = Y0;
+        oy1 = min(p.OH, Y0 + p.ty * (32 / p.tw)) - 1;
+        ix0 = X0 * p.sw - p.pw;
+    }
+    const int rows = (oy1 - oy0) * p.sh + p.kh;
+    const int iy0 = oy0 * p.sh - p.ph;
+    // wave -> (filter half, pixel group); the tiles are shared out evenly over the pixel groups
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wf = p.fwaves == 2 ? wave & 1 : 0, wp = p.fwaves == 2 ? wave >> 1 : wave;
+    const int wps = 4 / p.fwaves;
+    const int tile0 = wp * nt / wps;
+    int my_nt = (wp + 1) * nt / wps - tile0;
+    const int f0 = (h * p.fwaves + wf) * 64;
+    if (f0 >= p.F) my_nt = 0;                             // no filters for this wave: staging only
+    switch (my_nt) {
+        case 0: split_wave<0, FLUSH>(p, n, 0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        case 1: split_wave<1, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        case 2: split_wave<2, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        default:
+            if constexpr (!FLUSH) split_wave<3, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0);
+            break;
+    }
+}
+
+struct Plan {
+    bool ok, flush;
+    int fwaves, tiles, tw, tx, ty, gx, groups, pitch, npos;
+    size_t lds;
+};
+
+int compute_units()
+{
+    static std::atomic<int> cached{0};
+    int cus = cached.load(std::memory_order_relaxed);
+    if (cus <= 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
+            (void)hipGetLastError();
+            return 256;
+        }
+        cached.store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
+// How an image is cut into workgroups: 32 consecutive pixels per tile (no idle pixel slot but in an
+// image's last tile; the whole width of every row under them is staged), or two-dimensional tiles of
+// tw x 32 / tw pixels in blocks of tx x ty (only the block's own columns are staged: wide rows, large
+// windows).  A workgroup's time is that of its busiest wave plus half a tile time of staging and
+// epilogue, a tenth less where two workgroups fit a compute unit; a launch takes as many of those as
+// its busiest compute unit has workgroups, or, over more than four rounds, as many as a compute unit has
+// on average and half of one.  The cheapest that fits max_pos() positions is taken.
+Plan make_plan(const Geom &g)
+{
+    Plan pl{};
+    const int taps = g.kh * g.kw;
+    const long long OHW = (long long)g.OH * g.OW;
+    if (taps > kMaxTaps || OHW > (1 << 24) || (long long)g.C * g.H * g.W >= (1LL << 29)) return pl;
+    if ((long long)g.F * g.C * taps >= (1LL << 28)) return pl;      // (32-bit sizes; 1.5 GiB of split filters)
+    // (the fp32 matrix kernel's chains are as long as this one's; what it does not take runs one thread
+    //  per output otherwise)
+    pl.flush = !conv_fp32_mfma_supports(g);
+    pl.fwaves = g.F <= 64 ? 1 : 2;
+    const int wps = 4 / pl.fwaves, most = wps * wave_tiles(pl.flush);
+    const long long maxpos = max_pos(pl.flush);
+    const long long fgroups = ceil_div(g.F, 64 * pl.fwaves);
+    const int cus = compute_units();
+    double best = -1.0;
+    // `last`: the tiles of the short workgroups, one in every `period`
+    auto consider = [&](int tiles, int last, long long period, long long groups, long long rows, long long cols, int tw, int tx,
+                        int ty, int gx) {
+        const long long npos = rows * cols;
+        if (npos > maxpos || groups > (1 << 24)) return;
+        const size_t lds = 2 * (size_t)npos * kPosBytes;
+        const long long wgs = (long long)g.N * fgroups * groups;
+        const double whole = ceil_div(tiles, wps) + 0.5, part = ceil_div(last, wps) + 0.5;
+        const double mean = whole + (part - whole) / (double)period;
+        const double time = wgs <= 4LL * cus ? (double)((wgs + cus - 1) / cus) * whole : (double)wgs / cus * mean + 0.5 * whole;
+        const double cost = time * (lds <= kLdsShared ? 0.9 : 1.0) * (1.0 + 1e-3 * (double)npos / maxpos);
+        if (best >= 0.0 && cost >= best) return;
+        best = cost;
+        pl.ok = true; pl.tiles = tiles; pl.tw = tw; pl.tx = tx; pl.ty = ty; pl.gx = gx; pl.groups = (int)groups;
+        pl.pitch = (int)cols; pl.npos = (int)npos; pl.lds = lds;
+    };
+    const int total = (int)((OHW + 31) / 32);
+    for (int T = std::min(most, total); T >= 1; --T) {
+        const int orows = (int)std::min<long long>(g.OH, (32LL * T + g.OW - 2) / g.OW + 1);
+        const int groups = ceil_div(total, T);
+        consider(T, total - (groups - 1) * T, groups, groups, (long long)(orows - 1) * g.sh + g.kh, (long long)g.W + 2 * g.pw, 0, 1, 1, 1);
+    }
+    for (int tw = 32; tw >= 4; tw /= 2) {
+        const int th = 32 / tw;
+        if (tw > 4 && tw >= 2 * g.OW) continue;
+        for (int tx = 1; tx <= std::min(most, ceil_div(g.OW, tw)); ++tx)
+            for (int ty = 1; tx * ty <= most && ty <= ceil_div(g.OH, th); ++ty) {
+                const int ow = std::min(tx * tw, g.OW), oh = std::min(ty * th, g.OH);
+                const int gy = ceil_div(g.OH, ty * th), last = ceil_div(g.OH - (gy - 1) * ty * th, th);
+                consider(tx * ty, tx * last, gy, (long long)ceil_div(g.OW, tx * tw) * gy,
+                         (long long)(oh - 1) * g.sh + g.kh, (long long)(ow - 1) * g.sw + g.kw, tw, tx, ty, ceil_div(g.OW, tx * tw));
+            }
+    }
+    return pl;
+}
+
+template <bool FLUSH>
+hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
+{
+    if (lds > 64 * 1024) {
+        // raise the kernel's dynamic-LDS limit once per device
+        static std::atomic<unsigned long long> raised{0};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (!(raised.load() & bit)) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 2 * max_pos(FLUSH) * kPosBytes);
+            if (e != hipSuccess) return e;
+            raised.fetch_or(bit);
+        }
+    }
+    conv_fp32_split_kernel<FLUSH><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool conv_fp32_split_supports(const Geom &g) { return make_plan(g).ok; }
+
+size_t conv_fp32_split_workspace_bytes(const Geom &g)
+{
+    if (!make_plan(g).ok) return 0;
+    const size_t nchunks = ceil_div(g.C, kChan), ftiles = ceil_div(g.F, 32);
+    return ftiles * nchunks * ((size_t)g.kh * g.kw * kOperandBytes + 2 * sizeof(uint32_t));
+}
+
+hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace, hipStream_t st)
+{
+    const Plan pl = make_plan(g);
+    if (!pl.ok) return hipErrorInvalidValue;
+    const int taps = g.kh * g.kw;
+    Fp32SplitParams p;
+    p.I = I; p.Wt = Wt; p.Wx = static_cast<const unsigned char *>(workspace); p.out = out;
+    p.N = g.N; p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
+    p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW;
+    p.nchunks = ceil_div(g.C, kChan); p.ftiles = ceil_div(g.F, 32);
+    p.fwaves = pl.fwaves; p.fgroups = ceil_div(g.F, 64 * pl.fwaves); p.groups = pl.groups;
+    p.tiles = pl.tiles; p.tw = pl.tw; p.tx = pl.tx; p.ty = pl.ty; p.gx = pl.gx;
+    p.pitch = pl.pitch; p.npos = pl.npos;
+    p.inv_pitch = reciprocal((unsigned long long)pl.pitch);
+    const long long blocks = (long long)g.N * p.groups * p.fgroups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const size_t filter_lds = (size_t)32 * ((8 * taps) | 1) * sizeof(float);
+    split_filters_kernel<<<dim3((unsigned)(p.ftiles * 2 * p.nchunks)), dim3(kThreads), filter_lds, st>>>(
+        Wt, g.F, g.C, taps, p.nchunks, p.ftiles, static_cast<unsigned char *>(workspace));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return pl.flush ? launch_form<true>(p, (unsigned)blocks, pl.lds, st) : launch_form<false>(p, (unsigned)blocks, pl.lds, st);
+}
+
+}  // namespace xnor

@@ -52,6 +52,20 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
     return XNOR_ALGO_DIRECT;
 }
 
+// Where the three-term kernel is the faster real-valued convolution (given a workspace) and no less
+// exact.  Measured, fp32 matrix form -> split (relative error against 64-bit sums in brackets):
+// 128x512x28x28 F=512 3x3 5105 -> 2215 us (1.16e-6 -> 1.05e-6), 16x128x56x56 F=128 5x5 1702 -> 245 us
+// (9.7e-7 -> 8.7e-7), one 8-channel 3x3 layer of 8 x 96 x 96 28.2 -> 26.6 us (1.48e-7 -> 1.36e-7); with
+// 4 channels the padding to 16 costs exactness (1.06e-7 -> 1.34e-7), and with a reduction of 8 terms the
+// second launch costs time (10.2 -> 15.1 us).  What the fp32 matrix form does not take (large windows)
+// ran one thread per output: 16x128x56x56 F=128 7x7 22.07 -> 0.53 ms (1.67e-7 -> 1.43e-7), three channels
+// 16x224x224 F=64 7x7 stride 2 1020 -> 293 us (1.33e-7 -> 1.01e-7).
+bool fp32_split_pays(const xnor::Geom &g)
+{
+    if (g.F < 8 || (long long)g.C * g.kh * g.kw < 72) return false;
+    return g.C >= 8 || (g.C >= 3 && !xnor::conv_fp32_mfma_supports(g));
+}
+
 // The expanded filters of xnor_conv2d_fwd_static live here instead of in a caller's workspace.
 // One copy per GPU, held until the process ends.  In host code the name is only a handle: the
 // memory's address on the current device comes from hipGetSymbolAddress, once per device.
@@ -381,26 +395,55 @@ int xnor_bwn_conv2d_fwd(const float *I, const uint32_t *Wpk, const float *alpha,
     return xnor_bwn_conv2d_fwd_algo(I, Wpk, alpha, s, out, XNOR_ALGO_AUTO, stream);
 }
 
-int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape *s, float *out, int algo,
-                              void *stream)
+int xnor_conv2d_fp32_workspace_bytes(const xnor_shape *s, size_t *bytes)
+{
+    if (!s || !bytes) return XNOR_E_NULL;
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    if (rc) return rc;
+    *bytes = fp32_split_pays(g) ? xnor::conv_fp32_split_workspace_bytes(g) : 0;
+    return XNOR_OK;
+}
+
+int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,
+                            size_t workspace_bytes, int algo, void *stream)
 {
     if (!I || !Wt || !s || !out) return XNOR_E_NULL;
     xnor::Geom g;
     const int rc = make_geom(s, &g);
     if (rc) return rc;
     if (!aligned(I, 4) || !aligned(Wt, 4) || !aligned(out, 4)) return XNOR_E_ALIGN;
+    if (workspace && !aligned(workspace, 16)) return XNOR_E_ALIGN;
     // (a few channels or filters leave the matrix tiles mostly empty: one thread per output then)
-    if (algo == XNOR_ALGO_AUTO)
-        algo = (xnor::conv_fp32_mfma_supports(g) && g.F >= 8 && g.C >= 4) ? XNOR_ALGO_MFMA : XNOR_ALGO_DIRECT;
+    if (algo == XNOR_ALGO_AUTO) {
+        const size_t need = xnor::conv_fp32_split_workspace_bytes(g);
+        if (workspace && need > 0 && workspace_bytes >= need && fp32_split_pays(g))
+            algo = XNOR_ALGO_MFMA_SPLIT;
+        else
+            algo = (xnor::conv_fp32_mfma_supports(g) && g.F >= 8 && g.C >= 4) ? XNOR_ALGO_MFMA : XNOR_ALGO_DIRECT;
+    }
     switch (algo) {
         case XNOR_ALGO_DIRECT:
             return hip_status(xnor::launch_conv_fp32_direct(I, Wt, g, out, (hipStream_t)stream));
         case XNOR_ALGO_MFMA:
             if (!xnor::conv_fp32_mfma_supports(g)) return XNOR_E_UNSUPPORTED;
             return hip_status(xnor::launch_conv_fp32_mfma(I, Wt, g, out, (hipStream_t)stream));
+        case XNOR_ALGO_MFMA_SPLIT: {
+            const size_t need = xnor::conv_fp32_split_workspace_bytes(g);
+            if (need == 0) return XNOR_E_UNSUPPORTED;
+            if (!workspace || workspace_bytes < need) return XNOR_E_WORKSPACE;
+            return hip_status(xnor::launch_conv_fp32_split(I, Wt, g, out, workspace, (hipStream_t)stream));
+        }
         default:
             return XNOR_E_UNSUPPORTED;
     }
+}
+
+int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape *s, float *out, int algo,
+                              void *stream)
+{
+    if (algo == XNOR_ALGO_MFMA_SPLIT) algo = -1;       // needs a workspace: not this call's
+    return xnor_conv2d_fp32_fwd_ws(I, Wt, s, out, nullptr, 0, algo, stream);
 }
 
 int xnor_conv2d_fp32_fwd(const float *I, const float *Wt, const xnor_shape *s, float *out, void *stream)

@@ -1,0 +1,119 @@
+"""XNOR_ALGO_MFMA_SPLIT of xnor_conv2d_fp32_fwd_ws (both operands as three bf16 terms, six products)
+against the oracle, at the edges of its tiles, chunks and dispatch.
+
+The bar is that of the fp32 kernels (tests/test_gpu_conv_fp32.py): |got - ref| <= 1e-5 * S with S =
+sum |I * Wt| over the output's terms, and an RMS error of at most 2e-7 of the RMS of S.  The products
+left out of the split are below 2^-25 of a term, so the bar is not spent on them.
+"""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2007_14178_amd.workloads import random_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def xb():
+    from paper_2007_14178_amd import binding
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def split(xb, I, Wt, s):
+    ws = torch.empty((16 << 20,), dtype=torch.uint8, device="cuda")
+    out = torch.full((s.N, s.F, *xb.xnor_out_dim(s)), float("nan"), device="cuda")
+    xb.xnor_conv2d_fp32_fwd(I, Wt, s, out, algo=xb.ALGO_MFMA_SPLIT, workspace=ws)
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+#        N   C   H   W   F  kh kw sh sw ph pw
+SHAPES = [
+    (1, 1, 1, 1, 1, 1, 1, 1, 1, 0, 0),           # one value, one tap, one chunk
+    (2, 17, 9, 11, 33, 3, 3, 1, 1, 1, 1),        # one channel past a chunk, one filter past a tile
+    (1, 16, 8, 4, 64, 3, 3, 1, 1, 1, 1),         # whole chunk, 32 outputs, one filter wave
+    (1, 48, 13, 13, 65, 3, 3, 1, 1, 1, 1),       # 169 outputs, one filter past a wave
+    (3, 40, 28, 28, 200, 3, 3, 1, 1, 1, 1),      # six tiles per workgroup, a short last one
+    (2, 32, 56, 57, 130, 5, 5, 1, 1, 2, 2),      # two-dimensional tiles, ragged on both sides
+    (1, 33, 6, 500, 20, 3, 3, 1, 1, 1, 1),       # rows far wider than a workgroup's pixels
+    (2, 24, 31, 29, 70, 3, 5, 2, 3, 1, 2),       # strides, non-square window
+    (1, 20, 9, 9, 12, 3, 3, 1, 1, 4, 4),         # windows that are all padding
+    (2, 30, 23, 23, 66, 7, 7, 1, 1, 3, 3),       # short chains (49 taps)
+    (1, 130, 14, 15, 140, 7, 7, 2, 2, 3, 3),     # short chains, stride, tails everywhere
+    (1, 18, 3, 700, 9, 5, 5, 1, 1, 2, 2),        # a row wider than the fp32 matrix kernel stages
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_split_shapes_vs_oracle(xb, shape):
+    print(f"case conv_fp32 split shape={shape}", flush=True)
+    rng = np.random.default_rng(zlib.crc32(("split" + str(shape)).encode()))
+    _, I, Wt = random_layer(rng, "t", *shape)
+    O, S = oracle.conv_fp32(I, Wt, oracle.Shape(*shape), want_scale=True)
+    err = np.abs(split(xb, dev(I), dev(Wt), xb.Shape(*shape)) - O.astype(np.float64))
+    assert (err <= 1e-5 * S).all()
+    assert np.sqrt((err ** 2).mean()) <= 2e-7 * np.sqrt((S ** 2).mean()) + 1e-30
+
+
+@pytest.mark.parametrize("k", [3, 7])
+def test_split_inputs_that_are_not_finite(xb, k):
+    """Infinities, NaN and values at the top of the range give what the plain fp32 sum gives."""
+    shape = (1, 24, 20, 20, 40, k, k, 1, 1, 1, 1)
+    print(f"case conv_fp32 split not finite k={k}", flush=True)
+    rng = np.random.default_rng(5)
+    _, I, Wt = random_layer(rng, "t", *shape)
+    I[0, 3, 2, 2], I[0, 20, 17, 17], I[0, 5, 17, 2], I[0, 7, 2, 17] = np.inf, -np.inf, np.nan, 3.4028235e38
+    s = xb.Shape(*shape)
+    ref = xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, algo=xb.ALGO_DIRECT).cpu().numpy().astype(np.float64)
+    got = split(xb, dev(I), dev(Wt), s)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.isinf(ref).any()
+    fine = np.isfinite(ref)
+    assert np.array_equal(np.sign(got[~fine & ~np.isnan(ref)]), np.sign(ref[~fine & ~np.isnan(ref)]))
+    S = torch.nn.functional.conv2d(torch.from_numpy(I).double().abs(), torch.from_numpy(Wt).double().abs(), padding=1).numpy()
+    with np.errstate(invalid="ignore"):
+        assert (np.abs(got - ref)[fine] <= 1e-5 * S[fine]).all()
+
+
+@pytest.mark.parametrize("scale_I,scale_W", [(2.0 ** -110, 1.0), (1.0, 2.0 ** -112), (2.0 ** -60, 2.0 ** -60), (2.0 ** -100, 2.0 ** 90)])
+def test_split_at_the_bottom_of_the_range(xb, scale_I, scale_W):
+    """Scaling by powers of two: terms of the split fall below 2^-126 where the fp32 values do not.
+    The bar has the roundings of products and partial sums below the normal range beside the 1e-5."""
+    shape = (1, 20, 12, 12, 33, 3, 3, 1, 1, 1, 1)
+    print(f"case conv_fp32 split tiny {scale_I} {scale_W}", flush=True)
+    rng = np.random.default_rng(6)
+    I = (rng.standard_normal((1, 20, 12, 12)) * scale_I).astype(np.float32)
+    Wt = (rng.standard_normal((33, 20, 3, 3)) * scale_W).astype(np.float32)
+    O, S = oracle.conv_fp32(I, Wt, oracle.Shape(*shape), want_scale=True)
+    got = split(xb, dev(I), dev(Wt), xb.Shape(*shape))
+    assert (np.abs(got - O.astype(np.float64)) <= 1e-5 * S + 2 * 180 * 2.0 ** -149).all()
+
+
+def test_auto_takes_the_split_kernel_and_refusals_stay(xb):
+    s = xb.Shape(2, 40, 20, 20, 72, 3, 3, 1, 1, 1, 1)
+    _, I, Wt = random_layer(np.random.default_rng(8), "t", 2, 40, 20, 20, 72, 3, 3, 1, 1, 1, 1)
+    I, Wt = dev(I), dev(Wt)
+    assert xb.xnor_conv2d_fp32_workspace_bytes(s) > 0
+    ws = torch.empty((16 << 20,), dtype=torch.uint8, device="cuda")
+    auto = xb.xnor_conv2d_fp32_fwd(I, Wt, s)
+    forced = xb.xnor_conv2d_fp32_fwd(I, Wt, s, algo=xb.ALGO_MFMA_SPLIT, workspace=ws)
+    plain = xb.xnor_conv2d_fp32_fwd(I, Wt, s, workspace=None)
+    mfma = xb.xnor_conv2d_fp32_fwd(I, Wt, s, algo=xb.ALGO_MFMA)
+    torch.cuda.synchronize()
+    assert torch.equal(auto, forced) and torch.equal(plain, mfma)
+    with pytest.raises(xb.XnorError) as e:
+        xb.xnor_conv2d_fp32_fwd(I, Wt, s, algo=xb.ALGO_MFMA_SPLIT, workspace=ws[:1024])
+    assert e.value.status == xb.E_WORKSPACE
+    big = xb.Shape(1, 8, 20, 20, 8, 8, 8)          # 64 taps
+    with pytest.raises(xb.XnorError) as e:
+        xb.xnor_conv2d_fp32_fwd(torch.zeros((1, 8, 20, 20), device="cuda"), torch.zeros((8, 8, 8, 8), device="cuda"), big,
+                                algo=xb.ALGO_MFMA_SPLIT, workspace=ws)
+    assert e.value.status == xb.E_UNSUPPORTED
