@@ -232,6 +232,221 @@ __global__ __launch_bounds__(kThreads) void conv_image_kernel(ImageParams p)
     }
 }
 
+// Several filters: a workgroup takes a tile of output pixels and all filters (or a group of them).
+//   1. The input under the tile is read once, coalesced.  The 64 signs of a wave's 64 neighbouring
+//      pixels of a channel are one compare (its result mask is the row's bit map), the sum of the
+//      channels' magnitudes goes to LDS beside it; the filters' windows are packed in the same order.
+//   2. The magnitudes are summed along the window rows.
+//   3. A lane takes one or two output pixels.  A window row of a channel is K neighbouring bits of the bit
+//      map (two words, one v_alignbit_b32); 32 / K such pieces share a word.  K (Eq. 10) is the sum of K
+//      row sums.  Per filter and pixel: one v_bitop3_b32 ((window xor filter) and mask) and one
+//      v_bcnt_u32_b32 per word, four instructions for dot and output, one store (64 neighbouring pixels).
+// Both LDS arrays run along the rows first, so that the pieces and sums of a window are neighbours.
+// Bound by the output stores and by that vector arithmetic: 17 instructions per output for 7 x 7 x 3.
+template <int K, int C>
+struct Tile {
+    static constexpr int kPerWord = 32 / K;                              // pieces (K bits) in a word
+    static constexpr int kPieces = K * C;
+    static constexpr int kWords = (kPieces + kPerWord - 1) / kPerWord;
+    static constexpr int kRecord = kWords < 4 ? 4 : 8;                   // a filter's words, then its alpha in the last one
+    static constexpr uint32_t kBits = (1u << K) - 1u;
+};
+// (row, 64 columns) units a wave has in flight while staging: a tile's loads in one or two batches
+constexpr int units_ahead(int C) { return C == 1 ? 16 : 30 / C; }
+
+struct TileParams {
+    const float *I;
+    const uint32_t *Wpk;
+    const float *alpha;
+    float *out;
+    int32_t *dot;
+    int N, H, W, F, OH, OW, ph, pw, sh, sw;
+    int tw, th, gx, gy;      // output pixels of a tile, tiles of an image
+    int group, fgroups;      // filters per workgroup
+    int cols, chunks;        // staged columns, 64-column units of a row
+    int map_rows, mag_rows;  // (row, channel) entries of a 32-column bit-map word, rows of a column of sums (odd)
+    uint32_t inv_tw;         // ceil(2^32 / tw), 0 for 1
+    float kscale;            // 1 / (C * K * K)
+};
+
+template <int K, int C, int kPixels, bool DOT>     // pixels per lane and pass; the dot products are wanted
+__global__ __launch_bounds__(kThreads, 4) void conv_image_tile_kernel(TileParams p)
+{
+    using T = Tile<K, C>;
+    constexpr int kUnits = units_ahead(C);
+    extern __shared__ uint32_t lds[];
+    uint32_t *const rec = lds;                                           // [group][kRecord]
+    uint32_t *const map = rec + p.group * T::kRecord;                    // [2 * chunks + 1][rows][C]
+    float *const mag = reinterpret_cast<float *>(map + (2 * p.chunks + 1) * p.map_rows);   // [cols][mag_rows]
+    float *const row_sum = mag + p.cols * p.mag_rows;                    // [tw][mag_rows]
+
+    int b = blockIdx.x;
+    const int fg = b % p.fgroups; b /= p.fgroups;
+    const int bx = b % p.gx; b /= p.gx;
+    const int by = b % p.gy;
+    const int n = b / p.gy;
+    const int f0 = fg * p.group, nf = min(p.group, p.F - f0);
+    const int X0 = bx * p.tw, Y0 = by * p.th;
+    const int tw = min(p.tw, p.OW - X0), th = min(p.th, p.OH - Y0);
+    const int rows = (th - 1) * p.sh + K;
+    const int iy0 = Y0 * p.sh - p.ph, ix0 = X0 * p.sw - p.pw;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+
+    // the input under the tile: the first batch of loads is on its way while the filters are packed
+    const size_t HW = (size_t)p.H * p.W;
+    const float *img = p.I + (size_t)n * C * HW;
+    const int units = rows * p.chunks;
+    float v[kUnits][C];
+    bool in[kUnits];
+    auto fetch = [&](int u0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kUnits; ++k) {
+            const int u = min(u0 + k * kWaves, units - 1);               // (the last one again: loads without a branch)
+            const int r = u / p.chunks, x = (u - r * p.chunks) * 64 + lane;
+            const int iy = iy0 + r, ix = ix0 + x;
+            in[k] = (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W && x < p.cols;
+            const size_t at = in[k] ? (size_t)iy * p.W + ix : 0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[k][c] = img[(size_t)c * HW + at];
+        }
+    };
+    fetch(wave);
+    for (int i = threadIdx.x; i < nf * T::kRecord; i += kThreads) rec[i] = 0;
+    __syncthreads();
+    // filter windows: piece r * C + c of a filter holds channel c of its row r
+    for (int i = threadIdx.x; i < nf * K; i += kThreads) {
+        const int f = i / K, r = i - f * K;
+        uint32_t w[K];
+#pragma unroll
+        for (int kx = 0; kx < K; ++kx) w[kx] = p.Wpk[((size_t)(f0 + f) * K + r) * K + kx];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int kx = 0; kx < K; ++kx) bits |= ((w[kx] >> c) & 1u) << kx;
+            const int piece = r * C + c;
+            atomicOr(&rec[f * T::kRecord + piece / T::kPerWord], bits << ((piece % T::kPerWord) * K));
+        }
+        if (r == 0) rec[f * T::kRecord + T::kRecord - 1] = __float_as_uint(p.alpha[f0 + f]);
+    }
+    for (int u0 = wave; u0 < units; u0 += kWaves * kUnits) {
+        if (u0 != wave) fetch(u0);
+#pragma unroll
+        for (int k = 0; k < kUnits; ++k) {
+            const int u = u0 + k * kWaves;
+            if (u >= units) break;
+            const int r = u / p.chunks, ch = u - r * p.chunks, x = ch * 64 + lane;
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const unsigned long long signs = __ballot(in[k] && v[k][c] >= 0.f);
+                if (lane < 2) map[(2 * ch + lane) * p.map_rows + r * C + c] = (uint32_t)(lane ? signs >> 32 : signs);
+                s += fabsf(v[k][c]);
+            }
+            if (x < p.cols) mag[x * p.mag_rows + r] = in[k] ? s : 0.f;
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < tw * rows; i += kThreads) {
+        const int x = i / rows, r = i - x * rows;
+        const float *src = mag + x * p.sw * p.mag_rows + r;
+        float s = src[0];
+#pragma unroll
+        for (int kx = 1; kx < K; ++kx) s += src[kx * p.mag_rows];
+        row_sum[x * p.mag_rows + r] = s;
+    }
+    __syncthreads();
+
+    const int npx = tw * th;
+    const size_t OHW = (size_t)p.OH * p.OW;
+    const size_t plane0 = ((size_t)n * p.F + f0) * OHW;
+    for (int q0 = threadIdx.x; q0 < npx; q0 += kThreads * kPixels) {
+        uint32_t win[kPixels][T::kWords], m[kPixels][T::kWords];
+        float kk[kPixels];
+        int nvalid[kPixels];
+        uint32_t at[kPixels];
+#pragma unroll
+        for (int k = 0; k < kPixels; ++k) {
+            const int q = min(q0 + k * kThreads, npx - 1);
+            // (a ragged tile has its own width: a division for the image's last tile column only)
+            const int oy = tw == p.tw ? (p.inv_tw == 0 ? q : (int)__umulhi((uint32_t)q, p.inv_tw)) : q / tw;
+            const int ox = q - oy * tw;
+            const int x0 = ox * p.sw, y0 = oy * p.sh;
+            at[k] = ((uint32_t)(Y0 + oy) * (uint32_t)p.OW + (uint32_t)(X0 + ox)) * 4u;   // (a plane is below 2 GiB)
+            const int left = max(0, -(ix0 + x0)), right = max(0, ix0 + x0 + K - p.W);
+            const uint32_t cols_in = left + right >= K ? 0u : (T::kBits << left) & (T::kBits >> right);
+            const uint32_t sh = (uint32_t)x0 & 31u;
+            const uint32_t *src = map + (x0 >> 5) * p.map_rows + y0 * C;
+            const float *sums = row_sum + ox * p.mag_rows + y0;
+            float total = sums[0];
+#pragma unroll
+            for (int r = 1; r < K; ++r) total += sums[r];
+            kk[k] = total * p.kscale;
+#pragma unroll
+            for (int w = 0; w < T::kWords; ++w) win[k][w] = 0;
+            constexpr int per = T::kPerWord;
+#pragma unroll
+            for (int i = 0; i < T::kPieces; ++i) {                        // piece i = row i / C, channel i % C
+                const uint32_t bits = __builtin_amdgcn_alignbit(src[i + p.map_rows], src[i], sh) & T::kBits;
+                win[k][i / per] |= bits << ((i % per) * K);
+            }
+            const int top = iy0 + y0;
+            if (__all(top >= 0 && top + K <= p.H)) {                      // every word's pieces alike
+                uint32_t all = 0;
+#pragma unroll
+                for (int i = 0; i < per; ++i) all |= cols_in << (i * K);
+#pragma unroll
+                for (int w = 0; w < T::kWords; ++w) {
+                    const int live = min(per, T::kPieces - w * per) * K;  // (constant, at most 30 bits)
+                    m[k][w] = all & ((1u << live) - 1u);
+                }
+                nvalid[k] = C * K * __builtin_popcount(cols_in);
+            } else {
+#pragma unroll
+                for (int w = 0; w < T::kWords; ++w) m[k][w] = 0;
+                nvalid[k] = 0;
+#pragma unroll
+                for (int i = 0; i < T::kPieces; ++i) {
+                    const uint32_t piece = (unsigned)(top + i / C) < (unsigned)p.H ? cols_in : 0u;
+                    m[k][i / per] |= piece << ((i % per) * K);
+                    nvalid[k] += __builtin_popcount(piece);
+                }
+            }
+        }
+        // (a lane without a pixel of its own repeats the tile's last one: the same value to the same place)
+        const float *out = p.out + plane0;
+        const int32_t *dot = DOT ? p.dot + plane0 : nullptr;
+        const int plane_bytes = (int)(OHW * 4);
+        constexpr int kRaw = 0x00027000;                                  // (a plain buffer of dwords)
+#pragma unroll 2
+        for (int f = 0; f < nf; ++f) {
+            uint32_t w[T::kRecord];
+#pragma unroll
+            for (int i = 0; i < T::kRecord; i += 4) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(&rec[f * T::kRecord + i]);
+                w[i] = x.x; w[i + 1] = x.y; w[i + 2] = x.z; w[i + 3] = x.w;
+            }
+            const float al = __uint_as_float(w[T::kRecord - 1]);
+            // stores as scalar plane + lane offset: no vector arithmetic for the address
+            const auto to = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(out), 0, plane_bytes, kRaw);
+#pragma unroll
+            for (int k = 0; k < kPixels; ++k) {
+                uint32_t pop = 0;
+#pragma unroll
+                for (int i = 0; i < T::kWords; ++i) pop += __builtin_popcount((win[k][i] ^ w[i]) & m[k][i]);
+                const float d = fmaf(-2.f, (float)pop, (float)nvalid[k]);     // (small whole numbers: exact)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d * (kk[k] * al)), to, (int)at[k], 0, 0);
+                if constexpr (DOT)
+                    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(int)d,
+                        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(dot), 0, plane_bytes, kRaw), (int)at[k], 0, 0);
+            }
+            out += OHW;
+            if constexpr (DOT) dot += OHW;
+        }
+    }
+}
+
 template <int K, int C>
 hipError_t launch_kc(const ImageParams &p, dim3 grid, size_t lds, hipStream_t st)
 {
@@ -258,6 +473,88 @@ hipError_t launch_k(int C, const ImageParams &p, dim3 grid, size_t lds, hipStrea
     }
 }
 
+// Tiles of several filters' kernel: rows of a tile are the whole output rows where these are at most 256
+// pixels, else equal parts of them; about 512 pixels a tile (two per lane), fewer where the launch would
+// not give every compute unit four workgroups, and then the filters are shared out as well.
+struct TilePlan { int tw, th, gx, gy, group; };
+size_t tile_lds(const Geom &g, const TilePlan &pl, int record)
+{
+    const long long rows = (long long)(pl.th - 1) * g.sh + g.kh, cols = (long long)(pl.tw - 1) * g.sw + g.kw;
+    return 4 * ((size_t)pl.group * record + (size_t)(2 * ceil_div(cols, 64) + 1) * rows * g.C + (size_t)(cols + pl.tw) * (rows | 1));
+}
+
+TilePlan tile_plan(const Geom &g)
+{
+    TilePlan pl;
+    pl.group = std::min(g.F, 256);
+    pl.gx = ceil_div(g.OW, 256);
+    pl.tw = ceil_div(g.OW, pl.gx);
+    pl.th = std::min(g.OH, std::max(1, 512 / pl.tw));
+    // (large strides: what lies under the tile has to fit the LDS)
+    while (tile_lds(g, pl, 8) > kLdsBudget) {
+        if (pl.th > 1) pl.th = (pl.th + 1) / 2;
+        else pl.tw = (pl.tw + 1) / 2;
+    }
+    pl.gx = ceil_div(g.OW, pl.tw);
+    auto blocks = [&](int th) { return (long long)g.N * pl.gx * ceil_div(g.OH, th); };
+    if (pl.th > 1 && blocks(pl.th) < 768) pl.th = std::max(1, std::min(pl.th, 256 / pl.tw));
+    pl.gy = ceil_div(g.OH, pl.th);
+    while (pl.group > 16 && blocks(pl.th) * ceil_div(g.F, pl.group) < 768) pl.group = (pl.group + 1) / 2;
+    return pl;
+}
+
+// Where the tiles are the faster form.  The sliding window (conv_image_kernel) reads kw * C values per
+// lane and input row, several times over where filters are shared out or rows are skipped by a stride,
+// but costs little per output; the tiles pay about 200 instructions per output pixel once and then 17
+// or fewer per filter.  Measured, sliding window / tiles, 2 x C x 500 x 500 unless said otherwise:
+// 16 x 3 x 227 x 227 F=64 7x7 stride 2 67 / 24 us; C=3 7x7 F=64 49 / 34 us, F=8 1.17x, F=4 0.94x; the same
+// with stride 2 F=4 1.5x; C=3 3x3 F=16 1.28x, F=4 0.76x, stride 2 F=4 1.25x; C=1 3x3 F=16 0.97x, F=4 0.59x.
+bool tile_pays(const Geom &g)
+{
+    if (g.F < 2 || (long long)g.OH * g.OW >= (1LL << 29)) return false;    // (31-bit byte offsets in a plane)
+    const int kc = g.kw * g.C;
+    return (g.F >= 16 && kc >= 6) || (g.F >= 8 && kc >= 15) || (g.sh >= 2 && g.sw >= 2 && kc >= 9);
+}
+
+template <int K, int C>
+hipError_t launch_tile(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out, int32_t *dot,
+                       const TilePlan &pl, hipStream_t st)
+{
+    TileParams p;
+    p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out; p.dot = dot;
+    p.N = g.N; p.H = g.H; p.W = g.W; p.F = g.F; p.OH = g.OH; p.OW = g.OW; p.ph = g.ph; p.pw = g.pw; p.sh = g.sh; p.sw = g.sw;
+    p.tw = pl.tw; p.th = pl.th; p.gx = pl.gx; p.gy = pl.gy; p.group = pl.group; p.fgroups = ceil_div(g.F, pl.group);
+    p.cols = (pl.tw - 1) * g.sw + K; p.chunks = ceil_div(p.cols, 64);
+    const int rows = (pl.th - 1) * g.sh + K;
+    p.map_rows = rows * C; p.mag_rows = rows | 1;
+    p.inv_tw = pl.tw == 1 ? 0u : (uint32_t)(((1ULL << 32) + pl.tw - 1) / pl.tw);
+    p.kscale = 1.0f / (float)(C * K * K);
+    const long long blocks = (long long)g.N * pl.gx * pl.gy * p.fgroups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const size_t lds = tile_lds(g, pl, Tile<K, C>::kRecord);
+    const dim3 grid((unsigned)blocks);
+    if (pl.tw * pl.th <= kThreads) {
+        if (dot) conv_image_tile_kernel<K, C, 1, true><<<grid, dim3(kThreads), lds, st>>>(p);
+        else conv_image_tile_kernel<K, C, 1, false><<<grid, dim3(kThreads), lds, st>>>(p);
+    } else {
+        if (dot) conv_image_tile_kernel<K, C, 2, true><<<grid, dim3(kThreads), lds, st>>>(p);
+        else conv_image_tile_kernel<K, C, 2, false><<<grid, dim3(kThreads), lds, st>>>(p);
+    }
+    return hipGetLastError();
+}
+
+template <int K>
+hipError_t launch_tile_k(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out, int32_t *dot,
+                         const TilePlan &pl, hipStream_t st)
+{
+    switch (g.C) {
+        case 1: return launch_tile<K, 1>(I, Wpk, alpha, g, out, dot, pl, st);
+        case 2: return launch_tile<K, 2>(I, Wpk, alpha, g, out, dot, pl, st);
+        case 3: return launch_tile<K, 3>(I, Wpk, alpha, g, out, dot, pl, st);
+        default: return launch_tile<K, 4>(I, Wpk, alpha, g, out, dot, pl, st);
+    }
+}
+
 int window_words(int k, int C) { return (k + 32 / (k * C) - 1) / (32 / (k * C)); }
 
 }  // namespace
@@ -273,6 +570,14 @@ bool conv_image_supports(const Geom &g)
 hipError_t launch_conv_image(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
                              float *out, int32_t *dot, hipStream_t st)
 {
+    if (tile_pays(g)) {
+        const TilePlan pl = tile_plan(g);
+        switch (g.kh) {
+            case 3: return launch_tile_k<3>(I, Wpk, alpha, g, out, dot, pl, st);
+            case 5: return launch_tile_k<5>(I, Wpk, alpha, g, out, dot, pl, st);
+            default: return launch_tile_k<7>(I, Wpk, alpha, g, out, dot, pl, st);
+        }
+    }
     ImageParams p;
     p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out; p.dot = dot;
     p.N = g.N; p.H = g.H; p.W = g.W; p.F = g.F; p.OH = g.OH; p.OW = g.OW; p.ph = g.ph; p.pw = g.pw; p.sh = g.sh; p.sw = g.sw;
