@@ -482,14 +482,16 @@ def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch
     """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out.
 
     ``workspace``: a uint8 GPU tensor, None (run a kernel that needs none), or "auto" (allocate what
-    xnor_conv2d_fp32_workspace_bytes asks for, where the algorithm uses one)."""
+    xnor_conv2d_fp32_workspace_bytes asks for, where ALGO_AUTO uses one)."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
         out = torch.empty(oshape, dtype=torch.float32, device=I.device)
     if isinstance(workspace, str):
-        nbytes = xnor_conv2d_fp32_workspace_bytes(s) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
+        nbytes = xnor_conv2d_fp32_workspace_bytes(s) if algo == ALGO_AUTO else 0
         workspace = torch.empty((nbytes,), dtype=torch.uint8, device=I.device) if nbytes else None
+        if algo == ALGO_MFMA_SPLIT:
+            _ok(E_UNSUPPORTED, "xnor_conv2d_fp32_fwd[mfma_split] without a workspace")
     _ok(lib.xnor_conv2d_fp32_fwd_ws(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
         ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),

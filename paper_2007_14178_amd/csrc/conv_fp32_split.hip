@@ -586,7 +586,7 @@ int compute_units()
 // epilogue, a tenth less where two workgroups fit a compute unit; a launch takes as many of those as
 // its busiest compute unit has workgroups, or, over more than four rounds, as many as a compute unit has
 // on average and half of one.  The cheapest that fits max_pos() positions is taken.
-Plan make_plan(const Geom &g)
+Plan search_plan(const Geom &g)
 {
     Plan pl{};
     const int taps = g.kh * g.kw;
@@ -638,6 +638,12 @@ Plan make_plan(const Geom &g)
     return pl;
 }
 
+const Plan &make_plan(const Geom &g)
+{
+    static thread_local PlanMemo<Plan> memo;
+    return memo.get(g, 0, [&] { return search_plan(g); });
+}
+
 template <bool FLUSH>
 hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
 {
@@ -671,7 +677,7 @@ size_t conv_fp32_split_workspace_bytes(const Geom &g)
 
 hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace, hipStream_t st)
 {
-    const Plan pl = make_plan(g);
+    const Plan &pl = make_plan(g);
     if (!pl.ok) return hipErrorInvalidValue;
     const int taps = g.kh * g.kw;
     Fp32SplitParams p;

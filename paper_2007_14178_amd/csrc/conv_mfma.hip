@@ -664,7 +664,7 @@ struct MfmaPlan {
     int f_tiles;   // workgroup rows of kFilterTile filters
 };
 
-MfmaPlan make_plan(const Geom &g, const void *Ipk)
+MfmaPlan search_plan(const Geom &g, const void *Ipk)
 {
     MfmaPlan pl{};
     pl.ok = false;
@@ -739,25 +739,14 @@ MfmaPlan make_plan(const Geom &g, const void *Ipk)
     return pl;
 }
 
-}  // namespace
-
-// Which of the two kernels runs a layer (and so which workspace layout its filters take): the
-// persistent one where it takes the shape and its rounds of items come out even enough (or this
-// file's kernel does not take the shape), this file's one-workgroup-per-band kernel otherwise.
-static bool use_persistent(const Geom &g)
+MfmaPlan make_plan(const Geom &g, const void *Ipk)
 {
-    if (!conv_mfma_persistent_supports(g)) return false;
-    return conv_mfma_persistent_preferred(g) || !make_plan(g, nullptr).ok;
+    static thread_local PlanMemo<MfmaPlan> memo;
+    return memo.get(g, (int)(reinterpret_cast<uintptr_t>(Ipk) & 15), [&] { return search_plan(g, Ipk); });
 }
 
-bool conv_mfma_supports(const Geom &g)
+ExpandLayout bands_expand_layout(const Geom &g)
 {
-    return use_persistent(g) || make_plan(g, nullptr).ok;
-}
-
-ExpandLayout conv_mfma_expand_layout(const Geom &g)
-{
-    if (use_persistent(g)) return conv_mfma_persistent_expand_layout(g);
     const MfmaPlan pl = make_plan(g, nullptr);   // the workspace layout does not depend on alignment
     ExpandLayout L{};
     L.ok = pl.ok ? 1 : 0;
@@ -766,29 +755,59 @@ ExpandLayout conv_mfma_expand_layout(const Geom &g)
     return L;
 }
 
-static ExpandLayout bands_expand_layout(const Geom &g)
-{
-    const MfmaPlan pl = make_plan(g, nullptr);
-    ExpandLayout L{};
-    L.ok = pl.ok ? 1 : 0;
-    L.CH = pl.CH; L.nchunks = pl.nchunks; L.chunk_pad = pl.chunk_pad; L.tile_steps = pl.tile_steps;
-    L.Cw2 = 2 * pl.S2; L.ws_bytes = pl.ws_bytes;
-    return L;
-}
+// Which of the three kernels runs a layer, and so which workspace layout its filters take: small
+// independent workgroups for a layer of little work; else the persistent one where it takes the shape
+// and its rounds of items come out even enough (or this file's kernel does not take the shape), this
+// file's one-workgroup-per-band kernel otherwise.
+enum Kind { kNone, kTile, kPersistent, kBands };
+struct Route {
+    Kind kind;
+    ExpandLayout L;
+    size_t ws_bytes;     // enough for any of them, so that a caller's one workspace serves whatever variant it asks for
+    int sum_parts;       // partial sums of |out| per pixel that the chained epilogue leaves for chain_mean_kernel
+};
 
-bool conv_mfma_bands_supports(const Geom &g)
+Route find_route(const Geom &g)
 {
-    return make_plan(g, nullptr).ok;
-}
-
-// (enough for either kernel, so that a caller's one workspace serves whatever variant it asks for)
-size_t conv_mfma_workspace_bytes(const Geom &g)
-{
-    const ExpandLayout L = conv_mfma_expand_layout(g);
-    if (!L.ok) return 0;
+    Route r{};
     const ExpandLayout Lb = bands_expand_layout(g);
-    return std::max(L.ws_bytes, Lb.ok ? Lb.ws_bytes : (size_t)0);
+    if (conv_mfma_persistent_supports(g) && (conv_mfma_persistent_preferred(g) || !Lb.ok)) {
+        r.kind = kPersistent;
+        r.L = conv_mfma_persistent_expand_layout(g);
+        r.sum_parts = conv_mfma_persistent_sum_parts(g);
+    } else if (Lb.ok) {
+        r.kind = kBands;
+        r.L = Lb;
+        r.sum_parts = ceil_div(g.F, kFilterTile);
+    } else {
+        return r;
+    }
+    r.ws_bytes = std::max(r.L.ws_bytes, Lb.ok ? Lb.ws_bytes : (size_t)0);
+    if (conv_mfma_tile_preferred(g)) {
+        const ExpandLayout Lt = conv_mfma_tile_expand_layout(g);
+        // (a layer whose filters fit the library's own workspace has to go on fitting it)
+        if (Lt.ws_bytes <= XNOR_STATIC_SCRATCH_BYTES || r.ws_bytes > XNOR_STATIC_SCRATCH_BYTES) {
+            r.kind = kTile;
+            r.L = Lt;
+            r.ws_bytes = std::max(r.ws_bytes, Lt.ws_bytes);
+            r.sum_parts = conv_mfma_tile_sum_parts(g);
+        }
+    }
+    return r;
 }
+
+const Route &route_of(const Geom &g)
+{
+    static thread_local PlanMemo<Route> memo;
+    return memo.get(g, 0, [&] { return find_route(g); });
+}
+
+}  // namespace
+
+bool conv_mfma_supports(const Geom &g) { return route_of(g).kind != kNone; }
+ExpandLayout conv_mfma_expand_layout(const Geom &g) { return route_of(g).L; }
+bool conv_mfma_bands_supports(const Geom &g) { return make_plan(g, nullptr).ok; }
+size_t conv_mfma_workspace_bytes(const Geom &g) { return route_of(g).ws_bytes; }
 
 static hipError_t launch_expand_with(const ExpandLayout &L, const uint32_t *Wpk, const Geom &g, void *workspace,
                                      hipStream_t st)
@@ -810,7 +829,10 @@ static hipError_t launch_mfma(const uint32_t *Ipk, const float *K, const float *
                               const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,
                               const void *workspace, hipStream_t st, bool bands_kernel = false)
 {
-    if (!bands_kernel && use_persistent(g))
+    const Kind kind = bands_kernel ? kBands : route_of(g).kind;
+    if (kind == kTile)
+        return launch_conv_mfma_tile(Ipk, K, A, alpha, g, out, dot, Opk, P, workspace, st);
+    if (kind == kPersistent)
         return launch_conv_mfma_persistent(Ipk, K, A, alpha, g, out, dot, Opk, P, workspace, st);
     const MfmaPlan pl = make_plan(g, Ipk);
     if (!pl.ok) return hipErrorInvalidValue;
@@ -901,17 +923,11 @@ __global__ __launch_bounds__(256) void chain_mean_kernel(const float *__restrict
     A[i] = (float)(sum / (double)F);
 }
 
-// partial sums of |out| per pixel that the chained epilogue leaves for chain_mean_kernel
-static int chain_sum_parts(const Geom &g)
-{
-    return use_persistent(g) ? conv_mfma_persistent_sum_parts(g) : ceil_div(g.F, kFilterTile);
-}
-
 size_t conv_mfma_chain_workspace_bytes(const Geom &g)
 {
     const size_t ws = conv_mfma_workspace_bytes(g);
     if (ws == 0) return 0;
-    return ws + (size_t)g.N * g.OH * g.OW * chain_sum_parts(g) * sizeof(float);
+    return ws + (size_t)g.N * g.OH * g.OW * route_of(g).sum_parts * sizeof(float);
 }
 
 hipError_t launch_conv_mfma_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
@@ -927,7 +943,7 @@ hipError_t launch_conv_mfma_chain(const uint32_t *Ipk, const uint32_t *Wpk, cons
     e = launch_mfma(Ipk, K, A, alpha, g, nullptr, nullptr, Opk, P, workspace, st);   // K or A, the other null
     if (e != hipSuccess) return e;
     const long long npix = (long long)g.N * g.OH * g.OW;
-    chain_mean_kernel<<<ceil_div(npix, 256), 256, 0, st>>>(P, npix, chain_sum_parts(g), g.F, A_next);
+    chain_mean_kernel<<<ceil_div(npix, 256), 256, 0, st>>>(P, npix, route_of(g).sum_parts, g.F, A_next);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// Shared by the two matrix-core convolution kernels (Sec. III-A steps 1b-1d and 3, Eq. 11 on
+// Shared by the three matrix-core convolution kernels (Sec. III-A steps 1b-1d and 3, Eq. 11 on
 // v_mfma_f32_32x32x64_f8f6f4): tile constants, the exact-division helper, load-width types.
 #pragma once
 
@@ -50,5 +50,13 @@ int conv_mfma_persistent_sum_parts(const Geom &g);
 hipError_t launch_conv_mfma_persistent(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                                        const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,
                                        const void *workspace, hipStream_t st);
+
+// Small independent workgroups for layers of little work (conv_mfma_tile.hip).
+bool conv_mfma_tile_preferred(const Geom &g);          // takes the shape and is expected to be the faster kernel
+ExpandLayout conv_mfma_tile_expand_layout(const Geom &g);
+int conv_mfma_tile_sum_parts(const Geom &g);
+hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
+                                 const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,
+                                 const void *workspace, hipStream_t st);
 
 }  // namespace xnor

@@ -1520,7 +1520,7 @@ struct PPlan {
     size_t lds_bytes, ws_bytes;
 };
 
-PPlan make_pplan(const Geom &g, const void *Ipk)
+PPlan search_pplan(const Geom &g, const void *Ipk)
 {
     PPlan pl{};
     pl.ok = false;
@@ -1608,6 +1608,12 @@ PPlan make_pplan(const Geom &g, const void *Ipk)
     if ((ceil_div(total_rows, pl.TH) + 8) * (long long)pl.f_tiles > (1LL << 30)) return pl;
     pl.ok = true;
     return pl;
+}
+
+PPlan make_pplan(const Geom &g, const void *Ipk)
+{
+    static thread_local PlanMemo<PPlan> memo;
+    return memo.get(g, (int)(reinterpret_cast<uintptr_t>(Ipk) & 15), [&] { return search_pplan(g, Ipk); });
 }
 
 int compute_units(int dev)

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "xnor.h"
 #include "fp4_expand.hpp"
@@ -13,6 +14,29 @@ namespace xnor {
 struct Geom {
     int N, C, H, W, F, kh, kw, sh, sw, ph, pw;
     int OH, OW, Cw;
+};
+
+// The last few plans made on a thread, by geometry (and one more number: an operand's alignment).  A plan is
+// a function of these alone and costs the host several microseconds where it tries rows and shapes; a call
+// asks for it two to five times.
+template <class V, int N = 16>
+struct PlanMemo {
+    struct Key { Geom g; int extra; };
+    Key key[N];
+    V val[N];
+    int used = 0, next = 0;
+    template <class Make>
+    const V &get(const Geom &g, int extra, Make make)
+    {
+        for (int i = 0; i < used; ++i)
+            if (key[i].extra == extra && memcmp(&key[i].g, &g, sizeof g) == 0) return val[i];
+        const int at = next;
+        val[at] = make();
+        key[at] = Key{g, extra};
+        next = (next + 1) % N;
+        used = used < N ? used + 1 : N;
+        return val[at];
+    }
 };
 
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }

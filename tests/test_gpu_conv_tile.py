@@ -1,0 +1,71 @@
+"""The matrix-core convolution in small independent workgroups (what layers of little work run on), with K,
+with A and in the chained form, at the edges of its pixel tiles, filter groups and operand rings, against
+the oracle: dots and packed words bit for bit, the K and the A form bit for bit the same, fp32 within 1e-5."""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2007_14178_amd.workloads import random_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def xb():
+    from paper_2007_14178_amd import binding
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+#        N   C   H   W   F  kh kw sh sw ph pw
+SHAPES = [
+    (1, 32, 1, 1, 1, 1, 1, 1, 1, 0, 0),          # one step, one pixel, one filter
+    (1, 64, 32, 32, 64, 3, 3, 1, 1, 1, 1),       # nine steps: one turn of the ring and one left
+    (3, 65, 6, 11, 33, 3, 3, 1, 1, 1, 1),        # odd word count (scalar loads), a filter past a tile, tiles across images
+    (5, 100, 37, 53, 75, 3, 3, 1, 1, 1, 1),      # tiles of an image of their own, ragged
+    (2, 96, 27, 27, 130, 5, 5, 1, 1, 2, 2),      # two filter groups, the second nearly empty
+    (9, 128, 7, 7, 300, 3, 3, 1, 1, 1, 1),       # a tile over several images, three groups
+    (40, 64, 3, 2, 40, 2, 2, 1, 1, 1, 0),        # images far smaller than a tile
+    (2, 40, 31, 29, 96, 3, 5, 2, 3, 1, 2),       # strides, non-square window
+    (1, 160, 12, 12, 20, 3, 3, 1, 1, 4, 4),      # windows that are all padding
+    (6, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1),
+    (64, 32, 28, 28, 64, 3, 3, 1, 1, 1, 1),      # many pixels, 64 filters
+    (64, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1),    # 64 x 64 wave tiles, one workgroup per compute unit
+    (128, 384, 13, 13, 384, 1, 1, 1, 1, 0, 0),   # the same, two per unit, six steps
+    (2, 1024, 10, 10, 200, 3, 3, 1, 1, 1, 1),    # deep: much LDS per pixel
+    (1, 32, 4, 250, 40, 1, 3, 1, 1, 0, 1),       # rows wider than a tile
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_tiles_vs_oracle(xb, shape):
+    print(f"case conv tile shape={shape}", flush=True)
+    rng = np.random.default_rng(zlib.crc32(("tile" + str(shape)).encode()))
+    _, I, Wt = random_layer(rng, "t", *shape)
+    s = xb.Shape(*shape)
+    d_ref, K_ref, a_ref, O_ref = oracle.forward(I, Wt, oracle.Shape(*shape))
+    ws = torch.empty((xb.xnor_conv2d_chain_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
+    Ipk, K, A, Wpk, alpha, _ = xb.xnor_prepare(dev(I), dev(Wt), s, workspace=ws)
+    out, dot = xb.xnor_conv2d_fwd_expanded(Ipk, ws, K, alpha, s, want_dot=True)
+    outA, dotA = xb.xnor_conv2d_fwd_expanded(Ipk, ws, None, alpha, s, want_dot=True, A=A)
+    ws2 = torch.full_like(ws, 0x5A)                 # the filters' expansion by its own launch, over other contents
+    xb.xnor_filter_expand(Wpk, s, ws2)
+    out2, _ = xb.xnor_conv2d_fwd_expanded(Ipk, ws2, K, alpha, s)
+    Opk, A_next = xb.xnor_conv2d_fwd_chain(Ipk, None, K, alpha, s, workspace=ws)
+    OpkA, A_nextA = xb.xnor_conv2d_fwd_chain(Ipk, None, None, alpha, s, workspace=ws, A=A)
+    torch.cuda.synchronize()
+    assert np.array_equal(dot.cpu().numpy(), d_ref)
+    assert torch.equal(dotA, dot) and torch.equal(outA, out) and torch.equal(out2, out)
+    got, ref = out.cpu().numpy().astype(np.float64), O_ref.astype(np.float64)
+    floor = (0.5 * np.abs(d_ref.astype(np.float64)) * (a_ref.astype(np.float64)[None, :, None, None] + 1.0) + 1.0) * 2.0 ** -149
+    assert (np.abs(got - ref) <= np.maximum(1e-5 * np.abs(ref), floor)).all()
+    assert np.array_equal(Opk.cpu().numpy().view(np.uint32), oracle.pack(got.astype(np.float32)))
+    assert torch.equal(Opk, OpkA) and torch.equal(A_next, A_nextA)
+    mean = np.abs(got).mean(axis=1)
+    assert (np.abs(A_next.cpu().numpy() - mean) <= np.maximum(1e-5 * mean, 2.0 ** -149)).all()
