@@ -131,14 +131,22 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+# The current stream's handle.  torch.cuda.current_stream() makes a Stream object on the way to it (2.7 us a
+# call, of the 9 us that a call of this module takes); the two functions behind it take 0.1 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dev(t: torch.Tensor, dtype, shape=None, name="tensor") -> int:
-    if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
+    if not t.is_cuda or t.dtype is not dtype or not t.is_contiguous():
         raise TypeError(f"{name}: need a contiguous {dtype} GPU tensor, got {t.dtype} on {t.device}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)} != expected {tuple(shape)}")
     return t.data_ptr()
 
@@ -169,7 +177,7 @@ def xnor_binarize_pack(x: torch.Tensor, packed: torch.Tensor | None = None) -> t
     """x fp32 [N][C][H][W] -> int32-typed tensor of uint32 words [N][H][W][ceil(C/32)]."""
     N, C, H, W = x.shape
     if packed is None:
-        packed = torch.empty((N, H, W, (C + 31) // 32), dtype=torch.int32, device=x.device)
+        packed = x.new_empty((N, H, W, (C + 31) // 32), dtype=torch.int32)
     _ok(lib.xnor_binarize_pack(_dev(x, torch.float32, name="x"), N, C, H, W,
                                _dev(packed, torch.int32, (N, H, W, (C + 31) // 32), "packed"),
                                _stream()), "xnor_binarize_pack")
@@ -181,9 +189,9 @@ def xnor_scale_K(I: torch.Tensor, s: Shape, A_work: torch.Tensor | None = None,
     """Returns (K [N][OH][OW], A [N][H][W])."""
     OH, OW = xnor_out_dim(s)
     if A_work is None:
-        A_work = torch.empty((s.N, s.H, s.W), dtype=torch.float32, device=I.device)
+        A_work = I.new_empty((s.N, s.H, s.W), dtype=torch.float32)
     if K is None:
-        K = torch.empty((s.N, OH, OW), dtype=torch.float32, device=I.device)
+        K = I.new_empty((s.N, OH, OW), dtype=torch.float32)
     _ok(lib.xnor_scale_K(_dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), ctypes.byref(s.c()),
                          _dev(A_work, torch.float32, (s.N, s.H, s.W), "A_work"),
                          _dev(K, torch.float32, (s.N, OH, OW), "K"), _stream()), "xnor_scale_K")
@@ -193,7 +201,7 @@ def xnor_scale_K(I: torch.Tensor, s: Shape, A_work: torch.Tensor | None = None,
 def xnor_alpha(Wt: torch.Tensor, alpha: torch.Tensor | None = None) -> torch.Tensor:
     F, C, kh, kw = Wt.shape
     if alpha is None:
-        alpha = torch.empty((F,), dtype=torch.float32, device=Wt.device)
+        alpha = Wt.new_empty((F,), dtype=torch.float32)
     _ok(lib.xnor_alpha(_dev(Wt, torch.float32, name="Wt"), F, C, kh, kw,
                        _dev(alpha, torch.float32, (F,), "alpha"), _stream()), "xnor_alpha")
     return alpha
@@ -204,11 +212,11 @@ def xnor_input_prepare(I: torch.Tensor, s: Shape, Ipk: torch.Tensor | None = Non
     """One pass over I: returns (Ipk, K, A); with want_K=False K is not computed (returned as None)."""
     OH, OW = xnor_out_dim(s)
     if Ipk is None:
-        Ipk = torch.empty((s.N, s.H, s.W, s.Cw), dtype=torch.int32, device=I.device)
+        Ipk = I.new_empty((s.N, s.H, s.W, s.Cw), dtype=torch.int32)
     if A_work is None:
-        A_work = torch.empty((s.N, s.H, s.W), dtype=torch.float32, device=I.device)
+        A_work = I.new_empty((s.N, s.H, s.W), dtype=torch.float32)
     if K is None and want_K:
-        K = torch.empty((s.N, OH, OW), dtype=torch.float32, device=I.device)
+        K = I.new_empty((s.N, OH, OW), dtype=torch.float32)
     _ok(lib.xnor_input_prepare(_dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), ctypes.byref(s.c()),
                                _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"),
                                _dev(A_work, torch.float32, (s.N, s.H, s.W), "A_work"),
@@ -224,19 +232,18 @@ def xnor_prepare(I: torch.Tensor, Wt: torch.Tensor, s: Shape, Ipk: torch.Tensor 
     """Input side and filter side in one call: returns (Ipk, K or None, A, Wpk, alpha, M).
     With ``workspace`` (uint8, xnor_conv2d_workspace_bytes) the expanded filters are left in it."""
     OH, OW = xnor_out_dim(s)
-    dev = I.device
     if Ipk is None:
-        Ipk = torch.empty((s.N, s.H, s.W, s.Cw), dtype=torch.int32, device=dev)
+        Ipk = I.new_empty((s.N, s.H, s.W, s.Cw), dtype=torch.int32)
     if A_work is None:
-        A_work = torch.empty((s.N, s.H, s.W), dtype=torch.float32, device=dev)
+        A_work = I.new_empty((s.N, s.H, s.W), dtype=torch.float32)
     if K is None and want_K:
-        K = torch.empty((s.N, OH, OW), dtype=torch.float32, device=dev)
+        K = I.new_empty((s.N, OH, OW), dtype=torch.float32)
     if Wpk is None:
-        Wpk = torch.empty((s.F, s.kh, s.kw, s.Cw), dtype=torch.int32, device=dev)
+        Wpk = I.new_empty((s.F, s.kh, s.kw, s.Cw), dtype=torch.int32)
     if M_work is None:
-        M_work = torch.empty((s.F, s.kh, s.kw), dtype=torch.float32, device=dev)
+        M_work = I.new_empty((s.F, s.kh, s.kw), dtype=torch.float32)
     if alpha is None:
-        alpha = torch.empty((s.F,), dtype=torch.float32, device=dev)
+        alpha = I.new_empty((s.F,), dtype=torch.float32)
     _ok(lib.xnor_prepare(_dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
                          ctypes.byref(s.c()), _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"),
                          _dev(A_work, torch.float32, (s.N, s.H, s.W), "A_work"),
@@ -255,11 +262,11 @@ def xnor_filter_prepare(Wt: torch.Tensor, Wpk: torch.Tensor | None = None,
     F, C, kh, kw = Wt.shape
     Cw = (C + 31) // 32
     if Wpk is None:
-        Wpk = torch.empty((F, kh, kw, Cw), dtype=torch.int32, device=Wt.device)
+        Wpk = Wt.new_empty((F, kh, kw, Cw), dtype=torch.int32)
     if M_work is None:
-        M_work = torch.empty((F, kh, kw), dtype=torch.float32, device=Wt.device)
+        M_work = Wt.new_empty((F, kh, kw), dtype=torch.float32)
     if alpha is None:
-        alpha = torch.empty((F,), dtype=torch.float32, device=Wt.device)
+        alpha = Wt.new_empty((F,), dtype=torch.float32)
     _ok(lib.xnor_filter_prepare(_dev(Wt, torch.float32, name="Wt"), F, C, kh, kw,
                                 _dev(Wpk, torch.int32, (F, kh, kw, Cw), "Wpk"),
                                 _dev(M_work, torch.float32, (F, kh, kw), "M_work"),
@@ -268,9 +275,13 @@ def xnor_filter_prepare(Wt: torch.Tensor, Wpk: torch.Tensor | None = None,
 
 
 def xnor_conv2d_workspace_bytes(s: Shape) -> int:
-    n = ctypes.c_size_t()
-    _ok(lib.xnor_conv2d_workspace_bytes(ctypes.byref(s.c()), ctypes.byref(n)), "xnor_conv2d_workspace_bytes")
-    return n.value
+    nbytes = s.__dict__.get("_ws")          # asked on every call: remembered per Shape
+    if nbytes is None:
+        n = ctypes.c_size_t()
+        _ok(lib.xnor_conv2d_workspace_bytes(ctypes.byref(s.c()), ctypes.byref(n)), "xnor_conv2d_workspace_bytes")
+        nbytes = n.value
+        object.__setattr__(s, "_ws", nbytes)
+    return nbytes
 
 
 def xnor_conv2d_pick_algo(s: Shape, workspace_bytes: int = 0) -> int:
@@ -291,12 +302,12 @@ def xnor_conv2d_fwd(Ipk: torch.Tensor, Wpk: torch.Tensor, K: torch.Tensor, alpha
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=Ipk.device)
+        out = Ipk.new_empty(oshape, dtype=torch.float32)
     if dot is None and want_dot:
-        dot = torch.empty(oshape, dtype=torch.int32, device=Ipk.device)
+        dot = Ipk.new_empty(oshape, dtype=torch.int32)
     if isinstance(workspace, str):
         nbytes = xnor_conv2d_workspace_bytes(s)
-        workspace = torch.empty((nbytes,), dtype=torch.uint8, device=Ipk.device) if nbytes else None
+        workspace = Ipk.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
     ws_ptr = _dev(workspace, torch.uint8, name="workspace") if workspace is not None else None
     ws_bytes = workspace.numel() if workspace is not None else 0
     _ok(lib.xnor_conv2d_fwd_algo(
@@ -384,7 +395,7 @@ def xnor_probe_store_beside_mfma(workgroups: int, reps: int, wide: bool, matrix_
 def xnor_filter_expand(Wpk: torch.Tensor, s: Shape, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Per-model half of the matrix-core convolution: fills (and returns) the workspace."""
     if workspace is None:
-        workspace = torch.empty((xnor_conv2d_workspace_bytes(s),), dtype=torch.uint8, device=Wpk.device)
+        workspace = Wpk.new_empty((xnor_conv2d_workspace_bytes(s),), dtype=torch.uint8)
     _ok(lib.xnor_filter_expand(_dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk"), ctypes.byref(s.c()),
                                _dev(workspace, torch.uint8, name="workspace"), workspace.numel(), _stream()),
         "xnor_filter_expand")
@@ -399,9 +410,9 @@ def xnor_conv2d_fwd_expanded(Ipk: torch.Tensor, workspace: torch.Tensor, K: torc
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=Ipk.device)
+        out = Ipk.new_empty(oshape, dtype=torch.float32)
     if dot is None and want_dot:
-        dot = torch.empty(oshape, dtype=torch.int32, device=Ipk.device)
+        dot = Ipk.new_empty(oshape, dtype=torch.int32)
     _ok(lib.xnor_conv2d_fwd_expanded(
         _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"), _dev(workspace, torch.uint8, name="workspace"),
         workspace.numel(), _dev(K, torch.float32, (s.N, OH, OW), "K") if K is not None else None,
@@ -426,9 +437,9 @@ def xnor_forward_image(I: torch.Tensor, Wpk: torch.Tensor, alpha: torch.Tensor, 
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=I.device)
+        out = I.new_empty(oshape, dtype=torch.float32)
     if dot is None and want_dot:
-        dot = torch.empty(oshape, dtype=torch.int32, device=I.device)
+        dot = I.new_empty(oshape, dtype=torch.int32)
     _ok(lib.xnor_forward_image(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk"),
         _dev(alpha, torch.float32, (s.F,), "alpha"), ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),
@@ -459,7 +470,7 @@ def xnor_bwn_conv2d_fwd(I: torch.Tensor, Wpk: torch.Tensor, alpha: torch.Tensor,
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=I.device)
+        out = I.new_empty(oshape, dtype=torch.float32)
     _ok(lib.xnor_bwn_conv2d_fwd_algo(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk"),
         _dev(alpha, torch.float32, (s.F,), "alpha"), ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),
@@ -486,10 +497,10 @@ def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
-        out = torch.empty(oshape, dtype=torch.float32, device=I.device)
+        out = I.new_empty(oshape, dtype=torch.float32)
     if isinstance(workspace, str):
         nbytes = xnor_conv2d_fp32_workspace_bytes(s) if algo == ALGO_AUTO else 0
-        workspace = torch.empty((nbytes,), dtype=torch.uint8, device=I.device) if nbytes else None
+        workspace = I.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
         if algo == ALGO_MFMA_SPLIT:
             _ok(E_UNSUPPORTED, "xnor_conv2d_fp32_fwd[mfma_split] without a workspace")
     _ok(lib.xnor_conv2d_fp32_fwd_ws(
@@ -505,7 +516,7 @@ def xnor_box_filter_K(A: torch.Tensor, s: Shape, K: torch.Tensor | None = None) 
     """K [N][OH][OW] from a given A [N][H][W] (second half of Eq. 10)."""
     OH, OW = xnor_out_dim(s)
     if K is None:
-        K = torch.empty((s.N, OH, OW), dtype=torch.float32, device=A.device)
+        K = A.new_empty((s.N, OH, OW), dtype=torch.float32)
     _ok(lib.xnor_box_filter_K(_dev(A, torch.float32, (s.N, s.H, s.W), "A"), ctypes.byref(s.c()),
                               _dev(K, torch.float32, (s.N, OH, OW), "K"), _stream()), "xnor_box_filter_K")
     return K
@@ -526,13 +537,13 @@ def xnor_conv2d_fwd_chain(Ipk: torch.Tensor, Wpk: torch.Tensor | None, K: torch.
     OH, OW = xnor_out_dim(s)
     Cwn = (s.F + 31) // 32
     if Opk is None:
-        Opk = torch.empty((s.N, OH, OW, Cwn), dtype=torch.int32, device=Ipk.device)
+        Opk = Ipk.new_empty((s.N, OH, OW, Cwn), dtype=torch.int32)
     if A_next is None:
-        A_next = torch.empty((s.N, OH, OW), dtype=torch.float32, device=Ipk.device)
+        A_next = Ipk.new_empty((s.N, OH, OW), dtype=torch.float32)
     if workspace is None:
         if Wpk is None:
             raise ValueError("xnor_conv2d_fwd_chain: without Wpk the workspace with the expanded filters is needed")
-        workspace = torch.empty((xnor_conv2d_chain_workspace_bytes(s),), dtype=torch.uint8, device=Ipk.device)
+        workspace = Ipk.new_empty((xnor_conv2d_chain_workspace_bytes(s),), dtype=torch.uint8)
     _ok(lib.xnor_conv2d_fwd_chain(
         _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"),
         _dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk") if Wpk is not None else None,
