@@ -11,6 +11,17 @@
 
 namespace xnor {
 
+// Blocks go round the eight XCDs by their index, but neighbouring blocks share cache lines (a block's run of
+// a channel plane starts and ends anywhere), and each XCD has an L2 of its own: XCD x takes the x-th eighth
+// of the blocks.  A launch has 8 * ceil(blocks / 8) of them; a surplus one has nothing to do.  (Input pass:
+// 128 x 512 x 28 x 28 39.5 -> 36.3 us, 100 x 512 x 27 x 29 40.4 -> 32.8, 128 x 384 x 13 x 13 12.6 -> 10.5.)
+__device__ inline long long xcd_block(long long launched, long long blocks)
+{
+    const long long eighth = (blocks + 7) >> 3;
+    return (launched & 7) * eighth + (launched >> 3);
+}
+static long long xcd_blocks(long long blocks) { return (blocks + 7) / 8 * 8; }
+
 // ------------------------------------------------------------------------------------------------
 // Step 1a.  One lane owns one pixel and builds WPT packed words from 32*WPT channel planes; the 64
 // lanes of a wave read 64 consecutive pixels of one plane (256 contiguous bytes) per load.
@@ -19,12 +30,23 @@ namespace xnor {
 // ------------------------------------------------------------------------------------------------
 template <int WPT>
 __global__ __launch_bounds__(256) void binarize_pack_kernel(const float *__restrict__ x,
-                                                            long long NP, int C, int HW, int Cw,
+                                                            long long NP, int C, int HW, int Cw, int groups, bool eighths,
                                                             uint32_t *__restrict__ packed)
 {
-    const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-    const int w0 = blockIdx.y * WPT;
-    if (p >= NP) return;
+    // A grid row per group of words, the eighths taken of each (a multiple of 8 blocks a row); or a single
+    // row, the eighths taken of all blocks, so that no XCD gets a block more than its share.
+    const uint32_t blocks = (uint32_t)((NP + 255) / 256);
+    uint32_t g = blockIdx.y, block;
+    if (gridDim.y > 1 || groups == 1) {
+        block = eighths ? (uint32_t)xcd_block(blockIdx.x, blocks) : blockIdx.x;
+    } else {                                              // (below 2^31 blocks: 32-bit division)
+        const uint32_t b = (uint32_t)xcd_block(blockIdx.x, (long long)blocks * groups);
+        g = b / blocks;
+        block = b - g * blocks;
+    }
+    const int w0 = (int)g * WPT;
+    const long long p = (long long)block * 256 + threadIdx.x;
+    if (w0 >= Cw || p >= NP) return;
     const long long n = p / HW;
     const int hw = (int)(p - n * HW);
     const float *src = x + (n * C) * (long long)HW + hw;
@@ -62,13 +84,18 @@ hipError_t launch_binarize_pack(const float *x, int N, int C, int H, int W, uint
     const int HW = H * W, Cw = (C + 31) / 32;
     const long long NP = (long long)N * HW;
     const bool vec4 = (Cw % 4 == 0) && ((reinterpret_cast<uintptr_t>(packed) & 15) == 0);
-    if (vec4) {
-        dim3 grid(ceil_div(NP, 256), Cw / 4);
-        binarize_pack_kernel<4><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, packed);
-    } else {
-        dim3 grid(ceil_div(NP, 256), Cw);
-        binarize_pack_kernel<1><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, packed);
-    }
+    const int groups = vec4 ? Cw / 4 : Cw;                // of words: one per block and pixel
+    const long long pixel_blocks = ceil_div(NP, 256);
+    // (a row per group where the surplus blocks are few)
+    const bool rows = groups == 1 || pixel_blocks >= 512;
+    const long long blocks = rows ? xcd_blocks(pixel_blocks) : xcd_blocks(pixel_blocks * groups);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    // (100 x 512 x 27 x 29 39.5 -> 36.7 us, 16 x 128 x 56 x 56 7.1 -> 6.8; but 128 x 512 x 28 x 28, whose kilobyte runs
+    //  share few lines and do not fit the last-level cache, 42.8 -> 44.6: every block in turn there)
+    const bool eighths = HW % 4 != 0 || NP * C * 4 <= (128LL << 20);
+    const dim3 grid((unsigned)blocks, rows ? groups : 1);
+    if (vec4) binarize_pack_kernel<4><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, groups, eighths, packed);
+    else binarize_pack_kernel<1><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, groups, eighths, packed);
     return hipGetLastError();
 }
 
@@ -86,7 +113,7 @@ __global__ __launch_bounds__(64 * kMaxSlices) void channel_mean_abs_kernel(
 {
     __shared__ double part[kMaxSlices][64];
     const int lane = threadIdx.x, s = threadIdx.y, S = blockDim.y;
-    const long long p = (long long)blockIdx.x * 64 + lane;
+    const long long p = xcd_block(blockIdx.x, (NP + 63) / 64) * 64 + lane;
     double acc = 0.0;
     if (p < NP) {
         const long long n = p / HW;
@@ -121,7 +148,7 @@ hipError_t launch_channel_mean_abs(const float *I, int N, int C, int H, int W, f
     int S = 1;
     while (S < kMaxSlices && C / (2 * S) >= 8) S *= 2;
     const int chunk = (C + S - 1) / S;
-    channel_mean_abs_kernel<<<dim3(ceil_div(NP, 64)), dim3(64, S), 0, st>>>(I, NP, C, HW, chunk, A);
+    channel_mean_abs_kernel<<<dim3((unsigned)xcd_blocks(ceil_div(NP, 64))), dim3(64, S), 0, st>>>(I, NP, C, HW, chunk, A);
     return hipGetLastError();
 }
 
@@ -129,22 +156,49 @@ hipError_t launch_channel_mean_abs(const float *I, int N, int C, int H, int W, f
 // Step 1a and the first half of Eq. 10 in ONE pass over the fp32 tensor: every element is read
 // once, its sign goes into the packed word and its magnitude into the channel sum.  (The paper runs
 // the two as separate kernels on two streams; on an HBM-bound pre-stage the second read is the cost.)
-// Block = 64 pixels x S slices; slice s owns packed words s, s+S, ...  The words are collected in
-// LDS and written out as one contiguous run of 64*Cw words; the slices' partial |x| sums (double)
+// Block = 64 (or 32) pixels x S slices; slice s owns packed words s, s+S, ...  The words are collected in
+// LDS and written out as one contiguous run of words; the slices' partial |x| sums (double)
 // are combined in a fixed order.
 // ------------------------------------------------------------------------------------------------
-// Up to 4 slices: measured equal to 8 and faster than 16 (a 1024-thread block leaves one block per
-// CU and nothing to overlap its final barrier and write-out with).
-constexpr int kPackMeanSlices = 4;
+// At most 16 waves (1024 threads) a block.
+constexpr int kPackMeanWaves = 16;
 
+// Pixels and waves of a block.  A slice's words come one after the other, each with the whole latency of its
+// 32 loads, so a tensor that does not fill the chip's wave slots is bound by that chain: every word gets a
+// slice of its own, up to 16 waves per compute unit, and a tensor of few pixels and many channels blocks of
+// 32 pixels (a wave then takes two words at a time).  Above that the chains overlap with those of other
+// blocks, and fewer, longer slices leave more blocks per unit to cover a block's last barrier and write-out
+// (4 measured equal to 8 and faster than 16).  Input pass, 4 slices of 64 pixels -> this: 64 x 512 x 7 x 7
+// 10.6 -> 6.5 us, 64 x 256 x 14 x 14 6.6 -> 5.4 us.
+struct PackMeanShape { int px, waves; };
+static PackMeanShape pack_mean_shape(long long NP, int Cw)
+{
+    PackMeanShape s;
+    s.px = NP <= 64 * 64 && Cw >= 8 ? 32 : 64;
+    const int per_wave = 64 / s.px;
+    const long long blocks = (NP + s.px - 1) / s.px;
+    auto waves = [&](int rounds) { return ceil_div(ceil_div(Cw, rounds), per_wave); };
+    int rounds = 1;                                       // words of a slice
+    while (waves(rounds) > 4 && (waves(rounds) > kPackMeanWaves || blocks * waves(rounds) > 256 * 16)) ++rounds;
+    s.waves = waves(rounds);
+    return s;
+}
+static size_t pack_mean_smem(const PackMeanShape &s, int Cwp)
+{
+    return (size_t)s.waves * 64 * sizeof(double) + (size_t)s.px * Cwp * sizeof(uint32_t);
+}
+
+template <int PX>
 __device__ __attribute__((always_inline)) void pack_and_mean_block(
     const float *__restrict__ x, long long NP, int C, int HW, int Cw, int Cwp,
     uint32_t *__restrict__ packed, float *__restrict__ A, long long block, double *pm_smem)
 {
-    const int lane = threadIdx.x, s = threadIdx.y, S = blockDim.y;
-    double *part = pm_smem;                                              // [S][64]
-    uint32_t *words = reinterpret_cast<uint32_t *>(pm_smem + S * 64);    // [64][Cwp], Cwp odd
-    const long long p0 = block * 64;
+    // slice = wave * 64 / PX + (which part of the wave)
+    const int tid = threadIdx.y * 64 + threadIdx.x, threads = 64 * blockDim.y;
+    const int lane = tid & (PX - 1), s = tid / PX, S = threads / PX;
+    double *part = pm_smem;                                              // [S][PX]
+    uint32_t *words = reinterpret_cast<uint32_t *>(pm_smem + threads);   // [PX][Cwp], Cwp odd
+    const long long p0 = block * PX;
     const long long p = p0 + lane;
     double acc = 0.0;
     if (p < NP) {
@@ -175,28 +229,30 @@ __device__ __attribute__((always_inline)) void pack_and_mean_block(
             words[lane * Cwp + w] = word;
         }
     }
-    part[s * 64 + lane] = acc;
+    part[tid] = acc;
     __syncthreads();
     if (s == 0 && p < NP) {
         double sum = part[lane];
-        for (int k = 1; k < S; ++k) sum += part[k * 64 + lane];
+        for (int k = 1; k < S; ++k) sum += part[k * PX + lane];
         A[p] = (float)(sum / (double)C);
     }
-    const int npx = (int)min((long long)64, NP - p0);
+    const int npx = (int)min((long long)PX, NP - p0);
     const int nwords = npx * Cw;
     uint32_t *dst = packed + p0 * Cw;
-    for (int i = s * 64 + lane; i < nwords; i += 64 * S) {
+    for (int i = tid; i < nwords; i += threads) {
         const int px = i / Cw, w = i - px * Cw;
         dst[i] = words[px * Cwp + w];
     }
 }
 
-__global__ __launch_bounds__(64 * kPackMeanSlices) void pack_and_mean_kernel(
+template <int PX>
+__global__ __launch_bounds__(64 * kPackMeanWaves) void pack_and_mean_kernel(
     const float *__restrict__ x, long long NP, int C, int HW, int Cw, int Cwp,
     uint32_t *__restrict__ packed, float *__restrict__ A)
 {
     extern __shared__ double pm_smem[];
-    pack_and_mean_block(x, NP, C, HW, Cw, Cwp, packed, A, blockIdx.x, pm_smem);
+    const long long nb = (NP + PX - 1) / PX, block = xcd_block(blockIdx.x, nb);
+    if (block < nb) pack_and_mean_block<PX>(x, NP, C, HW, Cw, Cwp, packed, A, block, pm_smem);
 }
 
 // The same pass with four consecutive pixels per lane (one 16-byte load per lane and channel, 1 KB
@@ -305,7 +361,8 @@ __global__ __launch_bounds__(64 * kPack4Slices) void pack_and_mean4_kernel(
     uint32_t *__restrict__ packed, float *__restrict__ A, int ppb)
 {
     extern __shared__ double pm_smem[];
-    pack_and_mean4_block(x, NP, C, HW, Cw, Cwp, packed, A, blockIdx.x, ppb, pm_smem);
+    const long long nb = (NP + ppb - 1) / ppb, block = xcd_block(blockIdx.x, nb);
+    if (block < nb) pack_and_mean4_block(x, NP, C, HW, Cw, Cwp, packed, A, block, ppb, pm_smem);
 }
 
 // Pixels per block of the four-pixel pass.  A compute unit pulls from HBM at a rate of its own
@@ -353,16 +410,15 @@ hipError_t launch_pack_and_mean(const float *x, int N, int C, int H, int W, uint
         const size_t smem4 = (size_t)S4 * 256 * sizeof(double) + (size_t)256 * Cwp * sizeof(uint32_t);
         if (smem4 <= 64 * 1024) {
             const int ppb = pixels_per_block4(NP);
-            pack_and_mean4_kernel<<<dim3(ceil_div(NP, ppb)), dim3(64, S4), smem4, st>>>(x, NP, C, HW, Cw,
+            pack_and_mean4_kernel<<<dim3((unsigned)xcd_blocks(ceil_div(NP, ppb))), dim3(64, S4), smem4, st>>>(x, NP, C, HW, Cw,
                                                                                       Cwp, packed, A, ppb);
             return hipGetLastError();
         }
     }
-    int S = 1;
-    while (S < kPackMeanSlices && 2 * S <= Cw) S *= 2;
-    const size_t smem = (size_t)S * 64 * sizeof(double) + (size_t)64 * Cwp * sizeof(uint32_t);
-    pack_and_mean_kernel<<<dim3(ceil_div(NP, 64)), dim3(64, S), smem, st>>>(x, NP, C, HW, Cw, Cwp,
-                                                                           packed, A);
+    const PackMeanShape s = pack_mean_shape(NP, Cw);
+    const dim3 grid((unsigned)xcd_blocks(ceil_div(NP, s.px))), block(64, s.waves);
+    if (s.px == 32) pack_and_mean_kernel<32><<<grid, block, pack_mean_smem(s, Cwp), st>>>(x, NP, C, HW, Cw, Cwp, packed, A);
+    else pack_and_mean_kernel<64><<<grid, block, pack_mean_smem(s, Cwp), st>>>(x, NP, C, HW, Cw, Cwp, packed, A);
     return hipGetLastError();
 }
 
@@ -502,29 +558,34 @@ __global__ __launch_bounds__(64 * kPack4Slices) void prepare_both_kernel(
     float *__restrict__ M, float *__restrict__ alpha, uint4 *__restrict__ Wx, ExpandLayout L, int ppb)
 {
     extern __shared__ double both_smem[];
-    const long long nb_in = (NP + ppb - 1) / ppb;
-    if ((long long)blockIdx.x < nb_in)
-        pack_and_mean4_block(x, NP, C, HW, Cw, Cwp, packed, A, blockIdx.x, ppb, both_smem);
-    else
-        filter_pack_mean_block(Wt, C, taps, Cw, CH, Wpk, M, alpha, (int)(blockIdx.x - nb_in),
+    const long long nb_in = (NP + ppb - 1) / ppb, first_filter = (nb_in + 7) / 8 * 8;
+    if ((long long)blockIdx.x < first_filter) {
+        const long long block = xcd_block(blockIdx.x, nb_in);
+        if (block < nb_in) pack_and_mean4_block(x, NP, C, HW, Cw, Cwp, packed, A, block, ppb, both_smem);
+    } else
+        filter_pack_mean_block(Wt, C, taps, Cw, CH, Wpk, M, alpha, (int)(blockIdx.x - first_filter),
                                threadIdx.y * 64 + threadIdx.x, 64 * blockDim.y, both_smem, Wx, L, F);
 }
 
-// The same with the one-pixel-per-lane input pass (64 pixels per block): for inputs whose H*W is not
+// The same with the one-pixel-per-lane input pass (64 or 32 pixels per block): for inputs whose H*W is not
 // a multiple of 4, that are not 16-byte aligned, or that are too small to fill the chip with
-// 256-pixel blocks.
-__global__ __launch_bounds__(64 * kPackMeanSlices) void prepare_both1_kernel(
+// 256-pixel blocks.  A filter's chain (read, pack, sums, expansion) is as long as the whole input side of
+// such a layer and has to run beside it, so the filter blocks go first where that leaves the input room.
+template <int PX>
+__global__ __launch_bounds__(64 * kPackMeanWaves) void prepare_both1_kernel(
     const float *__restrict__ x, long long NP, int C, int HW, int Cw, int Cwp,
     uint32_t *__restrict__ packed, float *__restrict__ A,
     const float *__restrict__ Wt, int F, int taps, int CH, uint32_t *__restrict__ Wpk,
-    float *__restrict__ M, float *__restrict__ alpha, uint4 *__restrict__ Wx, ExpandLayout L)
+    float *__restrict__ M, float *__restrict__ alpha, uint4 *__restrict__ Wx, ExpandLayout L, bool filters_first)
 {
     extern __shared__ double both_smem[];
-    const long long nb_in = (NP + 63) / 64;
-    if ((long long)blockIdx.x < nb_in)
-        pack_and_mean_block(x, NP, C, HW, Cw, Cwp, packed, A, blockIdx.x, both_smem);
-    else
-        filter_pack_mean_block(Wt, C, taps, Cw, CH, Wpk, M, alpha, (int)(blockIdx.x - nb_in),
+    const long long nb_in = (NP + PX - 1) / PX, nb_launched = (nb_in + 7) / 8 * 8;
+    const int f = filters_first ? (int)blockIdx.x : (int)(blockIdx.x - nb_launched);
+    if (f < 0 || f >= F) {
+        const long long block = xcd_block(filters_first ? blockIdx.x - F : blockIdx.x, nb_in);
+        if (block < nb_in) pack_and_mean_block<PX>(x, NP, C, HW, Cw, Cwp, packed, A, block, both_smem);
+    } else
+        filter_pack_mean_block(Wt, C, taps, Cw, CH, Wpk, M, alpha, f,
                                threadIdx.y * 64 + threadIdx.x, 64 * blockDim.y, both_smem, Wx, L, F);
 }
 
@@ -566,6 +627,7 @@ static size_t filter_block_smem(int C, int taps, bool expand, int *CH_out)
 static int prepare_both_pass(const float *x, int N, int C, int H, int W, int taps, bool expand)
 {
     const int Cw = (C + 31) / 32, Cwp = Cw | 1;
+    const long long NP = (long long)N * H * W;
     if (Cw > 512 || taps > 256) return 0;
     int CH;
     const size_t smemf = filter_block_smem(C, taps, expand, &CH);
@@ -575,11 +637,9 @@ static int prepare_both_pass(const float *x, int N, int C, int H, int W, int tap
         if (smem4 <= 64 * 1024) return 4;
     }
     // (the one-pixel pass: the filter block gives every tap a thread of its own)
-    int S = 1;
-    while (S < kPackMeanSlices && 2 * S <= Cw) S *= 2;
-    if (64 * S < taps) return 0;
-    const size_t smem1 = (size_t)kPackMeanSlices * 64 * sizeof(double) + (size_t)64 * Cwp * sizeof(uint32_t);
-    return smem1 <= 64 * 1024 ? 1 : 0;
+    const PackMeanShape s = pack_mean_shape(NP, Cw);
+    if (64 * s.waves < taps) return 0;
+    return pack_mean_smem(s, Cwp) <= 64 * 1024 ? 1 : 0;
 }
 
 bool prepare_both_supports(const float *x, int N, int C, int H, int W, int taps)
@@ -604,21 +664,26 @@ hipError_t launch_prepare_both(const float *x, int N, int C, int H, int W, uint3
         const size_t smem4 = (size_t)kPack4Slices * 256 * sizeof(double) + (size_t)256 * Cwp * sizeof(uint32_t);
         const size_t smem = std::max(smem4, smemf);
         const int ppb = pixels_per_block4(NP, F);
-        const long long blocks = (long long)F + ceil_div(NP, ppb);
+        const long long blocks = (long long)F + xcd_blocks(ceil_div(NP, ppb));
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
         prepare_both_kernel<<<dim3((unsigned)blocks), dim3(64, kPack4Slices), smem, st>>>(
             x, NP, C, HW, Cw, Cwp, packed, A, Wt, F, taps, CH, Wpk, M, alpha, static_cast<uint4 *>(Wx), L, ppb);
         return hipGetLastError();
     }
     if (pass != 1) return hipErrorInvalidValue;   // (prepare_both_supports said no)
-    int S = 1;
-    while (S < kPackMeanSlices && 2 * S <= Cw) S *= 2;
-    const size_t smem1 = (size_t)S * 64 * sizeof(double) + (size_t)64 * Cwp * sizeof(uint32_t);
-    const size_t smem = std::max(smem1, smemf);
-    const long long blocks = (long long)F + ceil_div(NP, 64);
+    const PackMeanShape s = pack_mean_shape(NP, Cw);
+    const size_t smem = std::max(pack_mean_smem(s, Cwp), smemf);
+    const long long blocks = (long long)F + xcd_blocks(ceil_div(NP, s.px));
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    prepare_both1_kernel<<<dim3((unsigned)blocks), dim3(64, S), smem, st>>>(
-        x, NP, C, HW, Cw, Cwp, packed, A, Wt, F, taps, CH, Wpk, M, alpha, static_cast<uint4 *>(Wx), L);
+    // (in half of the chip's wave slots at most, and for inputs of up to 64 MB: 64 x 128 x 28 x 28 F=256 8.8 -> 7.7 us,
+    //  128 x 96 x 27 x 27 F=256 5x5 12.0 -> 11.2; with F=384 blocks of 768 threads 11.9 -> 14.5, at 160 MB 35.1 -> 36.3)
+    const bool filters_first = (long long)F * 64 * s.waves <= 256 * 1024 && NP * C * 4 <= (64LL << 20);
+    auto launch = [&](auto kernel) {
+        kernel<<<dim3((unsigned)blocks), dim3(64, s.waves), smem, st>>>(
+            x, NP, C, HW, Cw, Cwp, packed, A, Wt, F, taps, CH, Wpk, M, alpha, static_cast<uint4 *>(Wx), L, filters_first);
+    };
+    if (s.px == 32) launch(prepare_both1_kernel<32>);
+    else launch(prepare_both1_kernel<64>);
     return hipGetLastError();
 }
 
@@ -635,15 +700,18 @@ __global__ __launch_bounds__(256) void box_filter_K_kernel(const float *__restri
     const int oy = (int)(t % g.OH);
     const long long n = t / g.OH;
     const float *a = A + n * (long long)g.H * g.W;
+    // no branches around the loads (out-of-image taps read the image's first value and add 0), so that the
+    // unrolled loop has nine of them in flight: a chain of kh * kw load latencies otherwise
     double sum = 0.0;
-    for (int ky = 0; ky < g.kh; ++ky) {
-        const int iy = oy * g.sh - g.ph + ky;
-        if (iy < 0 || iy >= g.H) continue;
-        for (int kx = 0; kx < g.kw; ++kx) {
-            const int ix = ox * g.sw - g.pw + kx;
-            if (ix < 0 || ix >= g.W) continue;
-            sum += (double)a[iy * g.W + ix];
-        }
+    const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
+    int ky = 0, kx = 0;
+#pragma unroll 9
+    for (int t2 = 0; t2 < g.kh * g.kw; ++t2) {
+        const int iy = iy0 + ky, ix = ix0 + kx;
+        const bool in = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+        const float v = a[in ? iy * g.W + ix : 0];
+        sum += in ? (double)v : 0.0;
+        if (++kx == g.kw) { kx = 0; ++ky; }
     }
     K[o] = (float)(sum / (double)(g.kh * g.kw));
 }
