@@ -28,25 +28,25 @@ static long long xcd_blocks(long long blocks) { return (blocks + 7) / 8 * 8; }
 // The paper sets bits one by one in a register per spatial tile (Alg. 1); packing along channels
 // instead gives every bit of every word a use in the convolution.
 // ------------------------------------------------------------------------------------------------
-template <int WPT>
+template <int WPT, bool ROWS>
 __global__ __launch_bounds__(256) void binarize_pack_kernel(const float *__restrict__ x,
-                                                            long long NP, int C, int HW, int Cw, int groups, bool eighths,
+                                                            long long NP, int C, int HW, int Cw, int groups,
                                                             uint32_t *__restrict__ packed)
 {
     // A grid row per group of words, the eighths taken of each (a multiple of 8 blocks a row); or a single
     // row, the eighths taken of all blocks, so that no XCD gets a block more than its share.
     const uint32_t blocks = (uint32_t)((NP + 255) / 256);
     uint32_t g = blockIdx.y, block;
-    if (gridDim.y > 1 || groups == 1) {
-        block = eighths ? (uint32_t)xcd_block(blockIdx.x, blocks) : blockIdx.x;
+    if (ROWS) {
+        block = (uint32_t)xcd_block(blockIdx.x, blocks);
     } else {                                              // (below 2^31 blocks: 32-bit division)
         const uint32_t b = (uint32_t)xcd_block(blockIdx.x, (long long)blocks * groups);
-        g = b / blocks;
+        g = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b / blocks));   // (a quotient is a vector register otherwise)
         block = b - g * blocks;
     }
     const int w0 = (int)g * WPT;
     const long long p = (long long)block * 256 + threadIdx.x;
-    if (w0 >= Cw || p >= NP) return;
+    if ((!ROWS && w0 >= Cw) || p >= NP) return;
     const long long n = p / HW;
     const int hw = (int)(p - n * HW);
     const float *src = x + (n * C) * (long long)HW + hw;
@@ -90,12 +90,10 @@ hipError_t launch_binarize_pack(const float *x, int N, int C, int H, int W, uint
     const bool rows = groups == 1 || pixel_blocks >= 512;
     const long long blocks = rows ? xcd_blocks(pixel_blocks) : xcd_blocks(pixel_blocks * groups);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    // (100 x 512 x 27 x 29 39.5 -> 36.7 us, 16 x 128 x 56 x 56 7.1 -> 6.8; but 128 x 512 x 28 x 28, whose kilobyte runs
-    //  share few lines and do not fit the last-level cache, 42.8 -> 44.6: every block in turn there)
-    const bool eighths = HW % 4 != 0 || NP * C * 4 <= (128LL << 20);
     const dim3 grid((unsigned)blocks, rows ? groups : 1);
-    if (vec4) binarize_pack_kernel<4><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, groups, eighths, packed);
-    else binarize_pack_kernel<1><<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, groups, eighths, packed);
+    auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(x, NP, C, HW, Cw, groups, packed); };
+    if (vec4) rows ? launch(binarize_pack_kernel<4, true>) : launch(binarize_pack_kernel<4, false>);
+    else rows ? launch(binarize_pack_kernel<1, true>) : launch(binarize_pack_kernel<1, false>);
     return hipGetLastError();
 }
 
