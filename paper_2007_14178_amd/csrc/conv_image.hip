@@ -232,6 +232,153 @@ __global__ __launch_bounds__(kThreads) void conv_image_kernel(ImageParams p)
     }
 }
 
+// One channel, one filter, the paper's own workload, with "same" padding along x and 16-byte rows: a lane owns
+// four neighbouring columns, which it loads and stores 16 bytes at a time.  The K - 1 columns on either side
+// of its four are its neighbour lanes' (a wave shift of the registers) or, at the wave's ends, one more load that
+// serves the first and the last lane.  Rows slide down as in conv_image_kernel: a window is K * K bits, a
+// new row shifts in from the top.  Bound by memory (4 bytes read and 4 written per pixel): a quarter of the
+// load instructions and of the address arithmetic of one column per lane.  Sums and roundings are those
+// of conv_image_kernel: the same results bit for bit.
+struct Row4Params {
+    const float *I;
+    const uint32_t *Wpk;
+    const float *alpha;
+    float *out;
+    int32_t *dot;
+    int H, W, OH, ph;
+    int rows_per_band, bands, xtiles;
+    long long waves;
+    float kscale;
+};
+
+// lane l gets lane l - 1's (l + 1's) value; the wave's first (last) lane gets `end`
+__device__ inline float from_left(float v, float end)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(end), __float_as_uint(v), 0x138, 0xf, 0xf, false));
+}
+__device__ inline float from_right(float v, float end)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(end), __float_as_uint(v), 0x130, 0xf, 0xf, false));
+}
+
+template <int K>
+__global__ __launch_bounds__(kThreads) void conv_image_row4_kernel(Row4Params p)
+{
+    constexpr int R = K / 2, NV = 4 + 2 * R, D = 4;       // halo columns on a side, columns under a lane, rows ahead
+    constexpr uint32_t kRow = (1u << K) - 1u;
+    const int lane = threadIdx.x & 63;
+    const long long gw = (long long)blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (gw >= p.waves) return;
+    const int xt = __builtin_amdgcn_readfirstlane((int)(gw % p.xtiles));
+    const long long t = gw / p.xtiles;
+    const int band = __builtin_amdgcn_readfirstlane((int)(t % p.bands));
+    const int n = __builtin_amdgcn_readfirstlane((int)(t / p.bands));
+    const int x = xt * 256 + 4 * lane;
+    const bool mine = x < p.W;
+    // the extra column: the first lane's left ones, the last lane's right ones
+    const int xe = lane == 0 ? x - 1 : x + 4, de = lane == 0 ? -1 : 1;
+    const bool edge = lane == 0 || lane == 63;
+
+    uint32_t wf = 0;                                      // the filter's window in the window's bit order
+#pragma unroll
+    for (int r = 0; r < K * K; ++r) wf |= (p.Wpk[r] & 1u) << r;
+    const float a0 = p.alpha[0];
+    uint32_t row_mask[4], full[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        row_mask[j] = 0;
+#pragma unroll
+        for (int kx = 0; kx < K; ++kx) row_mask[j] |= (unsigned)(x + j - R + kx) < (unsigned)p.W ? 1u << kx : 0u;
+        full[j] = 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) full[j] |= row_mask[j] << (r * K);
+    }
+
+    const int y0 = band * p.rows_per_band, y1 = min(p.OH, y0 + p.rows_per_band);
+    const int nin = y1 - y0 + K - 1, yb = y0 - p.ph;
+    const float *img = p.I + (long long)n * p.H * p.W;
+    float4 own[D];
+    float ext[D][R];
+    auto issue = [&](int slot, int i) __attribute__((always_inline)) {
+        const int y = yb + i;
+        const bool rv = i < nin && y >= 0 && y < p.H;     // (uniform)
+        own[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < R; ++k) ext[slot][k] = 0.f;
+        if (!rv) return;
+        const float *row = img + (long long)y * p.W;
+        if (mine) own[slot] = *reinterpret_cast<const float4 *>(row + x);
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if (edge && (unsigned)(xe + k * de) < (unsigned)p.W) ext[slot][k] = row[xe + k * de];
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(d, d);
+
+    uint32_t win[4] = {0, 0, 0, 0};
+    float hs[K][4];
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hs[r][j] = 0.f;
+    for (int i0 = 0; i0 < nin; i0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int i = i0 + d;
+            if (i >= nin) break;
+            float v[NV];
+            v[R] = own[d].x; v[R + 1] = own[d].y; v[R + 2] = own[d].z; v[R + 3] = own[d].w;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                v[R - 1 - k] = from_left(v[R + 3 - k], ext[d][k]);
+                v[R + 4 + k] = from_right(v[R + k], ext[d][k]);
+            }
+            issue(d, i + D);
+            uint32_t bits = 0;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) bits |= v[k] >= 0.f ? 1u << k : 0u;
+#pragma unroll
+            for (int r = 0; r + 1 < K; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) hs[r][j] = hs[r + 1][j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // (a column outside the image is 0 and adds nothing; its bit is masked)
+                float s = 0.f;
+#pragma unroll
+                for (int kx = 0; kx < K; ++kx) s += fabsf(v[j + kx]);
+                hs[K - 1][j] = s;
+                win[j] = (win[j] >> K) | (((bits >> j) & kRow) << (K * (K - 1)));
+            }
+            if (i < K - 1) continue;
+            const int y = y0 + i - (K - 1), top = y - p.ph;
+            uint32_t rows_in = (1u << (K * K)) - 1u;      // (uniform) the window rows inside the image
+            if (top < 0 || top + K > p.H) {
+                rows_in = 0;
+#pragma unroll
+                for (int r = 0; r < K; ++r) rows_in |= top + r >= 0 && top + r < p.H ? kRow << (r * K) : 0u;
+            }
+            float o[4];
+            int dd[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t m = full[j] & rows_in;
+                float ksum = hs[0][j];
+#pragma unroll
+                for (int r = 1; r < K; ++r) ksum += hs[r][j];
+                const float kk = ksum * p.kscale;
+                dd[j] = __builtin_popcount(m) - 2 * __builtin_popcount((win[j] ^ wf) & m);
+                o[j] = (float)dd[j] * (kk * a0);
+            }
+            if (mine) {
+                const long long at = ((long long)n * p.OH + y) * p.W + x;
+                *reinterpret_cast<float4 *>(p.out + at) = make_float4(o[0], o[1], o[2], o[3]);
+                if (p.dot) *reinterpret_cast<int4 *>(p.dot + at) = make_int4(dd[0], dd[1], dd[2], dd[3]);
+            }
+        }
+    }
+}
+
 // Several filters: a workgroup takes a tile of output pixels and all filters (or a group of them).
 //   1. The input under the tile is read once, coalesced.  The 64 signs of a wave's 64 neighbouring
 //      pixels of a channel are one compare (its result mask is the row's bit map), the sum of the
@@ -577,6 +724,30 @@ hipError_t launch_conv_image(const float *I, const uint32_t *Wpk, const float *a
             case 5: return launch_tile_k<5>(I, Wpk, alpha, g, out, dot, pl, st);
             default: return launch_tile_k<7>(I, Wpk, alpha, g, out, dot, pl, st);
         }
+    }
+    // Four columns per lane from half a million pixels on; a smaller image is bound by latency and wants its rows
+    // spread over more waves.  Measured, one column / four: 4096^2 33.2 / 24.7 us, 2048^2 13.3 / 9.4 (5 x 5: 16.9 /
+    // 11.4), 1024^2 6.0 / 5.0, 4 x 300 x 500 5.2 / 4.7, 512^2 3.9 / 4.5, 256^2 3.9 / 4.4.
+    const uintptr_t ptrs = reinterpret_cast<uintptr_t>(I) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(dot);
+    if (g.F == 1 && g.C == 1 && g.sh == 1 && g.sw == 1 && (g.kw == 3 || g.kw == 5) && g.pw == g.kw / 2 && g.W % 4 == 0 &&
+        (ptrs & 15) == 0 && (long long)g.N * g.OH * g.W >= (1 << 19)) {
+        Row4Params p;
+        p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out; p.dot = dot;
+        p.H = g.H; p.W = g.W; p.OH = g.OH; p.ph = g.ph;
+        p.xtiles = ceil_div(g.W, 256);
+        // bands of 32 rows, halved until every SIMD has two waves, down to 4 (see the band heights below)
+        int rows = 32;
+        auto waves_with = [&](int r) { return (long long)g.N * p.xtiles * ceil_div(g.OH, r); };
+        while (rows > 4 && waves_with(rows) < 256LL * 4 * 2) rows /= 2;
+        p.rows_per_band = std::max(1, std::min(rows, g.OH));
+        p.bands = ceil_div(g.OH, p.rows_per_band);
+        p.waves = waves_with(p.rows_per_band);
+        p.kscale = 1.0f / (float)(g.kh * g.kw);
+        const long long blocks = (p.waves + kWaves - 1) / kWaves;
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        if (g.kw == 3) conv_image_row4_kernel<3><<<dim3((unsigned)blocks), dim3(kThreads), 0, st>>>(p);
+        else conv_image_row4_kernel<5><<<dim3((unsigned)blocks), dim3(kThreads), 0, st>>>(p);
+        return hipGetLastError();
     }
     ImageParams p;
     p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out; p.dot = dot;

@@ -49,3 +49,33 @@ def test_tiles_values_that_are_not_numbers(xb):  # noqa: F811
     under[19:22, 19:22] = True
     assert torch.equal(torch.isnan(out2), under.expand_as(out2))
     assert torch.equal(out[..., ~under], out2[..., ~under]) and torch.equal(dot2, dot3)
+
+
+#   N  C   H    W   F  k  pad: one channel, one filter, rows of whole 16 bytes, half a million pixels and more
+ROW4 = [
+    (1, 1, 131072, 4, 1, 3, 1),         # one lane per row: both neighbours are the image's edge
+    (1, 1, 2051, 256, 1, 3, 1),         # one wave per row, the last band short
+    (3, 1, 700, 260, 1, 3, 1),          # a lane past the wave's 256 columns
+    (2, 1, 261, 1020, 1, 5, 2),         # two columns from either side
+    (150000, 1, 1, 4, 1, 5, 2),         # images lower than the window
+    (1, 1, 1300, 508, 1, 5, 2),
+]
+
+
+@pytest.mark.parametrize("shape", ROW4, ids=lambda s: "x".join(map(str, s)))
+def test_four_columns_per_lane_vs_oracle(xb, shape):  # noqa: F811
+    print(f"case image row4 shape={shape}", flush=True)
+    run_case(xb, shape, "row4")
+
+
+def test_four_columns_per_lane_match_one_column(xb):  # noqa: F811
+    """The same image at an address that is no multiple of 16 goes through the one-column kernel: bit for bit the same."""
+    s = xb.Shape(1, 1, 800, 1024, 1, 3, 3, 1, 1, 1, 1)
+    I = torch.randn((1, 1, 800, 1024), generator=torch.Generator().manual_seed(4)).cuda()
+    Wpk, alpha, _ = xb.xnor_filter_prepare(torch.randn((1, 1, 3, 3), generator=torch.Generator().manual_seed(5)).cuda())
+    shifted = torch.empty(800 * 1024 + 1, device="cuda")[1:].view(1, 1, 800, 1024)
+    shifted.copy_(I)
+    a, da = xb.xnor_forward_image(I, Wpk, alpha, s, want_dot=True)
+    b, db = xb.xnor_forward_image(shifted, Wpk, alpha, s, want_dot=True)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and torch.equal(da, db)
