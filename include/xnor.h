@@ -65,12 +65,14 @@ typedef enum {
     XNOR_ALGO_AUTO = 0,     /* pick per shape (what xnor_conv2d_fwd does)                         */
     XNOR_ALGO_DIRECT = 1,   /* one thread per output, v_xor + v_bcnt, any shape                   */
     XNOR_ALGO_TILED = 2,    /* LDS-staged packed halo, wave-uniform filter words, register tile   */
-    XNOR_ALGO_MFMA = 3,     /* +-1 expanded to FP4 in LDS, v_mfma_f32_32x32x64_f8f6f4: persistent
-                               workgroups where the shape allows, else as XNOR_ALGO_MFMA_BANDS    */
+    XNOR_ALGO_MFMA = 3,     /* +-1 expanded to FP4 in LDS, v_mfma_f32_32x32x64_f8f6f4: many small
+                               workgroups for layers of little work, else persistent ones where the
+                               shape allows, else as XNOR_ALGO_MFMA_BANDS                         */
     XNOR_ALGO_MFMA_BANDS = 4, /* the same arithmetic with one workgroup per band of output rows
                                (xnor_conv2d_fwd_algo only; tests and measurements)                */
-    XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo only: the fp32 input split exactly into
-                               three bf16 terms, v_mfma_f32_32x32x16_bf16 against +-1 weights     */
+    XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split exactly into three bf16
+                               terms, v_mfma_f32_32x32x16_bf16 against +-1 weights;
+                               xnor_conv2d_fp32_fwd_ws: both operands split so, six products        */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
