@@ -169,21 +169,22 @@ constexpr int kPackMeanWaves = 16;
 // (4 measured equal to 8 and faster than 16).  Input pass, 4 slices of 64 pixels -> this: 64 x 512 x 7 x 7
 // 10.6 -> 6.5 us, 64 x 256 x 14 x 14 6.6 -> 5.4 us.
 struct PackMeanShape { int px, waves; };
+static size_t pack_mean_smem(const PackMeanShape &s, int Cwp)
+{
+    return (size_t)s.waves * 64 * sizeof(double) + (size_t)s.px * Cwp * sizeof(uint32_t);
+}
 static PackMeanShape pack_mean_shape(long long NP, int Cw)
 {
     PackMeanShape s;
     s.px = NP <= 64 * 64 && Cw >= 8 ? 32 : 64;
     const int per_wave = 64 / s.px;
     const long long blocks = (NP + s.px - 1) / s.px;
-    auto waves = [&](int rounds) { return ceil_div(ceil_div(Cw, rounds), per_wave); };
-    int rounds = 1;                                       // words of a slice
-    while (waves(rounds) > 4 && (waves(rounds) > kPackMeanWaves || blocks * waves(rounds) > 256 * 16)) ++rounds;
-    s.waves = waves(rounds);
-    return s;
-}
-static size_t pack_mean_smem(const PackMeanShape &s, int Cwp)
-{
-    return (size_t)s.waves * 64 * sizeof(double) + (size_t)s.px * Cwp * sizeof(uint32_t);
+    for (int rounds = 1;; ++rounds) {                     // words of a slice
+        s.waves = ceil_div(ceil_div(Cw, rounds), per_wave);
+        // (more than four waves only in the 64 KB of LDS that need no raised limit)
+        if (s.waves <= 4 || (s.waves <= kPackMeanWaves && blocks * s.waves <= 256 * 16 && pack_mean_smem(s, Cw | 1) <= 64 * 1024))
+            return s;
+    }
 }
 
 template <int PX>
