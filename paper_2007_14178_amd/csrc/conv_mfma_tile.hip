@@ -363,7 +363,8 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
                     const int row = 8 * (r >> 2) + (r & 3);               // (+ 4 * kg)
                     const float o = acc[i][j][r] * (kv[j] * al[r]);
                     word |= (o >= 0.f ? 1u : 0u) << row;
-                    sum += (double)fabsf(o);                              // (filters past the last: alpha 0)
+                    // (filters that exist only: past the last one alpha is 0, but an infinite K makes that NaN)
+                    sum += row + 4 * kg < nfilt ? (double)fabsf(o) : 0.0;
                 }
                 word <<= 4 * kg;
                 word |= (uint32_t)__shfl_xor((int)word, 32);

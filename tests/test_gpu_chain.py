@@ -132,3 +132,37 @@ def test_two_chained_layers(xb):
     assert np.array_equal(dot2.cpu().numpy(), d2_ref)
     assert_rel(K2.cpu().numpy(), K2_ref, "K of layer 2", rtol=3e-5)
     assert_rel(out2.cpu().numpy(), O2_ref, "output of layer 2", rtol=3e-5)
+
+
+def chained(xb, I, Wt, shape):
+    """Opk and A_next of one layer: the form that is given K, checked equal to the one that is given A."""
+    s = xb.Shape(*shape)
+    Ipk, K, A = xb.xnor_input_prepare(dev(I), s)
+    Wpk, alpha, _ = xb.xnor_filter_prepare(dev(Wt))
+    Opk, A_next = xb.xnor_conv2d_fwd_chain(Ipk, Wpk, K, alpha, s)
+    Opk2, A_next2 = xb.xnor_conv2d_fwd_chain(Ipk, Wpk, None, alpha, s, A=A)
+    torch.cuda.synchronize()
+    A_next = A_next.cpu().numpy()
+    assert torch.equal(Opk, Opk2) and np.array_equal(A_next, A_next2.cpu().numpy(), equal_nan=True)
+    return Opk.cpu().numpy().view(np.uint32), A_next
+
+
+@pytest.mark.parametrize("F", [9, 33, 75, 130])
+def test_infinite_K_and_a_partly_filled_filter_tile(xb, F):
+    """An infinity in the input makes K infinite under it: every output there is +-inf (an odd number of
+    channels and taps, so no dot is 0), their signs are those of the dots and their mean is inf, whatever
+    the kernel holds in the rows of a filter tile past the last filter.  A pixel under a NaN: NaN, signs 0."""
+    shape = (2, 33, 12, 11, F, 3, 3, 1, 1, 1, 1)
+    print(f"case chain infinite K F={F}", flush=True)
+    rng = np.random.default_rng(F)
+    _, I, Wt = random_layer(rng, "t", *shape)
+    I[0, 7, 5, 5], I[0, 8, 5, 5], I[1, 3, 6, 2] = np.inf, -np.inf, np.nan
+    with np.errstate(all="ignore"):
+        _, _, _, O = oracle.forward(I, Wt, oracle.Shape(*shape))
+        A_ref = oracle.channel_mean_abs(O)
+    assert np.isinf(A_ref[0, 4:7, 4:7]).all() and np.isnan(A_ref[1, 5:8, 1:4]).all()
+    Opk, A_next = chained(xb, I, Wt, shape)
+    assert np.array_equal(Opk, oracle.pack(O))
+    assert np.array_equal(np.isinf(A_next), np.isinf(A_ref)) and np.array_equal(np.isnan(A_next), np.isnan(A_ref))
+    fine = np.isfinite(A_ref)
+    assert_rel(A_next[fine], A_ref[fine], "channel mean of |out|")
