@@ -765,11 +765,13 @@ struct Route {
     ExpandLayout L;
     size_t ws_bytes;     // enough for any of them, so that a caller's one workspace serves whatever variant it asks for
     int sum_parts;       // partial sums of |out| per pixel that the chained epilogue leaves for chain_mean_kernel
+    int sum_scale;       // ... each divided by this
 };
 
 Route find_route(const Geom &g)
 {
     Route r{};
+    r.sum_scale = 1;
     const ExpandLayout Lb = bands_expand_layout(g);
     if (conv_mfma_persistent_supports(g) && (conv_mfma_persistent_preferred(g) || !Lb.ok)) {
         r.kind = kPersistent;
@@ -791,6 +793,7 @@ Route find_route(const Geom &g)
             r.L = Lt;
             r.ws_bytes = std::max(r.ws_bytes, Lt.ws_bytes);
             r.sum_parts = conv_mfma_tile_sum_parts(g);
+            r.sum_scale = conv_mfma_tile_sum_scale(g);
         }
     }
     return r;
@@ -912,15 +915,15 @@ hipError_t launch_conv_mfma_expanded_from_A(const uint32_t *Ipk, const float *A,
 }
 
 // Eq. 10's channel mean for the next layer from the partial sums over groups of filters:
-// A[pix] = sum_t P[pix][t] / F
+// A[pix] = sum_t P[pix][t] / (F / the scale of the sums)
 __global__ __launch_bounds__(256) void chain_mean_kernel(const float *__restrict__ P, long long npix,
-                                                         int f_tiles, int F, float *__restrict__ A)
+                                                         int f_tiles, double filters, float *__restrict__ A)
 {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= npix) return;
     double sum = 0.0;
     for (int t = 0; t < f_tiles; ++t) sum += (double)P[i * f_tiles + t];
-    A[i] = (float)(sum / (double)F);
+    A[i] = (float)(sum / filters);
 }
 
 size_t conv_mfma_chain_workspace_bytes(const Geom &g)
@@ -943,7 +946,8 @@ hipError_t launch_conv_mfma_chain(const uint32_t *Ipk, const uint32_t *Wpk, cons
     e = launch_mfma(Ipk, K, A, alpha, g, nullptr, nullptr, Opk, P, workspace, st);   // K or A, the other null
     if (e != hipSuccess) return e;
     const long long npix = (long long)g.N * g.OH * g.OW;
-    chain_mean_kernel<<<ceil_div(npix, 256), 256, 0, st>>>(P, npix, route_of(g).sum_parts, g.F, A_next);
+    const Route &r = route_of(g);
+    chain_mean_kernel<<<ceil_div(npix, 256), 256, 0, st>>>(P, npix, r.sum_parts, (double)g.F / r.sum_scale, A_next);
     return hipGetLastError();
 }
 

@@ -55,6 +55,7 @@ hipError_t launch_conv_mfma_persistent(const uint32_t *Ipk, const float *K, cons
 bool conv_mfma_tile_preferred(const Geom &g);          // takes the shape and is expected to be the faster kernel
 ExpandLayout conv_mfma_tile_expand_layout(const Geom &g);
 int conv_mfma_tile_sum_parts(const Geom &g);
+int conv_mfma_tile_sum_scale(const Geom &g);            // its partial sums are stored divided by this
 hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                                  const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,
                                  const void *workspace, hipStream_t st);

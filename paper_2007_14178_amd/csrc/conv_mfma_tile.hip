@@ -354,32 +354,39 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
                 const float4 v = *reinterpret_cast<const float4 *>(&Al[(wf * NF + i) * 32 + 2 * r + 4 * kg]);
                 al[r] = v.x; al[r + 1] = v.y; al[r + 2] = v.z; al[r + 3] = v.w;
             }
+            auto filter_tile = [&](auto whole) __attribute__((always_inline)) {
+                // (filters that exist only: past the last one alpha is 0, but an infinite K makes that NaN)
+                constexpr bool WHOLE = decltype(whole)::value;
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                uint32_t word = 0;
-                double sum = 0.0;
+                for (int j = 0; j < NP; ++j) {
+                    uint32_t word = 0;
+                    double sum = 0.0;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + (r & 3);               // (+ 4 * kg)
-                    const float o = acc[i][j][r] * (kv[j] * al[r]);
-                    word |= (o >= 0.f ? 1u : 0u) << row;
-                    // (filters that exist only: past the last one alpha is 0, but an infinite K makes that NaN)
-                    sum += row + 4 * kg < nfilt ? (double)fabsf(o) : 0.0;
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = 8 * (r >> 2) + (r & 3);           // (+ 4 * kg)
+                        const float o = acc[i][j][r] * (kv[j] * al[r]);
+                        word |= (o >= 0.f ? 1u : 0u) << row;
+                        sum += (double)(WHOLE || row + 4 * kg < nfilt ? fabsf(o) : 0.f);
+                    }
+                    word <<= 4 * kg;
+                    word |= (uint32_t)__shfl_xor((int)word, 32);
+                    if (!WHOLE) word &= (1u << nfilt) - 1u;
+                    total[j] += sum;
+                    if (kg == 0 && opix[j] >= 0)
+                        p.Opk[(long long)(p0 + (wp * NP + j) * 32 + l32) * p.Cwn + (ft >> 5)] = word;
                 }
-                word <<= 4 * kg;
-                word |= (uint32_t)__shfl_xor((int)word, 32);
-                if (nfilt < 32) word &= (1u << nfilt) - 1u;
-                total[j] += sum;
-                if (kg == 0 && opix[j] >= 0)
-                    p.Opk[(long long)(p0 + (wp * NP + j) * 32 + l32) * p.Cwn + (ft >> 5)] = word;
-            }
+            };
+            if (nfilt >= 32) filter_tile(std::true_type{});
+            else filter_tile(std::false_type{});
         }
         const int part = fgrp * WF + wf;
         if (f0 + wf * NF * 32 < p.F) {
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
                 const double sum = total[j] + __shfl_xor(total[j], 32);
-                if (kg == 0 && opix[j] >= 0) p.P[(long long)(p0 + (wp * NP + j) * 32 + l32) * p.parts + part] = (float)sum;
+                // (as the mean of the sums over 32 filters: a larger one would leave fp32's range sooner than they do)
+                if (kg == 0 && opix[j] >= 0)
+                    p.P[(long long)(p0 + (wp * NP + j) * 32 + l32) * p.parts + part] = (float)(sum * (1.0 / NF));
             }
         }
     } else {
@@ -593,6 +600,8 @@ int conv_mfma_tile_sum_parts(const Geom &g)
     const TPlan &pl = make_tplan(g);
     return pl.ok ? ceil_div(g.F, 32 * pl.NF) : 0;
 }
+
+int conv_mfma_tile_sum_scale(const Geom &g) { return make_tplan(g).NF; }
 
 hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                                  const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,

@@ -166,3 +166,20 @@ def test_infinite_K_and_a_partly_filled_filter_tile(xb, F):
     assert np.array_equal(np.isinf(A_next), np.isinf(A_ref)) and np.array_equal(np.isnan(A_next), np.isnan(A_ref))
     fine = np.isfinite(A_ref)
     assert_rel(A_next[fine], A_ref[fine], "channel mean of |out|")
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 14, 14, 256, 1, 1, 1, 1, 0, 0), (64, 128, 28, 28, 256, 1, 1, 1, 1, 0, 0),
+                                   (1, 64, 32, 32, 64, 1, 1, 1, 1, 0, 0)], ids=lambda s: "x".join(map(str, s)))
+def test_outputs_whose_sum_over_64_filters_overflows(xb, shape):
+    """Magnitudes around 6e36: any 32 filters' sum is a finite fp32 value and so is the mean, the sum of 64 is not."""
+    print(f"case chain large outputs shape={shape}", flush=True)
+    rng = np.random.default_rng(3)
+    N, C, H, W, F = shape[:5]
+    I = np.where(rng.random((N, C, H, W)) < 0.5, -1.0, 1.0).astype(np.float32) * np.float32(8e35 * 8 / C ** 0.5)
+    Wt = np.where(rng.random((F, C, 1, 1)) < 0.5, -1.0, 1.0).astype(np.float32)
+    _, _, _, O = oracle.forward(I, Wt, oracle.Shape(*shape))
+    sums = np.abs(O.astype(np.float64)).reshape(N, F // 32, 32, H, W).sum(axis=2)
+    assert sums.max() < 3.4e38 and (sums[:, 0] + sums[:, 1]).max() > 3.5e38
+    Opk, A_next = chained(xb, I, Wt, shape)
+    assert np.array_equal(Opk, oracle.pack(O))
+    assert_rel(A_next, np.abs(O.astype(np.float64)).mean(axis=1), "channel mean of |out|")
