@@ -72,7 +72,7 @@ typedef enum {
                                (xnor_conv2d_fwd_algo only; tests and measurements)                */
     XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split exactly into three bf16
                                terms, v_mfma_f32_32x32x16_bf16 against +-1 weights;
-                               xnor_conv2d_fp32_fwd_ws: both operands split so, six products        */
+                               xnor_conv2d_fp32_fwd_ws: both operands split so, eight products      */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
@@ -329,9 +329,9 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
 
 /*
  * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
- * both operands split exactly into three bf16 terms and the six products of them that reach the last
- * bit of an fp32 product summed in fp32 by the bf16 matrix instruction.  Results are as close to the
- * exact sum as those of the fp32 matrix instruction; infinities and NaN come out as fp32 arithmetic
+ * both operands split exactly into three bf16 terms and eight of their nine products (all but the
+ * one below 2^-32 of the whole) summed in fp32 by the bf16 matrix instruction.  Results are closer to the
+ * exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32 arithmetic
  * gives them, and an output so small that values below the bf16 instruction's normal range could
  * matter to it is formed by the plain fp32 sum.
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the

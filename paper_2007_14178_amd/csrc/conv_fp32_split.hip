@@ -1,30 +1,37 @@
 // Real-valued fp32 convolution (the float comparison of Sec. IV, Table I) on the bf16 matrix
 // instruction.  Both operands are split into three bf16 terms, x = hi + mid + lo, each the nearest
 // bf16 to what the terms before it left over (3 x 8 significand bits hold all 24 of an fp32, both
-// differences are exact), and six of the nine products are summed in fp32:
-//     x*w ~ hi*hi + hi*mid + mid*hi + mid*mid + hi*lo + lo*hi.
-// The three left out are below 2^-25 of |x*w| and of either sign, less than the rounding of the
-// product to fp32.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each) do the work of eight
-// v_mfma_f32_32x32x2_f32 (64 cycles each), and the accumulator is rounded six times per sixteen
-// channels instead of eight: measured against 64-bit sums the result is no further off (see the
-// dispatch rule in xnor_api.hip for both kernels' figures).
+// differences are exact: |mid| <= 2^-8, |lo| <= 2^-17 of x's leading bit), and eight of the nine products
+// are summed in fp32.  The one left out, lo*lo, is below 2^-32 of |x*w|: less than the others' sum is
+// rounded by.
+//
+// What the sum loses.  The eight products of a (tap, 16 channels) step form a chain of their own that
+// starts at zero, small products first, and joins the output's sum in one addition: the large sum is
+// rounded once per 16 terms (the fp32 matrix instruction rounds it once per two, and six products in one
+// chain with it were no better).  The bf16 instruction shifts what it adds to the exponent of the
+// largest and drops the rest towards minus infinity, which left every output the same amount too low
+// (0.27e-6 of their root mean square for 7 x 7 x 416 terms): the weights of every other chain are therefore
+// stored negated and its sum is subtracted.  Measured against 64-bit sums over layers of 32 to 512 channels,
+// 1 x 1 to 7 x 7: 0.17 to 0.57 of the error of the kernels that run without a workspace, for values of
+// either sign as for positive ones.
 //
 //   split_filters_kernel: filters -> the A operands of the convolution in its order, into the
 //   caller's workspace, 6 bytes per weight: [filter tile of 32][chunk of 16 channels][tap][term]
 //   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7).
-//   conv_fp32_split_kernel: workgroup = 4 waves = 128 filters x up to 6 tiles of 32 output pixels of
-//   one image (64 filters x up to 12 tiles for layers of at most 64 filters); wave = 64 filters x up
-//   to three tiles.  Per chunk of 16 channels the input under the pixels is fetched a chunk ahead,
+//   conv_fp32_split_kernel: workgroup = 4 waves = 128 filters x up to 4 tiles of 32 output pixels of
+//   one image (64 filters x up to 8 tiles for layers of at most 64 filters); wave = 64 filters x up
+//   to two tiles (a third one's accumulators would leave no registers for the chains).  Per chunk of 16 channels the input under the pixels is fetched a chunk ahead,
 //   split and staged in LDS as [position][term][16 channels] (112 bytes a position: sixteen lanes'
 //   16-byte reads at consecutive positions touch distinct banks), zero outside the image; a B
-//   operand is one 16-byte LDS read per lane and feeds four matrix instructions on average, an A operand is
-//   one 16-byte load per lane from the L2, a tap ahead, and feeds six.
+//   operand is one 16-byte LDS read per lane and feeds more than five matrix instructions on average, an A operand
+//   is one 16-byte load per lane from the L2, a tap ahead, and feeds as many.
+//   Bound by the matrix instructions: 128 x 512 x 28 x 28 F=512 3x3 takes 3.11 ms, 2.70 of them at their rate
+//   (six products in one chain: 2.24 ms, at three times the error).
 //
 // FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
-// chains, a long chain of matrix instructions would be the less exact of the two.  This form keeps two
-// accumulators per output: the matrix instructions sum four taps of a chunk (24 instructions), then that
-// sum is added to the other accumulator and what the addition rounded off is where the next four taps
-// start from.
+// chains, that is still the less exact of the two.  This form keeps two accumulators per output: the
+// matrix instructions sum two taps of a chunk, then that sum is added to the other accumulator and what the
+// addition rounded off is where the next chain starts from (0.43 of the error of one thread per output).
 //
 // What the bf16 instruction does differently from the fp32 one is put right at the end: an output
 // that came out infinite or NaN (an input that is not finite, a term that overflowed, or a sum that
@@ -48,12 +55,12 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int kThreads = 256;
 constexpr int kChan = 16;              // channels per chunk = the reduction length of one matrix instruction
 constexpr int kPosBytes = 112;         // 3 terms x 32 bytes + 16: see above
-// granules (8 channels of one position) a thread fetches ahead per chunk; pixel tiles per wave.  The form
-// with short chains (see FLUSH) holds two accumulators per output and has fewer registers for both.
+// Granules (8 channels of one position) a thread fetches ahead per chunk.  The form with short chains (see
+// FLUSH) holds two accumulators per output and has fewer registers for them.
 constexpr int gran(bool flush) { return flush ? 3 : 4; }
-constexpr int wave_tiles(bool flush) { return flush ? 2 : 3; }
+constexpr int kWaveTiles = 2;          // pixel tiles per wave
 constexpr int max_pos(bool flush) { return gran(flush) * 128; }   // staged positions of a workgroup
-constexpr int kFlushTaps = 4;
+constexpr int chain_taps(bool flush) { return flush ? 2 : 1; }   // taps of a chunk in a chain
 constexpr int kMaxTaps = 49;           // 7 x 7; the filter pass holds 32 x 8 channels x taps in LDS
 constexpr int kOperandBytes = 3 * 1024;   // the three A operands of a (filter tile, chunk, tap)
 constexpr size_t kLdsShared = 80 * 1024;  // two workgroups per compute unit
@@ -98,7 +105,7 @@ __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
 // one run in memory), then per (tap, filter) eight values from LDS, split, and three 16-byte writes of
 // 32 lanes side by side.  HBM-bound: 4 bytes read and 6 written per weight.
 __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__restrict__ Wt, int F, int C, int taps,
-                                                                 int nchunks, int ftiles, unsigned char *__restrict__ Wx)
+                                                                 int nchunks, int ftiles, int chain_taps, unsigned char *__restrict__ Wx)
 {
     extern __shared__ float wl[];
     __shared__ uint32_t stat[2];
@@ -127,10 +134,11 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
     unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * kOperandBytes + (oc & 1) * 512;
     for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
         const int f = i & 31, t = i >> 5;
+        const float sgn = (((oc >> 1) * taps + t) / chain_taps) & 1 ? -1.f : 1.f;    // (every other chain: see above)
         uint32_t h[4], m[4], l[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            float a = wl[f * pitch + (2 * k) * taps + t], b = wl[f * pitch + (2 * k + 1) * taps + t];
+            float a = sgn * wl[f * pitch + (2 * k) * taps + t], b = sgn * wl[f * pitch + (2 * k + 1) * taps + t];
             h[k] = pack_bf16(a, b);
             subtract_pair(a, b, h[k]);
             m[k] = pack_bf16(a, b);
@@ -212,7 +220,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         base[j] = ((oy - oy0) * p.sh * p.pitch + (ox * p.sw - p.pw - ix0)) * kPosBytes + half * 16;
     }
 
-    floatx16 acc[2][NT > 0 ? NT : 1], sum[2][FLUSH && NT > 0 ? NT : 1];
+    floatx16 acc[2][NT > 0 ? NT : 1], sum[2][FLUSH && NT > 0 ? NT : 1], tapsum[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -222,7 +230,16 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 acc[i][j][r] = 0.f;
                 if (FLUSH) sum[i][j][r] = 0.f;
             }
-    int chain = kFlushTaps;                      // taps until the next flush
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tapsum[1][r] = 0.f;
+    float sgn = FLUSH ? 1.f : -1.f;              // of the current chain's weights (plain form: turned at the head of a tap)
+    int chain = chain_taps(true);                // FLUSH: taps until the next flush
+    // plain form: a step's products with filter tile i join the output's sum
+    auto settle = [&](int i, int j, float sign) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = fmaf(sign, tapsum[i][r], acc[i][j][r]);
+    };
+    // FLUSH: a chain joins the output's sum, what the addition rounds off starts the next one
     auto flush = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -230,10 +247,11 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             for (int j = 0; j < NT; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const float s = sum[i][j][r] + acc[i][j][r];
-                    acc[i][j][r] -= s - sum[i][j][r];
+                    const float s = fmaf(sgn, acc[i][j][r], sum[i][j][r]);
+                    acc[i][j][r] = fmaf(sgn, s - sum[i][j][r], -acc[i][j][r]);
                     sum[i][j][r] = s;
                 }
+        sgn = -sgn;
     };
     constexpr int kGran = gran(FLUSH);
 
@@ -364,7 +382,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         const bool more = ch + 1 < p.nchunks;
         int pc = more ? 0 : kPieces;                     // the next piece of chunk ch + 1 to commit
         if constexpr (NT > 0) {
-            // The flat sequence of (tap, pixel tile) steps, twelve matrix instructions each; a step's
+            // The flat sequence of (tap, pixel tile) steps, sixteen matrix instructions each; a step's
             // three B operands are read one step ahead, and the chunk's first steps carry one piece
             // of the next chunk's commit each.
             const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
@@ -383,12 +401,22 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 read3(bn, next_off);
                 __builtin_amdgcn_sched_barrier(0);
                 auto unit = [&](auto m_c) __attribute__((always_inline)) {
-                    constexpr int M = decltype(m_c)::value, P = M >> 1;
-                    // hi*hi, mid*hi, hi*mid, lo*hi, mid*mid, hi*lo
-                    constexpr int ta = P == 0 ? 0 : P == 1 ? 1 : P == 2 ? 0 : P == 3 ? 2 : P == 4 ? 1 : 0;
-                    constexpr int tb = P == 0 ? 0 : P == 1 ? 0 : P == 2 ? 1 : P == 3 ? 0 : P == 4 ? 1 : 2;
-                    acc[M & 1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8, a[M & 1][ta]), __builtin_bit_cast(bf16x8, bc[tb]), acc[M & 1][j], 0, 0, 0);
+                    // filter tile and product of the M-th instruction: the tiles' chains run side by side, the
+                    // first tile's one instruction ahead
+                    constexpr int M = decltype(m_c)::value;
+                    constexpr int i = M == 0 ? 0 : M == 15 ? 1 : (M & 1) ^ 1, P = M == 0 ? 0 : M == 15 ? 7 : i ? (M >> 1) - 1 : (M + 1) >> 1;
+                    // mid*lo, lo*mid, lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
+                    constexpr int ta = P == 0 ? 1 : P == 1 ? 2 : P == 2 ? 2 : P == 3 ? 0 : P == 4 ? 1 : P == 5 ? 1 : 0;
+                    constexpr int tb = P == 0 ? 2 : P == 1 ? 1 : P == 2 ? 0 : P == 3 ? 2 : P == 4 ? 1 : P == 5 ? 0 : P == 6 ? 1 : 0;
+                    const bf16x8 fa = __builtin_bit_cast(bf16x8, a[i][ta]), xb = __builtin_bit_cast(bf16x8, bc[tb]);
+                    if constexpr (FLUSH) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, xb, acc[i][j], 0, 0, 0);
+                    } else {
+                        const floatx16 none = {};
+                        tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, xb, P == 0 ? none : tapsum[i], 0, 0, 0);
+                        if constexpr (M == 1) settle(1, j > 0 ? j - 1 : NT - 1, j > 0 ? sgn : -sgn);   // (of the step before)
+                        if constexpr (M == 15) settle(0, j, sgn);
+                    }
                     if constexpr (S >= 0) commit_unit(piece_c, m_c, ch + 1);
                     __builtin_amdgcn_sched_barrier(0);
                 };
@@ -404,6 +432,10 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 unit(std::integral_constant<int, 9>{});
                 unit(std::integral_constant<int, 10>{});
                 unit(std::integral_constant<int, 11>{});
+                unit(std::integral_constant<int, 12>{});
+                unit(std::integral_constant<int, 13>{});
+                unit(std::integral_constant<int, 14>{});
+                unit(std::integral_constant<int, 15>{});
 #pragma unroll
                 for (int t = 0; t < 3; ++t) bc[t] = bn[t];
             };
@@ -413,16 +445,16 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
 #pragma unroll
                 for (int t = 0; t < 3; ++t) { a[0][t] = an[0][t]; a[1][t] = an[1][t]; }
                 load_next();
+                if constexpr (!FLUSH) sgn = -sgn;
                 const bool wrap = kx + 1 == p.kw, further = tap + 1 < taps;
                 const int off_n = further ? off + (wrap ? row_step : kPosBytes) : off;
                 kx = wrap ? 0 : kx + 1;
                 step(std::integral_constant<int, (FIRST >= 0 && FIRST < kPieces) ? FIRST : -1>{}, 0, NT > 1 ? base[NT > 1 ? 1 : 0] + off : base[0] + off_n);
-                if constexpr (NT > 1) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 1 < kPieces) ? FIRST + 1 : -1>{}, 1, NT > 2 ? base[NT > 2 ? 2 : 0] + off : base[0] + off_n);
-                if constexpr (NT > 2) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 2 < kPieces) ? FIRST + 2 : -1>{}, 2, base[0] + off_n);
-                static_assert(NT <= 3, "one line per step");
+                if constexpr (NT > 1) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 1 < kPieces) ? FIRST + 1 : -1>{}, 1, base[0] + off_n);
+                static_assert(NT <= 2, "one line per step");
                 off = off_n;
                 if constexpr (FLUSH)
-                    if (--chain == 0) { flush(); chain = kFlushTaps; }
+                    if (--chain == 0) { flush(); chain = chain_taps(true); }
             };
             int tap = 0;
             if (more) {
@@ -443,6 +475,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         if (pc < kPieces) commit_rest(pc, ch + 1);       // what the chunk's steps did not carry
         __syncthreads();                                 // chunk ch has been read, chunk ch + 1 is written
     }
+
+    if constexpr (!FLUSH && NT > 0) settle(1, NT - 1, sgn);
 
     // Below which magnitude an output is doubtful.  A term below 2^-126 is flushed: with nothing staged
     // or weighted below 2^-50 that takes a product below 2^-116, no concern.  Otherwise the flushed terms
@@ -488,7 +522,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const float v = FLUSH ? sum[i][j][r] + acc[i][j][r] : acc[i][j][r];
+                    const float v = FLUSH ? fmaf(sgn, acc[i][j][r], sum[i][j][r]) : acc[i][j][r];
                     if (f < p.F) {
                         dst[(size_t)f * OHW + px] = v;
                         if (!(fabsf(v) >= doubtful && fabsf(v) <= 3.402823466e38f)) again[j] |= 1u << (16 * i + r);
@@ -498,7 +532,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     }
 #pragma unroll 1
     for (int j = 0; j < NT; ++j) {
-        uint32_t bits = j == 0 ? again[0] : j == 1 ? again[NT > 1 ? 1 : 0] : again[NT > 2 ? 2 : 0];
+        uint32_t bits = j == 0 ? again[0] : again[NT > 1 ? 1 : 0];
         while (bits) {
             const int b = __builtin_ctz(bits);
             bits &= bits - 1;
@@ -550,10 +584,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitP
     switch (my_nt) {
         case 0: split_wave<0, FLUSH>(p, n, 0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
         case 1: split_wave<1, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-        case 2: split_wave<2, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-        default:
-            if constexpr (!FLUSH) split_wave<3, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0);
-            break;
+        default: split_wave<2, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
     }
 }
 
@@ -597,7 +628,7 @@ Plan search_plan(const Geom &g)
     //  per output otherwise)
     pl.flush = !conv_fp32_mfma_supports(g);
     pl.fwaves = g.F <= 64 ? 1 : 2;
-    const int wps = 4 / pl.fwaves, most = wps * wave_tiles(pl.flush);
+    const int wps = 4 / pl.fwaves, most = wps * kWaveTiles;
     const long long maxpos = max_pos(pl.flush);
     const long long fgroups = ceil_div(g.F, 64 * pl.fwaves);
     const int cus = compute_units();
@@ -693,7 +724,7 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t filter_lds = (size_t)32 * ((8 * taps) | 1) * sizeof(float);
     split_filters_kernel<<<dim3((unsigned)(p.ftiles * 2 * p.nchunks)), dim3(kThreads), filter_lds, st>>>(
-        Wt, g.F, g.C, taps, p.nchunks, p.ftiles, static_cast<unsigned char *>(workspace));
+        Wt, g.F, g.C, taps, p.nchunks, p.ftiles, chain_taps(pl.flush), static_cast<unsigned char *>(workspace));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return pl.flush ? launch_form<true>(p, (unsigned)blocks, pl.lds, st) : launch_form<false>(p, (unsigned)blocks, pl.lds, st);
