@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in xnor.h: argument validation, geometry, kernel choice.
 // Nothing here allocates or synchronises; every call enqueues on the caller's stream.
+#include <algorithm>
 #include <atomic>
 #include <stdio.h>
 #include <string.h>
@@ -52,18 +53,33 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
     return XNOR_ALGO_DIRECT;
 }
 
-// Where the three-term kernel is the faster real-valued convolution (given a workspace) and no less
-// exact.  Measured, fp32 matrix form -> split (relative error against 64-bit sums in brackets):
-// 128x512x28x28 F=512 3x3 5105 -> 2215 us (1.16e-6 -> 1.05e-6), 16x128x56x56 F=128 5x5 1702 -> 245 us
-// (9.7e-7 -> 8.7e-7), one 8-channel 3x3 layer of 8 x 96 x 96 28.2 -> 26.6 us (1.48e-7 -> 1.36e-7); with
-// 4 channels the padding to 16 costs exactness (1.06e-7 -> 1.34e-7), and with a reduction of 8 terms the
-// second launch costs time (10.2 -> 15.1 us).  What the fp32 matrix form does not take (large windows)
-// ran one thread per output: 16x128x56x56 F=128 7x7 22.07 -> 0.53 ms (1.67e-7 -> 1.43e-7), three channels
-// 16x224x224 F=64 7x7 stride 2 1020 -> 293 us (1.33e-7 -> 1.01e-7).
+// Where the three-term kernel is the faster real-valued convolution (given a workspace).  It is the more
+// exact one everywhere (see conv_fp32_split.hip).  Measured, what runs without a workspace -> split:
+// 128x512x28x28 F=512 3x3 5.11 -> 3.11 ms, 16x128x56x56 F=128 5x5 1702 -> 304 us, 7x7 22.04 -> 0.68 ms,
+// 16x224x224 three channels F=64 7x7 stride 2 1020 -> 359 us.  A launch that does not fill the chip is as long as a
+// workgroup's chain of 16-channel chunks behind a filter pass and a first fetch of 12 to 14 us, and this decides:
+//  * against the fp32 matrix form, whose chain is 8 channels a chunk.  With its four-wide filter fetch (C % 8 == 0,
+//    up to 9 taps) 3 x 3 layers of 2 x 32 x 32 take 8.7 / 13 / 22 / 40 us with 8 / 16 / 32 / 64 channels (split 18 /
+//    19 / 23 / 32), without it 25 us with 9 (split 18); on larger layers the split form wins from 32 channels on
+//    at 16 x 28 x 28 (29.3 / 25.8) and from 8 on at 32 x 56 x 56 (44.8 / 34.2);
+//  * against one thread per output, for windows that form does not take: there the estimates below hold within
+//    a third over 1x7x7 .. 16x112x112, C = 3 .. 128, F = 8 .. 128, 7 x 7.
 bool fp32_split_pays(const xnor::Geom &g)
 {
-    if (g.F < 8 || (long long)g.C * g.kh * g.kw < 72) return false;
-    return g.C >= 8 || (g.C >= 3 && !xnor::conv_fp32_mfma_supports(g));
+    const double taps = (double)g.kh * g.kw, red = g.C * taps, pixels = (double)g.N * g.OH * g.OW;
+    if (g.F < 8 || red < 72) return false;
+    if (xnor::conv_fp32_mfma_supports(g)) {
+        if (g.C < 8) return false;
+        if (g.C % 8 != 0 || taps > 9 || g.C >= 40) return true;
+        const double rounds = pixels * xnor::ceil_div(g.F, 128);
+        return (g.C >= 32 && rounds >= 12000) || rounds * red >= 7e6;
+    }
+    if (g.C < 3) return false;
+    const double chunks = xnor::ceil_div(g.C, 16);
+    const double direct_us = g.C <= 4 ? 10 + 3.2e-7 * pixels * g.F * red
+                                      : std::max(5 + 0.075 * red, 14 + 2.8e-7 * pixels * g.F * red);
+    const double split_us = 12 + taps * chunks * (0.5 + 1.1e-5 * pixels * xnor::ceil_div(g.F, 64));
+    return direct_us > split_us;
 }
 
 // The expanded filters of xnor_conv2d_fwd_static live here instead of in a caller's workspace.
