@@ -332,8 +332,8 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
  * both operands split exactly into three bf16 terms and eight of their nine products (all but the
  * one below 2^-32 of the whole) summed in fp32 by the bf16 matrix instruction.  Results are closer to the
  * exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32 arithmetic
- * gives them, and an output so small that values below the bf16 instruction's normal range could
- * matter to it is formed by the plain fp32 sum.
+ * gives them, and an output so small that bits of a value below bf16's range could matter to it is
+ * formed by the plain fp32 sum.
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes

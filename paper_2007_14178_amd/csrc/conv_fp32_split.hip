@@ -33,11 +33,12 @@
 // matrix instructions sum two taps of a chunk, then that sum is added to the other accumulator and what the
 // addition rounded off is where the next chain starts from (0.43 of the error of one thread per output).
 //
-// What the bf16 instruction does differently from the fp32 one is put right at the end: an output
-// that came out infinite or NaN (an input that is not finite, a term that overflowed, or a sum that
-// really does) is computed again by the plain fp32 sum, and so is one that is so small that terms
-// flushed to zero below 2^-126 could matter to it (only where an input or weight below 2^-50 was
-// seen, see `doubtful`).
+// What the split cannot hold goes by the fp32 matrix instruction instead (plain_tiles), a wave's outputs at
+// a time: all outputs of a workgroup that stages an infinity, a NaN or a value whose first term
+// overflows (it leaves the loop at the chunk that has one), outputs that came out infinite or NaN, and
+// outputs so small that bits of a value below 2^-133, bf16's last one, could matter to them (only
+// where an input or weight below 2^-110 was seen, see `doubtful`).  The instructions themselves keep subnormals.
+// A launch whose every output goes that way: see plain_tiles.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -82,8 +83,9 @@ struct Fp32SplitParams {
 };
 
 constexpr uint32_t kTinyBit = 0x80000000u;
-constexpr float kTiny = 8.8817841970012523e-16f;          // 2^-50
-constexpr float kDoubt = 2.5243548967072378e-29f;         // 2^-95
+constexpr float kTiny = 0x1p-110f;
+constexpr float kDoubt = 0x1p-104f;
+constexpr uint32_t kHuge = 0x7f7f8000u << 1;              // (doubled bits) from here on bf16 rounds to infinity
 
 __device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
 uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
@@ -156,28 +158,128 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
     }
 }
 
-// One output by the plain sum: fp32 products, per tap over the channels, then over the taps.
-__device__ float plain_output(const Fp32SplitParams &p, int n, int f, int oy, int ox)
+// The outputs of a wave's tiles by the plain sum, on the fp32 matrix instruction: per tap chains of 32
+// channels, each added to the output's sum where the tap is inside the image (an infinite weight over padding adds
+// nothing).  `put(i, j, r, v)` takes the value of accumulator register r of filter tile i and pixel tile j.
+//   The filters come from the workspace, hi + mid + lo, which is the weight again; a lane whose weights are not
+//   all held there (infinite, NaN, too large for bf16 or so small that bits are missing) reads its own from the
+//   layer's filters.  32 x 256 x 28 x 28 F=256 3x3 takes 0.25 ms, with one NaN in the input 0.41, all NaN 0.57, with
+//   filters of 1e-36 among the others 0.89 (0.45 for any without a workspace; 15 to 36 ms where lanes formed
+//   such outputs one by one).  The operands of a (tap, chunk) step are loaded a step ahead: a lane of half h holds channels
+//   8 h .. 8 h + 7 of the chunk, and a matrix instruction takes one of either half.
+template <int NT, bool FLUSH, class Pixel, class Put>
+__device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams &p, int n, int f0, Pixel pixel_of, Put put)
 {
-    const size_t HW = (size_t)p.H * p.W;
-    const int taps = p.kh * p.kw;
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int HW = p.H * p.W, taps = p.kh * p.kw;
     const float *img = p.I + (size_t)n * p.C * HW;
-    const float *flt = p.Wt + (size_t)f * p.C * taps;
-    float acc = 0.f;
-    for (int t = 0; t < taps; ++t) {
-        const int ky = t / p.kw, iy = oy * p.sh - p.ph + ky, ix = ox * p.sw - p.pw + t - ky * p.kw;
-        if ((unsigned)iy >= (unsigned)p.H || (unsigned)ix >= (unsigned)p.W) continue;
-        const float *src = img + (size_t)iy * p.W + ix;
-        float tap = 0.f;
-        for (int c0 = 0; c0 < p.C; c0 += 32) {
-            const int cn = min(32, p.C - c0);
-            float part = 0.f;
-            for (int j = 0; j < cn; ++j) part += src[(size_t)(c0 + j) * HW] * flt[(size_t)(c0 + j) * taps + t];
-            tap += part;
-        }
-        acc += tap;
+    const uint32_t *stats = reinterpret_cast<const uint32_t *>(p.Wx + (size_t)p.ftiles * p.nchunks * taps * kOperandBytes);
+    int ft[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) ft[i] = min((f0 >> 5) + i, p.ftiles - 1);
+    int y[NT], x[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int oy, ox;
+        pixel_of(j, oy, ox);
+        y[j] = oy * p.sh - p.ph;
+        x[j] = ox * p.sw - p.pw;
     }
-    return acc;
+    auto inside = [&](int j, int t, int &at) -> bool {
+        const int ky = t / p.kw, iy = y[j] + ky, ix = x[j] + t - ky * p.kw;
+        const bool in = (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
+        at = in ? iy * p.W + ix : 0;
+        return in;
+    };
+    uint4 raw[2][3];
+    float bn[NT][8];
+    auto fetch = [&](int t, int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(p.Wx + (((size_t)ft[i] * p.nchunks + ch) * taps + t) * kOperandBytes) + lane;
+            raw[i][0] = src[0];
+            raw[i][1] = src[64];
+            raw[i][2] = src[128];
+        }
+        const int c0 = ch * kChan + 8 * half;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            int at;
+            inside(j, t, at);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float v = img[(size_t)(c0 + k < p.C ? c0 + k : 0) * HW + at];
+                bn[j][k] = c0 + k < p.C ? v : 0.f;
+            }
+        }
+    };
+    floatx16 total[2][NT], part[2][NT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) { total[i][j] = floatx16{}; part[i][j] = floatx16{}; }
+    fetch(0, 0);
+    for (int t = 0, ch = 0; t < taps;) {
+        const float sgn = ((ch * taps + t) / chain_taps(FLUSH)) & 1 ? -1.f : 1.f;
+        float w[2][8], b[NT][8];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            bool held = true;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const auto term = [&](int q) {
+                    const uint32_t u = (k >> 1) == 0 ? raw[i][q].x : (k >> 1) == 1 ? raw[i][q].y : (k >> 1) == 2 ? raw[i][q].z : raw[i][q].w;
+                    return __uint_as_float(k & 1 ? u & 0xffff0000u : u << 16);
+                };
+                const float hi = term(0);
+                held &= fabsf(hi) >= kTiny && fabsf(hi) < INFINITY;
+                w[i][k] = sgn * ((hi + term(1)) + term(2));
+            }
+            // (uniform) does the operand hold all weights as they are, but for zeros?
+            const uint32_t s0 = stats[(ft[i] * p.nchunks + ch) * 2], s1 = stats[(ft[i] * p.nchunks + ch) * 2 + 1];
+            const bool all_held = ((s0 | s1) & kTinyBit) == 0 && max(s0 & ~kTinyBit, s1 & ~kTinyBit) < (kHuge >> 1);
+            if (!all_held && !held) {
+                const int f = ft[i] * 32 + col, c0 = ch * kChan + 8 * half;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    w[i][k] = f < p.F && c0 + k < p.C ? p.Wt[((size_t)f * p.C + c0 + k) * taps + t] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) b[j][k] = bn[j][k];
+        const int tap = t;
+        const bool add = (ch & 1) || ch + 1 == p.nchunks;
+        if (++ch == p.nchunks) { ch = 0; ++t; }
+        if (t < taps) fetch(t, ch);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) part[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i][k], b[j][k], part[i][j], 0, 0, 0);
+        if (add) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                int at;
+                const bool in = inside(j, tap, at);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        total[i][j][r] += in ? part[i][j][r] : 0.f;
+                        part[i][j][r] = 0.f;
+                    }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) put(i, j, r, total[i][j][r]);
 }
 
 // The work of one wave with NT pixel tiles (0: it only takes part in the staging).  X0, Y0: the output
@@ -299,6 +401,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     constexpr int kPieces = 2 * kGran + 1;
     float pv[4];
     uint32_t ph[2], pm[2], pl[2];
+    uint32_t *const huge_seen = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);   // by the chunks, in turn
     uint32_t xtop = 0, xlow = 0xffffffffu;     // largest and smallest non-zero magnitude seen (doubled bits, less one)
     auto commit_unit = [&](auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
         constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
@@ -376,9 +479,15 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
 
     prefetch(0);
     if constexpr (NT > 0) load_next();
-    commit_rest(0, 0);
+    if (threadIdx.x < 2) huge_seen[threadIdx.x] = 0;
     __syncthreads();
+    commit_rest(0, 0);
+    if (xtop >= kHuge) huge_seen[0] = 1;
+    __syncthreads();
+    bool by_plain_sum = false;                 // (uniform over the workgroup)
     for (int ch = 0; ch < p.nchunks; ++ch) {
+        // (written before the barrier behind which it is read, and again only behind the next one)
+        const uint32_t huge = huge_seen[ch & 1];
         const bool more = ch + 1 < p.nchunks;
         int pc = more ? 0 : kPieces;                     // the next piece of chunk ch + 1 to commit
         if constexpr (NT > 0) {
@@ -473,16 +582,18 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             for (; tap < taps; ++tap) tap_body(std::integral_constant<int, -1>{}, tap);
         }
         if (pc < kPieces) commit_rest(pc, ch + 1);       // what the chunk's steps did not carry
+        if (more && xtop >= kHuge) huge_seen[(ch + 1) & 1] = 1;
         __syncthreads();                                 // chunk ch has been read, chunk ch + 1 is written
+        by_plain_sum = __builtin_amdgcn_readfirstlane((int)huge) != 0;
+        if (by_plain_sum) break;
     }
 
     if constexpr (!FLUSH && NT > 0) settle(1, NT - 1, sgn);
 
-    // Below which magnitude an output is doubtful.  A term below 2^-126 is flushed: with nothing staged
-    // or weighted below 2^-50 that takes a product below 2^-116, no concern.  Otherwise the flushed terms
-    // add up to at most 2^-125 * Nred * (max |x| + max |w| + 1), and an output of 2^30 times that is
-    // not touched by them.
-    uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (everything staged has been read)
+    // Below which magnitude an output is doubtful.  A value of 2^-110 and above is held in full; of a smaller one up to
+    // 2^-134 is lost.  The losses add up to at most 2^-134 * Nred * (max |x| + max |w|), and an output of 2^30
+    // times that is not touched by them.
+    uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (nothing staged is used past the last barrier)
 #pragma unroll
     for (int s = 1; s < 64; s *= 2) {
         xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, s));
@@ -504,13 +615,13 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     if (xlow < (__float_as_uint(kTiny) << 1) - 1u || __any((wtiny & kTinyBit) != 0)) {
 #pragma unroll
         for (int s = 1; s < 64; s *= 2) wstat = max(wstat, (uint32_t)__shfl_xor((int)wstat, s));
-        doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wstat) + 1.f);
+        doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wstat));
     }
 
     // accumulator register r of a lane: filter row 8*(r/4) + 4*half + r%4 of the filter tile,
     // pixel column `col`
     float *dst = p.out + (size_t)n * p.F * OHW;
-    uint32_t again[NT > 0 ? NT : 1];
+    uint32_t again[NT > 0 ? NT : 1], any = 0;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         again[j] = 0;
@@ -524,23 +635,22 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                     const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
                     const float v = FLUSH ? fmaf(sgn, acc[i][j][r], sum[i][j][r]) : acc[i][j][r];
                     if (f < p.F) {
-                        dst[(size_t)f * OHW + px] = v;
-                        if (!(fabsf(v) >= doubtful && fabsf(v) <= 3.402823466e38f)) again[j] |= 1u << (16 * i + r);
+                        if (!by_plain_sum) dst[(size_t)f * OHW + px] = v;
+                        if (by_plain_sum || !(fabsf(v) >= doubtful && fabsf(v) <= 3.402823466e38f)) again[j] |= 1u << (16 * i + r);
                     }
                 }
         }
+        any |= again[j];
     }
-#pragma unroll 1
-    for (int j = 0; j < NT; ++j) {
-        uint32_t bits = j == 0 ? again[0] : again[NT > 1 ? 1 : 0];
-        while (bits) {
-            const int b = __builtin_ctz(bits);
-            bits &= bits - 1;
-            int oy, ox;
-            pixel_of(tile0 + j, oy, ox);
-            const int f = f0 + (b >> 4) * 32 + 8 * ((b >> 2) & 3) + 4 * half + (b & 3);
-            dst[(size_t)f * OHW + oy * p.OW + ox] = plain_output(p, n, f, oy, ox);
-        }
+    if constexpr (NT > 0) {
+        if (!__any(any != 0)) return;
+        plain_tiles<NT, FLUSH>(p, n, f0, [&](int j, int &oy, int &ox) { pixel_of(tile0 + j, oy, ox); },
+                        [&](int i, int j, int r, float v) __attribute__((always_inline)) {
+                            int oy, ox;
+                            pixel_of(tile0 + j, oy, ox);
+                            const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                            if ((again[j] >> (16 * i + r)) & 1u) dst[(size_t)f * OHW + oy * p.OW + ox] = v;
+                        });
     }
 }
 
@@ -638,7 +748,7 @@ Plan search_plan(const Geom &g)
                         int ty, int gx) {
         const long long npos = rows * cols;
         if (npos > maxpos || groups > (1 << 24)) return;
-        const size_t lds = 2 * (size_t)npos * kPosBytes;
+        const size_t lds = 2 * (size_t)npos * kPosBytes + 2 * sizeof(uint32_t);
         const long long wgs = (long long)g.N * fgroups * groups;
         const double whole = ceil_div(tiles, wps) + 0.5, part = ceil_div(last, wps) + 0.5;
         const double mean = whole + (part - whole) / (double)period;
@@ -686,7 +796,8 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
         const unsigned long long bit = 1ull << (dev & 63);
         if (!(raised.load() & bit)) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 2 * max_pos(FLUSH) * kPosBytes);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     2 * max_pos(FLUSH) * kPosBytes + 2 * (int)sizeof(uint32_t));
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }

@@ -164,3 +164,64 @@ def test_split_products_of_equal_operands(xb):
     got = split(xb, dev(I), dev(Wt), xb.Shape(1, 80, 1, 64, 64, 1, 1))[0, :, 0, :].diagonal()
     bias = (got / (80 * v ** 2) - 1).mean()
     assert abs(bias) <= 0.5 * left_out, (bias, left_out)
+
+
+@pytest.mark.parametrize("shape", [(1, 37, 14, 13, 70, 3), (2, 16, 9, 40, 33, 5), (1, 50, 15, 14, 66, 7)], ids=lambda s: "x".join(map(str, s)))
+def test_split_weights_and_inputs_that_three_terms_do_not_hold(xb, shape):
+    """Infinite, NaN, huge and tiny weights (and zeros beside them) in some filters, tiny values and regions of
+    zeros in the input: what one thread per output gives, an infinite weight over padding adding nothing."""
+    N, C, H, W, F, k = shape
+    print(f"case conv_fp32 split weights shape={shape}", flush=True)
+    rng = np.random.default_rng(11)
+    I = np.maximum(rng.standard_normal((N, C, H, W)), 0).astype(np.float32)
+    I[:, :, :k + 2, :k + 2] = 0
+    I[:, C - 1, H - 2:, :] = 1e-40
+    Wt = rng.standard_normal((F, C, k, k)).astype(np.float32)
+    Wt[1, C - 1, 0, 0], Wt[2, 0, k - 1, 0], Wt[3, 1, 1, 1], Wt[33 % F, 2, 0, 0] = np.inf, -np.inf, np.nan, 3.402e38
+    Wt[4], Wt[5], Wt[6, :, 1:], Wt[F - 1] = 0, Wt[5] * 1e-36, 0, Wt[F - 1] * 1e-42
+    Wt[7, 0, 0, 0], Wt[8, 1, 0, 0] = 1e-44, 1e-34
+    s = xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2)
+    ref = xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, algo=xb.ALGO_DIRECT).cpu().numpy().astype(np.float64)
+    got = split(xb, dev(I), dev(Wt), s)
+    assert np.isnan(ref).any() and np.isinf(ref).any() and np.isfinite(ref[:, 1]).any()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+    # (a finite output has no weight that is not finite inside the image: S of the others)
+    S = torch.nn.functional.conv2d(torch.from_numpy(I).double(), torch.from_numpy(np.where(np.isfinite(Wt), np.abs(Wt), 0)).double(),
+                                   padding=k // 2).numpy()
+    fine = np.isfinite(ref)
+    assert (np.abs(got[fine] - ref[fine]) <= 1e-5 * S[fine] + 2 * C * k * k * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("what", ["one NaN", "all NaN", "overflow", "zeros and a tiny weight", "dead filters"])
+@pytest.mark.parametrize("shape", [(16, 128, 28, 28, 128, 5), (16, 256, 28, 28, 256, 3), (4, 128, 28, 28, 128, 7)], ids=lambda s: "x".join(map(str, s)))
+def test_split_costs_no_multiple_where_it_forms_outputs_again(xb, shape, what):
+    """Outputs that the split cannot give are formed on the fp32 matrix instruction, a wave's at a time: 0.3 to 2.0
+    times the whole call without a workspace.  One by one, as lanes' own sums, they took 3 to 80 times."""
+    N, C, H, W, F, k = shape
+    print(f"case conv_fp32 split cost shape={shape} {what}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    I, Wt = torch.randn((N, C, H, W), generator=g, device="cuda"), torch.randn((F, C, k, k), generator=g, device="cuda")
+    if what == "one NaN":
+        I[0, 5, 5, 5] = float("nan")
+    elif what == "all NaN":
+        I.fill_(float("nan"))
+    elif what == "overflow":
+        I, Wt = I * 1e25, Wt * 1e25
+    elif what == "dead filters":
+        Wt[::13] *= 1e-36
+    else:
+        I, Wt[::13, 0, 0, 0] = I.clamp(min=0), 1e-38
+        I[:, :, :H // 2] = 0
+    s = xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2)
+    out = torch.empty((N, F, H, W), device="cuda")
+    best = {}
+    for workspace in (None, "auto"):
+        for _ in range(4):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            xb.xnor_conv2d_fp32_fwd(I, Wt, s, out, workspace=workspace)
+            end.record()
+            end.synchronize()
+            best[workspace] = min(best.get(workspace, 1e9), start.elapsed_time(end))
+    assert best["auto"] <= 2.8 * best[None], best
