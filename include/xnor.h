@@ -337,12 +337,17 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes
- * bytes are given, else what xnor_conv2d_fp32_fwd takes.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_UNSUPPORTED for
- * kh*kw > 49 or a window whose input rows exceed 512 staged positions, XNOR_E_WORKSPACE for a workspace
- * that is missing or too small.  Other values as in xnor_conv2d_fp32_fwd_algo.
- *   xnor_conv2d_fp32_workspace_bytes   host only; 0 where no workspace would be used by XNOR_ALGO_AUTO.
+ * bytes are given, else what xnor_conv2d_fp32_fwd takes.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_WORKSPACE for a
+ * workspace that is missing or too small; XNOR_E_UNSUPPORTED for kh*kw > 49, OH*OW > 2^24, C*H*W >= 2^29,
+ * F*C*kh*kw >= 2^28, or where the input under 32 output pixels exceeds 512 staged positions (384 for shapes that
+ * XNOR_ALGO_MFMA does not take).  Other values as in xnor_conv2d_fp32_fwd_algo.
+ *   xnor_conv2d_fp32_workspace_bytes        host only; 0 where no workspace would be used by XNOR_ALGO_AUTO.
+ *   xnor_conv2d_fp32_algo_workspace_bytes   host only; the same for the kernel that `algo` asks for:
+ *                                           XNOR_E_UNSUPPORTED where the call would return it, 0 for kernels
+ *                                           that use none.
  */
 int xnor_conv2d_fp32_workspace_bytes(const xnor_shape *s, size_t *bytes);
+int xnor_conv2d_fp32_algo_workspace_bytes(const xnor_shape *s, int algo, size_t *bytes);
 int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,
                             size_t workspace_bytes, int algo, void *stream);
 

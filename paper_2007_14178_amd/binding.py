@@ -107,6 +107,7 @@ def _load() -> ctypes.CDLL:
     L.xnor_conv2d_fp32_fwd.argtypes = [vp, vp, sp, vp, vp]
     L.xnor_conv2d_fp32_fwd_algo.argtypes = [vp, vp, sp, vp, ci, vp]
     L.xnor_conv2d_fp32_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
+    L.xnor_conv2d_fp32_algo_workspace_bytes.argtypes = [sp, ci, ctypes.POINTER(sz)]
     L.xnor_conv2d_fp32_fwd_ws.argtypes = [vp, vp, sp, vp, vp, sz, ci, vp]
     L.xnor_conv2d_pick_algo.argtypes = [sp, sz]
     L.xnor_bwn_pick_algo.argtypes = [sp]
@@ -123,7 +124,7 @@ def _load() -> ctypes.CDLL:
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
                  "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
-                 "xnor_conv2d_fp32_workspace_bytes"):
+                 "xnor_conv2d_fp32_workspace_bytes", "xnor_conv2d_fp32_algo_workspace_bytes"):
         getattr(L, name).restype = ci
     return L
 
@@ -478,13 +479,16 @@ def xnor_bwn_conv2d_fwd(I: torch.Tensor, Wpk: torch.Tensor, alpha: torch.Tensor,
     return out
 
 
-def xnor_conv2d_fp32_workspace_bytes(s: Shape) -> int:
-    nbytes = s.__dict__.get("_fp32_ws")     # asked on every call: remembered per Shape
+def xnor_conv2d_fp32_workspace_bytes(s: Shape, algo: int = ALGO_AUTO) -> int:
+    """Workspace that xnor_conv2d_fp32_fwd uses with ``algo``."""
+    nbytes = s.__dict__.get("_fp32_ws") if algo == ALGO_AUTO else None      # asked on every call: remembered per Shape
     if nbytes is None:
         n = ctypes.c_size_t()
-        _ok(lib.xnor_conv2d_fp32_workspace_bytes(ctypes.byref(s.c()), ctypes.byref(n)), "xnor_conv2d_fp32_workspace_bytes")
+        _ok(lib.xnor_conv2d_fp32_algo_workspace_bytes(ctypes.byref(s.c()), algo, ctypes.byref(n)),
+            f"xnor_conv2d_fp32_workspace_bytes[{ALGO_NAMES.get(algo, algo)}]")
         nbytes = n.value
-        object.__setattr__(s, "_fp32_ws", nbytes)
+        if algo == ALGO_AUTO:
+            object.__setattr__(s, "_fp32_ws", nbytes)
     return nbytes
 
 
@@ -493,16 +497,14 @@ def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch
     """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out.
 
     ``workspace``: a uint8 GPU tensor, None (run a kernel that needs none), or "auto" (allocate what
-    xnor_conv2d_fp32_workspace_bytes asks for, where ALGO_AUTO uses one)."""
+    xnor_conv2d_fp32_workspace_bytes asks for)."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
         out = I.new_empty(oshape, dtype=torch.float32)
     if isinstance(workspace, str):
-        nbytes = xnor_conv2d_fp32_workspace_bytes(s) if algo == ALGO_AUTO else 0
+        nbytes = xnor_conv2d_fp32_workspace_bytes(s, algo) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
         workspace = I.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
-        if algo == ALGO_MFMA_SPLIT:
-            _ok(E_UNSUPPORTED, "xnor_conv2d_fp32_fwd[mfma_split] without a workspace")
     _ok(lib.xnor_conv2d_fp32_fwd_ws(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
         ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),

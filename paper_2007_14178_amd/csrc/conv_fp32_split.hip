@@ -808,8 +808,6 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
 
 }  // namespace
 
-bool conv_fp32_split_supports(const Geom &g) { return make_plan(g).ok; }
-
 size_t conv_fp32_split_workspace_bytes(const Geom &g)
 {
     if (!make_plan(g).ok) return 0;

@@ -413,12 +413,31 @@ int xnor_bwn_conv2d_fwd(const float *I, const uint32_t *Wpk, const float *alpha,
 
 int xnor_conv2d_fp32_workspace_bytes(const xnor_shape *s, size_t *bytes)
 {
+    return xnor_conv2d_fp32_algo_workspace_bytes(s, XNOR_ALGO_AUTO, bytes);
+}
+
+int xnor_conv2d_fp32_algo_workspace_bytes(const xnor_shape *s, int algo, size_t *bytes)
+{
     if (!s || !bytes) return XNOR_E_NULL;
     xnor::Geom g;
     const int rc = make_geom(s, &g);
     if (rc) return rc;
-    *bytes = fp32_split_pays(g) ? xnor::conv_fp32_split_workspace_bytes(g) : 0;
-    return XNOR_OK;
+    switch (algo) {
+        case XNOR_ALGO_AUTO:
+            *bytes = fp32_split_pays(g) ? xnor::conv_fp32_split_workspace_bytes(g) : 0;
+            return XNOR_OK;
+        case XNOR_ALGO_DIRECT:
+            *bytes = 0;
+            return XNOR_OK;
+        case XNOR_ALGO_MFMA:
+            *bytes = 0;
+            return xnor::conv_fp32_mfma_supports(g) ? XNOR_OK : XNOR_E_UNSUPPORTED;
+        case XNOR_ALGO_MFMA_SPLIT:
+            *bytes = xnor::conv_fp32_split_workspace_bytes(g);
+            return *bytes > 0 ? XNOR_OK : XNOR_E_UNSUPPORTED;
+        default:
+            return XNOR_E_UNSUPPORTED;
+    }
 }
 
 int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,

@@ -82,7 +82,6 @@ hipError_t launch_bwn_split(const float *I, const uint32_t *Wpk, const float *al
                             float *out, hipStream_t st);
 bool conv_fp32_mfma_supports(const Geom &g);
 hipError_t launch_conv_fp32_mfma(const float *I, const float *Wt, const Geom &g, float *out, hipStream_t st);
-bool conv_fp32_split_supports(const Geom &g);
 size_t conv_fp32_split_workspace_bytes(const Geom &g);   // 0 if the shape is not supported
 hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace,
                                   hipStream_t st);

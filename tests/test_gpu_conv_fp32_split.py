@@ -225,3 +225,26 @@ def test_split_costs_no_multiple_where_it_forms_outputs_again(xb, shape, what):
             end.synchronize()
             best[workspace] = min(best.get(workspace, 1e9), start.elapsed_time(end))
     assert best["auto"] <= 2.8 * best[None], best
+
+
+def test_split_by_name_with_the_default_workspace(xb):
+    """ALGO_MFMA_SPLIT where ALGO_AUTO would not take it: the size can be asked for, and "auto" allocates it."""
+    shape = (1, 3, 20, 21, 5, 3, 3, 1, 1, 1, 1)
+    _, I, Wt = random_layer(np.random.default_rng(9), "t", *shape)
+    s = xb.Shape(*shape)
+    assert xb.xnor_conv2d_fp32_workspace_bytes(s) == 0
+    nbytes = xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT)
+    assert nbytes > 0 and xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA) == 0
+    ws = torch.empty((nbytes,), dtype=torch.uint8, device="cuda")
+    a = xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, algo=xb.ALGO_MFMA_SPLIT)
+    b = xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, algo=xb.ALGO_MFMA_SPLIT, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and np.array_equal(a.cpu().numpy().astype(np.float64), split(xb, dev(I), dev(Wt), s))
+    with pytest.raises(xb.XnorError) as e:
+        xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, algo=xb.ALGO_MFMA_SPLIT, workspace=None)
+    assert e.value.status == xb.E_WORKSPACE
+    big = xb.Shape(1, 8, 20, 20, 8, 8, 8)          # 64 taps
+    with pytest.raises(xb.XnorError) as e:
+        xb.xnor_conv2d_fp32_fwd(torch.zeros((1, 8, 20, 20), device="cuda"), torch.zeros((8, 8, 8, 8), device="cuda"), big,
+                                algo=xb.ALGO_MFMA_SPLIT)
+    assert e.value.status == xb.E_UNSUPPORTED
