@@ -504,7 +504,12 @@ def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch
         out = I.new_empty(oshape, dtype=torch.float32)
     if isinstance(workspace, str):
         nbytes = xnor_conv2d_fp32_workspace_bytes(s, algo) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
-        workspace = I.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
+        try:
+            workspace = I.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
+        except torch.OutOfMemoryError:
+            if algo != ALGO_AUTO:
+                raise
+            workspace = None            # (a kernel that needs none)
     _ok(lib.xnor_conv2d_fp32_fwd_ws(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
         ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),

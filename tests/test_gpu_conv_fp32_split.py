@@ -248,3 +248,21 @@ def test_split_by_name_with_the_default_workspace(xb):
         xb.xnor_conv2d_fp32_fwd(torch.zeros((1, 8, 20, 20), device="cuda"), torch.zeros((8, 8, 8, 8), device="cuda"), big,
                                 algo=xb.ALGO_MFMA_SPLIT)
     assert e.value.status == xb.E_UNSUPPORTED
+
+
+def test_auto_without_memory_for_the_workspace(xb, monkeypatch):
+    """The default call works on a card that has no room for the split filters: the kernel that needs none."""
+    s = xb.Shape(2, 64, 20, 20, 72, 3, 3, 1, 1, 1, 1)
+    _, I, Wt = random_layer(np.random.default_rng(10), "t", 2, 64, 20, 20, 72, 3, 3, 1, 1, 1, 1)
+    I, Wt, out = dev(I), dev(Wt), torch.empty((2, 72, 20, 20), device="cuda")
+    assert xb.xnor_conv2d_fp32_workspace_bytes(s) > 0
+    plain = xb.xnor_conv2d_fp32_fwd(I, Wt, s, workspace=None)
+
+    def no_memory(*args, **kwargs):
+        raise torch.OutOfMemoryError("no memory")
+    monkeypatch.setattr(torch.Tensor, "new_empty", no_memory)
+    xb.xnor_conv2d_fp32_fwd(I, Wt, s, out)
+    with pytest.raises(torch.OutOfMemoryError):
+        xb.xnor_conv2d_fp32_fwd(I, Wt, s, out, algo=xb.ALGO_MFMA_SPLIT)
+    torch.cuda.synchronize()
+    assert torch.equal(out, plain)
