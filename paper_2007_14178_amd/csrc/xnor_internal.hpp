@@ -16,26 +16,35 @@ struct Geom {
     int OH, OW, Cw;
 };
 
-// The last few plans made on a thread, by geometry (and one more number: an operand's alignment).  A plan is
-// a function of these alone and costs the host several microseconds where it tries rows and shapes; a call
-// asks for it two to five times.
-template <class V, int N = 16>
+// The last plans made on a thread, by geometry (and one more number: an operand's alignment), four to a set.  A plan
+// is a function of these alone and costs the host several microseconds where it tries rows and shapes; a
+// call asks for it two to five times.
+template <class V, int SETS = 32>
 struct PlanMemo {
-    struct Key { Geom g; int extra; };
-    Key key[N];
-    V val[N];
-    int used = 0, next = 0;
+    static constexpr int kWays = 4;
+    struct Set {
+        Geom g[kWays];
+        int extra[kWays];
+        V val[kWays];
+        int used = 0, next = 0;
+    };
+    Set set[SETS];
     template <class Make>
     const V &get(const Geom &g, int extra, Make make)
     {
-        for (int i = 0; i < used; ++i)
-            if (key[i].extra == extra && memcmp(&key[i].g, &g, sizeof g) == 0) return val[i];
-        const int at = next;
-        val[at] = make();
-        key[at] = Key{g, extra};
-        next = (next + 1) % N;
-        used = used < N ? used + 1 : N;
-        return val[at];
+        const int *w = reinterpret_cast<const int *>(&g);
+        uint32_t h = (uint32_t)extra;
+        for (unsigned i = 0; i < sizeof g / sizeof(int); ++i) h = (h ^ (uint32_t)w[i]) * 0x9E3779B1u;
+        Set &s = set[(h >> 20) % SETS];
+        for (int i = 0; i < s.used; ++i)
+            if (s.extra[i] == extra && memcmp(&s.g[i], &g, sizeof g) == 0) return s.val[i];
+        const int at = s.next;
+        s.val[at] = make();
+        s.g[at] = g;
+        s.extra[at] = extra;
+        s.next = (at + 1) % kWays;
+        s.used = s.used < kWays ? s.used + 1 : kWays;
+        return s.val[at];
     }
 };
 
