@@ -479,18 +479,7 @@ SplitPlan make_split_plan(const Geom &g, int cus = 0)
     // 28 outputs, 25 tiles, 6,6,6,6,1 against 5 x 5: 2 % faster; 56 x 56 with 16 images and 128
     // filters: 272 workgroups of six tiles are two rounds of one workgroup per unit, the second
     // nearly empty.)
-    static std::atomic<int> cus_cached{0};
-    if (cus <= 0) cus = cus_cached.load(std::memory_order_relaxed);
-    if (cus <= 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
-            (void)hipGetLastError();
-            cus = 256;
-        } else {
-            cus_cached.store(cus, std::memory_order_relaxed);
-        }
-    }
+    if (cus <= 0) cus = compute_units();
     // Two ways to cut an image into tiles: 32 consecutive pixels (no pixel slot idle but in an image's
     // last tile; a workgroup's pixels straddle rows, which costs a staged row), or 32-pixel segments
     // of single rows (the last segment of a row short; whole rows per workgroup, which on wide rows

@@ -704,22 +704,6 @@ struct Plan {
     size_t lds;
 };
 
-int compute_units()
-{
-    static std::atomic<int> cached{0};
-    int cus = cached.load(std::memory_order_relaxed);
-    if (cus <= 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
-            (void)hipGetLastError();
-            return 256;
-        }
-        cached.store(cus, std::memory_order_relaxed);
-    }
-    return cus;
-}
-
 // How an image is cut into workgroups: 32 consecutive pixels per tile (no idle pixel slot but in an
 // image's last tile; the whole width of every row under them is staged), or two-dimensional tiles of
 // tw x 32 / tw pixels in blocks of tx x ty (only the block's own columns are staged: wide rows, large
@@ -741,7 +725,7 @@ Plan search_plan(const Geom &g)
     const int wps = 4 / pl.fwaves, most = wps * kWaveTiles;
     const long long maxpos = max_pos(pl.flush);
     const long long fgroups = ceil_div(g.F, 64 * pl.fwaves);
-    const int cus = compute_units();
+    const int cus = kPlanUnits;
     double best = -1.0;
     // `last`: the tiles of the short workgroups, one in every `period`
     auto consider = [&](int tiles, int last, long long period, long long groups, long long rows, long long cols, int tw, int tx,

@@ -1616,17 +1616,6 @@ PPlan make_pplan(const Geom &g, const void *Ipk)
     return memo.get(g, (int)(reinterpret_cast<uintptr_t>(Ipk) & 15), [&] { return search_pplan(g, Ipk); });
 }
 
-int compute_units(int dev)
-{
-    static std::atomic<int> cached[64];
-    if (dev < 0 || dev >= 64) return 256;
-    int v = cached[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    cached[dev].store(v, std::memory_order_relaxed);
-    return v;
-}
-
 template <int VW, bool CHAIN>
 hipError_t raise_lds_once(int dev)
 {
@@ -1665,8 +1654,7 @@ bool conv_mfma_persistent_preferred(const Geom &g)
     // out by the hardware as compute units fall free, ends sooner.
     const PPlan pl = make_pplan(g, nullptr);
     if (!pl.ok) return false;
-    int dev = 0;
-    const int cus = hipGetDevice(&dev) == hipSuccess ? compute_units(dev) : 256;
+    const int cus = kPlanUnits;
     const long long bands = ceil_div((long long)g.N * g.OH, pl.TH);
     const long long items_per_xcd = ceil_div(bands, kXcds) * pl.f_tiles;
     const long long nslot = 2LL * std::max(1, cus / kXcds);
@@ -1729,7 +1717,7 @@ hipError_t launch_conv_mfma_persistent(const uint32_t *Ipk, const float *K, cons
     p.items_per_xcd = p.bands_per_xcd * pl.f_tiles;
     p.stagger = 0;
     // One workgroup per compute unit, two groups each: 2 * CUs slots per XCD.
-    const int cus_per_xcd = std::max(1, compute_units(dev) / kXcds);
+    const int cus_per_xcd = std::max(1, compute_units() / kXcds);
     if (p.items_per_xcd < 2 * cus_per_xcd) {
         // A layer that does not give every group an item: as many items as the slots allow go out
         // as two half items, spread over the compute units first and over their second groups

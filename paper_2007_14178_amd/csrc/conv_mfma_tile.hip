@@ -452,22 +452,6 @@ long long slots_of(const Geom &g, int pt, bool per_image, long long wp, long lon
     return most * wp;
 }
 
-int compute_units()
-{
-    static std::atomic<int> cached{0};
-    int cus = cached.load(std::memory_order_relaxed);
-    if (cus <= 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
-            (void)hipGetLastError();
-            return 256;
-        }
-        cached.store(cus, std::memory_order_relaxed);
-    }
-    return cus;
-}
-
 // Wave tiles: NF, NP, WF.  64 x 64 needs two LDS reads and two filter loads per four matrix instructions,
 // which is about what the vector cache delivers (64 bytes a cycle); 64 x 96 is gentler on it, the smaller
 // ones spread a small layer over more SIMDs; four waves along the filters halve the input under a workgroup
@@ -487,7 +471,7 @@ TPlan search_tplan(const Geom &g)
     const int S2 = (g.Cw + 1) / 2;
     const long long T = (long long)g.kh * g.kw * S2;
     if (T > 8192) return best;
-    const int cus = compute_units();
+    const int cus = kPlanUnits;
     const int pitch16 = (2 * S2) | 1;
     double least = 0;
     for (const auto &s : kShapes) {
@@ -581,7 +565,7 @@ bool conv_mfma_tile_preferred(const Geom &g)
 {
     const TPlan &pl = make_tplan(g);
     if (!pl.ok) return false;
-    const double per_simd = (double)g.N * g.OH * g.OW * (double)(ceil_div(g.F, 32) * 32) * pl.T * 32 / 1024 / (4.0 * compute_units());
+    const double per_simd = (double)g.N * g.OH * g.OW * (double)(ceil_div(g.F, 32) * 32) * pl.T * 32 / 1024 / (4.0 * kPlanUnits);
     return per_simd <= 18500.0;
 }
 

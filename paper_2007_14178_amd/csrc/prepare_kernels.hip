@@ -376,15 +376,7 @@ __global__ __launch_bounds__(64 * kPack4Slices) void pack_and_mean4_kernel(
 // shorter than with 512 equal input blocks and the filter blocks after them).
 static int pixels_per_block4(long long NP, int filter_blocks = 0)
 {
-    static std::atomic<int> cus_cached{0};
-    int cus = cus_cached.load(std::memory_order_relaxed);
-    if (cus <= 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-        cus_cached.store(cus, std::memory_order_relaxed);
-    }
+    const int cus = compute_units();
     if (filter_blocks > 0) {
         const long long rem = ((NP + 255) / 256) % cus, idle = rem ? cus - rem : 0;
         if (idle > 0 && filter_blocks <= 5 * idle) return 256;

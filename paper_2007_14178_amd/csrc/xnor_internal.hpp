@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <stdint.h>
 #include <string.h>
 
@@ -15,6 +16,11 @@ struct Geom {
     int N, C, H, W, F, kh, kw, sh, sw, ph, pw;
     int OH, OW, Cw;
 };
+
+// Compute units that plans and routes are made for.  A route fixes the layout of the expanded filters, which one
+// call writes and another reads, perhaps from another thread: it is a function of the geometry alone, whatever
+// the current device counts.  (Launch sizes go by compute_units().)
+constexpr int kPlanUnits = 256;
 
 // The last plans made on a thread, by geometry (and one more number: an operand's alignment), four to a set.  A plan
 // is a function of these alone and costs the host several microseconds where it tries rows and shapes; a
@@ -47,6 +53,25 @@ struct PlanMemo {
         return s.val[at];
     }
 };
+
+// Compute units of the current device.
+inline int compute_units()
+{
+    static std::atomic<int> cached[64];
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        (void)hipGetLastError();
+        return kPlanUnits;
+    }
+    v = cached[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) {
+        (void)hipGetLastError();
+        return kPlanUnits;
+    }
+    cached[dev].store(v, std::memory_order_relaxed);
+    return v;
+}
 
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 

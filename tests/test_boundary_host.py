@@ -322,3 +322,30 @@ def test_plans_of_a_network_of_many_shapes_are_kept(xb):
             best = min(best, (time.perf_counter() - start) / 400)
         return best
     assert per_query([ctypes.byref(s) for s in shapes]) <= 2.5 * per_query([ctypes.byref(shapes[0])])
+
+
+def test_filter_layouts_do_not_depend_on_the_device(xb, tmp_path):
+    """One call expands the filters, another reads them, perhaps from another thread with another history: the
+    route, and the layout and workspace with it, is the same whatever number of compute units the current
+    device reports (a partition has fewer).  The runtime's two queries are answered by a stand-in here."""
+    import subprocess
+    import sys
+    stub = tmp_path / "stub.c"
+    stub.write_text("#include <stdlib.h>\nint hipGetDevice(int *d) { *d = 0; return 0; }\n"
+                    "int hipDeviceGetAttribute(int *v, int a, int d) { *v = atoi(getenv(\"STUB_UNITS\")); return 0; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(tmp_path / "stub.so"), str(stub)], check=True)
+    prog = f"""
+import ctypes
+ctypes.CDLL({str(tmp_path / "stub.so")!r}, mode=ctypes.RTLD_GLOBAL)
+L = ctypes.CDLL({xb.LIB_PATH!r})
+n = ctypes.c_size_t()
+for N, C, H, F, k, st in ((64, 256, 14, 256, 3, 1), (128, 384, 13, 384, 3, 1), (64, 128, 28, 256, 3, 2), (128, 512, 28, 512, 3, 1),
+                          (16, 128, 56, 128, 5, 1), (16, 128, 56, 128, 7, 1), (128, 96, 27, 256, 5, 1), (8, 256, 28, 128, 3, 1)):
+    s = (ctypes.c_int * 11)(N, C, H, H, F, k, k, st, st, k // 2, k // 2)
+    for query in (L.xnor_conv2d_workspace_bytes, L.xnor_conv2d_chain_workspace_bytes, L.xnor_conv2d_fp32_workspace_bytes):
+        assert query(ctypes.byref(s), ctypes.byref(n)) == 0
+        print(n.value)
+"""
+    answers = [subprocess.run([sys.executable, "-c", prog], env={**os.environ, "STUB_UNITS": str(units)}, check=True,
+                              capture_output=True, text=True).stdout for units in (256, 64, 32)]
+    assert answers[0].count("\n") == 24 and answers[0] == answers[1] == answers[2]
