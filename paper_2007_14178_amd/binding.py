@@ -59,6 +59,10 @@ class Shape:
             object.__setattr__(self, "_c", cs)
         return cs
 
+    def __getstate__(self):
+        # (what is remembered here is this library's: a copy or a saved Shape asks its own again)
+        return {k: v for k, v in self.__dict__.items() if not k.startswith("_")}
+
     @property
     def Cw(self) -> int:
         return (self.C + 31) // 32

@@ -349,3 +349,14 @@ for N, C, H, F, k, st in ((64, 256, 14, 256, 3, 1), (128, 384, 13, 384, 3, 1), (
     answers = [subprocess.run([sys.executable, "-c", prog], env={**os.environ, "STUB_UNITS": str(units)}, check=True,
                               capture_output=True, text=True).stdout for units in (256, 64, 32)]
     assert answers[0].count("\n") == 24 and answers[0] == answers[1] == answers[2]
+
+
+def test_a_saved_shape_asks_the_library_that_loads_it(xb):
+    """Workspace sizes are remembered in a Shape; saved with it, they would be another build's."""
+    import copy
+    import pickle
+    s = xb.Shape(2, 64, 20, 20, 72, 3, 3, 1, 1, 1, 1)
+    sizes = xb.xnor_conv2d_workspace_bytes(s), xb.xnor_conv2d_fp32_workspace_bytes(s)
+    for t in (pickle.loads(pickle.dumps(s)), copy.copy(s), copy.deepcopy(s)):
+        assert t == s and not [k for k in t.__dict__ if k.startswith("_")]
+        assert (xb.xnor_conv2d_workspace_bytes(t), xb.xnor_conv2d_fp32_workspace_bytes(t)) == sizes
