@@ -302,7 +302,6 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
             for (int m = 0; m < M; ++m) {
                 product(m / NP, m % NP, a[u][m / NP], b[u % RB][m % NP]);
                 if (m < NF) load_a(a[(u + RA - 1) % RA][m], m, u + RA - 1);
-                if (M == 2 && m == 0) load_a(a[(u + RA - 1) % RA][NF - 1], NF - 1, u + RA - 1);
                 if (m >= M - NP) read_b(b[(u + RB - 1) % RB][m - (M - NP)], m - (M - NP), off_of(u));
                 if (WITH_K && m < NP) k_add(m);
                 if (WITH_K && m == M - 1) { ++ktap; k_read(); }
