@@ -457,6 +457,20 @@ long long slots_of(const Geom &g, int pt, bool per_image, long long wp, long lon
 // (many channels).
 constexpr int kShapes[][3] = {{2, 2, 2}, {2, 3, 2}, {2, 2, 4}, {2, 1, 2}, {1, 1, 2}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
 
+// The hardware may put a third workgroup on one unit while another has one: where a unit is to have r = one or
+// two, a launch asks for so much LDS that no more of it fit, and no more than that: what is left (half or a
+// third) is for the kernels of other streams.  (Asking for all of it or for half keeps those off the unit; the same
+// times to 0.1 us over 1 x 256 x 7 x 7 .. 64 x 256 x 14 x 14.)
+constexpr size_t kLdsGranule = 1280;
+constexpr size_t lds_to_ask_for(size_t lds, long long r)
+{
+    if (r > 2) return lds;
+    const size_t no_more = kLdsMax / (r + 1) / kLdsGranule * kLdsGranule + kLdsGranule;
+    return lds > no_more || lds > kLdsMax / r ? lds : no_more;
+}
+static_assert(lds_to_ask_for(1024, 1) > kLdsMax / 2 && lds_to_ask_for(1024, 1) + 64 * 1024 <= kLdsMax, "one and others'");
+static_assert(3 * lds_to_ask_for(1024, 2) > kLdsMax && 2 * lds_to_ask_for(1024, 2) + 48 * 1024 <= kLdsMax, "two and others'");
+
 // The shape with the smallest estimate of the launch's length in cycles: with r = the most workgroups a
 // compute unit gets, r times (steps x what a step costs, matrix instructions or operand loads, and the
 // stores), and once per batch of resident workgroups the set-up and the first loads (5000: stamps on 64 x
@@ -500,9 +514,7 @@ TPlan search_tplan(const Geom &g)
         best.ok = true;
         best.NF = NF; best.NP = NP; best.WF = WF; best.slots_max = (int)slots; best.per_image = own ? (int)per_image : 0;
         best.ptiles = ptiles; best.lds = lds;
-        // The hardware may put a third workgroup on one unit while another has one: where a unit is to have
-        // one or two, ask for so much LDS that no more fit.
-        best.lds_request = r <= 2 && lds <= kLdsMax / r ? kLdsMax / r : lds;
+        best.lds_request = lds_to_ask_for(lds, r);
     }
     best.Wp = (int)wp; best.RHfull = (int)rh; best.S2 = S2; best.T = (int)T; best.pitch16 = pitch16;
     best.tile_steps = (int)T + kTailSteps;
