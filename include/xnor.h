@@ -70,6 +70,9 @@ typedef enum {
                                shape allows, else as XNOR_ALGO_MFMA_BANDS                         */
     XNOR_ALGO_MFMA_BANDS = 4, /* the same arithmetic with one workgroup per band of output rows
                                (xnor_conv2d_fwd_algo only; tests and measurements)                */
+    XNOR_ALGO_MFMA_PERSISTENT = 6, /* ... with persistent workgroups, two wave groups each, and      */
+    XNOR_ALGO_MFMA_TILE = 7,  /* ... with many small workgroups: by name, whatever XNOR_ALGO_MFMA takes
+                               (the _algo calls only; tests and measurements)                     */
     XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split exactly into three bf16
                                terms, v_mfma_f32_32x32x16_bf16 against +-1 weights;
                                xnor_conv2d_fp32_fwd_ws: both operands split so, eight products      */
@@ -192,7 +195,20 @@ int xnor_conv2d_workspace_bytes(const xnor_shape *s, size_t *bytes);
  *                             xnor_conv2d_fwd.
  * Both return XNOR_E_UNSUPPORTED where xnor_conv2d_workspace_bytes reports 0 and XNOR_E_WORKSPACE
  * for a workspace that is too small.
+ * With the kernel chosen by the caller (XNOR_ALGO_MFMA: as without; XNOR_ALGO_MFMA_TILE, _PERSISTENT, _BANDS;
+ * else XNOR_E_UNSUPPORTED), the same one in all calls on a workspace, whose layout is that kernel's own:
+ *   xnor_conv2d_mfma_kernel            which of the three XNOR_ALGO_MFMA stands for on this shape,
+ *                                      XNOR_E_UNSUPPORTED if none takes it.  Host only.
+ *   xnor_conv2d_algo_workspace_bytes   workspace of the _algo calls, of xnor_conv2d_fwd_chain_algo if
+ *                                      `chained`; 0 if the kernel does not take the shape.  Host only.
  */
+int xnor_conv2d_mfma_kernel(const xnor_shape *s);
+int xnor_conv2d_algo_workspace_bytes(const xnor_shape *s, int algo, int chained, size_t *bytes);
+int xnor_filter_expand_algo(const uint32_t *Wpk, const xnor_shape *s, void *workspace,
+                            size_t workspace_bytes, int algo, void *stream);
+int xnor_conv2d_fwd_expanded_algo(const uint32_t *Ipk, const void *workspace, size_t workspace_bytes,
+                                  const float *K, const float *A, const float *alpha, const xnor_shape *s,
+                                  float *out, int32_t *dot, int algo, void *stream);
 int xnor_filter_expand(const uint32_t *Wpk, const xnor_shape *s, void *workspace,
                        size_t workspace_bytes, void *stream);
 int xnor_conv2d_fwd_expanded(const uint32_t *Ipk, const void *workspace, size_t workspace_bytes,
@@ -231,6 +247,9 @@ int xnor_conv2d_chain_workspace_bytes(const xnor_shape *s, size_t *bytes);
 int xnor_conv2d_fwd_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
                           const float *alpha, const xnor_shape *s, uint32_t *Opk, float *A_next,
                           void *workspace, size_t workspace_bytes, void *stream);
+int xnor_conv2d_fwd_chain_algo(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
+                               const float *alpha, const xnor_shape *s, uint32_t *Opk, float *A_next,
+                               void *workspace, size_t workspace_bytes, int algo, void *stream);
 
 /*
  * Second half of Eq. 10 on its own: K = box filter of a given A (taps 1/(kh*kw), zero outside the

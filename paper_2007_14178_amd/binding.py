@@ -17,8 +17,10 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libxnor_hip.so")
 
 ALGO_AUTO, ALGO_DIRECT, ALGO_TILED, ALGO_MFMA, ALGO_MFMA_BANDS, ALGO_MFMA_SPLIT = 0, 1, 2, 3, 4, 5
+ALGO_MFMA_PERSISTENT, ALGO_MFMA_TILE = 6, 7
 ALGO_NAMES = {ALGO_AUTO: "auto", ALGO_DIRECT: "direct", ALGO_TILED: "tiled", ALGO_MFMA: "mfma",
-              ALGO_MFMA_BANDS: "mfma_bands", ALGO_MFMA_SPLIT: "mfma_split"}
+              ALGO_MFMA_BANDS: "mfma_bands", ALGO_MFMA_SPLIT: "mfma_split",
+              ALGO_MFMA_PERSISTENT: "mfma_persistent", ALGO_MFMA_TILE: "mfma_tile"}
 E_NULL, E_SHAPE, E_ALIGN, E_HIP, E_UNSUPPORTED, E_WORKSPACE = -1, -2, -3, -4, -5, -6
 
 
@@ -111,6 +113,11 @@ def _load() -> ctypes.CDLL:
     L.xnor_conv2d_fp32_fwd.argtypes = [vp, vp, sp, vp, vp]
     L.xnor_conv2d_fp32_fwd_algo.argtypes = [vp, vp, sp, vp, ci, vp]
     L.xnor_conv2d_fp32_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
+    L.xnor_conv2d_mfma_kernel.argtypes = [sp]
+    L.xnor_conv2d_algo_workspace_bytes.argtypes = [sp, ci, ci, ctypes.POINTER(sz)]
+    L.xnor_filter_expand_algo.argtypes = [vp, sp, vp, sz, ci, vp]
+    L.xnor_conv2d_fwd_expanded_algo.argtypes = [vp, vp, sz, vp, vp, vp, sp, vp, vp, ci, vp]
+    L.xnor_conv2d_fwd_chain_algo.argtypes = [vp, vp, vp, vp, vp, sp, vp, vp, vp, sz, ci, vp]
     L.xnor_conv2d_fp32_algo_workspace_bytes.argtypes = [sp, ci, ctypes.POINTER(sz)]
     L.xnor_conv2d_fp32_fwd_ws.argtypes = [vp, vp, sp, vp, vp, sz, ci, vp]
     L.xnor_conv2d_pick_algo.argtypes = [sp, sz]
@@ -128,7 +135,9 @@ def _load() -> ctypes.CDLL:
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
                  "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
-                 "xnor_conv2d_fp32_workspace_bytes", "xnor_conv2d_fp32_algo_workspace_bytes"):
+                 "xnor_conv2d_fp32_workspace_bytes", "xnor_conv2d_fp32_algo_workspace_bytes",
+                 "xnor_conv2d_mfma_kernel", "xnor_conv2d_algo_workspace_bytes", "xnor_filter_expand_algo",
+                 "xnor_conv2d_fwd_expanded_algo", "xnor_conv2d_fwd_chain_algo"):
         getattr(L, name).restype = ci
     return L
 
@@ -289,6 +298,22 @@ def xnor_conv2d_workspace_bytes(s: Shape) -> int:
     return nbytes
 
 
+def xnor_conv2d_algo_workspace_bytes(s: Shape, algo: int, chained: bool = False) -> int:
+    """Workspace of the matrix-core kernel ``algo`` names, with that kernel's filter layout; 0 if it does not take s."""
+    n = ctypes.c_size_t()
+    _ok(lib.xnor_conv2d_algo_workspace_bytes(ctypes.byref(s.c()), algo, int(chained), ctypes.byref(n)),
+        "xnor_conv2d_algo_workspace_bytes")
+    return n.value
+
+
+def xnor_conv2d_mfma_kernel(s: Shape) -> int:
+    """The kernel that ALGO_MFMA stands for on this shape: ALGO_MFMA_TILE, _PERSISTENT or _BANDS."""
+    r = lib.xnor_conv2d_mfma_kernel(ctypes.byref(s.c()))
+    if r < 0:
+        raise XnorError(r, "xnor_conv2d_mfma_kernel")
+    return r
+
+
 def xnor_conv2d_pick_algo(s: Shape, workspace_bytes: int = 0) -> int:
     r = lib.xnor_conv2d_pick_algo(ctypes.byref(s.c()), workspace_bytes)
     if r < 0:
@@ -311,7 +336,8 @@ def xnor_conv2d_fwd(Ipk: torch.Tensor, Wpk: torch.Tensor, K: torch.Tensor, alpha
     if dot is None and want_dot:
         dot = Ipk.new_empty(oshape, dtype=torch.int32)
     if isinstance(workspace, str):
-        nbytes = xnor_conv2d_workspace_bytes(s)
+        by_name = algo == ALGO_MFMA_PERSISTENT or algo == ALGO_MFMA_TILE
+        nbytes = xnor_conv2d_algo_workspace_bytes(s, algo) if by_name else xnor_conv2d_workspace_bytes(s)
         workspace = Ipk.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
     ws_ptr = _dev(workspace, torch.uint8, name="workspace") if workspace is not None else None
     ws_bytes = workspace.numel() if workspace is not None else 0
@@ -397,20 +423,22 @@ def xnor_probe_store_beside_mfma(workgroups: int, reps: int, wide: bool, matrix_
         "xnor_probe_store_beside_mfma")
 
 
-def xnor_filter_expand(Wpk: torch.Tensor, s: Shape, workspace: torch.Tensor | None = None) -> torch.Tensor:
+def xnor_filter_expand(Wpk: torch.Tensor, s: Shape, workspace: torch.Tensor | None = None,
+                       algo: int = ALGO_MFMA) -> torch.Tensor:
     """Per-model half of the matrix-core convolution: fills (and returns) the workspace."""
     if workspace is None:
-        workspace = Wpk.new_empty((xnor_conv2d_workspace_bytes(s),), dtype=torch.uint8)
-    _ok(lib.xnor_filter_expand(_dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk"), ctypes.byref(s.c()),
-                               _dev(workspace, torch.uint8, name="workspace"), workspace.numel(), _stream()),
+        nbytes = xnor_conv2d_workspace_bytes(s) if algo == ALGO_MFMA else xnor_conv2d_algo_workspace_bytes(s, algo)
+        workspace = Wpk.new_empty((nbytes,), dtype=torch.uint8)
+    _ok(lib.xnor_filter_expand_algo(_dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk"), ctypes.byref(s.c()),
+                                    _dev(workspace, torch.uint8, name="workspace"), workspace.numel(), algo, _stream()),
         "xnor_filter_expand")
     return workspace
 
 
 def xnor_conv2d_fwd_expanded(Ipk: torch.Tensor, workspace: torch.Tensor, K: torch.Tensor | None, alpha: torch.Tensor,
                              s: Shape, out: torch.Tensor | None = None, dot: torch.Tensor | None = None,
-                             want_dot: bool = False, A: torch.Tensor | None = None):
-    """Per-input half: the convolution on a workspace filled by xnor_filter_expand for this shape.
+                             want_dot: bool = False, A: torch.Tensor | None = None, algo: int = ALGO_MFMA):
+    """Per-input half: the convolution on a workspace filled by xnor_filter_expand for this shape (and algo).
     Exactly one of K [N][OH][OW] and A [N][H][W] (K is then formed inside the kernel) is given."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
@@ -418,13 +446,13 @@ def xnor_conv2d_fwd_expanded(Ipk: torch.Tensor, workspace: torch.Tensor, K: torc
         out = Ipk.new_empty(oshape, dtype=torch.float32)
     if dot is None and want_dot:
         dot = Ipk.new_empty(oshape, dtype=torch.int32)
-    _ok(lib.xnor_conv2d_fwd_expanded(
+    _ok(lib.xnor_conv2d_fwd_expanded_algo(
         _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"), _dev(workspace, torch.uint8, name="workspace"),
         workspace.numel(), _dev(K, torch.float32, (s.N, OH, OW), "K") if K is not None else None,
         _dev(A, torch.float32, (s.N, s.H, s.W), "A") if A is not None else None,
         _dev(alpha, torch.float32, (s.F,), "alpha"),
         ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),
-        _dev(dot, torch.int32, oshape, "dot") if dot is not None else None, _stream()), "xnor_conv2d_fwd_expanded")
+        _dev(dot, torch.int32, oshape, "dot") if dot is not None else None, algo, _stream()), "xnor_conv2d_fwd_expanded")
     return out, dot
 
 
@@ -541,7 +569,7 @@ def xnor_conv2d_chain_workspace_bytes(s: Shape) -> int:
 
 def xnor_conv2d_fwd_chain(Ipk: torch.Tensor, Wpk: torch.Tensor | None, K: torch.Tensor | None, alpha: torch.Tensor,
                           s: Shape, Opk: torch.Tensor | None = None, A_next: torch.Tensor | None = None,
-                          workspace: torch.Tensor | None = None, A: torch.Tensor | None = None):
+                          workspace: torch.Tensor | None = None, A: torch.Tensor | None = None, algo: int = ALGO_MFMA):
     """Returns (Opk int32-typed words [N][OH][OW][ceil(F/32)], A_next fp32 [N][OH][OW]).  Exactly one of
     K and A (this layer's channel mean) is given; Wpk None: the filters are already expanded at the
     start of `workspace` (xnor_filter_expand / xnor_prepare on a buffer of xnor_conv2d_chain_workspace_bytes)."""
@@ -554,13 +582,13 @@ def xnor_conv2d_fwd_chain(Ipk: torch.Tensor, Wpk: torch.Tensor | None, K: torch.
     if workspace is None:
         if Wpk is None:
             raise ValueError("xnor_conv2d_fwd_chain: without Wpk the workspace with the expanded filters is needed")
-        workspace = Ipk.new_empty((xnor_conv2d_chain_workspace_bytes(s),), dtype=torch.uint8)
-    _ok(lib.xnor_conv2d_fwd_chain(
+        workspace = Ipk.new_empty((xnor_conv2d_algo_workspace_bytes(s, algo, chained=True),), dtype=torch.uint8)
+    _ok(lib.xnor_conv2d_fwd_chain_algo(
         _dev(Ipk, torch.int32, (s.N, s.H, s.W, s.Cw), "Ipk"),
         _dev(Wpk, torch.int32, (s.F, s.kh, s.kw, s.Cw), "Wpk") if Wpk is not None else None,
         _dev(K, torch.float32, (s.N, OH, OW), "K") if K is not None else None,
         _dev(A, torch.float32, (s.N, s.H, s.W), "A") if A is not None else None,
         _dev(alpha, torch.float32, (s.F,), "alpha"), ctypes.byref(s.c()),
         _dev(Opk, torch.int32, (s.N, OH, OW, Cwn), "Opk"), _dev(A_next, torch.float32, (s.N, OH, OW), "A_next"),
-        _dev(workspace, torch.uint8, name="workspace"), workspace.numel(), _stream()), "xnor_conv2d_fwd_chain")
+        _dev(workspace, torch.uint8, name="workspace"), workspace.numel(), algo, _stream()), "xnor_conv2d_fwd_chain")
     return Opk, A_next

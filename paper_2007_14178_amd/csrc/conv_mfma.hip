@@ -768,49 +768,72 @@ struct Route {
     int sum_scale;       // ... each divided by this
 };
 
-Route find_route(const Geom &g)
+Route route_by(const Geom &g, Kind kind)
 {
     Route r{};
     r.sum_scale = 1;
-    const ExpandLayout Lb = bands_expand_layout(g);
-    if (conv_mfma_persistent_supports(g) && (conv_mfma_persistent_preferred(g) || !Lb.ok)) {
-        r.kind = kPersistent;
+    if (kind == kTile && conv_mfma_tile_supports(g)) {
+        r.L = conv_mfma_tile_expand_layout(g);
+        r.sum_parts = conv_mfma_tile_sum_parts(g);
+        r.sum_scale = conv_mfma_tile_sum_scale(g);
+    } else if (kind == kPersistent && conv_mfma_persistent_supports(g)) {
         r.L = conv_mfma_persistent_expand_layout(g);
         r.sum_parts = conv_mfma_persistent_sum_parts(g);
-    } else if (Lb.ok) {
-        r.kind = kBands;
-        r.L = Lb;
+    } else if (kind == kBands) {
+        r.L = bands_expand_layout(g);
         r.sum_parts = ceil_div(g.F, kFilterTile);
-    } else {
-        return r;
     }
-    r.ws_bytes = std::max(r.L.ws_bytes, Lb.ok ? Lb.ws_bytes : (size_t)0);
+    r.kind = r.L.ok ? kind : kNone;
+    r.ws_bytes = r.L.ok ? r.L.ws_bytes : 0;
+    return r;
+}
+
+Route find_route(const Geom &g)
+{
+    const Route bands = route_by(g, kBands), persistent = route_by(g, kPersistent);
+    Route r = persistent.kind && (conv_mfma_persistent_preferred(g) || !bands.kind) ? persistent : bands;
+    if (!r.kind) return r;
+    r.ws_bytes = std::max(r.ws_bytes, bands.ws_bytes);
     if (conv_mfma_tile_preferred(g)) {
-        const ExpandLayout Lt = conv_mfma_tile_expand_layout(g);
+        Route tile = route_by(g, kTile);
         // (a layer whose filters fit the library's own workspace has to go on fitting it)
-        if (Lt.ws_bytes <= XNOR_STATIC_SCRATCH_BYTES || r.ws_bytes > XNOR_STATIC_SCRATCH_BYTES) {
-            r.kind = kTile;
-            r.L = Lt;
-            r.ws_bytes = std::max(r.ws_bytes, Lt.ws_bytes);
-            r.sum_parts = conv_mfma_tile_sum_parts(g);
-            r.sum_scale = conv_mfma_tile_sum_scale(g);
+        if (tile.ws_bytes <= XNOR_STATIC_SCRATCH_BYTES || r.ws_bytes > XNOR_STATIC_SCRATCH_BYTES) {
+            tile.ws_bytes = std::max(tile.ws_bytes, r.ws_bytes);
+            return tile;
         }
     }
     return r;
 }
 
-const Route &route_of(const Geom &g)
+// `algo`: XNOR_ALGO_MFMA for the choice above, or one of the kernels by name.
+const Route &route_of(const Geom &g, int algo = XNOR_ALGO_MFMA)
 {
     static thread_local PlanMemo<Route> memo;
-    return memo.get(g, 0, [&] { return find_route(g); });
+    return memo.get(g, algo, [&] {
+        switch (algo) {
+            case XNOR_ALGO_MFMA: return find_route(g);
+            case XNOR_ALGO_MFMA_TILE: return route_by(g, kTile);
+            case XNOR_ALGO_MFMA_PERSISTENT: return route_by(g, kPersistent);
+            case XNOR_ALGO_MFMA_BANDS: return route_by(g, kBands);
+            default: return route_by(g, kNone);
+        }
+    });
 }
 
 }  // namespace
 
-bool conv_mfma_supports(const Geom &g) { return route_of(g).kind != kNone; }
+int conv_mfma_kernel_of(const Geom &g)
+{
+    switch (route_of(g).kind) {
+        case kTile: return XNOR_ALGO_MFMA_TILE;
+        case kPersistent: return XNOR_ALGO_MFMA_PERSISTENT;
+        case kBands: return XNOR_ALGO_MFMA_BANDS;
+        default: return XNOR_E_UNSUPPORTED;
+    }
+}
 ExpandLayout conv_mfma_expand_layout(const Geom &g) { return route_of(g).L; }
 bool conv_mfma_bands_supports(const Geom &g) { return make_plan(g, nullptr).ok; }
-size_t conv_mfma_workspace_bytes(const Geom &g) { return route_of(g).ws_bytes; }
+size_t conv_mfma_workspace_bytes(const Geom &g, int algo) { return route_of(g, algo).ws_bytes; }
 
 static hipError_t launch_expand_with(const ExpandLayout &L, const uint32_t *Wpk, const Geom &g, void *workspace,
                                      hipStream_t st)
@@ -823,16 +846,16 @@ static hipError_t launch_expand_with(const ExpandLayout &L, const uint32_t *Wpk,
     return hipGetLastError();
 }
 
-hipError_t launch_expand_filters(const uint32_t *Wpk, const Geom &g, void *workspace, hipStream_t st)
+hipError_t launch_expand_filters(const uint32_t *Wpk, const Geom &g, void *workspace, hipStream_t st, int algo)
 {
-    return launch_expand_with(conv_mfma_expand_layout(g), Wpk, g, workspace, st);
+    return launch_expand_with(route_of(g, algo).L, Wpk, g, workspace, st);
 }
 
 static hipError_t launch_mfma(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                               const Geom &g, float *out, int32_t *dot, uint32_t *Opk, float *P,
-                              const void *workspace, hipStream_t st, bool bands_kernel = false)
+                              const void *workspace, hipStream_t st, int algo)
 {
-    const Kind kind = bands_kernel ? kBands : route_of(g).kind;
+    const Kind kind = route_of(g, algo).kind;
     if (kind == kTile)
         return launch_conv_mfma_tile(Ipk, K, A, alpha, g, out, dot, Opk, P, workspace, st);
     if (kind == kPersistent)
@@ -900,18 +923,11 @@ static hipError_t launch_mfma(const uint32_t *Ipk, const float *K, const float *
     }
 }
 
-hipError_t launch_conv_mfma_expanded(const uint32_t *Ipk, const float *K, const float *alpha,
+hipError_t launch_conv_mfma_expanded(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                                      const Geom &g, float *out, int32_t *dot, const void *workspace,
-                                     hipStream_t st)
+                                     hipStream_t st, int algo)
 {
-    return launch_mfma(Ipk, K, nullptr, alpha, g, out, dot, nullptr, nullptr, workspace, st);
-}
-
-hipError_t launch_conv_mfma_expanded_from_A(const uint32_t *Ipk, const float *A, const float *alpha,
-                                            const Geom &g, float *out, int32_t *dot,
-                                            const void *workspace, hipStream_t st)
-{
-    return launch_mfma(Ipk, nullptr, A, alpha, g, out, dot, nullptr, nullptr, workspace, st);
+    return launch_mfma(Ipk, K, A, alpha, g, out, dot, nullptr, nullptr, workspace, st, algo);   // K or A, the other null
 }
 
 // Eq. 10's channel mean for the next layer from the partial sums over groups of filters:
@@ -926,52 +942,37 @@ __global__ __launch_bounds__(256) void chain_mean_kernel(const float *__restrict
     A[i] = (float)(sum / filters);
 }
 
-size_t conv_mfma_chain_workspace_bytes(const Geom &g)
+size_t conv_mfma_chain_workspace_bytes(const Geom &g, int algo)
 {
-    const size_t ws = conv_mfma_workspace_bytes(g);
-    if (ws == 0) return 0;
-    return ws + (size_t)g.N * g.OH * g.OW * route_of(g).sum_parts * sizeof(float);
+    const Route &r = route_of(g, algo);
+    return r.ws_bytes ? r.ws_bytes + (size_t)g.N * g.OH * g.OW * r.sum_parts * sizeof(float) : 0;
 }
 
 hipError_t launch_conv_mfma_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
                                   const float *alpha, const Geom &g, uint32_t *Opk, float *A_next,
-                                  void *workspace, hipStream_t st)
+                                  void *workspace, hipStream_t st, int algo)
 {
-    const size_t ws = conv_mfma_workspace_bytes(g);
+    const size_t ws = conv_mfma_workspace_bytes(g, algo);
     if (ws == 0) return hipErrorInvalidValue;
     float *P = reinterpret_cast<float *>(static_cast<char *>(workspace) + ws);
     // (no Wpk: the caller has left the expanded filters at the start of the workspace)
-    hipError_t e = Wpk ? launch_expand_filters(Wpk, g, workspace, st) : hipSuccess;
+    hipError_t e = Wpk ? launch_expand_filters(Wpk, g, workspace, st, algo) : hipSuccess;
     if (e != hipSuccess) return e;
-    e = launch_mfma(Ipk, K, A, alpha, g, nullptr, nullptr, Opk, P, workspace, st);   // K or A, the other null
+    e = launch_mfma(Ipk, K, A, alpha, g, nullptr, nullptr, Opk, P, workspace, st, algo);   // K or A, the other null
     if (e != hipSuccess) return e;
     const long long npix = (long long)g.N * g.OH * g.OW;
-    const Route &r = route_of(g);
+    const Route &r = route_of(g, algo);
     chain_mean_kernel<<<ceil_div(npix, 256), 256, 0, st>>>(P, npix, r.sum_parts, (double)g.F / r.sum_scale, A_next);
     return hipGetLastError();
 }
 
-}  // namespace xnor
-
-namespace xnor {
-
 hipError_t launch_conv_mfma(const uint32_t *Ipk, const uint32_t *Wpk, const float *K,
                             const float *alpha, const Geom &g, float *out, int32_t *dot,
-                            void *workspace, hipStream_t st)
+                            void *workspace, hipStream_t st, int algo)
 {
     // filters -> FP4 in A-operand order, then the convolution
-    const hipError_t e = launch_expand_filters(Wpk, g, workspace, st);
-    return e != hipSuccess ? e : launch_conv_mfma_expanded(Ipk, K, alpha, g, out, dot, workspace, st);
-}
-
-hipError_t launch_conv_mfma_bands(const uint32_t *Ipk, const uint32_t *Wpk, const float *K,
-                                  const float *alpha, const Geom &g, float *out, int32_t *dot,
-                                  void *workspace, hipStream_t st)
-{
-    // the same two steps with this file's kernel and its workspace layout, whatever the shape
-    const hipError_t e = launch_expand_with(bands_expand_layout(g), Wpk, g, workspace, st);
-    return e != hipSuccess ? e
-                           : launch_mfma(Ipk, K, nullptr, alpha, g, out, dot, nullptr, nullptr, workspace, st, true);
+    const hipError_t e = launch_expand_filters(Wpk, g, workspace, st, algo);
+    return e != hipSuccess ? e : launch_conv_mfma_expanded(Ipk, K, nullptr, alpha, g, out, dot, workspace, st, algo);
 }
 
 }  // namespace xnor

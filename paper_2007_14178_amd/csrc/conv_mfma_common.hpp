@@ -52,6 +52,7 @@ hipError_t launch_conv_mfma_persistent(const uint32_t *Ipk, const float *K, cons
                                        const void *workspace, hipStream_t st);
 
 // Small independent workgroups for layers of little work (conv_mfma_tile.hip).
+bool conv_mfma_tile_supports(const Geom &g);
 bool conv_mfma_tile_preferred(const Geom &g);          // takes the shape and is expected to be the faster kernel
 ExpandLayout conv_mfma_tile_expand_layout(const Geom &g);
 int conv_mfma_tile_sum_parts(const Geom &g);

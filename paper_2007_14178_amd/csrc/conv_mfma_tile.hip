@@ -561,6 +561,8 @@ hipError_t launch_shape(const TileParams &p, bool vec4, unsigned grid, size_t ld
 
 }  // namespace
 
+bool conv_mfma_tile_supports(const Geom &g) { return make_tplan(g).ok; }
+
 // Up to 18.5 k cycles of matrix instructions per SIMD; above that the set-up is a small part of the persistent
 // kernel and its larger wave tiles (half the operand traffic per instruction) count for more.  Measured with
 // K given / with A given, us per launch in a replayed graph, the faster of the persistent and the

@@ -289,16 +289,18 @@ int xnor_conv2d_fwd_algo(const uint32_t *Ipk, const uint32_t *Wpk, const float *
         case XNOR_ALGO_TILED:
             if (!xnor::conv_tiled_supports(g)) return XNOR_E_UNSUPPORTED;
             return hip_status(xnor::launch_conv_tiled(Ipk, Wpk, K, alpha, g, out, dot, st));
-        case XNOR_ALGO_MFMA: {
-            const size_t need = xnor::conv_mfma_workspace_bytes(g);
+        case XNOR_ALGO_MFMA:
+        case XNOR_ALGO_MFMA_PERSISTENT:
+        case XNOR_ALGO_MFMA_TILE: {
+            const size_t need = xnor::conv_mfma_workspace_bytes(g, algo);
             if (need == 0) return XNOR_E_UNSUPPORTED;
             if (workspace_bytes < need) return XNOR_E_WORKSPACE;
-            return hip_status(xnor::launch_conv_mfma(Ipk, Wpk, K, alpha, g, out, dot, workspace, st));
+            return hip_status(xnor::launch_conv_mfma(Ipk, Wpk, K, alpha, g, out, dot, workspace, st, algo));
         }
         case XNOR_ALGO_MFMA_BANDS: {
             if (!xnor::conv_mfma_bands_supports(g)) return XNOR_E_UNSUPPORTED;
             if (workspace_bytes < xnor::conv_mfma_workspace_bytes(g)) return XNOR_E_WORKSPACE;
-            return hip_status(xnor::launch_conv_mfma_bands(Ipk, Wpk, K, alpha, g, out, dot, workspace, st));
+            return hip_status(xnor::launch_conv_mfma(Ipk, Wpk, K, alpha, g, out, dot, workspace, st, algo));
         }
         default:
             return XNOR_E_UNSUPPORTED;
@@ -496,10 +498,35 @@ int xnor_conv2d_chain_workspace_bytes(const xnor_shape *s, size_t *bytes)
     return XNOR_OK;
 }
 
+int xnor_conv2d_mfma_kernel(const xnor_shape *s)
+{
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    return rc ? rc : xnor::conv_mfma_kernel_of(g);
+}
+
+int xnor_conv2d_algo_workspace_bytes(const xnor_shape *s, int algo, int chained, size_t *bytes)
+{
+    if (!s || !bytes) return XNOR_E_NULL;
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    if (rc) return rc;
+    *bytes = chained ? xnor::conv_mfma_chain_workspace_bytes(g, algo) : xnor::conv_mfma_workspace_bytes(g, algo);
+    return XNOR_OK;
+}
+
 // (Wpk null: the filters are already expanded in the workspace; exactly one of K, A)
 int xnor_conv2d_fwd_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
                           const float *alpha, const xnor_shape *s, uint32_t *Opk, float *A_next,
                           void *workspace, size_t workspace_bytes, void *stream)
+{
+    return xnor_conv2d_fwd_chain_algo(Ipk, Wpk, K, A, alpha, s, Opk, A_next, workspace, workspace_bytes,
+                                      XNOR_ALGO_MFMA, stream);
+}
+
+int xnor_conv2d_fwd_chain_algo(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
+                               const float *alpha, const xnor_shape *s, uint32_t *Opk, float *A_next,
+                               void *workspace, size_t workspace_bytes, int algo, void *stream)
 {
     if (!Ipk || (!K == !A) || !alpha || !s || !Opk || !A_next || !workspace) return XNOR_E_NULL;
     xnor::Geom g;
@@ -508,30 +535,43 @@ int xnor_conv2d_fwd_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float 
     if (!aligned(Ipk, 4) || (Wpk && !aligned(Wpk, 4)) || (K && !aligned(K, 4)) || (A && !aligned(A, 4)) || !aligned(alpha, 4) || !aligned(Opk, 4) ||
         !aligned(A_next, 4) || !aligned(workspace, 16))
         return XNOR_E_ALIGN;
-    const size_t need = xnor::conv_mfma_chain_workspace_bytes(g);
+    const size_t need = xnor::conv_mfma_chain_workspace_bytes(g, algo);
     if (need == 0) return XNOR_E_UNSUPPORTED;
     if (workspace_bytes < need) return XNOR_E_WORKSPACE;
     return hip_status(xnor::launch_conv_mfma_chain(Ipk, Wpk, K, A, alpha, g, Opk, A_next, workspace,
-                                                   (hipStream_t)stream));
+                                                   (hipStream_t)stream, algo));
 }
 
 int xnor_filter_expand(const uint32_t *Wpk, const xnor_shape *s, void *workspace,
                        size_t workspace_bytes, void *stream)
+{
+    return xnor_filter_expand_algo(Wpk, s, workspace, workspace_bytes, XNOR_ALGO_MFMA, stream);
+}
+
+int xnor_filter_expand_algo(const uint32_t *Wpk, const xnor_shape *s, void *workspace,
+                            size_t workspace_bytes, int algo, void *stream)
 {
     if (!Wpk || !s || !workspace) return XNOR_E_NULL;
     xnor::Geom g;
     const int rc = make_geom(s, &g);
     if (rc) return rc;
     if (!aligned(Wpk, 4) || !aligned(workspace, 16)) return XNOR_E_ALIGN;
-    const size_t need = xnor::conv_mfma_workspace_bytes(g);
+    const size_t need = xnor::conv_mfma_workspace_bytes(g, algo);
     if (need == 0) return XNOR_E_UNSUPPORTED;
     if (workspace_bytes < need) return XNOR_E_WORKSPACE;
-    return hip_status(xnor::launch_expand_filters(Wpk, g, workspace, (hipStream_t)stream));
+    return hip_status(xnor::launch_expand_filters(Wpk, g, workspace, (hipStream_t)stream, algo));
 }
 
 int xnor_conv2d_fwd_expanded(const uint32_t *Ipk, const void *workspace, size_t workspace_bytes,
                              const float *K, const float *A, const float *alpha, const xnor_shape *s,
                              float *out, int32_t *dot, void *stream)
+{
+    return xnor_conv2d_fwd_expanded_algo(Ipk, workspace, workspace_bytes, K, A, alpha, s, out, dot, XNOR_ALGO_MFMA, stream);
+}
+
+int xnor_conv2d_fwd_expanded_algo(const uint32_t *Ipk, const void *workspace, size_t workspace_bytes,
+                                  const float *K, const float *A, const float *alpha, const xnor_shape *s,
+                                  float *out, int32_t *dot, int algo, void *stream)
 {
     if (!Ipk || !workspace || (!K == !A) || !alpha || !s || !out) return XNOR_E_NULL;   // (exactly one of K, A)
     xnor::Geom g;
@@ -540,12 +580,10 @@ int xnor_conv2d_fwd_expanded(const uint32_t *Ipk, const void *workspace, size_t 
     if (!aligned(Ipk, 4) || (K && !aligned(K, 4)) || (A && !aligned(A, 4)) || !aligned(alpha, 4) || !aligned(out, 4) ||
         (dot && !aligned(dot, 4)) || !aligned(workspace, 16))
         return XNOR_E_ALIGN;
-    const size_t need = xnor::conv_mfma_workspace_bytes(g);
+    const size_t need = xnor::conv_mfma_workspace_bytes(g, algo);
     if (need == 0) return XNOR_E_UNSUPPORTED;
     if (workspace_bytes < need) return XNOR_E_WORKSPACE;
-    if (K) return hip_status(xnor::launch_conv_mfma_expanded(Ipk, K, alpha, g, out, dot, workspace, (hipStream_t)stream));
-    return hip_status(xnor::launch_conv_mfma_expanded_from_A(Ipk, A, alpha, g, out, dot, workspace,
-                                                             (hipStream_t)stream));
+    return hip_status(xnor::launch_conv_mfma_expanded(Ipk, K, A, alpha, g, out, dot, workspace, (hipStream_t)stream, algo));
 }
 
 int xnor_conv2d_fwd(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *alpha,

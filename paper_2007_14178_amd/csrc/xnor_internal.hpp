@@ -125,26 +125,23 @@ hipError_t launch_bwn_mfma(const float *I, const uint32_t *Wpk, const float *alp
 hipError_t launch_bwn_direct(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
                              float *out, hipStream_t st);
 
-bool conv_mfma_supports(const Geom &g);
-size_t conv_mfma_workspace_bytes(const Geom &g);   // 0 if the shape is not supported
+// The matrix-core convolution.  `algo`: XNOR_ALGO_MFMA for the kernel that the shape's rule picks, or one of the
+// three by name, with its own workspace layout.
+int conv_mfma_kernel_of(const Geom &g);                  // by name; XNOR_E_UNSUPPORTED if none takes the shape
+size_t conv_mfma_workspace_bytes(const Geom &g, int algo = XNOR_ALGO_MFMA);         // 0 if the shape is not supported
+size_t conv_mfma_chain_workspace_bytes(const Geom &g, int algo = XNOR_ALGO_MFMA);   // 0 if the shape is not supported
 ExpandLayout conv_mfma_expand_layout(const Geom &g);
-hipError_t launch_expand_filters(const uint32_t *Wpk, const Geom &g, void *workspace, hipStream_t st);
-hipError_t launch_conv_mfma_expanded(const uint32_t *Ipk, const float *K, const float *alpha,
+bool conv_mfma_bands_supports(const Geom &g);
+hipError_t launch_expand_filters(const uint32_t *Wpk, const Geom &g, void *workspace, hipStream_t st,
+                                 int algo = XNOR_ALGO_MFMA);
+hipError_t launch_conv_mfma_expanded(const uint32_t *Ipk, const float *K, const float *A, const float *alpha,
                                      const Geom &g, float *out, int32_t *dot, const void *workspace,
-                                     hipStream_t st);
-hipError_t launch_conv_mfma_expanded_from_A(const uint32_t *Ipk, const float *A, const float *alpha,
-                                            const Geom &g, float *out, int32_t *dot,
-                                            const void *workspace, hipStream_t st);
-size_t conv_mfma_chain_workspace_bytes(const Geom &g);   // 0 if the shape is not supported
+                                     hipStream_t st, int algo);
 hipError_t launch_conv_mfma_chain(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *A,
                                   const float *alpha, const Geom &g, uint32_t *Opk, float *A_next,
-                                  void *workspace, hipStream_t st);   // exactly one of K, A is given
-hipError_t launch_conv_mfma(const uint32_t *Ipk, const uint32_t *Wpk, const float *K,
-                            const float *alpha, const Geom &g, float *out, int32_t *dot,
-                            void *workspace, hipStream_t st);
-bool conv_mfma_bands_supports(const Geom &g);
-hipError_t launch_conv_mfma_bands(const uint32_t *Ipk, const uint32_t *Wpk, const float *K,
-                                  const float *alpha, const Geom &g, float *out, int32_t *dot,
-                                  void *workspace, hipStream_t st);
+                                  void *workspace, hipStream_t st, int algo);
+hipError_t launch_conv_mfma(const uint32_t *Ipk, const uint32_t *Wpk, const float *K, const float *alpha,
+                            const Geom &g, float *out, int32_t *dot, void *workspace, hipStream_t st,
+                            int algo = XNOR_ALGO_MFMA);
 
 }  // namespace xnor

@@ -260,8 +260,8 @@ def test_dot_null_gives_same_out(xb):
                          ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
 def test_fp32_output_alone_through_16_byte_stores(xb, shape, misalign):
     """Without the dot output, where planes and bands are whole groups of four pixels, `out` is
-    16-byte aligned and the layer is more than one round of the kernel's items, the matrix-core
-    kernel writes four consecutive pixels per lane through an LDS transposition.  Same bits as the run that also returns the dot products (whose stores are one
+    16-byte aligned and the layer is more than one round of the kernel's items, the persistent matrix-core
+    kernel (by name: layers of this size run on another one) writes four consecutive pixels per lane through an LDS transposition.  Same bits as the run that also returns the dot products (whose stores are one
     pixel per lane), the oracle's values, every element written and nothing outside the tensor;
     with `out` only 4-byte aligned the one-pixel path runs and gives the same."""
     print(f"case quad stores shape={shape} misalign={misalign}", flush=True)
@@ -274,7 +274,7 @@ def test_fp32_output_alone_through_16_byte_stores(xb, shape, misalign):
     K, _ = xb.xnor_scale_K(dI, s)
     alpha = xb.xnor_alpha(dW)
     try:
-        ref, dot = xb.xnor_conv2d_fwd(Ipk, Wpk, K, alpha, s, want_dot=True, algo=xb.ALGO_MFMA)
+        ref, dot = xb.xnor_conv2d_fwd(Ipk, Wpk, K, alpha, s, want_dot=True, algo=xb.ALGO_MFMA_PERSISTENT)
     except xb.XnorError as e:
         if e.status == xb.E_UNSUPPORTED:
             pytest.skip("shape not taken by the matrix-core kernel")
@@ -284,7 +284,7 @@ def test_fp32_output_alone_through_16_byte_stores(xb, shape, misalign):
     buf = torch.full((n + 2 * guard + 4,), float("nan"), dtype=torch.float32, device="cuda")
     out = buf[guard + misalign:guard + misalign + n].view(s.N, s.F, OH, OW)
     assert out.data_ptr() % 16 == 4 * misalign
-    xb.xnor_conv2d_fwd(Ipk, Wpk, K, alpha, s, out=out, algo=xb.ALGO_MFMA)
+    xb.xnor_conv2d_fwd(Ipk, Wpk, K, alpha, s, out=out, algo=xb.ALGO_MFMA_PERSISTENT)
     torch.cuda.synchronize()
     assert not bool(torch.isnan(out).any())
     assert bool(torch.isnan(buf[:guard + misalign]).all()) and bool(torch.isnan(buf[guard + misalign + n:]).all())
