@@ -410,6 +410,7 @@ def test_conv_that_forms_K_itself(xb, shape):
                                    (84, 288, 28, 28, 33, 5, 5, 1, 1, 2, 2),      # the same, ragged blocks, channel words 9
                                    (2, 64, 13, 13, 40, 3, 3, 1, 1, 1, 1),        # one launch, one-pixel input pass (H*W odd)
                                    (3, 96, 27, 27, 130, 5, 5, 1, 1, 2, 2),       # the same, three channel words, partial filter tile
+                                   (64, 160, 29, 29, 9, 15, 15, 1, 1, 7, 7),     # 225 taps, five channel words: four waves a block
                                    (2, 16, 20, 20, 5, 9, 9, 1, 1, 4, 4),         # more taps than a one-slice block has threads: separate launches
                                    (1, 1552, 256, 256, 3, 3, 3, 1, 1, 1, 1)],    # 49 channel words: the four-pixel pass's LDS would pass 64 KB
                          ids=lambda s: "x".join(map(str, s)))
