@@ -398,8 +398,9 @@ struct Tile {
     static constexpr int kRecord = kWords < 4 ? 4 : 8;                   // a filter's words, then its alpha in the last one
     static constexpr uint32_t kBits = (1u << K) - 1u;
 };
-// (row, 64 columns) units a wave has in flight while staging: a tile's loads in one or two batches
-constexpr int units_ahead(int C) { return C == 1 ? 16 : 30 / C; }
+// (row, 64 columns) units a wave has in flight while staging: a tile's loads in one to three batches.  (Each holds a
+// lane mask: with 15 or 16 of them the scalar registers spilled, 4 x 160 x 160 C=2 3x3 F=32 14.4 us, 11.9 with ten.)
+constexpr int units_ahead(int C) { return C <= 3 ? 10 : 30 / C; }
 
 struct TileParams {
     const float *I;
