@@ -646,6 +646,9 @@ TilePlan tile_plan(const Geom &g)
     pl.gx = ceil_div(g.OW, pl.tw);
     auto blocks = [&](int th) { return (long long)g.N * pl.gx * ceil_div(g.OH, th); };
     if (pl.th > 1 && blocks(pl.th) < 768) pl.th = std::max(1, std::min(pl.th, 256 / pl.tw));
+    // (a launch that leaves units idle is as long as one workgroup: what it stages in one batch of loads)
+    auto units = [&](int th) { return (long long)((th - 1) * g.sh + g.kh) * ceil_div((pl.tw - 1) * g.sw + g.kw, 64); };
+    while (pl.th > 1 && blocks(pl.th) < 64 && units(pl.th) > kWaves * units_ahead(g.C)) pl.th = (pl.th + 1) / 2;
     pl.gy = ceil_div(g.OH, pl.th);
     while (pl.group > 16 && blocks(pl.th) * ceil_div(g.F, pl.group) < 768) pl.group = (pl.group + 1) / 2;
     return pl;

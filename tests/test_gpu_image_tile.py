@@ -24,6 +24,7 @@ SHAPES = [
     (16, 3, 115, 117, 64, 7, 3, 2, 2),
     (1, 3, 900, 3000, 20, 7, 3, 9, 11), # strides so large that a tile has to shrink to fit the LDS
     (1, 4, 130, 128, 2, 7, 0, 4, 4),    # few filters, strided
+    (4, 3, 79, 69, 49, 3, 1, 4, 4),     # few workgroups: tiles of what one batch of loads stages
 ]
 
 
