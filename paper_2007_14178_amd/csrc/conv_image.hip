@@ -660,11 +660,16 @@ TilePlan tile_plan(const Geom &g)
 // or fewer per filter.  Measured, sliding window / tiles, 2 x C x 500 x 500 unless said otherwise:
 // 16 x 3 x 227 x 227 F=64 7x7 stride 2 67 / 24 us; C=3 7x7 F=64 49 / 34 us, F=8 1.17x, F=4 0.94x; the same
 // with stride 2 F=4 1.5x; C=3 3x3 F=16 1.28x, F=4 0.76x, stride 2 F=4 1.25x; C=1 3x3 F=16 0.97x, F=4 0.59x.
+// On large images the sliding window has waves enough without sharing out its filters: 8 x 300 x 300 C=2 3x3 F=16 16.4 / 17.3,
+// C=3 5x5 F=8 18.3 / 19.7, F=16 and C=3 7x7 1.0 to 1.1x; stride 2 C=3 3x3 F=2 8.8 / 10.3 (8 x 128 x 128: 1.24x).
 bool tile_pays(const Geom &g)
 {
     if (g.F < 2 || (long long)g.OH * g.OW >= (1LL << 29)) return false;    // (31-bit byte offsets in a plane)
     const int kc = g.kw * g.C;
-    return (g.F >= 16 && kc >= 6) || (g.F >= 8 && kc >= 15) || (g.sh >= 2 && g.sw >= 2 && kc >= 9);
+    const long long pixels = (long long)g.N * g.OH * g.OW;
+    if (g.sh >= 2 && g.sw >= 2 && kc >= 9) return g.F >= 8 || pixels < 150000;
+    if (pixels >= 400000 && g.sh == 1 && g.sw == 1) return g.F >= 16 && kc >= 10;
+    return (g.F >= 16 && kc >= 6) || (g.F >= 8 && kc >= 15);
 }
 
 template <int K, int C>
