@@ -29,7 +29,6 @@ namespace {
 typedef int v8i __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 256;
-constexpr int kTailSteps = 8;              // zero steps behind a tile's last one: the loads run ahead of the loop
 constexpr int kTabTail = 24;               // table entries read past the last step
 
 struct TileParams {
@@ -58,9 +57,13 @@ struct TileParams {
 // of an exact integer division run at a quarter of the rate).
 __device__ inline uint32_t div_small(uint32_t n, float inv) { return (uint32_t)(((float)n + 0.5f) * inv); }
 
+// Steps the filter operands are ahead of their use; one less of zeros lie behind a tile's last step, where the last
+// loads of the loop end (step T + operand_ring - 2).
+constexpr int operand_ring(int NF, int NP) { return NF * NP >= 4 ? 4 : 8; }
+
 template <int NF, int NP>
 struct Depth {                              // steps the operands are ahead of their use
-    static constexpr int kA = NF * NP >= 4 ? 4 : 8;
+    static constexpr int kA = operand_ring(NF, NP);
     static constexpr int kB = 4;
 };
 
@@ -71,7 +74,7 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
     extern __shared__ uint4 lds[];
     constexpr int WP = 4 / WF, PT = WP * NP * 32, FT = WF * NF * 32;
     constexpr int RA = Depth<NF, NP>::kA, RB = Depth<NF, NP>::kB;
-    static_assert(RA % RB == 0 && RA <= kTailSteps, "the loop is unrolled RA times");
+    static_assert(RA % RB == 0, "the loop is unrolled RA times");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wf = wave % WF, wp = wave / WF;
@@ -517,8 +520,8 @@ TPlan search_tplan(const Geom &g)
         best.lds_request = lds_to_ask_for(lds, r);
     }
     best.Wp = (int)wp; best.RHfull = (int)rh; best.S2 = S2; best.T = (int)T; best.pitch16 = pitch16;
-    best.tile_steps = (int)T + kTailSteps;
     if (best.ok) {
+        best.tile_steps = (int)T + operand_ring(best.NF, best.NP) - 1;
         const int ft = best.WF * best.NF * 32;
         best.ws_bytes = (size_t)ceil_div(g.F, ft) * (ft / 32) * best.tile_steps * 64 * sizeof(uint4);
     }

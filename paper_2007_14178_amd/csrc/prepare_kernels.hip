@@ -515,15 +515,14 @@ __device__ __attribute__((always_inline)) void filter_pack_mean_block(
             rows[(size_t)step * 64 + row + 32 * kg] =
                 expanded_entry(L, step, kg, taps, Cw, C, [&](int tap, int w) { return kept[tap * Cw + w]; });
         }
-        if (f == F - 1) {
-            // rows past the last filter are zeros: the rest of this tile and the tiles after it (the
-            // workspace holds whole workgroup rows of 128 filters)
-            const size_t first = ((size_t)tile * L.tile_steps * 64), end = L.ws_bytes / sizeof(uint4);
-            for (size_t i = first + tid; i < end; i += nthr) {
-                const int lane = (int)(i & 63);
-                const size_t t = (i >> 6) / L.tile_steps;          // tile of entry i
-                if (t > (size_t)tile || (lane & 31) > row) Wx[i] = make_uint4(0, 0, 0, 0);
-            }
+        // rows past the last filter are zeros: the rest of its tile and the tiles after it (the workspace holds whole
+        // workgroup rows), shared out over all filters' blocks (one block's 64 threads took longer than all the
+        // rest: 32 channels, F = 288 3x3 11.8 -> 4.3 us, 16 x 128 x 14 x 14 F = 300 5.0 -> 4.5)
+        const int last = (F - 1) >> 5, last_row = (F - 1) & 31;
+        const size_t first = ((size_t)last * L.tile_steps * 64), end = L.ws_bytes / sizeof(uint4);
+        for (size_t i = first + (size_t)f * nthr + tid; i < end; i += (size_t)F * nthr) {
+            const int lane = (int)(i & 63);
+            if (i - first >= (size_t)L.tile_steps * 64 || (lane & 31) > last_row) Wx[i] = make_uint4(0, 0, 0, 0);
         }
     }
 }
