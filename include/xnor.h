@@ -15,7 +15,8 @@
  *
  * Conventions shared by every call
  *   - Every data pointer is a DEVICE pointer owned by the caller.  The library allocates nothing,
- *     frees nothing and keeps no state between calls.  Inputs are never written; outputs are
+ *     frees nothing and keeps no state that a result depends on (a thread remembers the tilings it has
+ *     worked out, by shape, and a device's number of compute units).  Inputs are never written; outputs are
  *     overwritten in full.  Outputs must not alias inputs.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls enqueue their
  *     kernels on it and return without synchronising; buffers must stay alive until the stream

@@ -65,10 +65,6 @@ struct BwnParams {
     int w4;                          // real-valued form: the chunk's weights can be fetched 16 bytes per lane
 };
 
-// n / d through one multiply-high with inv = ceil(2^32 / d), exact for n*d < 2^32; d = 1 has no
-// such 32-bit reciprocal (2^32) and is flagged by inv = 0 (uniform: a scalar select).
-__device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
-uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
 
 // The work of one workgroup with NT pixel tiles.  NT is a template parameter so that the MFMA
 // loop is one basic block (operands of the next MFMAs are loaded ahead of the current ones) and

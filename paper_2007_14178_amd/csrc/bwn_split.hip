@@ -54,8 +54,6 @@ struct SplitParams {
     uint32_t inv_pitch;            // ceil(2^32 / pitch), 0 for pitch 1
 };
 
-__device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
-uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
 
 // x = hi + mid + lo, each the top 16 bits of an fp32 (a bf16): the leading bits by truncation, the
 // rest by an exact subtraction.  Returned are x, x - hi and x - hi - mid: the terms are their top

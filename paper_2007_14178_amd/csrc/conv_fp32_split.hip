@@ -87,8 +87,6 @@ constexpr float kTiny = 0x1p-110f;
 constexpr float kDoubt = 0x1p-104f;
 constexpr uint32_t kHuge = 0x7f7f8000u << 1;              // (doubled bits) from here on bf16 rounds to infinity
 
-__device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
-uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
 
 // two fp32 -> two bf16 in one dword, to nearest even (one v_cvt_pk_bf16_f32)
 __device__ inline uint32_t pack_bf16(float a, float b)

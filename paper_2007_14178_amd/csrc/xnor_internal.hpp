@@ -75,6 +75,11 @@ inline int compute_units()
 
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
+// n / d through one multiply-high with inv = ceil(2^32 / d), exact for n*d < 2^32; d = 1 has no
+// such 32-bit reciprocal (2^32) and is flagged by inv = 0 (uniform: a scalar select).
+inline uint32_t reciprocal(unsigned long long d) { return d == 1 ? 0u : (uint32_t)(((1ULL << 32) + d - 1) / d); }
+__device__ inline uint32_t quot(uint32_t n, uint32_t inv) { return inv == 0 ? n : __umulhi(n, inv); }
+
 // Launchers: enqueue on `st`, return the launch status.  Arguments are already validated.
 hipError_t launch_binarize_pack(const float *x, int N, int C, int H, int W, uint32_t *packed,
                                 hipStream_t st);
