@@ -30,16 +30,25 @@ static long long xcd_blocks(long long blocks) { return (blocks + 7) / 8 * 8; }
 // ------------------------------------------------------------------------------------------------
 template <int WPT>
 __global__ __launch_bounds__(256) void binarize_pack_kernel(const float *__restrict__ x,
-                                                            long long NP, int C, int HW, int Cw, int groups,
+                                                            long long NP, int C, int HW, int Cw, int groups, int full,
                                                             uint32_t *__restrict__ packed)
 {
     // A pixel block's groups of words one after the other on the same XCD: its L2 puts their words together to whole
     // cache lines.  (With a group's blocks side by side instead, words of other XCDs between them, 49 x 396 x 32 x 32
     // took 20.9 us, 12.5 so, 85 x 326 x 23 x 23 16.4 / 11.3, 128 x 512 x 28 x 28 43.4 / 37.4.)
-    const uint32_t blocks = (uint32_t)((NP + 255) / 256);                 // (blocks * groups below 2^31)
-    const uint32_t b = (uint32_t)xcd_block(blockIdx.x, (long long)blocks * groups);
-    const uint32_t block = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b / (uint32_t)groups));   // (a quotient is a vector register otherwise)
-    const int w0 = (int)(b - block * (uint32_t)groups) * WPT;
+    // `full` < groups: the last group has few channels.  Its blocks come behind the others of their XCD, where they fill up
+    // the launch's end (94 x 34 x 60 x 60: 10.4 us one after the other, 7.8 so; 22 x 161 x 46 x 46 5.5 / 5.1).
+    const uint32_t blocks = (uint32_t)((NP + 255) / 256), eighth = (blocks + 7) >> 3;   // (blocks * groups below 2^31)
+    uint32_t b = (uint32_t)xcd_block(blockIdx.x, (long long)blocks * groups), first = 0;
+    bool behind = false;
+    if (full < groups) {
+        b = blockIdx.x >> 3;
+        first = (blockIdx.x & 7) * eighth;
+        behind = b >= eighth * (uint32_t)full;
+    }
+    const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b / (uint32_t)full));   // (a quotient is a vector register otherwise)
+    const uint32_t block = first + (behind ? b - eighth * (uint32_t)full : q);
+    const int w0 = (int)(behind ? (uint32_t)full : b - q * (uint32_t)full) * WPT;
     const long long p = (long long)block * 256 + threadIdx.x;
     if (p >= NP) return;
     const long long n = p / HW;
@@ -80,10 +89,11 @@ hipError_t launch_binarize_pack(const float *x, int N, int C, int H, int W, uint
     const long long NP = (long long)N * HW;
     const bool vec4 = (Cw % 4 == 0) && ((reinterpret_cast<uintptr_t>(packed) & 15) == 0);
     const int groups = vec4 ? Cw / 4 : Cw;                // of words: one per block and pixel
-    const long long blocks = xcd_blocks((long long)ceil_div(NP, 256) * groups);
+    const int full = !vec4 && groups > 1 && C % 32 != 0 && C % 32 <= 8 ? groups - 1 : groups;
+    const long long blocks = full < groups ? xcd_blocks(ceil_div(NP, 256)) * groups : xcd_blocks((long long)ceil_div(NP, 256) * groups);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (vec4) binarize_pack_kernel<4><<<dim3((unsigned)blocks), 256, 0, st>>>(x, NP, C, HW, Cw, groups, packed);
-    else binarize_pack_kernel<1><<<dim3((unsigned)blocks), 256, 0, st>>>(x, NP, C, HW, Cw, groups, packed);
+    if (vec4) binarize_pack_kernel<4><<<dim3((unsigned)blocks), 256, 0, st>>>(x, NP, C, HW, Cw, groups, full, packed);
+    else binarize_pack_kernel<1><<<dim3((unsigned)blocks), 256, 0, st>>>(x, NP, C, HW, Cw, groups, full, packed);
     return hipGetLastError();
 }
 
