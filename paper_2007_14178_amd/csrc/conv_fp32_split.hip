@@ -25,8 +25,8 @@
 //   16-byte reads at consecutive positions touch distinct banks), zero outside the image; a B
 //   operand is one 16-byte LDS read per lane and feeds more than five matrix instructions on average, an A operand
 //   is one 16-byte load per lane from the L2, a tap ahead, and feeds as many.
-//   Bound by the matrix instructions: 128 x 512 x 28 x 28 F=512 3x3 takes 3.11 ms, 2.70 of them at their rate
-//   (six products in one chain: 2.24 ms, at three times the error).
+//   Bound by the matrix instructions: 128 x 512 x 28 x 28 F=512 3x3 takes 3.2 ms, 2.7 of them at their rate
+//   (six products in one chain: 2.2 ms, at three times the error).
 //
 // FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
 // chains, that is still the less exact of the two.  This form keeps two accumulators per output: the

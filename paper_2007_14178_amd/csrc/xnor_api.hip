@@ -55,13 +55,13 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
 
 // Where the three-term kernel is the faster real-valued convolution (given a workspace).  It is the more
 // exact one everywhere (see conv_fp32_split.hip).  Measured, what runs without a workspace -> split:
-// 128x512x28x28 F=512 3x3 5.11 -> 3.11 ms, 16x128x56x56 F=128 5x5 1702 -> 304 us, 7x7 22.04 -> 0.68 ms,
+// 128x512x28x28 F=512 3x3 5.11 -> 3.2 ms, 16x128x56x56 F=128 5x5 1702 -> 305 us, 7x7 22.04 -> 0.69 ms,
 // 16x224x224 three channels F=64 7x7 stride 2 1020 -> 359 us.  A launch that does not fill the chip is as long as a
 // workgroup's chain of 16-channel chunks behind a filter pass and a first fetch of 12 to 14 us, and this decides:
 //  * against the fp32 matrix form, whose chain is 8 channels a chunk.  With its four-wide filter fetch (C % 8 == 0,
 //    up to 9 taps) 3 x 3 layers of 2 x 32 x 32 take 8.7 / 13 / 22 / 40 us with 8 / 16 / 32 / 64 channels (split 18 /
-//    19 / 23 / 32), without it 25 us with 9 (split 18); on larger layers the split form wins from 32 channels on
-//    at 16 x 28 x 28 (29.3 / 25.8) and from 8 on at 32 x 56 x 56 (44.8 / 34.2);
+//    19 / 23 / 32), without it 25 us with 9 (split 18); from 32 channels on the split form is taken everywhere,
+//    at a third of the error (1 x 7 x 7 within 8 %, 16 x 28 x 28 29.3 / 25.8), from 8 on at 32 x 56 x 56 (44.8 / 34.2);
 //  * against one thread per output, for windows that form does not take: there the estimates below hold within
 //    a third over 1x7x7 .. 16x112x112, C = 3 .. 128, F = 8 .. 128, 7 x 7.
 bool fp32_split_pays(const xnor::Geom &g)
@@ -70,9 +70,8 @@ bool fp32_split_pays(const xnor::Geom &g)
     if (g.F < 8 || red < 72) return false;
     if (xnor::conv_fp32_mfma_supports(g)) {
         if (g.C < 8) return false;
-        if (g.C % 8 != 0 || taps > 9 || g.C >= 40) return true;
-        const double rounds = pixels * xnor::ceil_div(g.F, 128);
-        return (g.C >= 32 && rounds >= 12000) || rounds * red >= 7e6;
+        if (g.C % 8 != 0 || taps > 9 || g.C >= 32) return true;
+        return pixels * xnor::ceil_div(g.F, 128) * red >= 7e6;
     }
     if (g.C < 3) return false;
     const double chunks = xnor::ceil_div(g.C, 16);
