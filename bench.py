@@ -743,7 +743,7 @@ def run_image(args, xb, torch, side):
                    "binary_macs": 9 * side * side},
         "graph_ms_per_step": graph_ms, "graph_replays_match_eager": ok,
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
-                     "traffic": None, "kernel": "conv_image_kernel (xnor_forward_image)", "kernel_ms": kernel_ms,
+                     "traffic": None, "kernel": "xnor_forward_image (one channel: conv_image_kernel, conv_image_row4_kernel from half a million pixels on)", "kernel_ms": kernel_ms,
                      "timing": f"{reps} back-to-back launches per graph replay, events on the launch stream"},
     }
     if not args.no_cpu_baseline:
