@@ -562,9 +562,11 @@ def run_vanilla_layer(args, xb, torch, layer, make_input, make_weights):
     out = torch.empty((s.N, s.F, OH, OW), dtype=torch.float32, device="cuda")
     ms = time_call(torch, lambda: xb.xnor_conv2d_fp32_fwd(dI, dW, s, out=out), args.warmup, args.steps)
     macs = layer.binary_macs                      # the same count of multiply-accumulates, now real-valued
-    # with its workspace the call splits both operands into three bf16 terms and sums eight of their products
+    # with its workspace the call splits both operands into three bf16 terms: six matrix instructions' worth of
+    # products for windows of up to 5 x 5 or so, eight where the kernel with short chains runs (7 x 7)
     split = xb.xnor_conv2d_fp32_workspace_bytes(s) > 0
-    flops_per_mac = 16.0 if split else 2.0
+    products = 8 if layer.kh * layer.kw >= 49 else 6
+    flops_per_mac = 2.0 * products if split else 2.0
     peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     achieved = flops_per_mac * macs / (ms * 1e-3) / 1e12
     rec = {
@@ -572,7 +574,7 @@ def run_vanilla_layer(args, xb, torch, layer, make_input, make_weights):
         "value": macs / (ms * 1e-3) / 1e9, "unit": "GMAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "fp32 input and weights, fp32 accumulate " +
-                 ("(each operand split into three bf16 terms, eight products, v_mfma_f32_32x32x16_bf16)" if split
+                 (f"(each operand split into three bf16 terms, {products} products, v_mfma_f32_32x32x16_bf16/f16)" if split
                   else "(v_mfma_f32_32x32x2_f32)"),
         "data": "synthetic (seeded; shapes and value distributions of the benchmark layer)",
         "config": {"workload": f"{layer.name} as a real-valued layer: N={layer.N} C={layer.C} {layer.H}x{layer.W} "

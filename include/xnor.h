@@ -76,7 +76,7 @@ typedef enum {
                                (the _algo calls only; tests and measurements)                     */
     XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split exactly into three bf16
                                terms, v_mfma_f32_32x32x16_bf16 against +-1 weights;
-                               xnor_conv2d_fp32_fwd_ws: both operands split so, eight products      */
+                               xnor_conv2d_fp32_fwd_ws: both operands split so                      */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
@@ -349,11 +349,11 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
 
 /*
  * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
- * both operands split exactly into three bf16 terms and eight of their nine products (all but the
- * one below 2^-32 of the whole) summed in fp32 by the bf16 matrix instruction.  Results are closer to the
- * exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32 arithmetic
- * gives them, and an output so small that bits of a value below bf16's range could matter to it is
- * formed by the plain fp32 sum.
+ * both operands split exactly into three bf16 terms whose products are summed in fp32 by the bf16 and f16
+ * matrix instructions (the smallest ones, together at most 2^-16 of the whole, from terms rounded to 11 bits).  Results are
+ * closer to the exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32
+ * arithmetic gives them, and an output so small that bits of a value could matter to it that is small beside the
+ * largest of its image or filters is formed by the plain fp32 sum.
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes

@@ -1,47 +1,59 @@
-// Real-valued fp32 convolution (the float comparison of Sec. IV, Table I) on the bf16 matrix
-// instruction.  Both operands are split into three bf16 terms, x = hi + mid + lo, each the nearest
+// Real-valued fp32 convolution (the float comparison of Sec. IV, Table I) on the 16-bit matrix
+// instructions.  Both operands are split into three bf16 terms, x = hi + mid + lo, each the nearest
 // bf16 to what the terms before it left over (3 x 8 significand bits hold all 24 of an fp32, both
-// differences are exact: |mid| <= 2^-8, |lo| <= 2^-17 of x's leading bit), and eight of the nine products
-// are summed in fp32.  The one left out, lo*lo, is below 2^-32 of |x*w|: less than the others' sum is
-// rounded by.
+// differences are exact: |mid| <= 2^-8, |lo| <= 2^-17 of x's leading bit).  With r = mid + lo a product is
+//   hi*hi + hi*mid + hi*lo + mid*hi + lo*hi + r*r,
+// the first five on the bf16 instruction and the last one, at most 2^-16 of the whole, on the f16 one with r
+// rounded to f16's 11 bits (2^-29 of the whole lost on average, of either sign; 2^-26 at most): six matrix instructions per 16
+// channels where bf16 alone takes eight (mid*mid, mid*lo and lo*mid in place of r*r; 3.2 against 2.6 ms below).
+//   f16's range is kept by powers of two: an image is multiplied by the one that brings its largest magnitude to
+// 2^23 .. 2^24, a filter tile's chunk of 16 channels by its own, and a chain's sum is divided by both where it joins the output's.
 //
-// What the sum loses.  The eight products of a (tap, 16 channels) step form a chain of their own that
-// starts at zero, small products first, and joins the output's sum in one addition: the large sum is
-// rounded once per 16 terms (the fp32 matrix instruction rounds it once per two, and six products in one
-// chain with it were no better).  The bf16 instruction shifts what it adds to the exponent of the
-// largest and drops the rest towards minus infinity, which left every output the same amount too low
-// (0.27e-6 of their root mean square for 7 x 7 x 416 terms): the weights of every other chain are therefore
-// stored negated and its sum is subtracted.  Measured against 64-bit sums over layers of 32 to 512 channels,
-// 1 x 1 to 7 x 7: 0.17 to 0.57 of the error of the kernels that run without a workspace, for values of
-// either sign as for positive ones.
+// What the sum loses.  The products of two taps x 16 channels form a chain of their own that starts at zero,
+// small products first, and joins the output's sum in one addition: the large sum is rounded once per 32
+// terms (the fp32 matrix instruction rounds it once per two, and six products in one chain with it were
+// no better).  The instructions shift what they add to the exponent of the largest and drop the rest towards
+// minus infinity, which left every output the same amount too low (0.27e-6 of their root mean square for 7 x 7 x 416
+// terms): the weights of every other chain are therefore stored negated and its sum is subtracted.  Measured
+// against 64-bit sums over layers of 32 to 512 channels, 1 x 1 to 7 x 7, normal, positive, constant and
+// log-normal values and channels of very different sizes: at the median 0.83 of the error of chains of one tap
+// with eight products (0.74 with many terms), which had 0.17 to 0.57 of that of the kernels without a workspace.
 //
-//   split_filters_kernel: filters -> the A operands of the convolution in its order, into the
-//   caller's workspace, 6 bytes per weight: [filter tile of 32][chunk of 16 channels][tap][term]
-//   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7).
+//   split_operands_kernel: filters -> the A operands of the convolution in its order, into the
+//   caller's workspace, 8 bytes per weight: [filter tile of 32][chunk of 16 channels][tap][hi, mid, lo, r]
+//   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7); beside it the largest and
+//   smallest magnitudes of the images' parts (the read of the input that this takes is 1.5 % of the whole).
 //   conv_fp32_split_kernel: workgroup = 4 waves = 128 filters x up to 4 tiles of 32 output pixels of
 //   one image (64 filters x up to 8 tiles for layers of at most 64 filters); wave = 64 filters x up
-//   to two tiles (a third one's accumulators would leave no registers for the chains).  Per chunk of 16 channels the input under the pixels is fetched a chunk ahead,
-//   split and staged in LDS as [position][term][16 channels] (112 bytes a position: sixteen lanes'
-//   16-byte reads at consecutive positions touch distinct banks), zero outside the image; a B
-//   operand is one 16-byte LDS read per lane and feeds more than five matrix instructions on average, an A operand
-//   is one 16-byte load per lane from the L2, a tap ahead, and feeds as many.
-//   Bound by the matrix instructions: 128 x 512 x 28 x 28 F=512 3x3 takes 3.2 ms, 2.7 of them at their rate
-//   (six products in one chain: 2.2 ms, at three times the error).
+//   to two tiles (a third one's accumulators would leave no registers for the chains).  Per chunk of 16 channels
+//   the input under the pixels is fetched a chunk ahead (buffer loads: outside the image they give the zeros of
+//   the padding), split and staged in LDS as [position][term][16 channels] (144 bytes a position: sixteen
+//   lanes' 16-byte reads at consecutive positions touch distinct banks).  A B operand is one 16-byte LDS read per
+//   lane and feeds three matrix instructions on average, an A operand is one 16-byte load per lane from the L2
+//   and feeds as many; each is fetched again into its registers behind its last use, 7 (LDS) and 15 (L2) matrix
+//   instructions ahead of its next one.
+//   128 x 512 x 28 x 28 F=512 3x3: 3.19 -> 2.64 ms against eight products in chains of one tap, 16 x 128 x 56 x 56 F=128
+//   5x5 308 -> 233 us.  Bound by power as much as by time: the chip runs at 1.77 GHz, the matrix pipe is busy for
+//   59 % of the cycles (a register-only loop of the bf16 instruction on random operands keeps 1.74 GHz).  Timing-only builds of
+//   the first layer: without the filter loads 2.21 ms, without the split and staging 2.32, without the additions of
+//   chains to sums 2.36, without all three 1.91.  One wave per SIMD with four tiles (half the filter loads): 2.94 ms.
 //
 // FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
 // chains, that is still the less exact of the two.  This form keeps two accumulators per output: the
 // matrix instructions sum two taps of a chunk, then that sum is added to the other accumulator and what the
-// addition rounded off is where the next chain starts from (0.43 of the error of one thread per output).
+// addition rounded off is where the next chain starts from (0.43 of the error of one thread per output).  It has no
+// registers for a fourth term: three, unscaled, and eight products (all but lo*lo, below 2^-32 of the whole).
 //
 // What the split cannot hold goes by the fp32 matrix instruction instead (plain_tiles), a wave's outputs at
-// a time: all outputs of a workgroup that stages an infinity, a NaN or a value whose first term
-// overflows (it leaves the loop at the chunk that has one), outputs that came out infinite or NaN, and
-// outputs so small that bits of a value below 2^-133, bf16's last one, could matter to them (only
-// where an input or weight below 2^-110 was seen, see `doubtful`).  The instructions themselves keep subnormals.
+// a time: outputs that came out infinite or NaN, and outputs so small that bits of a value that is small beside
+// the largest of its image (filter tile) could matter to them, only where such values were seen (`doubtful`); with
+// FLUSH also all outputs of a workgroup that stages an infinity, a NaN or a value whose first term overflows (it
+// leaves the loop at the chunk that has one).  The instructions themselves keep subnormals.
 // A launch whose every output goes that way: see plain_tiles.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "xnor_internal.hpp"
 
@@ -52,24 +64,37 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kChan = 16;              // channels per chunk = the reduction length of one matrix instruction
-constexpr int kPosBytes = 112;         // 3 terms x 32 bytes + 16: see above
-// Granules (8 channels of one position) a thread fetches ahead per chunk.  The form with short chains (see
-// FLUSH) holds two accumulators per output and has fewer registers for them.
-constexpr int gran(bool flush) { return flush ? 3 : 4; }
+// Terms of a split operand: hi, mid, lo in bf16, and but for the form with short chains (see FLUSH) mid + lo in f16.
+constexpr int terms(bool flush) { return flush ? 3 : 4; }
+constexpr int pos_bytes(bool flush) { return terms(flush) * 32 + 16; }         // see above
+constexpr int operand_bytes(bool flush) { return terms(flush) * 1024; }        // the A operands of a (filter tile, chunk, tap)
+// Granules (8 channels of one position) a thread fetches ahead per chunk: three, or four where 32 pixels stage more
+// positions than that (the form with short chains has no such variant).
+constexpr int kGranules = 3, kMostGranules = 4;
+constexpr int max_pos(int granules) { return granules * 128; }   // staged positions of a workgroup
 constexpr int kWaveTiles = 2;          // pixel tiles per wave
-constexpr int max_pos(bool flush) { return gran(flush) * 128; }   // staged positions of a workgroup
-constexpr int chain_taps(bool flush) { return flush ? 2 : 1; }   // taps of a chunk in a chain
+// Chains of the form without short ones: the taps of a chunk two and two, the last one alone where their number is odd.
+// (The other form counts the taps of all chunks in a row.)
+__device__ inline bool chain_negated(bool flush, int chunk, int tap, int taps)
+{
+    return (flush ? (chunk * taps + tap) >> 1 : chunk * ((taps + 1) / 2) + (tap >> 1)) & 1;
+}
 constexpr int kMaxTaps = 49;           // 7 x 7; the filter pass holds 32 x 8 channels x taps in LDS
-constexpr int kOperandBytes = 3 * 1024;   // the three A operands of a (filter tile, chunk, tap)
 constexpr size_t kLdsShared = 80 * 1024;  // two workgroups per compute unit
 
 struct Fp32SplitParams {
     const float *I;
     const float *Wt;
-    const unsigned char *Wx;       // split filters, then one word per (filter tile, 8 channels): kTinyBit | max
+    const unsigned char *Wx;       // split filters
+    const uint32_t *wstat;         // one word per (filter tile, 8 channels): kTinyBit | largest magnitude
+    const int *wexp;               // per (filter tile, chunk): the power of two its weights are stored times
+    const uint32_t *xstat;         // per (image, part of it): largest and smallest non-zero magnitude
+    int xparts;
     float *out;
     int N, C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW;
     int nchunks, ftiles;
@@ -82,17 +107,36 @@ struct Fp32SplitParams {
     uint32_t inv_pitch;
 };
 
+constexpr int kRaw = 0x00027000;             // (buffer descriptor: a plain buffer of dwords)
+constexpr uint32_t kOutside = 0xfffffff0u;   // (an offset beyond any buffer: the load is 0)
 constexpr uint32_t kTinyBit = 0x80000000u;
 constexpr float kTiny = 0x1p-110f;
 constexpr float kDoubt = 0x1p-104f;
 constexpr uint32_t kHuge = 0x7f7f8000u << 1;              // (doubled bits) from here on bf16 rounds to infinity
+constexpr uint32_t kInfBits = 0x7f800000u;
 
+// The power of two that brings a largest magnitude (its bits) to 2^23 .. 2^24 (see above), as far as two factors and
+// their product stay in fp32's range.
+constexpr int kTop = 23, kMostX = 90, kMostW = 59;
+__device__ inline int scale_of(uint32_t top, int most) { return top == 0 ? 0 : min(most, kTop + 127 - (int)(top >> 23)); }
+constexpr int kHeldExp = -6;                              // scaled values from 2^-6 on: see `doubtful`
+// 2^e for e >= -149, infinite from 2^128 on
+__device__ inline uint32_t power_bits(int e)
+{
+    return e > 127 ? kInfBits : e > -127 ? (uint32_t)(e + 127) << 23 : 1u << max(0, e + 149);
+}
 
 // two fp32 -> two bf16 in one dword, to nearest even (one v_cvt_pk_bf16_f32)
 __device__ inline uint32_t pack_bf16(float a, float b)
 {
     const floatx2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// two fp32 -> two f16 in one dword, to nearest even (one v_cvt_pk_f16_f32)
+__device__ inline uint32_t pack_f16(float a, float b)
+{
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
 }
 // what the bf16 pair `t` leaves of (a, b); exact
 __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
@@ -101,58 +145,132 @@ __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
     b -= __uint_as_float(t & 0xffff0000u);
 }
 
-// 32 filters x 8 channels x all taps per workgroup: a coalesced read into LDS (a filter's channels are
-// one run in memory), then per (tap, filter) eight values from LDS, split, and three 16-byte writes of
-// 32 lanes side by side.  HBM-bound: 4 bytes read and 6 written per weight.
-__global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__restrict__ Wt, int F, int C, int taps,
-                                                                 int nchunks, int ftiles, int chain_taps, unsigned char *__restrict__ Wx)
+// Filters: 32 of them x 8 channels x all taps per workgroup: a read in runs (a filter's channels are one run in
+// memory) into LDS, then per (tap, filter) eight values from LDS, split, and 16-byte writes of 32 lanes side by
+// side.  4 bytes read and 8 (6) written per weight.  The chunk's other eight channels are read for their largest
+// magnitude alone: the chunk has one power of two.
+//   Images (not with FLUSH): the workgroups past those find the magnitudes of a part of an image each.
+struct Fp32StatParams {
+    const float *I;
+    uint32_t *xstat;
+    int per_image, parts, per_part;     // values
+};
+
+template <bool FLUSH>
+__global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *__restrict__ Wt, int F, int C, int taps, int nchunks, int ftiles,
+                                                                  uint32_t inv_run, Fp32StatParams x, unsigned char *__restrict__ Wx)
 {
     extern __shared__ float wl[];
-    __shared__ uint32_t stat[2];
-    const int octs = 2 * nchunks;
+    __shared__ uint32_t stat[3];
+    const int octs = 2 * nchunks, fblocks = ftiles * octs;
+    if (threadIdx.x < 3) stat[threadIdx.x] = threadIdx.x == 1 ? 0xffffffffu : 0u;
+    __syncthreads();
+    uint32_t top = 0, low = 0xffffffffu;         // of the magnitudes' bits; low: less one (0 - 1 wraps to the top)
+    constexpr int kBatch = 8;                    // loads of a thread in flight
+    if (!FLUSH && (int)blockIdx.x >= fblocks) {
+        const int b = (int)blockIdx.x - fblocks, n = b / x.parts, first = (b - n * x.parts) * x.per_part;
+        const float *src = x.I + (size_t)n * x.per_image;
+        const int end = min(first + x.per_part, x.per_image);
+        for (int i = first + (int)threadIdx.x; i < end; i += kBatch * kThreads) {
+            uint32_t u[kBatch];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) u[k] = __float_as_uint(src[min(i + k * kThreads, end - 1)]) & ~kTinyBit;
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                top = max(top, u[k] < kInfBits ? u[k] : 0u);
+                low = min(low, u[k] - 1u);
+            }
+        }
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) {
+            top = max(top, (uint32_t)__shfl_xor((int)top, m));
+            low = min(low, (uint32_t)__shfl_xor((int)low, m));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&stat[0], top);
+            atomicMin(&stat[1], low);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            x.xstat[2 * b] = stat[0];
+            x.xstat[2 * b + 1] = stat[1];
+        }
+        return;
+    }
     const int ft = blockIdx.x / octs, oc = blockIdx.x - ft * octs;
     const int run = 8 * taps, pitch = run | 1;                     // (odd: filters fall into distinct banks)
-    const int live = max(0, min(8, C - 8 * oc)) * taps;            // values of the run that exist
-    if (threadIdx.x < 2) stat[threadIdx.x] = threadIdx.x ? 0xffffffffu : 0u;
-    __syncthreads();
-    uint32_t top = 0, low = 0xffffffffu;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int f = wave; f < 32; f += kThreads / 64) {
-        const int fg = 32 * ft + f;
-        const float *src = Wt + ((size_t)min(fg, F - 1) * C + 8 * oc) * taps;
-        for (int i = lane; i < run; i += 64) {
-            const float v = fg < F && i < live ? src[i] : 0.f;
-            wl[f * pitch + i] = v;
-            const uint32_t twice = __float_as_uint(v) << 1;        // magnitude; 0 - 1 wraps to the top
-            top = max(top, twice);
-            low = min(low, twice - 1u);
+    // values of the run that exist, in this half of the chunk and in the other
+    const int live = max(0, min(8, C - 8 * oc)) * taps, live2 = FLUSH ? 0 : max(0, min(8, C - 8 * (oc ^ 1))) * taps;
+    uint32_t finite = 0;
+    for (int i0 = threadIdx.x; i0 < 32 * run; i0 += kBatch * kThreads) {
+        float v[kBatch], o[kBatch];
+        int at[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const int idx = min(i0 + k * kThreads, 32 * run - 1);
+            const int f = (int)quot((uint32_t)idx, inv_run), i = idx - f * run, fg = 32 * ft + f;
+            const float *src = Wt + (size_t)min(fg, F - 1) * C * taps;
+            const bool in = fg < F && i < live, in2 = fg < F && i < live2;
+            at[k] = f * pitch + i;
+            v[k] = src[in ? 8 * oc * taps + i : 0];
+            v[k] = in ? v[k] : 0.f;
+            if constexpr (!FLUSH) {
+                o[k] = src[in2 ? 8 * (oc ^ 1) * taps + i : 0];
+                o[k] = in2 ? o[k] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            wl[at[k]] = v[k];                                      // (the last value again: the same to the same place)
+            const uint32_t u = __float_as_uint(v[k]) & ~kTinyBit;
+            top = max(top, u);
+            low = min(low, u - 1u);
+            if constexpr (!FLUSH) {
+                const uint32_t u2 = __float_as_uint(o[k]) & ~kTinyBit;
+                finite = max(finite, max(u < kInfBits ? u : 0u, u2 < kInfBits ? u2 : 0u));
+            }
         }
     }
-    atomicMax(&stat[0], top);
-    atomicMin(&stat[1], low);
+#pragma unroll
+    for (int m = 1; m < 64; m *= 2) {
+        top = max(top, (uint32_t)__shfl_xor((int)top, m));
+        low = min(low, (uint32_t)__shfl_xor((int)low, m));
+        if constexpr (!FLUSH) finite = max(finite, (uint32_t)__shfl_xor((int)finite, m));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&stat[0], top);
+        atomicMin(&stat[1], low);
+        if constexpr (!FLUSH) atomicMax(&stat[2], finite);
+    }
     __syncthreads();
-    unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * kOperandBytes + (oc & 1) * 512;
+    const int e = FLUSH ? 0 : scale_of(stat[2], kMostW);
+    unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * operand_bytes(FLUSH) + (oc & 1) * 512;
     for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
         const int f = i & 31, t = i >> 5;
-        const float sgn = (((oc >> 1) * taps + t) / chain_taps) & 1 ? -1.f : 1.f;    // (every other chain: see above)
-        uint32_t h[4], m[4], l[4];
+        const bool negated = chain_negated(FLUSH, oc >> 1, t, taps);               // (every other chain: see above)
+        const float factor = negated ? -ldexpf(1.f, e) : ldexpf(1.f, e);
+        uint32_t h[4], m[4], l[4], r[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            float a = sgn * wl[f * pitch + (2 * k) * taps + t], b = sgn * wl[f * pitch + (2 * k + 1) * taps + t];
+            float a = factor * wl[f * pitch + (2 * k) * taps + t], b = factor * wl[f * pitch + (2 * k + 1) * taps + t];
             h[k] = pack_bf16(a, b);
             subtract_pair(a, b, h[k]);
+            r[k] = pack_f16(a, b);
             m[k] = pack_bf16(a, b);
             subtract_pair(a, b, m[k]);
             l[k] = pack_bf16(a, b);
         }
-        uint4 *o = reinterpret_cast<uint4 *>(dst + (size_t)t * kOperandBytes + f * 16);
+        uint4 *o = reinterpret_cast<uint4 *>(dst + (size_t)t * operand_bytes(FLUSH) + f * 16);
         o[0] = make_uint4(h[0], h[1], h[2], h[3]);
         o[64] = make_uint4(m[0], m[1], m[2], m[3]);
         o[128] = make_uint4(l[0], l[1], l[2], l[3]);
+        if constexpr (!FLUSH) o[192] = make_uint4(r[0], r[1], r[2], r[3]);
     }
     if (threadIdx.x == 0) {
-        uint32_t *stats = reinterpret_cast<uint32_t *>(Wx + (size_t)ftiles * nchunks * taps * kOperandBytes);
-        stats[blockIdx.x] = (stat[0] >> 1) | (stat[1] < (__float_as_uint(kTiny) << 1) - 1u ? kTinyBit : 0u);
+        uint32_t *stats = reinterpret_cast<uint32_t *>(Wx + (size_t)ftiles * nchunks * taps * operand_bytes(FLUSH));
+        const float tiny = FLUSH ? kTiny : ldexpf(1.f, kHeldExp - e);
+        stats[blockIdx.x] = stat[0] | (stat[1] < __float_as_uint(tiny) - 1u ? kTinyBit : 0u);
+        if (!FLUSH && (oc & 1) == 0) reinterpret_cast<int *>(stats + fblocks)[ft * nchunks + (oc >> 1)] = e;
     }
 }
 
@@ -171,7 +289,7 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
     const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
     const int HW = p.H * p.W, taps = p.kh * p.kw;
     const float *img = p.I + (size_t)n * p.C * HW;
-    const uint32_t *stats = reinterpret_cast<const uint32_t *>(p.Wx + (size_t)p.ftiles * p.nchunks * taps * kOperandBytes);
+    const uint32_t *stats = p.wstat;
     int ft[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) ft[i] = min((f0 >> 5) + i, p.ftiles - 1);
@@ -194,7 +312,7 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
     auto fetch = [&](int t, int ch) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(p.Wx + (((size_t)ft[i] * p.nchunks + ch) * taps + t) * kOperandBytes) + lane;
+            const uint4 *src = reinterpret_cast<const uint4 *>(p.Wx + (((size_t)ft[i] * p.nchunks + ch) * taps + t) * operand_bytes(FLUSH)) + lane;
             raw[i][0] = src[0];
             raw[i][1] = src[64];
             raw[i][2] = src[128];
@@ -218,11 +336,12 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
         for (int j = 0; j < NT; ++j) { total[i][j] = floatx16{}; part[i][j] = floatx16{}; }
     fetch(0, 0);
     for (int t = 0, ch = 0; t < taps;) {
-        const float sgn = ((ch * taps + t) / chain_taps(FLUSH)) & 1 ? -1.f : 1.f;
+        const float sgn = chain_negated(FLUSH, ch, t, taps) ? -1.f : 1.f;
         float w[2][8], b[NT][8];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             bool held = true;
+            const float back = FLUSH ? sgn : sgn * ldexpf(1.f, -p.wexp[ft[i] * p.nchunks + ch]);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const auto term = [&](int q) {
@@ -231,7 +350,7 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
                 };
                 const float hi = term(0);
                 held &= fabsf(hi) >= kTiny && fabsf(hi) < INFINITY;
-                w[i][k] = sgn * ((hi + term(1)) + term(2));
+                w[i][k] = back * ((hi + term(1)) + term(2));
             }
             // (uniform) does the operand hold all weights as they are, but for zeros?
             const uint32_t s0 = stats[(ft[i] * p.nchunks + ch) * 2], s1 = stats[(ft[i] * p.nchunks + ch) * 2 + 1];
@@ -280,14 +399,24 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
             for (int r = 0; r < 16; ++r) put(i, j, r, total[i][j][r]);
 }
 
+// f(0) .. f(23), each number a constant
+template <class F, int... M>
+__device__ __attribute__((always_inline)) inline void for_each_of(F f, std::integer_sequence<int, M...>)
+{
+    (f(std::integral_constant<int, M>{}), ...);
+}
+template <class F>
+__device__ __attribute__((always_inline)) inline void for_units(F f) { for_each_of(f, std::make_integer_sequence<int, 24>{}); }
+
 // The work of one wave with NT pixel tiles (0: it only takes part in the staging).  X0, Y0: the output
 // pixel of the workgroup's first tile (tw > 0); ix0, iy0: the input position of the staged block's corner.
-template <int NT, bool FLUSH>
+template <int NT, bool FLUSH, int GRAN>
 __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams &p, int n, int f0, int t0, int X0, int Y0,
                                                           int oy0, int iy0, int ix0, int rows, int tile0)
 {
-    // LDS: two input buffers, taken in turn by the chunks, each [npos][3][16] bf16 at a 112-byte pitch
+    // LDS: two input buffers, taken in turn by the chunks, each [npos][term][16 channels]
     extern __shared__ unsigned char lds_raw[];
+    constexpr int kGran = GRAN, kPosBytes = pos_bytes(FLUSH), kOperandBytes = operand_bytes(FLUSH);
     const int tile_bytes = p.npos * kPosBytes;
     const int lane = threadIdx.x & 63;
     const int col = lane & 31, half = lane >> 5;
@@ -332,13 +461,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             }
 #pragma unroll
     for (int r = 0; r < 16; ++r) tapsum[1][r] = 0.f;
-    float sgn = FLUSH ? 1.f : -1.f;              // of the current chain's weights (plain form: turned at the head of a tap)
-    int chain = chain_taps(true);                // FLUSH: taps until the next flush
-    // plain form: a step's products with filter tile i join the output's sum
-    auto settle = [&](int i, int j, float sign) __attribute__((always_inline)) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = fmaf(sign, tapsum[i][r], acc[i][j][r]);
-    };
+    float sgn = 1.f;                             // FLUSH: of the current chain's weights
+    int chain = 2;                               // ... taps until the next flush
     // FLUSH: a chain joins the output's sum, what the addition rounds off starts the next one
     auto flush = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -353,7 +477,32 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 }
         sgn = -sgn;
     };
-    constexpr int kGran = gran(FLUSH);
+    // else: a finished chain joins the output's sum, times what its operands are not scaled by and its sign
+    // (a quarter of its registers)
+    auto settle = [&](int i, int j, uint32_t factor, int quarter) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 4 * quarter; r < 4 * quarter + 4; ++r) acc[i][j][r] = fmaf(__uint_as_float(factor), tapsum[i][r], acc[i][j][r]);
+    };
+    // The image's power of two
+    uint32_t xtop = 0, xlow = 0xffffffffu;       // largest and smallest non-zero magnitude (FLUSH: of what was staged, doubled bits; low: less one)
+    int xexp = 0;
+    if constexpr (!FLUSH) {
+        if (lane < p.xparts) {
+            const uint2 v = reinterpret_cast<const uint2 *>(p.xstat)[n * p.xparts + lane];
+            xtop = v.x;
+            xlow = v.y;
+        }
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) {
+            xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, m));
+            xlow = min(xlow, (uint32_t)__shfl_xor((int)xlow, m));
+        }
+        xtop = __builtin_amdgcn_readfirstlane((int)xtop);
+        xlow = __builtin_amdgcn_readfirstlane((int)xlow);
+        xexp = scale_of(xtop, kMostX);
+    }
+    const float xscale = __uint_as_float(power_bits(xexp));
+
 
     const float *img = p.I + (size_t)n * p.C * HW;
 
@@ -367,7 +516,6 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     const int oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);
     uint32_t voff[kGran];
     int wr_off[kGran];
-    uint32_t okbits = 0;
 #pragma unroll
     for (int q = 0; q < kGran; ++q) {
         const int pos = min(q * 128 + tl, p.npos - 1);
@@ -376,20 +524,18 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         const int xw = (int)((uint32_t)pos - r * (uint32_t)p.pitch);
         const int iy = iy0 + (int)r, ix = ix0 + xw;
         const bool ok = (int)r < rows && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-        voff[q] = ok ? (uint32_t)(iy * p.W + ix) * 4u : 0u;
-        okbits |= ok ? 1u << q : 0u;
+        voff[q] = ok ? (uint32_t)(iy * p.W + ix) * 4u : kOutside;
     }
     float nxt[kGran][8];
     auto prefetch = [&](int ch) __attribute__((always_inline)) {
         const int c0 = ch * kChan + 8 * oct;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int c = c0 + k < p.C ? c0 + k : 0;                             // (scalar)
-            const char *plane_c = reinterpret_cast<const char *>(img + (size_t)c * HW);
+            // (scalar; a channel past the last one: an empty buffer, every load is 0)
+            const int c = min(c0 + k, p.C - 1);
+            const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(img + (size_t)c * HW), 0, c0 + k < p.C ? HW * 4 : 0, kRaw);
 #pragma unroll
-            for (int q = 0; q < kGran; ++q) {
-                nxt[q][k] = *reinterpret_cast<const float *>(plane_c + voff[q]);
-            }
+            for (int q = 0; q < kGran; ++q) nxt[q][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, (int)voff[q], 0, 0));
         }
     };
     // The commit of chunk `ch` into buffer ch % 2 comes in pieces, each laid among the matrix
@@ -398,26 +544,29 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     // last one issues the loads of chunk ch + 1 into the registers just freed.
     constexpr int kPieces = 2 * kGran + 1;
     float pv[4];
-    uint32_t ph[2], pm[2], pl[2];
-    uint32_t *const huge_seen = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);   // by the chunks, in turn
-    uint32_t xtop = 0, xlow = 0xffffffffu;     // largest and smallest non-zero magnitude seen (doubled bits, less one)
+    uint32_t ph[2], pm[2], pl[2], pr[2];
+    uint32_t *const huge_seen = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);   // (FLUSH) by the chunks, in turn
     auto commit_unit = [&](auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
         constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
         if constexpr (S < 2 * kGran) {
             constexpr int q = S >> 1, hf = S & 1;
             if constexpr (U == 0 || U == 3) {
                 constexpr int k = U ? 2 : 0;
-                const int c0 = ch * kChan + 8 * oct + 4 * hf + k;
-                const bool ok = (okbits >> q) & 1u;
-                pv[k] = (ok && c0 < p.C) ? nxt[q][4 * hf + k] : 0.f;
-                pv[k + 1] = (ok && c0 + 1 < p.C) ? nxt[q][4 * hf + k + 1] : 0.f;
-                const uint32_t a = __float_as_uint(pv[k]) << 1, b = __float_as_uint(pv[k + 1]) << 1;
-                xtop = max(max(xtop, a), b);
-                xlow = min(min(xlow, a - 1u), b - 1u);
+                pv[k] = nxt[q][4 * hf + k];
+                pv[k + 1] = nxt[q][4 * hf + k + 1];
+                if constexpr (FLUSH) {
+                    const uint32_t a = __float_as_uint(pv[k]) << 1, b = __float_as_uint(pv[k + 1]) << 1;
+                    xtop = max(max(xtop, a), b);
+                    xlow = min(min(xlow, a - 1u), b - 1u);
+                } else {
+                    pv[k] *= xscale;
+                    pv[k + 1] *= xscale;
+                }
             } else if constexpr (U == 1 || U == 4) {
                 constexpr int e = U == 4;
                 ph[e] = pack_bf16(pv[2 * e], pv[2 * e + 1]);
                 subtract_pair(pv[2 * e], pv[2 * e + 1], ph[e]);
+                if constexpr (!FLUSH) pr[e] = pack_f16(pv[2 * e], pv[2 * e + 1]);
             } else if constexpr (U == 2 || U == 5) {
                 constexpr int e = U == 5;
                 pm[e] = pack_bf16(pv[2 * e], pv[2 * e + 1]);
@@ -428,6 +577,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 dst[0] = make_uint2(ph[0], ph[1]);
                 dst[4] = make_uint2(pm[0], pm[1]);
                 dst[8] = make_uint2(pl[0], pl[1]);
+                if constexpr (!FLUSH) dst[12] = make_uint2(pr[0], pr[1]);
             }
         } else if constexpr (U == 0) {
             if (ch + 1 < p.nchunks) prefetch(ch + 1);
@@ -458,37 +608,62 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         static_assert(kPieces <= 9, "one line per piece");
     };
 
-    // The A operands of both filter tiles walk linearly through the workspace, chunk by chunk and tap by
-    // tap; those of the next tap are loaded at the head of a tap.
+    // The A operands of both filter tiles walk linearly through the workspace, chunk by chunk and tap by tap.
     const int ft0 = f0 >> 5, ft1 = min(ft0 + 1, p.ftiles - 1);
     const size_t per_tile = (size_t)p.nchunks * taps * kOperandBytes;
     const unsigned char *wx0 = p.Wx + ft0 * per_tile, *wx1 = p.Wx + ft1 * per_tile;
+    // FLUSH: those of the next tap are loaded at the head of a tap.
     int steps_left = p.nchunks * taps - 1;       // taps still to be fetched
-    uint4 a[2][3], an[2][3];
+    uint4 fa[FLUSH ? 2 : 1][3], fan[FLUSH ? 2 : 1][3];
     auto load_next = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            an[0][t] = reinterpret_cast<const uint4 *>(wx0)[t * 64 + lane];
-            an[1][t] = reinterpret_cast<const uint4 *>(wx1)[t * 64 + lane];
+            fan[0][t] = reinterpret_cast<const uint4 *>(wx0)[t * 64 + lane];
+            fan[FLUSH][t] = reinterpret_cast<const uint4 *>(wx1)[t * 64 + lane];
         }
         const int d = steps_left > 0 ? kOperandBytes : 0;          // (the last one is fetched again, unused)
         wx0 += d; wx1 += d; --steps_left;
     };
+    // else: a chain's taps at a time, each operand loaded again for the next chain behind its last use, in the
+    // order of their uses: twelve matrix instructions or more ahead.
+    int taps_left = p.nchunks * taps;            // from the chain on whose operands the pointers stand at
+    int second = taps_left > 1 ? kOperandBytes : 0;
+    uint4 a[2][2][4];                            // [tap of the chain][filter tile][hi, mid, lo, mid + lo]
+    auto load_a = [&](int tap, int i, int term) __attribute__((always_inline)) {
+        a[tap][i][term] = reinterpret_cast<const uint4 *>((i ? wx1 : wx0) + (tap ? second : 0))[term * 64 + lane];
+    };
+    auto next_chain = [&](int n) __attribute__((always_inline)) {   // n taps on (past the last chain: the last tap again, unused)
+        const int d = min(n, taps_left - 1);
+        wx0 += d * kOperandBytes; wx1 += d * kOperandBytes; taps_left -= d;
+        second = taps_left > 1 ? kOperandBytes : 0;
+    };
+    // What a chain's sum is to be multiplied by, in bits: per filter tile for this chunk and, of the second tile, for the
+    // chain that is still to be settled; the sign is that of the current chain's weights, turned at its head.
+    uint32_t factor[2] = {0, 0}, pending = 0, sign = 0x80000000u;
 
     prefetch(0);
-    if constexpr (NT > 0) load_next();
-    if (threadIdx.x < 2) huge_seen[threadIdx.x] = 0;
+    if constexpr (NT > 0) {
+        if constexpr (FLUSH) {
+            load_next();
+        } else {
+#pragma unroll
+            for (int t = 3; t >= 0; --t)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) load_a(k >> 1, k & 1, t);
+        }
+    }
+    if (FLUSH && threadIdx.x < 2) huge_seen[threadIdx.x] = 0;
     __syncthreads();
     commit_rest(0, 0);
-    if (xtop >= kHuge) huge_seen[0] = 1;
+    if (FLUSH && xtop >= kHuge) huge_seen[0] = 1;
     __syncthreads();
     bool by_plain_sum = false;                 // (uniform over the workgroup)
     for (int ch = 0; ch < p.nchunks; ++ch) {
         // (written before the barrier behind which it is read, and again only behind the next one)
-        const uint32_t huge = huge_seen[ch & 1];
+        const uint32_t huge = FLUSH ? huge_seen[ch & 1] : 0;
         const bool more = ch + 1 < p.nchunks;
         int pc = more ? 0 : kPieces;                     // the next piece of chunk ch + 1 to commit
-        if constexpr (NT > 0) {
+        if constexpr (NT > 0 && FLUSH) {
             // The flat sequence of (tap, pixel tile) steps, sixteen matrix instructions each; a step's
             // three B operands are read one step ahead, and the chunk's first steps carry one piece
             // of the next chunk's commit each.
@@ -515,15 +690,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                     // mid*lo, lo*mid, lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
                     constexpr int ta = P == 0 ? 1 : P == 1 ? 2 : P == 2 ? 2 : P == 3 ? 0 : P == 4 ? 1 : P == 5 ? 1 : 0;
                     constexpr int tb = P == 0 ? 2 : P == 1 ? 1 : P == 2 ? 0 : P == 3 ? 2 : P == 4 ? 1 : P == 5 ? 0 : P == 6 ? 1 : 0;
-                    const bf16x8 fa = __builtin_bit_cast(bf16x8, a[i][ta]), xb = __builtin_bit_cast(bf16x8, bc[tb]);
-                    if constexpr (FLUSH) {
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, xb, acc[i][j], 0, 0, 0);
-                    } else {
-                        const floatx16 none = {};
-                        tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, xb, P == 0 ? none : tapsum[i], 0, 0, 0);
-                        if constexpr (M == 1) settle(1, j > 0 ? j - 1 : NT - 1, j > 0 ? sgn : -sgn);   // (of the step before)
-                        if constexpr (M == 15) settle(0, j, sgn);
-                    }
+                    const bf16x8 wa = __builtin_bit_cast(bf16x8, fa[i][ta]), xb = __builtin_bit_cast(bf16x8, bc[tb]);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xb, acc[i][j], 0, 0, 0);
                     if constexpr (S >= 0) commit_unit(piece_c, m_c, ch + 1);
                     __builtin_amdgcn_sched_barrier(0);
                 };
@@ -550,9 +718,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             auto tap_body = [&](auto first_c, int tap) __attribute__((always_inline)) {
                 constexpr int FIRST = decltype(first_c)::value;
 #pragma unroll
-                for (int t = 0; t < 3; ++t) { a[0][t] = an[0][t]; a[1][t] = an[1][t]; }
+                for (int t = 0; t < 3; ++t) { fa[0][t] = fan[0][t]; fa[1][t] = fan[1][t]; }
                 load_next();
-                if constexpr (!FLUSH) sgn = -sgn;
                 const bool wrap = kx + 1 == p.kw, further = tap + 1 < taps;
                 const int off_n = further ? off + (wrap ? row_step : kPosBytes) : off;
                 kx = wrap ? 0 : kx + 1;
@@ -560,8 +727,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 if constexpr (NT > 1) step(std::integral_constant<int, (FIRST >= 0 && FIRST + 1 < kPieces) ? FIRST + 1 : -1>{}, 1, base[0] + off_n);
                 static_assert(NT <= 2, "one line per step");
                 off = off_n;
-                if constexpr (FLUSH)
-                    if (--chain == 0) { flush(); chain = chain_taps(true); }
+                if (--chain == 0) { flush(); chain = 2; }
             };
             int tap = 0;
             if (more) {
@@ -572,48 +738,167 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 if constexpr (4 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 4 * NT>{}, tap); ++tap; }
                 if constexpr (5 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 5 * NT>{}, tap); ++tap; }
                 if constexpr (6 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 6 * NT>{}, tap); ++tap; }
-                if constexpr (7 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 7 * NT>{}, tap); ++tap; }
-                if constexpr (8 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 8 * NT>{}, tap); ++tap; }
-                static_assert(kPieces <= 9, "one line per tap that carries pieces");
+                static_assert(kPieces == 7, "one line per tap that carries pieces");
                 pc = min(tap * NT, kPieces);
             }
             for (; tap < taps; ++tap) tap_body(std::integral_constant<int, -1>{}, tap);
+        } else if constexpr (NT > 0) {
+            // The sequence of (chain, pixel tile) steps, twelve matrix instructions a tap; a step's B operands
+            // are read during the step before, each behind the last use of its register, and the chunk's first
+            // steps carry the pieces of the next chunk's commit.
+#pragma unroll
+            for (int i = 0; i < 2; ++i) factor[i] = power_bits(-(xexp + p.wexp[(i ? ft1 : ft0) * p.nchunks + ch]));
+            const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
+            auto read_b = [&](uint4 &to, int term, int byte_off) __attribute__((always_inline)) {
+                to = *reinterpret_cast<const uint4 *>(tile_r + byte_off + 32 * term);
+            };
+            const int row_step = (p.pitch - p.kw + 1) * kPosBytes;
+            int kx = 0;                                  // window column of the last tap that has an offset
+            int off[2], off_n[2];                        // byte offsets of the chain's taps and of the next one's
+            auto next_tap = [&](int o) -> int {
+                const bool wrap = kx + 1 == p.kw;
+                kx = wrap ? 0 : kx + 1;
+                return o + (wrap ? row_step : kPosBytes);
+            };
+            off[0] = 0;
+            off[1] = taps > 1 ? next_tap(0) : 0;
+            uint4 b[2][4];                               // [tap of the chain][hi, mid, lo, mid + lo]
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int k = 3; k >= 0; --k) read_b(b[t][k], k, base[0] + off[t]);
+            // TAPS taps of tile j, with pieces FIRST .. FIRST + COUNT - 1 of the commit; `to` the next step's tile
+            auto step = [&](auto taps_c, auto first_c, auto count_c, auto j_c, int to0, int to1) __attribute__((always_inline)) {
+                constexpr int TAPS = decltype(taps_c)::value, FIRST = decltype(first_c)::value, COUNT = decltype(count_c)::value;
+                constexpr int j = decltype(j_c)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                auto unit = [&](auto m_c) __attribute__((always_inline)) {
+                    // filter tile, product and tap of the M-th instruction: one tile's chain after the other's, so that
+                    // a chain's sum is settled under the instructions of the next one, four values to each
+                    constexpr int M = decltype(m_c)::value, LEN = 6 * TAPS;
+                    if constexpr (M < 2 * LEN) {
+                        constexpr int i = M / LEN, at = M % LEN, P = at / TAPS, tap = at % TAPS;
+                        // r*r, hi*lo, hi*mid, lo*hi, mid*hi, hi*hi with r = mid + lo
+                        constexpr int ta = P == 0 ? 3 : P == 3 ? 2 : P == 4 ? 1 : 0;
+                        constexpr int tb = P == 0 ? 3 : P == 1 ? 2 : P == 2 ? 1 : 0;
+                        if constexpr (P == 0) {
+                            const floatx16 none = {};
+                            tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[tap][i][ta]), __builtin_bit_cast(halfx8, b[tap][tb]),
+                                                                               at == 0 ? none : tapsum[i], 0, 0, 0);
+                        } else {
+                            tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[tap][i][ta]), __builtin_bit_cast(bf16x8, b[tap][tb]),
+                                                                                tapsum[i], 0, 0, 0);
+                        }
+                        if constexpr (at > 0 && at < 5) {
+                            if constexpr (i == 0) settle(1, j > 0 ? j - 1 : NT - 1, pending, at - 1);   // (of the step before)
+                            else settle(0, j, factor[0] ^ sign, at - 1);
+                        }
+                        if constexpr (M == 2 * LEN - 1) pending = factor[1] ^ sign;
+                        if constexpr (j == NT - 1 && (P == 0 || P > 2)) {                               // this term's last use
+                            load_a(tap, i, ta);
+                            if constexpr (TAPS == 1) load_a(1, i, ta);
+                        }
+                        if constexpr (i == 1 && (P < 3 || P == 5)) {
+                            read_b(b[tap][tb], tb, tap ? to1 : to0);
+                            if constexpr (TAPS == 1) read_b(b[1][tb], tb, to1);
+                        }
+                        // (behind the instructions without such values)
+                        constexpr int piece = TAPS == 2 ? i : 0, unit = TAPS == 2 ? at - 5 : M - 5;
+                        if constexpr (unit >= 0 && piece < COUNT) commit_unit(std::integral_constant<int, FIRST + piece>{}, std::integral_constant<int, unit>{}, ch + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                for_units(unit);
+            };
+            // one chain of TAPS taps: its NT steps, with up to PER pieces of the commit each from FIRST on
+            constexpr int kPer = 2;                      // (a step has room for two)
+            int left = taps;                             // taps from this chain on
+            auto chain_body = [&](auto taps_c, auto first_c, auto per_c) __attribute__((always_inline)) {
+                constexpr int TAPS = decltype(taps_c)::value, FIRST = decltype(first_c)::value, PER = decltype(per_c)::value;
+                constexpr int C0 = std::max(0, std::min(PER, kPieces - FIRST)), C1 = std::max(0, std::min(PER, kPieces - FIRST - PER));
+                next_chain(TAPS);
+                sign ^= 0x80000000u;
+                left -= TAPS;
+                // (past the last tap: any staged position, read and not used)
+                off_n[0] = left > 0 ? next_tap(off[TAPS - 1]) : 0;
+                off_n[1] = left > 1 ? next_tap(off_n[0]) : off_n[0];
+                using std::integral_constant;
+                if constexpr (NT == 1) {
+                    step(taps_c, first_c, integral_constant<int, C0>{}, integral_constant<int, 0>{}, base[0] + off_n[0], base[0] + off_n[1]);
+                } else {
+                    constexpr int J = NT - 1;
+                    step(taps_c, first_c, integral_constant<int, C0>{}, integral_constant<int, 0>{}, base[J] + off[0], base[J] + off[TAPS - 1]);
+                    step(taps_c, integral_constant<int, FIRST + C0>{}, integral_constant<int, C1>{}, integral_constant<int, J>{}, base[0] + off_n[0], base[0] + off_n[1]);
+                }
+                static_assert(NT <= 2, "one line per step");
+                off[0] = off_n[0];
+                off[1] = off_n[1];
+            };
+            constexpr std::integral_constant<int, 1> one{};
+            constexpr std::integral_constant<int, 2> two{};
+            constexpr std::integral_constant<int, kPieces> none_left{};
+            constexpr std::integral_constant<int, kPer> per{};
+            if (more) {
+                constexpr int kA = kPer * NT, kB = 2 * kA, kC = 3 * kA;
+                if (left > 1) { chain_body(two, std::integral_constant<int, 0>{}, per); pc = std::min(kA, kPieces); }
+                if (left > 1) { chain_body(two, std::integral_constant<int, kA>{}, per); pc = std::min(kB, kPieces); }
+                if constexpr (kB < kPieces) if (left > 1) { chain_body(two, std::integral_constant<int, kB>{}, per); pc = std::min(kC, kPieces); }
+                if constexpr (kC < kPieces) if (left > 1) { chain_body(two, std::integral_constant<int, kC>{}, per); pc = std::min(4 * kA, kPieces); }
+                if (taps == 1) { chain_body(one, std::integral_constant<int, 0>{}, one); pc = NT; }
+            }
+            while (left > 1) chain_body(two, none_left, per);
+            if (left > 0) chain_body(one, none_left, per);
         }
         if (pc < kPieces) commit_rest(pc, ch + 1);       // what the chunk's steps did not carry
-        if (more && xtop >= kHuge) huge_seen[(ch + 1) & 1] = 1;
+        if (FLUSH && more && xtop >= kHuge) huge_seen[(ch + 1) & 1] = 1;
         __syncthreads();                                 // chunk ch has been read, chunk ch + 1 is written
         by_plain_sum = __builtin_amdgcn_readfirstlane((int)huge) != 0;
         if (by_plain_sum) break;
     }
 
-    if constexpr (!FLUSH && NT > 0) settle(1, NT - 1, sgn);
-
-    // Below which magnitude an output is doubtful.  A value of 2^-110 and above is held in full; of a smaller one up to
-    // 2^-134 is lost.  The losses add up to at most 2^-134 * Nred * (max |x| + max |w|), and an output of 2^30
-    // times that is not touched by them.
-    uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (nothing staged is used past the last barrier)
+    if constexpr (NT > 0 && !FLUSH) {
 #pragma unroll
-    for (int s = 1; s < 64; s *= 2) {
-        xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, s));
-        xlow = min(xlow, (uint32_t)__shfl_xor((int)xlow, s));
+        for (int k = 0; k < 4; ++k) settle(1, NT - 1, pending, k);
     }
-    if (lane == 0) { wgstat[2 * (threadIdx.x >> 6)] = xtop; wgstat[2 * (threadIdx.x >> 6) + 1] = xlow; }
-    __syncthreads();
+
+    // Below which magnitude an output is doubtful.
+    //   FLUSH: a value of 2^-110 and above is held in full; of a smaller one up to 2^-134 is lost.  The losses add up
+    // to at most 2^-134 * Nred * (max |x| + max |w|), and an output of 2^30 times that is not touched by them.
+    //   Else: scaled values of 2^-6 and above are held in full and mid + lo to 2^-11 of itself; of a smaller one up to
+    // 2^-25 of mid + lo is lost, times at most 2^-8 of the other operand, and an output of 2^24 times that is not touched.
+    if constexpr (FLUSH) {
+        uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (nothing staged is used past the last barrier)
+#pragma unroll
+        for (int s = 1; s < 64; s *= 2) {
+            xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, s));
+            xlow = min(xlow, (uint32_t)__shfl_xor((int)xlow, s));
+        }
+        if (lane == 0) { wgstat[2 * (threadIdx.x >> 6)] = xtop; wgstat[2 * (threadIdx.x >> 6) + 1] = xlow; }
+        __syncthreads();
+        if constexpr (NT == 0) return;
+        xtop = max(max(wgstat[0], wgstat[2]), max(wgstat[4], wgstat[6]));
+        xlow = min(min(wgstat[1], wgstat[3]), min(wgstat[5], wgstat[7]));
+    }
     if constexpr (NT == 0) return;
-    xtop = max(max(wgstat[0], wgstat[2]), max(wgstat[4], wgstat[6]));
-    xlow = min(min(wgstat[1], wgstat[3]), min(wgstat[5], wgstat[7]));
-    const uint32_t *stats = reinterpret_cast<const uint32_t *>(p.Wx + (size_t)p.ftiles * per_tile);
-    uint32_t wstat = 0, wtiny = 0;
+    uint32_t wtop = 0, wtiny = 0;
     for (int i = lane; i < 2 * p.nchunks; i += 64) {
-        const uint32_t s0 = stats[ft0 * 2 * p.nchunks + i], s1 = stats[ft1 * 2 * p.nchunks + i];
-        wstat = max(wstat, max(s0 & ~kTinyBit, s1 & ~kTinyBit));
+        const uint32_t s0 = p.wstat[ft0 * 2 * p.nchunks + i], s1 = p.wstat[ft1 * 2 * p.nchunks + i];
+        wtop = max(wtop, max(s0 & ~kTinyBit, s1 & ~kTinyBit));
         wtiny |= s0 | s1;
     }
+    const bool wlost = __any((wtiny & kTinyBit) != 0);
+    const bool xlost = FLUSH ? xlow < (__float_as_uint(kTiny) << 1) - 1u : xlow < power_bits(kHeldExp - xexp) - 1u;
     float doubtful = 0.f;
-    if (xlow < (__float_as_uint(kTiny) << 1) - 1u || __any((wtiny & kTinyBit) != 0)) {
+    if (xlost || wlost) {
 #pragma unroll
-        for (int s = 1; s < 64; s *= 2) wstat = max(wstat, (uint32_t)__shfl_xor((int)wstat, s));
-        doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wstat));
+        for (int s = 1; s < 64; s *= 2) wtop = max(wtop, (uint32_t)__shfl_xor((int)wtop, s));
+        if constexpr (FLUSH) {
+            doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wtop));
+        } else {
+            const float x = __uint_as_float(xtop), w = __uint_as_float(wtop);
+            const float by_x = xlost ? w * fmaxf(x * 0x1p-23f, ldexpf(1.f, -kMostX)) : 0.f, by_w = wlost ? x * fmaxf(w * 0x1p-23f, ldexpf(1.f, -kMostW)) : 0.f;
+            doubtful = 0x1p-9f * (float)(p.C * taps) * (by_x + by_w);
+        }
     }
 
     // accumulator register r of a lane: filter row 8*(r/4) + 4*half + r%4 of the filter tile,
@@ -652,7 +937,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     }
 }
 
-template <bool FLUSH>
+template <bool FLUSH, int GRAN>
 __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitParams p)
 {
     int b = blockIdx.x;
@@ -690,14 +975,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitP
     const int f0 = (h * p.fwaves + wf) * 64;
     if (f0 >= p.F) my_nt = 0;                             // no filters for this wave: staging only
     switch (my_nt) {
-        case 0: split_wave<0, FLUSH>(p, n, 0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-        case 1: split_wave<1, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-        default: split_wave<2, FLUSH>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        case 0: split_wave<0, FLUSH, GRAN>(p, n, 0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        case 1: split_wave<1, FLUSH, GRAN>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        default: split_wave<2, FLUSH, GRAN>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
     }
 }
 
 struct Plan {
     bool ok, flush;
+    int granules;
     int fwaves, tiles, tw, tx, ty, gx, groups, pitch, npos;
     size_t lds;
 };
@@ -709,9 +995,10 @@ struct Plan {
 // epilogue, a tenth less where two workgroups fit a compute unit; a launch takes as many of those as
 // its busiest compute unit has workgroups, or, over more than four rounds, as many as a compute unit has
 // on average and half of one.  The cheapest that fits max_pos() positions is taken.
-Plan search_plan(const Geom &g)
+Plan search_plan(const Geom &g, int granules)
 {
     Plan pl{};
+    pl.granules = granules;
     const int taps = g.kh * g.kw;
     const long long OHW = (long long)g.OH * g.OW;
     if (taps > kMaxTaps || OHW > (1 << 24) || (long long)g.C * g.H * g.W >= (1LL << 29)) return pl;
@@ -721,7 +1008,7 @@ Plan search_plan(const Geom &g)
     pl.flush = !conv_fp32_mfma_supports(g);
     pl.fwaves = g.F <= 64 ? 1 : 2;
     const int wps = 4 / pl.fwaves, most = wps * kWaveTiles;
-    const long long maxpos = max_pos(pl.flush);
+    const long long maxpos = max_pos(granules);
     const long long fgroups = ceil_div(g.F, 64 * pl.fwaves);
     const int cus = kPlanUnits;
     double best = -1.0;
@@ -730,7 +1017,7 @@ Plan search_plan(const Geom &g)
                         int ty, int gx) {
         const long long npos = rows * cols;
         if (npos > maxpos || groups > (1 << 24)) return;
-        const size_t lds = 2 * (size_t)npos * kPosBytes + 2 * sizeof(uint32_t);
+        const size_t lds = 2 * (size_t)npos * pos_bytes(pl.flush) + 2 * sizeof(uint32_t);
         const long long wgs = (long long)g.N * fgroups * groups;
         const double whole = ceil_div(tiles, wps) + 0.5, part = ceil_div(last, wps) + 0.5;
         const double mean = whole + (part - whole) / (double)period;
@@ -764,10 +1051,13 @@ Plan search_plan(const Geom &g)
 const Plan &make_plan(const Geom &g)
 {
     static thread_local PlanMemo<Plan> memo;
-    return memo.get(g, 0, [&] { return search_plan(g); });
+    return memo.get(g, 0, [&] {
+        const Plan pl = search_plan(g, kGranules);
+        return pl.ok || pl.flush ? pl : search_plan(g, kMostGranules);
+    });
 }
 
-template <bool FLUSH>
+template <bool FLUSH, int GRAN>
 hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
 {
     if (lds > 64 * 1024) {
@@ -777,24 +1067,45 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
         if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
         const unsigned long long bit = 1ull << (dev & 63);
         if (!(raised.load() & bit)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     2 * max_pos(FLUSH) * kPosBytes + 2 * (int)sizeof(uint32_t));
+                                                     2 * max_pos(GRAN) * pos_bytes(FLUSH) + 2 * (int)sizeof(uint32_t));
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }
     }
-    conv_fp32_split_kernel<FLUSH><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
+    conv_fp32_split_kernel<FLUSH, GRAN><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
     return hipGetLastError();
 }
 
 }  // namespace
 
+namespace {
+// The workspace: split filters, their words, their powers of two, the words of the images' parts.
+struct Layout {
+    size_t wstat, wexp, xstat, bytes;
+    int xparts, xper;
+};
+Layout layout_of(const Geom &g, bool flush)
+{
+    const size_t nchunks = ceil_div(g.C, kChan), ftiles = ceil_div(g.F, 32);
+    const long long per_image = (long long)g.C * g.H * g.W;
+    Layout l{};
+    // (a part is 32 values a thread or more; a wave reads an image's parts, one per lane)
+    l.xparts = flush ? 0 : (int)std::max<long long>(1, std::min<long long>(64, per_image / (32 * kThreads)));
+    l.xper = flush ? 0 : ceil_div(per_image, l.xparts);
+    l.wstat = ftiles * nchunks * g.kh * g.kw * operand_bytes(flush);
+    l.wexp = l.wstat + ftiles * nchunks * 2 * sizeof(uint32_t);
+    l.xstat = (l.wexp + (flush ? 0 : ftiles * nchunks * sizeof(int)) + 7) & ~(size_t)7;
+    l.bytes = l.xstat + (size_t)g.N * l.xparts * 2 * sizeof(uint32_t);
+    return l;
+}
+}  // namespace
+
 size_t conv_fp32_split_workspace_bytes(const Geom &g)
 {
-    if (!make_plan(g).ok) return 0;
-    const size_t nchunks = ceil_div(g.C, kChan), ftiles = ceil_div(g.F, 32);
-    return ftiles * nchunks * ((size_t)g.kh * g.kw * kOperandBytes + 2 * sizeof(uint32_t));
+    const Plan &pl = make_plan(g);
+    return pl.ok ? layout_of(g, pl.flush).bytes : 0;
 }
 
 hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace, hipStream_t st)
@@ -802,8 +1113,14 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     const Plan &pl = make_plan(g);
     if (!pl.ok) return hipErrorInvalidValue;
     const int taps = g.kh * g.kw;
+    const Layout l = layout_of(g, pl.flush);
+    unsigned char *const ws = static_cast<unsigned char *>(workspace);
     Fp32SplitParams p;
-    p.I = I; p.Wt = Wt; p.Wx = static_cast<const unsigned char *>(workspace); p.out = out;
+    p.I = I; p.Wt = Wt; p.Wx = ws; p.out = out;
+    p.wstat = reinterpret_cast<const uint32_t *>(ws + l.wstat);
+    p.wexp = reinterpret_cast<const int *>(ws + l.wexp);
+    p.xstat = reinterpret_cast<const uint32_t *>(ws + l.xstat);
+    p.xparts = l.xparts;
     p.N = g.N; p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
     p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW;
     p.nchunks = ceil_div(g.C, kChan); p.ftiles = ceil_div(g.F, 32);
@@ -812,13 +1129,17 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     p.pitch = pl.pitch; p.npos = pl.npos;
     p.inv_pitch = reciprocal((unsigned long long)pl.pitch);
     const long long blocks = (long long)g.N * p.groups * p.fgroups;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const long long first = (long long)p.ftiles * 2 * p.nchunks + (long long)g.N * l.xparts;
+    if (blocks > 0x7fffffffLL || first > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t filter_lds = (size_t)32 * ((8 * taps) | 1) * sizeof(float);
-    split_filters_kernel<<<dim3((unsigned)(p.ftiles * 2 * p.nchunks)), dim3(kThreads), filter_lds, st>>>(
-        Wt, g.F, g.C, taps, p.nchunks, p.ftiles, chain_taps(pl.flush), static_cast<unsigned char *>(workspace));
+    const Fp32StatParams x{I, reinterpret_cast<uint32_t *>(ws + l.xstat), (int)((long long)g.C * g.H * g.W), l.xparts, l.xper};
+    const auto split = pl.flush ? split_operands_kernel<true> : split_operands_kernel<false>;
+    split<<<dim3((unsigned)first), dim3(kThreads), filter_lds, st>>>(Wt, g.F, g.C, taps, p.nchunks, p.ftiles, reciprocal(8ull * taps), x, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return pl.flush ? launch_form<true>(p, (unsigned)blocks, pl.lds, st) : launch_form<false>(p, (unsigned)blocks, pl.lds, st);
+    if (pl.flush) return launch_form<true, kGranules>(p, (unsigned)blocks, pl.lds, st);
+    return pl.granules == kGranules ? launch_form<false, kGranules>(p, (unsigned)blocks, pl.lds, st)
+                                    : launch_form<false, kMostGranules>(p, (unsigned)blocks, pl.lds, st);
 }
 
 }  // namespace xnor

@@ -55,7 +55,7 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
 
 // Where the three-term kernel is the faster real-valued convolution (given a workspace).  It is the more
 // exact one everywhere (see conv_fp32_split.hip).  Measured, what runs without a workspace -> split:
-// 128x512x28x28 F=512 3x3 5.11 -> 3.2 ms, 16x128x56x56 F=128 5x5 1702 -> 305 us, 7x7 22.04 -> 0.69 ms,
+// 128x512x28x28 F=512 3x3 5.11 -> 2.64 ms, 16x128x56x56 F=128 5x5 1702 -> 233 us, 7x7 22.04 -> 0.61 ms,
 // 16x224x224 three channels F=64 7x7 stride 2 1020 -> 359 us.  A launch that does not fill the chip is as long as a
 // workgroup's chain of 16-channel chunks behind a filter pass and a first fetch of 12 to 14 us, and this decides:
 //  * against the fp32 matrix form, whose chain is 8 channels a chunk.  With its four-wide filter fetch (C % 8 == 0,

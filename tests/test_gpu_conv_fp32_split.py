@@ -1,4 +1,4 @@
-"""XNOR_ALGO_MFMA_SPLIT of xnor_conv2d_fp32_fwd_ws (both operands as three bf16 terms, eight products)
+"""XNOR_ALGO_MFMA_SPLIT of xnor_conv2d_fp32_fwd_ws (both operands as three bf16 terms)
 against the oracle, at the edges of its tiles, chunks and dispatch.
 
 The bar against the oracle is that of the fp32 kernels (tests/test_gpu_conv_fp32.py): |got - ref| <=
@@ -266,3 +266,45 @@ def test_auto_without_memory_for_the_workspace(xb, monkeypatch):
         xb.xnor_conv2d_fp32_fwd(I, Wt, s, out, algo=xb.ALGO_MFMA_SPLIT)
     torch.cuda.synchronize()
     assert torch.equal(out, plain)
+
+
+@pytest.mark.parametrize("shape", [(3, 17, 9, 11, 33, 1), (3, 48, 13, 12, 70, 3), (2, 33, 14, 15, 130, 5), (3, 16, 8, 9, 64, 2)], ids=lambda s: "x".join(map(str, s)))
+def test_split_images_channels_and_filters_of_very_different_sizes(xb, shape):
+    """The powers of two that an image and a filter chunk are multiplied by: images of 1e-25 .. 1e15, a channel and a
+    corner far below or above the rest, filters and chunks of filters likewise, zeros.  Against 64-bit sums: an output's
+    sum is rounded once per chain of two taps and 16 channels, a chain's about six times (each by at most 2^-23 of S, the
+    sum of |I * Wt|), and the smallest products lose at most 2^-24 together: (chains + 8) * 2^-23 * S; an output
+    formed again by the plain sum is rounded once per two terms."""
+    N, C, H, W, F, k = shape
+    print(f"case conv_fp32 split sizes shape={shape}", flush=True)
+    rng = np.random.default_rng(zlib.crc32(("sizes" + str(shape)).encode()))
+    I, Wt = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((F, C, k, k)).astype(np.float32)
+    for n, size in zip(range(N), (1e-25, 1e15, 1.0)):
+        I[n] *= np.float32(size)
+    I[:, C // 2] *= np.float32(1e-9)
+    I[N - 1, 0, :2, :2] *= np.float32(1e12)
+    I[0, :, H // 2] = 0
+    Wt[1] *= np.float32(1e-7)
+    Wt[2, : C // 2] *= np.float32(1e-12)
+    Wt[F // 2] = 0
+    Wt[:, C - 1] *= np.float32(1e6)
+    Wt[min(F - 1, 32):, : min(C, 16)] *= np.float32(1e-4)
+    s = xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2)
+    got = split(xb, dev(I), dev(Wt), s)
+    d = [torch.from_numpy(a).double() for a in (I, Wt)]
+    ref = torch.nn.functional.conv2d(*d, padding=k // 2).numpy()
+    S = torch.nn.functional.conv2d(d[0].abs(), d[1].abs(), padding=k // 2).numpy()
+    chains = (k * k + 1) // 2 * -(-C // 16)
+    bar = max(chains + 8, C * k * k / 2 + 8) * 2.0 ** -23 * S
+    assert (np.abs(got - ref) <= bar + 2.0 ** -149).all()
+    assert np.sqrt(((got - ref) ** 2).sum()) <= 3e-7 * np.sqrt((S ** 2).sum())
+
+
+def test_split_more_positions_than_three_granules(xb):
+    """32 pixels over more than 384 staged positions (wide strides): the variant that fetches four granules ahead."""
+    for shape in ((1, 64, 19, 202, 24, 3, 3, 4, 5, 3, 0), (3, 20, 67, 49, 200, 4, 4, 4, 5, 4, 4), (2, 8, 67, 174, 9, 5, 3, 4, 4, 2, 3)):
+        print(f"case conv_fp32 split positions shape={shape}", flush=True)
+        _, I, Wt = random_layer(np.random.default_rng(12), "t", *shape)
+        O, S = oracle.conv_fp32(I, Wt, oracle.Shape(*shape), want_scale=True)
+        got = split(xb, dev(I), dev(Wt), xb.Shape(*shape))
+        assert (np.abs(got - O) <= 1e-5 * S).all()
