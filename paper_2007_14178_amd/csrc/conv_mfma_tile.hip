@@ -15,6 +15,10 @@
 //     (every image under a tile then gets its own halo rows): few idle pixel slots at any image size.
 //   * Filter operands come from the L2 a few steps ahead of their use (a ring of registers), pixel operands
 //     from LDS (slot pitch an odd number of 16-byte units: conflict-free).
+//   * Half of a small launch is a workgroup's way to its first matrix instruction, about 1200 instructions at one or two
+//     waves a SIMD.  Scalar divisions by reciprocals, all first loads before the first wait and the padding's zeros
+//     out of the lookup that expands the words took it from 7.8 to 6.2 k cycles for 64 x 128 x 28 x 28 F=256 3x3 stride 2
+//     (with its input pass 17.1 -> 16.2 us), from 6.2 to 5.8 k for 64 x 256 x 14 x 14 F=256 3x3.
 //   * Given the channel mean A instead of K, A is staged beside the input, one value per slot, and a lane
 //     sums its own pixels' windows from LDS (the sum, order and rounding of box_filter_K_kernel).
 #include <algorithm>
@@ -50,12 +54,26 @@ struct TileParams {
     int pitch16;        // slot pitch in 16-byte units (odd)
     int tab16, al16, a16;   // start of the step table, alpha and the staged A in LDS (16-byte units)
     float iCHV, iWp, iRH, iOW, iOH, iS2, ikw;   // reciprocals for div_small
+    uint32_t mGroups, mImage, mOW, mOH;         // ... and for div_scalar
 };
 
 // n / d for n < 2^20: (n + 0.5) / d is at least 0.5 / d away from a whole number and the rounding of the
 // reciprocal and the product moves it by less (four full-rate instructions; the 32-bit multiplications
 // of an exact integer division run at a quarter of the rate).
 __device__ inline uint32_t div_small(uint32_t n, float inv) { return (uint32_t)(((float)n + 0.5f) * inv); }
+
+// n / d and the rest for n < 2^32 in scalar registers: with m = floor(2^32 / d) the high half of n * m is the
+// quotient or one less.  (The compiler's own division is a chain of 25 instructions through the vector unit: four of
+// them, one behind the other, stood before a workgroup's first load.)
+inline uint32_t scalar_reciprocal(long long d) { return d <= 1 ? 0xffffffffu : (uint32_t)((1LL << 32) / d); }
+__device__ inline int div_scalar(uint32_t n, uint32_t d, uint32_t m, int &rest)
+{
+    uint32_t q = __umulhi(n, m), r = n - q * d;
+    const bool more = r >= d;
+    q += more ? 1u : 0u;
+    rest = (int)(more ? r - d : r);
+    return (int)q;
+}
 
 // Steps the filter operands are ahead of their use; one less of zeros lie behind a tile's last step, where the last
 // loads of the loop end (step T + operand_ring - 2).
@@ -86,24 +104,24 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
     // of the tiles: with three filter groups of 169 tiles, 66 workgroups on an XCD's 32 compute units
     // instead of 64 meant a third round.)
     const int item = (blockIdx.x & (kXcds - 1)) * p.wgs_per_xcd + (blockIdx.x >> kXcdShift);
-    const int ptile = __builtin_amdgcn_readfirstlane(item / p.fgroups);
-    const int fgrp = item - ptile * p.fgroups;
+    int fgrp;
+    const int ptile = div_scalar((uint32_t)item, (uint32_t)p.fgroups, p.mGroups, fgrp);
     if (ptile >= p.ptiles) return;           // padding of the last XCD's range (uniform over the workgroup)
 
     // (tiles of an image of their own, or of the whole batch where these would leave too many slots idle)
     int p0 = ptile * PT, p1 = min(p.npix, p0 + PT);
     if (p.per_image) {
-        const int n = __builtin_amdgcn_readfirstlane(ptile / p.per_image), k = ptile - n * p.per_image;
+        int k;
+        const int n = div_scalar((uint32_t)ptile, (uint32_t)p.per_image, p.mImage, k);
         p0 = n * OHW + k * PT;
         p1 = min((n + 1) * OHW, p0 + PT);
     }
-    const int R0 = __builtin_amdgcn_readfirstlane(p0 / p.OW);
-    const int in_row = p0 - R0 * p.OW;       // the first pixel's column
-    const int n_first = __builtin_amdgcn_readfirstlane(R0 / p.OH), oy0 = R0 - n_first * p.OH;
-    const int rows = __builtin_amdgcn_readfirstlane((int)div_small((uint32_t)(in_row + p1 - p0 - 1), p.iOW)) + 1;
+    int in_row, oy0, oy_last, unused;        // the first pixel's column and row, the last pixel's row
+    const int R0 = div_scalar((uint32_t)p0, (uint32_t)p.OW, p.mOW, in_row);
+    const int n_first = div_scalar((uint32_t)R0, (uint32_t)p.OH, p.mOH, oy0);
+    const int rows = div_scalar((uint32_t)(in_row + p1 - p0 - 1), (uint32_t)p.OW, p.mOW, unused) + 1;
     const int r0 = (p.OH - 1 - oy0) * p.sh + p.kh;   // staged rows of the first image if the tile runs past it
-    const int dn_last = __builtin_amdgcn_readfirstlane((int)div_small((uint32_t)(oy0 + rows - 1), p.iOH));
-    const int oy_last = oy0 + rows - 1 - dn_last * p.OH;
+    const int dn_last = div_scalar((uint32_t)(oy0 + rows - 1), (uint32_t)p.OH, p.mOH, oy_last);
     const int srows = dn_last == 0 ? (oy_last - oy0) * p.sh + p.kh
                                    : r0 + (dn_last - 1) * p.RHfull + oy_last * p.sh + p.kh;
     const int nslots = srows * p.Wp;
@@ -111,23 +129,24 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
     // where staged slot `slot` lies in the input: pixel index from the first image, or -1 outside
     auto slot_pixel = [&](uint32_t slot) -> int {
         const uint32_t row = div_small(slot, p.iWp);
-        const int ix = (int)(slot - __umul24(row, (uint32_t)p.Wp)) - p.pw;
-        int dn = 0, iy = oy0 * p.sh - p.ph + (int)row;
-        if ((int)row >= r0) {
+        const uint32_t ix = slot - __umul24(row, (uint32_t)p.Wp) - (uint32_t)p.pw;
+        uint32_t dn = 0, iy = (uint32_t)(oy0 * p.sh - p.ph) + row;
+        if (dn_last > 0) {                   // (uniform)
             const uint32_t t = row - (uint32_t)r0, sg = div_small(t, p.iRH);
-            dn = 1 + (int)sg;
-            iy = (int)(t - __umul24(sg, (uint32_t)p.RHfull)) - p.ph;
+            const bool past = (int)row >= r0;
+            dn = past ? 1 + sg : 0u;
+            iy = past ? t - __umul24(sg, (uint32_t)p.RHfull) - (uint32_t)p.ph : iy;
         }
-        const bool in = (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W && n_first + dn < p.N;
-        return in ? (int)(__umul24(__umul24((uint32_t)dn, (uint32_t)p.H) + (uint32_t)iy, (uint32_t)p.W)) + ix : -1;
+        const bool in = iy < (uint32_t)p.H && ix < (uint32_t)p.W;
+        const uint32_t px = __umul24(__umul24(dn, (uint32_t)p.H) + iy, (uint32_t)p.W) + ix;
+        return in ? (int)px : -1;
     };
     typedef typename WordVec<VW>::type wvec;
     const int CHV = p.Cw / VW, items = nslots * CHV;
     const uint32_t *const src = p.Ipk + (long long)n_first * p.H * p.W * p.Cw;
     constexpr int UP = 4;                    // items per thread in flight
     wvec sv[UP];
-    int dst[UP];
-    bool live[UP];
+    int dst[UP], at[UP];                     // LDS slot and word, pixel of an item
     auto fetch = [&](int first) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
@@ -136,9 +155,10 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
             const uint32_t slot = div_small(it, p.iCHV);
             const int w = (int)(it - __umul24(slot, (uint32_t)CHV)) * VW;
             const int px = slot_pixel(slot);
-            live[u] = px >= 0;
-            dst[u] = (int)__umul24(slot, (uint32_t)p.pitch16) + w;
-            sv[u] = *reinterpret_cast<const wvec *>(src + (live[u] ? __umul24((uint32_t)px, (uint32_t)p.Cw) + (uint32_t)w : 0u));
+            at[u] = px;
+            dst[u] = (int)(__umul24(slot, (uint32_t)p.pitch16) + (uint32_t)w);
+            const uint32_t off = (__umul24((uint32_t)px, (uint32_t)p.Cw) + (uint32_t)w) * 4u;
+            sv[u] = *reinterpret_cast<const wvec *>(reinterpret_cast<const char *>(src) + (px >= 0 ? off : 0u));
         }
     };
     auto put = [&](int first) __attribute__((always_inline)) {
@@ -148,14 +168,29 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
             uint32_t words[VW];
             if constexpr (VW == 1) words[0] = sv[u];
             if constexpr (VW == 4) { words[0] = sv[u].x; words[1] = sv[u].y; words[2] = sv[u].z; words[3] = sv[u].w; }
+            const uint32_t mask = at[u] >= 0 ? 0x03030303u : 0u, zero = at[u] >= 0 ? 0u : kZeroBytes;
 #pragma unroll
             for (int k = 0; k < VW; ++k) {
-                const uint4 e = expand_word(words[k], 32);   // (tail channels meet filter zeros)
-                lds[dst[u] + k] = live[u] ? e : make_uint4(0, 0, 0, 0);
+                lds[dst[u] + k] = expand_word_or_zero(words[k], mask, zero);   // (tail channels meet filter zeros)
             }
         }
     };
     fetch(0);
+    // The channel mean of the slots, fetched beside the words (a load and its LDS write in one loop waited for
+    // everything in flight, once per 256 slots).
+    constexpr int UA = 4;
+    static_assert(UA == UP, "items are slots where a slot is one item");
+    float av[UA];
+    int apx[UA];
+    const float *const amean = p.A + (FROM_A ? (long long)n_first * p.H * p.W : 0);
+    if constexpr (FROM_A) {
+#pragma unroll
+        for (int u = 0; u < UA; ++u) {
+            if (u * kThreads >= nslots) break;                                   // (uniform)
+            apx[u] = CHV == 1 ? at[u] : slot_pixel((uint32_t)min(u * kThreads + tid, nslots - 1));
+            av[u] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(amean) + (uint32_t)max(apx[u], 0) * 4u);
+        }
+    }
     // The XCD's workgroups of this filter group are about to walk the same filter operands at the same
     // pace, each line's first reader waiting for memory.  Each of them touches an eighth of the lines now.
     const int f0 = fgrp * FT;
@@ -166,7 +201,7 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
 #pragma unroll
     for (int k = 0; k < kTouch; ++k) {
         const int line = ((k * 8 + (ptile & 7)) * kThreads) + tid;
-        touched[k] = *reinterpret_cast<const int *>(wx_lines + (size_t)min(line, nlines - 1) * 128);
+        touched[k] = *reinterpret_cast<const int *>(wx_lines + (uint32_t)min(line, nlines - 1) * 128u);
     }
     // alpha and A beside it
     float *const Al = reinterpret_cast<float *>(lds + p.al16);
@@ -181,14 +216,6 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
         Tab[s] = (__umul24(slot, (uint32_t)p.pitch16) + 2u * (st - __umul24(tap, (uint32_t)p.S2))) * 16u;
     }
     const float a_mine = tid < FT && f0 + tid < p.F ? p.alpha[f0 + tid] : 0.f;
-    if constexpr (FROM_A) {
-        const float *a = p.A + (long long)n_first * p.H * p.W;
-        for (int s = tid; s < nslots; s += kThreads) {
-            const int px = slot_pixel((uint32_t)s);
-            const float v = a[max(px, 0)];
-            As[s] = px >= 0 ? v : 0.f;
-        }
-    }
 
     // this lane's pixels
     uint32_t bB[NP];                          // LDS byte address of tap (0,0), its half of the channels
@@ -221,6 +248,18 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
         it += UP * kThreads;
         if (it >= items) break;               // (uniform)
         fetch(it);
+    }
+    if constexpr (FROM_A) {
+#pragma unroll
+        for (int u = 0; u < UA; ++u) {
+            if (u * kThreads >= nslots) break;                                   // (uniform)
+            As[min(u * kThreads + tid, nslots - 1)] = apx[u] >= 0 ? av[u] : 0.f; // (the last slot again: the same value)
+        }
+        for (int s = UA * kThreads + tid; s < nslots; s += kThreads) {
+            const int px = slot_pixel((uint32_t)s);
+            const float v = amean[max(px, 0)];
+            As[s] = px >= 0 ? v : 0.f;
+        }
     }
 #pragma unroll
     for (int k = 0; k < kTouch; ++k) asm volatile("" : : "v"(touched[k]));    // (long since arrived)
@@ -627,6 +666,10 @@ hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const floa
     p.iCHV = 1.0f / (float)(g.Cw / (vec4 ? 4 : 1));
     p.iWp = 1.0f / (float)pl.Wp;
     p.iRH = 1.0f / (float)pl.RHfull;
+    p.mGroups = scalar_reciprocal(p.fgroups);
+    p.mImage = scalar_reciprocal(p.per_image);
+    p.mOW = scalar_reciprocal(g.OW);
+    p.mOH = scalar_reciprocal(g.OH);
     p.iOW = 1.0f / (float)g.OW;
     p.iOH = 1.0f / (float)g.OH;
     p.iS2 = 1.0f / (float)pl.S2;

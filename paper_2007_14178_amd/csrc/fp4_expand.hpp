@@ -42,6 +42,15 @@ __device__ inline uint4 expand_word(uint32_t w, int nvalid)
     return e;
 }
 
+// The same for a whole word or, with mask = 0 and zero = kZeroBytes instead of 0x03030303 and 0, 32 zeros (a lookup
+// byte of 0x0c gives 0): the choice costs two selects a word instead of four, none behind the lookups.
+constexpr uint32_t kZeroBytes = 0x0c0c0c0cu;
+__device__ inline uint4 expand_word_or_zero(uint32_t w, uint32_t mask, uint32_t zero)
+{
+    return make_uint4(pair_codes((w & mask) | zero), pair_codes(((w >> 2) & mask) | zero),
+                      pair_codes(((w >> 4) & mask) | zero), pair_codes(((w >> 6) & mask) | zero));
+}
+
 // Filter workspace Wx[tile32][step][lane] (one uint4 per lane): the steps of a tile run
 // chunk-major, then tap-major, each chunk padded with zero steps to a whole number of register
 // rings: step = chunk*chunk_pad + tap*steps_c + s, packed word = chunk*CH + 2*s + lane/32,

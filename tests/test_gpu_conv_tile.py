@@ -69,3 +69,12 @@ def test_tiles_vs_oracle(xb, shape):
     assert torch.equal(Opk, OpkA) and torch.equal(A_next, A_nextA)
     mean = np.abs(got).mean(axis=1)
     assert (np.abs(A_next.cpu().numpy() - mean) <= np.maximum(1e-5 * mean, 2.0 ** -149)).all()
+
+
+@pytest.mark.parametrize("shape", [(2, 64, 41, 300, 64, 3, 3, 2, 2, 1, 1), (2, 128, 41, 300, 40, 3, 3, 2, 2, 1, 1), (1, 33, 30, 400, 33, 5, 5, 2, 2, 2, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_tiles_of_more_slots_than_are_fetched_at_once(xb, shape):
+    """1505 and more staged slots a tile: the channel mean's and the words' loops behind the first four fetches, with one
+    and with two items a slot."""
+    assert xb.xnor_conv2d_mfma_kernel(xb.Shape(*shape)) == xb.ALGO_MFMA_TILE
+    test_tiles_vs_oracle(xb, shape)
