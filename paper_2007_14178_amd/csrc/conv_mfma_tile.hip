@@ -52,6 +52,7 @@ struct TileParams {
     int S2, T;          // steps (64 channels) of a tap, of all taps
     int tile_steps;     // ... and behind a filter tile in the workspace
     int pitch16;        // slot pitch in 16-byte units (odd)
+    int write_through;      // stores go past the L2 (see launch_conv_mfma_tile)
     int tab16, al16, a16;   // start of the step table, alpha and the staged A in LDS (16-byte units)
     float iCHV, iWp, iRH, iOW, iOH, iS2, ikw;   // reciprocals for div_small
     uint32_t mGroups, mImage, mOW, mOH;         // ... and for div_scalar
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
                 al[r] = v.x; al[r + 1] = v.y; al[r + 2] = v.z; al[r + 3] = v.w;
             }
             const long long plane = ((long long)n_first * p.F + ft) * OHW;
-            auto store_tile = [&](auto value, void *base) __attribute__((always_inline)) {
+            auto store_tile = [&](auto aux, auto value, void *base) __attribute__((always_inline)) {
                 // (a scalar buffer per row of filters: no vector arithmetic for the addresses)
                 const auto buf = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, kRaw);
 #pragma unroll
@@ -456,16 +457,20 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
                     if (nfilt >= 32) {
 #pragma unroll
                         for (int j = 0; j < NP; ++j)
-                            __builtin_amdgcn_raw_buffer_store_b32(value(j, r), buf, (int)voff[j], row * OHW * 4, 0);
+                            __builtin_amdgcn_raw_buffer_store_b32(value(j, r), buf, (int)voff[j], row * OHW * 4, aux);
                     } else {
 #pragma unroll
                         for (int j = 0; j < NP; ++j)
-                            __builtin_amdgcn_raw_buffer_store_b32(value(j, r), buf, (int)(row + 4 * kg < nfilt ? voff[j] : 0xfffffff0u), row * OHW * 4, 0);
+                            __builtin_amdgcn_raw_buffer_store_b32(value(j, r), buf, (int)(row + 4 * kg < nfilt ? voff[j] : 0xfffffff0u), row * OHW * 4, aux);
                     }
                 }
             };
-            store_tile([&](int j, int r) { return __float_as_uint(acc[i][j][r] * (kv[j] * al[r])); }, p.out + plane);
-            if (p.dot) store_tile([&](int j, int r) { return (uint32_t)(int)acc[i][j][r]; }, p.dot + plane);
+            auto store_both = [&](auto aux) __attribute__((always_inline)) {
+                store_tile(aux, [&](int j, int r) { return __float_as_uint(acc[i][j][r] * (kv[j] * al[r])); }, p.out + plane);
+                if (p.dot) store_tile(aux, [&](int j, int r) { return (uint32_t)(int)acc[i][j][r]; }, p.dot + plane);
+            };
+            if (p.write_through) store_both(std::integral_constant<int, kWriteThrough>{});
+            else store_both(std::integral_constant<int, 0>{});
         }
     }
 }
@@ -659,6 +664,14 @@ hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const floa
     p.ptiles = (int)pl.ptiles; p.fgroups = ceil_div(g.F, ft);
     p.wgs_per_xcd = ceil_div((long long)p.ptiles * p.fgroups, kXcds);
     p.Wp = pl.Wp; p.RHfull = pl.RHfull; p.S2 = pl.S2; p.T = pl.T; p.tile_steps = pl.tile_steps; p.pitch16 = pl.pitch16;
+    // Where the planes of `out` and `dot` begin on 16-byte boundaries, their stores leave the L2 as they come (agent
+    // scope): otherwise it is written back when the kernel ends, while nothing computes.  Planes that begin anywhere share
+    // 16-byte units with their neighbours, written twice then.  us per launch, written back -> through:
+    //   64 x 256 x 28 x 28 F=512 1x1  27.6 -> 22.3   16 x 128 x 56 x 56 F=128 5x5     15.7 -> 14.0
+    //   64 x 128 x 28 x 28 F=128 3x3  10.6 -> 9.4    64 x 128 x 28 x 28 F=256 3x3 s2   8.7 -> 8.3 (196 pixels)
+    //   1 x 256 x 14 x 14 F=256 3x3    5.2 -> 5.3    16 x 128 x 54 x 54 F=128 3x3     11.0 -> 10.9
+    // and for planes of 169, 729, 12321 and 12210 (8-byte boundaries) pixels 18.8 -> 19.6, 11.1 -> 11.7, 16.8 -> 18.7, 14.0 -> 15.7.
+    p.write_through = ((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(dot)) & 15) == 0 && g.OH * g.OW % 4 == 0;
     p.tab16 = pl.slots_max * pl.pitch16;
     p.al16 = p.tab16 + (pl.T + kTabTail + 3) / 4;
     p.a16 = p.al16 + ft / 4;

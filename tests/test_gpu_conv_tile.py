@@ -78,3 +78,22 @@ def test_tiles_of_more_slots_than_are_fetched_at_once(xb, shape):
     and with two items a slot."""
     assert xb.xnor_conv2d_mfma_kernel(xb.Shape(*shape)) == xb.ALGO_MFMA_TILE
     test_tiles_vs_oracle(xb, shape)
+
+
+@pytest.mark.parametrize("shape", [(6, 64, 14, 14, 72, 3, 3, 1, 1, 1, 1), (2, 64, 16, 24, 64, 3, 3, 1, 1, 1, 1), (3, 64, 13, 13, 40, 3, 3, 1, 1, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_outputs_that_begin_on_any_boundary(xb, shape):
+    """Stores go past the L2 or not by the alignment of `out`, `dot` and their planes: the same bits, nothing beside them."""
+    rng = np.random.default_rng(5)
+    _, I, Wt = random_layer(rng, "t", *shape)
+    s = xb.Shape(*shape)
+    ws = torch.empty((xb.xnor_conv2d_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
+    Ipk, K, A, Wpk, alpha, _ = xb.xnor_prepare(dev(I), dev(Wt), s, workspace=ws)
+    out0, dot0 = xb.xnor_conv2d_fwd_expanded(Ipk, ws, K, alpha, s, want_dot=True)
+    n = out0.numel()
+    for a, b in ((0, 0), (1, 0), (0, 3), (2, 2)):
+        big, bigd = torch.full((n + 8,), -7.0, device="cuda"), torch.full((n + 8,), -7, dtype=torch.int32, device="cuda")
+        xb.xnor_conv2d_fwd_expanded(Ipk, ws, K, alpha, s, big[a:a + n].view_as(out0), bigd[b:b + n].view_as(dot0))
+        torch.cuda.synchronize()
+        assert torch.equal(big[a:a + n].view_as(out0), out0) and torch.equal(bigd[b:b + n].view_as(dot0), dot0)
+        assert (big[:a] == -7).all() and (big[a + n:] == -7).all() and (bigd[:b] == -7).all() and (bigd[b + n:] == -7).all()
