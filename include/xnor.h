@@ -74,9 +74,10 @@ typedef enum {
     XNOR_ALGO_MFMA_PERSISTENT = 6, /* ... with persistent workgroups, two wave groups each, and      */
     XNOR_ALGO_MFMA_TILE = 7,  /* ... with many small workgroups: by name, whatever XNOR_ALGO_MFMA takes
                                (the _algo calls only; tests and measurements)                     */
-    XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split exactly into three bf16
-                               terms, v_mfma_f32_32x32x16_bf16 against +-1 weights;
-                               xnor_conv2d_fp32_fwd_ws: both operands split so                      */
+    XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split into five FP6 digits with a
+                               scale per position and 32 channels, v_mfma_scale_f32_32x32x64_f8f6f4
+                               against +-1 weights, or, where that form does not take the shape, into three bf16
+                               terms; xnor_conv2d_fp32_fwd_ws: both operands split into bf16 terms  */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
@@ -296,10 +297,12 @@ int xnor_forward_image(const float *I, const uint32_t *Wpk, const float *alpha, 
  * MFMA_SPLIT, MFMA, DIRECT that takes the shape), XNOR_ALGO_DIRECT (any shape), XNOR_ALGO_MFMA (fp32
  * matrix instruction with +-1.0 as one operand; XNOR_E_UNSUPPORTED where the input rows under 32
  * output pixels do not fit in 128 KB of LDS, or kh*kw > 64) or XNOR_ALGO_MFMA_SPLIT (every input
- * value split into three bf16 terms whose sum is the value, bf16 matrix instruction with +-1
- * weights, fp32 accumulation: the same products, three instructions at 16 times the rate instead of
- * eight; an input that is not finite gives NaN, not an infinity, and a term below the normal range
- * is flushed, which adds at most alpha * 2^-125 per input value under the window to the error;
+ * value split into terms that the matrix instruction takes, +-1 weights, fp32 accumulation.  Terms:
+ * five FP6 digits under a power of two that 32 channels of a position share, which hold every
+ * value to within 2^-23.9 of the largest of the 32 and those of about its binade exactly; or, where the
+ * rows under 32 output pixels are too wide for that kernel or an image has 2 GiB, three bf16 terms, which hold it
+ * exactly.  An input that is not finite gives NaN, not an infinity; at the bottom of fp32's range
+ * the error grows by at most alpha * 2^-125 per input value under the window;
  * XNOR_E_UNSUPPORTED where the input rows under 32 output pixels are more than 512 staged
  * positions or do not fit, twice over and with two sets of filter words, in 160 KB of LDS, or
  * kh*kw > 64); other values XNOR_E_UNSUPPORTED.
@@ -314,8 +317,8 @@ int xnor_bwn_conv2d_fwd_algo(const float *I, const uint32_t *Wpk, const float *a
 int xnor_bwn_pick_algo(const xnor_shape *s);
 
 /*
- * The launch XNOR_ALGO_MFMA_SPLIT makes for this shape on a GPU of `compute_units` units (0: the
- * current device's, 256 where there is none).  Host only; for tests and for reading a timing.
+ * The launch that XNOR_ALGO_MFMA_SPLIT's bf16 form makes for this shape on a GPU of `compute_units` units (0: the
+ * current device's, 256 where there is none), whichever of the two forms runs it.  Host only; for tests and for reading a timing.
  *   *tiles         32-pixel tiles of one image a workgroup takes (1..6; an image's last workgroup
  *                  the rest)
  *   *row_segments  0: a tile is 32 consecutive output pixels; k > 0: a tile is one of the k

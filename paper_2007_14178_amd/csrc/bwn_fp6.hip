@@ -1,0 +1,508 @@
+// Binary-Weight-Network convolution (Sec. II-A, Eq. 1) on the matrix instruction for 6- and 4-bit
+// operands (v_mfma_scale_f32_32x32x64_f8f6f4, four times the bf16 instruction's rate): the 32
+// channels of one packed word at one position are a block with one power of two as its scale, and
+// every value x of the block is a sum of five FP6 (E2M3) digits,
+//
+//   x = s * (d0 + d1 2^-4 + d2 2^-9 + d3 2^-14 + d4 2^-19) + e,   |e| <= 2^-22 s,
+//
+// each digit what the ones before it left over, rounded to four significant bits.  s is chosen so that
+// the block's largest magnitude lies in [3.875, 7.75) s (E2M3 ends at 7.5, and 7.75 still rounds to it with a
+// remainder of 0.25): |e| is about half an ulp of the block's largest value, and values from about that one's
+// binade up have no error at all.  The differences are exact in fp32.  The weights are +-1 in FP4, so the
+// products are exact; the powers of the digits ride on the filters' scale, s on the input's, and the sum is
+// accumulated in fp32: five instructions per 64 channels where the bf16 terms of csrc/bwn_split.hip need twelve
+// of the same length.
+//
+//   bwn_fp6_kernel: a workgroup (1..8 waves) owns 32 * NF filters x one tile of 32 consecutive output pixels of one
+//   image per wave.  Per chunk of G words the rows under the pixels (whole rows: one run of the plane per
+//   channel) are read, a position and word per lane, cut into digits in registers and laid into LDS as
+//   [word][position][5 digits x 24 bytes, scale]; the last position is zeros, which is where padding and
+//   the pixels past the last one read.  The filters' words of the chunk lie beside it as [tap][word][filter].
+//   A step multiplies two (tap, word) blocks, one per lane half: NF * 5 matrix instructions.  What a step's
+//   matrix instructions used is loaded again for the next one right behind its last use, and the sign words
+//   of the next step become FP4 codes between them.  The chunk's staging stands between two barriers; the two or
+//   more workgroups on a compute unit fill each other's.
+//
+//   Bound by: the matrix pipe at the card's power (6.3 PFLOP/s of this pair of formats in a loop of random digits, 9.0 of
+//   zeros; an instruction takes 32 cycles), then by the digits' conversions (about 1200 cycles per 64 blocks,
+//   again for every filter group) and the wait for a chunk's loads, which other workgroups fill in part.
+//   Passes against the bf16 terms: 128x384x13x13 F=384 3x3 180 -> 112 us; loops of launches: 128x512x28x28 F=512 3x3
+//   1300 -> 735 us, 16x128x56x56 F=128 7x7 291 -> 118, 64x512x28x28 F=256 1x1 184 -> 86, 1x256x14x14 F=256 3x3 48 -> 22.
+//   Relative error against 64-bit sums 5.2e-7 -> 2.6e-7 (fewer roundings of the sum: five per 64 channels, not twelve).
+//   Inputs that are not finite give NaN in every window that holds them (the block's scale is NaN).
+//   Scales end at 2^-104: below, a value's error is at most 2^-126, and no digit's product leaves the normal range.
+#include <algorithm>
+#include <atomic>
+
+#include "xnor_internal.hpp"
+
+namespace xnor {
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v32f __attribute__((ext_vector_type(32)));
+typedef uint32_t v6u __attribute__((ext_vector_type(6)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int kPosBytes = 136;     // five digits, the scale, four bytes so that 32 lanes' 8-byte accesses at
+                                   // consecutive positions touch every bank once (17 bank pairs apart)
+constexpr int kDigits = 5;
+constexpr int kMaxWaves = 8;
+constexpr int kMinScale = 23;      // exponent field of the smallest scale, 2^-104
+constexpr size_t kLds = 160 * 1024;
+
+struct Fp6Params {
+    const float *I;
+    const uint32_t *Wpk;
+    const float *alpha;
+    float *out;
+    int C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW, Cw;
+    int G;                         // words per chunk (the last chunk of an odd number of words has one)
+    int wgs;                       // workgroups of an image (per filter group)
+    int fgroups, units;            // filter groups; N * wgs
+    int positions;                 // staged positions there is room for; the zero position is the next one
+};
+
+// Power of the digit t against the block's scale: 0, -4, -9, -14, -19.
+__device__ constexpr int digit_exp(int t) { return t == 0 ? 0 : 1 - 5 * t; }
+
+// Both conversions write their result over several cycles while they still read: the result may not share registers
+// with an operand (the early clobber), and the next instruction may not read it at once (the wait states).
+__device__ inline v6u to_fp6(const v16f &even, const v16f &odd, float scale)
+{
+    v6u r;
+    asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3\n\ts_nop 1" : "=&v"(r) : "v"(even), "v"(odd), "v"(scale));
+    return r;
+}
+
+__device__ inline v32f from_fp6(const v6u &d, float scale)
+{
+    v32f r;
+    asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2\n\ts_nop 1" : "=&v"(r) : "v"(d), "v"(scale));
+    return r;
+}
+
+// The block's values, in the order of the FP4 codes of expand_word: field 2i of a digit is even[i], channel
+// 8 (i % 4) + 2 (i / 4) of the word, field 2i + 1 is odd[i], the channel behind it.
+struct Block {
+    v16f even, odd;
+};
+__device__ constexpr int channel_of(int i) { return 8 * (i & 3) + 2 * (i >> 2); }
+
+// `src` is the image's rows, `lane` the byte offset of the lane's block, `first` the bytes before the chunk's first
+// channel, `plane` those of a channel's plane; `nvalid` of the block's channels are there.
+__device__ inline void load_block(Block &b, __amdgpu_buffer_rsrc_t src, int lane, int first, int plane, bool whole, int nvalid)
+{
+    if (whole) {                   // (uniform)
+        auto load = [&](int c) __attribute__((always_inline)) {
+            return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, lane, first + c * plane, 0));
+        };
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            b.even[i] = load(channel_of(i));
+            b.odd[i] = load(channel_of(i) + 1);
+        }
+    } else {                       // the last word of C % 32 channels: reads stay inside, the rest is zero
+        auto load = [&](int c) __attribute__((always_inline)) {
+            const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, lane + min(c, nvalid - 1) * plane, first, 0));
+            return c < nvalid ? v : 0.f;
+        };
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            b.even[i] = load(channel_of(i));
+            b.odd[i] = load(channel_of(i) + 1);
+        }
+    }
+}
+
+// The block's digits and scale to `at` (where `keep`: lanes past the last position take part in the arithmetic only).
+__device__ inline void split_block(Block &b, char *at, bool keep)
+{
+    float m = 0.f;                 // (propagates NaN)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(b.even[i])), fabsf(b.odd[i]));
+    const uint32_t bits = __float_as_uint(m);
+    // the exponent, one more from 1.9375 times the power of two up, less two
+    const uint32_t scale = (bits & 0x7fffffffu) >= 0x7f800000u ? 255u
+                           : (uint32_t)max((int)((bits + (1u << 19)) >> 23) - 2, kMinScale);
+    if (keep) *reinterpret_cast<uint32_t *>(at + 120) = scale;
+#pragma unroll
+    for (int t = 0; t < kDigits; ++t) {
+        const float s = __uint_as_float((scale + digit_exp(t)) << 23);
+        const v6u d = to_fp6(b.even, b.odd, s);
+        if (keep) {
+            v2u *o = reinterpret_cast<v2u *>(at + 24 * t);
+            o[0] = (v2u){d[0], d[1]};
+            o[1] = (v2u){d[2], d[3]};
+            o[2] = (v2u){d[4], d[5]};
+        }
+        if (t + 1 < kDigits) {
+            const v32f back = from_fp6(d, s);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                b.even[i] -= back[2 * i];
+                b.odd[i] -= back[2 * i + 1];
+            }
+        }
+    }
+}
+
+template <int NF>
+struct Fp6Wave {
+    static constexpr int kFilters = 32 * NF;
+
+    // Digit T of the pixels' blocks against one filter tile.  The digits' powers are the bytes of two registers.
+    template <int T>
+    static __device__ __attribute__((always_inline)) inline void product(v16f &acc, const v4i &a, const v6u &d, int scale)
+    {
+        constexpr int powers = T < 4 ? (127 + digit_exp(0)) | (127 + digit_exp(1)) << 8 | (127 + digit_exp(2)) << 16 | (127 + digit_exp(3)) << 24
+                                     : 127 + digit_exp(4);
+        const v8i b = {(int)d[0], (int)d[1], (int)d[2], (int)d[3], (int)d[4], (int)d[5], 0, 0};
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1), b, acc, 4, 2,
+                                                              T & 3, powers, 0, scale);
+    }
+    template <int T>
+    static __device__ __attribute__((always_inline)) inline void digit(v16f (&acc)[NF], const v4i (&A)[NF], const v6u &d, int scale)
+    {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) product<T>(acc[f], A[f], d, scale);
+    }
+
+    // One chunk's steps: two (tap, word) blocks each.  With two words in the chunk lane half h takes word h of the
+    // step's tap, with one the word of tap 2 * step + h.
+    static __device__ __attribute__((always_inline)) inline void steps(v16f (&acc)[NF], const Fp6Params &p, const char *dig, const uint32_t *words,
+                                                                       bool two, int iy, int ix, int row0, int half, int col)
+    {
+        const int taps = p.kh * p.kw, nsteps = two ? taps : (taps + 1) >> 1;
+        const int word_bytes = (p.positions + 1) * kPosBytes, zero = p.positions * kPosBytes;
+        const int group = two && half ? word_bytes : 0;
+        // the lane's tap: its row and column in the image, its column in the window, its place
+        int y = iy, x = ix, kx = 0, to = ((iy - row0) * p.W + ix) * kPosBytes;
+        const int y_end = iy + p.kh, back = (p.W - p.kw + 1) * kPosBytes;
+        auto next_tap = [&]() __attribute__((always_inline)) {
+            const bool wrap = kx + 1 == p.kw;
+            to += wrap ? back : kPosBytes;
+            x = wrap ? ix : x + 1;
+            kx = wrap ? 0 : kx + 1;
+            y += wrap ? 1 : 0;
+        };
+        if (!two && half) next_tap();
+        auto place = [&]() __attribute__((always_inline)) {
+            const bool in = y < y_end & (unsigned)y < (unsigned)p.H & (unsigned)x < (unsigned)p.W;
+            const int at = in ? to : zero;
+            next_tap();
+            if (!two) next_tap();
+            return dig + (at + group);
+        };
+        v6u B[kDigits];
+        auto read_digit = [&](int t, const char *at) __attribute__((always_inline)) {
+            const v2u *o = reinterpret_cast<const v2u *>(at + 24 * t);
+            const v2u a = o[0], b = o[1], c = o[2];
+            B[t] = (v6u){a.x, a.y, b.x, b.y, c.x, c.y};
+        };
+        const uint32_t *wat = words + half * kFilters + col;
+        uint32_t wnext[NF];
+        auto read_words = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) wnext[f] = wat[32 * f];
+            wat += 2 * kFilters;
+        };
+        v4i A[NF];
+        auto expand = [&](int f) __attribute__((always_inline)) {
+            const uint4 e = expand_word(wnext[f], 32);
+            A[f] = (v4i){(int)e.x, (int)e.y, (int)e.z, (int)e.w};
+        };
+        const char *at = place();
+#pragma unroll
+        for (int t = 0; t < kDigits; ++t) read_digit(t, at);
+        int scale = *reinterpret_cast<const int *>(at + 120);
+        read_words();
+#pragma unroll
+        for (int f = 0; f < NF; ++f) expand(f);
+        for (int s = 0; s < nsteps; ++s) {
+            // the next step's place (past the last step: the zero position, and two rows of words that nothing filled)
+            at = place();
+            read_words();
+            const int scale_next = *reinterpret_cast<const int *>(at + 120);
+            digit<0>(acc, A, B[0], scale);
+            read_digit(0, at);
+            __builtin_amdgcn_sched_barrier(0);
+            digit<1>(acc, A, B[1], scale);
+            read_digit(1, at);
+            __builtin_amdgcn_sched_barrier(0);
+            digit<2>(acc, A, B[2], scale);
+            read_digit(2, at);
+            __builtin_amdgcn_sched_barrier(0);
+            digit<3>(acc, A, B[3], scale);
+            read_digit(3, at);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                product<4>(acc[f], A[f], B[4], scale);
+                expand(f);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read_digit(4, at);
+            __builtin_amdgcn_sched_barrier(0);
+            scale = scale_next;
+        }
+    }
+
+    static __device__ __attribute__((always_inline)) inline void run(const Fp6Params &p)
+    {
+        extern __shared__ __attribute__((aligned(16))) char smem[];
+        const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int taps = p.kh * p.kw;
+        const int word_bytes = (p.positions + 1) * kPosBytes;
+        const int G = p.G;
+        char *dig = smem;
+        uint32_t *words = reinterpret_cast<uint32_t *>(smem + G * word_bytes);
+
+        // a unit's filter groups run one behind the other on one XCD (workgroup ids go round the eight)
+        const int k = blockIdx.x >> 3, fg = k % p.fgroups, unit = (k / p.fgroups) * 8 + (blockIdx.x & 7);
+        if (unit >= p.units) return;
+        const int n = unit / p.wgs, waves = nt >> 6;
+        const int OHW = p.OH * p.OW, HW = p.H * p.W;
+        const int px0 = (unit - n * p.wgs) * waves * 32, px1 = min(OHW, px0 + waves * 32) - 1;
+        const int row0 = max(0, px0 / p.OW * p.sh - p.ph);
+        const int row1 = min(p.H - 1, px1 / p.OW * p.sh - p.ph + p.kh - 1);
+        const int npos = max(0, row1 - row0 + 1) * p.W;       // <= p.positions
+        const int f0 = fg * kFilters, nfil = min(kFilters, p.F - f0);
+
+        const int px = px0 + wave * 32 + col;
+        const int oy = px / p.OW, ox = px - oy * p.OW;
+        const int iy = px < OHW ? oy * p.sh - p.ph : -128, ix = ox * p.sw - p.pw;
+
+        // (bytes of an image < 2^31, so every offset is)
+        const __amdgpu_buffer_rsrc_t in = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(p.I + (size_t)n * p.C * HW + (size_t)row0 * p.W), 0, 0x7fffffff, 0x00027000);
+        const int plane = HW * 4;
+        const int nchunks = (p.Cw + G - 1) / G;
+        for (int i = tid; i < G * (kPosBytes / 4); i += nt)
+            reinterpret_cast<uint32_t *>(dig + (i / (kPosBytes / 4)) * word_bytes + p.positions * kPosBytes)[i % (kPosBytes / 4)] = 0;
+
+        // staging rounds of a chunk: nt blocks each, the positions of its first word and then those of its second
+        auto words_in = [&](int ch) { return min(G, p.Cw - ch * G); };
+        auto place_of = [&](int r, int &g, int &pos) __attribute__((always_inline)) {
+            const int i = r * nt + tid;
+            g = i >= npos ? 1 : 0;
+            pos = i - (g ? npos : 0);
+            return i;
+        };
+        auto load_round = [&](Block &b, int ch, int r) __attribute__((always_inline)) {
+            int g, pos;
+            if (place_of(r, g, pos) < npos * words_in(ch))
+                load_block(b, in, pos * 4 + g * 32 * plane, ch * G * 32 * plane, plane, (ch + 1) * G * 32 <= p.C, p.C - 32 * (ch * G + g));
+        };
+        // Filter words go from memory into LDS without a register, 64 lanes' words side by side, in rows of the filters'
+        // words (tap, word).  Filters past the last one, whose outputs are not stored, read the last one's
+        // words; a row past the last one, that one's.  (A filter's words side by side, so that 64 lanes touch a few
+        // lines and not one each, cost the loop an address per tile and were slower: 114 for 102 us at
+        // 128x384x13x13 F=384 3x3.)
+        const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint32_t *>(p.Wpk + (size_t)f0 * taps * p.Cw), 0, 0x7fffffff, 0x00027000);
+        auto load_words = [&](int ch) __attribute__((always_inline)) {
+            const bool two = words_in(ch) == 2;
+            const int rows = two ? 2 * taps : taps;
+            auto *to = (__attribute__((address_space(3))) char *)words;
+            for (int item = wave; item * 64 < rows * kFilters; item += waves) {
+                const int i = item * 64 + lane, f = i % kFilters, row = min(i / kFilters, rows - 1);
+                const int tap = two ? row >> 1 : row, g = two ? row & 1 : 0;
+                const int at = (min(f, nfil - 1) * taps + tap) * (p.Cw * 4) + g * 4;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wsrc, (__attribute__((address_space(3))) void *)(to + item * 256), 4, at,
+                                                         ch * G * 4, 0, 0);
+            }
+        };
+
+        v16f acc[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[f][r] = 0.f;
+
+        for (int ch = 0; ch < nchunks; ++ch) {
+            const int blocks = npos * words_in(ch);
+            __syncthreads();                             // the chunk before has been read
+            load_words(ch);
+            for (int r = 0; r * nt < blocks; ++r) {
+                int g, pos;
+                const bool keep = place_of(r, g, pos) < blocks;
+                Block cur;
+                load_round(cur, ch, r);
+                split_block(cur, dig + g * word_bytes + pos * kPosBytes, keep);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the words are in LDS
+            __syncthreads();
+            if (px0 + wave * 32 < OHW)
+                steps(acc, p, dig, words, words_in(ch) == 2, iy, ix, row0, half, col);
+        }
+
+        // accumulator register r of a lane: filter row 8*(r/4) + 4*half + r%4 of the tile, pixel column `col`
+        if (px < OHW) {
+            float *dst = p.out + ((size_t)n * p.F + f0) * OHW + px;
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 32 * f + 8 * (r >> 2) + 4 * half + (r & 3);
+                    if (row < nfil) dst[(size_t)row * OHW] = acc[f][r] * p.alpha[f0 + row];
+                }
+        }
+    }
+};
+
+template <int NF>
+__global__ __launch_bounds__(64 * kMaxWaves, 3) void bwn_fp6_kernel(Fp6Params p)
+{
+    Fp6Wave<NF>::run(p);
+}
+
+struct Fp6Plan {
+    bool ok;
+    int nf, G, waves, wgs, positions;
+    size_t lds;
+};
+
+// LDS of a workgroup: the staged positions of G words and the zero position; the filter words of G * taps rows, up to
+// whole steps, and of two steps that are read ahead of use (the rows' last 64 words may reach into these).
+size_t fp6_lds(const Geom &g, int nf, int G, int positions)
+{
+    const int taps = g.kh * g.kw, steps = G == 2 ? taps : (taps + 1) / 2;
+    return (size_t)G * (positions + 1) * kPosBytes + (size_t)(steps + 2) * 8 * (32 * nf);
+}
+
+// Most positions that a workgroup of `waves` tiles stages: whole rows under the output rows it can touch.
+long long fp6_positions(const Geom &g, int waves)
+{
+    const long long orows = std::min(g.OH, (32 * waves + g.OW - 2) / g.OW + 1);
+    return std::min((long long)g.H, (orows - 1) * g.sh + g.kh) * g.W;
+}
+
+// About what a launch takes on its busiest compute unit, in cycles: `wgs` workgroups on `cus` units, in batches of those
+// that a unit holds.  A batch is through when its matrix instructions and conversions are, on the SIMD that
+// has most of its waves, or when one workgroup's chain is: load, convert, barrier, multiply.  The constants are
+// a fit to 2700 timed launches of 45 layers (1 to 128 images, 32 to 512 channels and filters, 1x1 to 7x7, 7 to 64
+// wide); the shape taken is 2 % slower than the best of the up to 64 on average, 17 % at most.
+double fp6_cost(const Geom &g, int nf, int G, int waves, int positions, size_t lds, long long wgs, int cus)
+{
+    constexpr double kContended = 1.3;                    // matrix instructions beside others', at the card's power
+    constexpr double kConvert = 1850, kLoad = 2100;       // a round of blocks: the conversions; the wait for its loads
+    constexpr double kChunk = 3300, kWords = 260;         // barriers and the first operands; an instruction of filter words
+    constexpr double kSteps = 430, kStores = 840;         // into the steps, per chunk; outputs of a filter tile
+    const int taps = g.kh * g.kw, nt = 64 * waves;
+    double mfma = 0, convert = 0, wait = 0;
+    auto chunks = [&](int n, int words) {
+        const int steps = words == 2 ? taps : (taps + 1) / 2, rounds = ceil_div((long long)positions * words, nt);
+        mfma += n * (steps * nf * kDigits * 32 + kSteps);
+        convert += n * rounds * kConvert;
+        wait += n * (kChunk + rounds * kLoad + kWords * taps * words * nf * 0.5 / waves);
+    };
+    chunks(g.Cw / G, G);
+    if (g.Cw % G) chunks(1, 1);
+    const double alone = mfma + convert + wait + kStores * nf;
+    // registers hold three waves on a SIMD, four with one filter tile
+    const int held = std::max(1, std::min((int)(kLds / lds), (nf == 1 ? 16 : 12) / waves));
+    auto batch = [&](long long n) {
+        return std::max(alone, ceil_div(n * waves, 4) * (mfma * kContended + convert) + wait / n);
+    };
+    const long long busiest = (wgs + cus - 1) / cus, full = busiest / held, rest = busiest % held;
+    return full * batch(held) + (rest ? batch(rest) : 0.0);
+}
+
+Fp6Plan search_fp6_plan(const Geom &g, int cus, int force_nf = 0, int force_G = 0, int force_waves = 0)
+{
+    Fp6Plan pl{};
+    const long long OHW = (long long)g.OH * g.OW, taps = (long long)g.kh * g.kw;
+    if (taps > 64 || OHW > (1 << 24) || (long long)g.C * g.H * g.W >= (1LL << 29)) return pl;     // (32-bit byte offsets)
+    if ((long long)g.F * taps * g.Cw >= (1LL << 29)) return pl;
+    const int tiles = ceil_div(OHW, 32);
+    double best = -1.0;
+    for (int nf = 4; nf >= 1; --nf) {
+        if (nf > 1 && 32 * (nf - 1) >= g.F) continue;
+        for (int G = std::min(2, g.Cw); G >= 1; --G)
+            for (int waves = std::min(kMaxWaves, tiles); waves >= 1; --waves) {
+                if ((force_nf && nf != force_nf) || (force_G && G != force_G) || (force_waves && waves != force_waves)) continue;
+                const long long positions = fp6_positions(g, waves);
+                if (positions > (long long)(kLds / kPosBytes)) continue;
+                const size_t lds = fp6_lds(g, nf, G, (int)positions);
+                if (lds > kLds) continue;
+                const int wgs = ceil_div(tiles, waves);
+                const long long all = (long long)g.N * wgs * ceil_div(g.F, 32 * nf);
+                if (all > 0x7ffffff0LL) continue;
+                const double cost = fp6_cost(g, nf, G, waves, (int)positions, lds, all, cus);
+                if (best < 0 || cost < best) {
+                    best = cost;
+                    pl = {true, nf, G, waves, wgs, (int)positions, lds};
+                }
+            }
+    }
+    return pl;
+}
+
+const Fp6Plan &make_fp6_plan(const Geom &g)
+{
+    static thread_local PlanMemo<Fp6Plan> memo;
+    const int cus = compute_units();
+    return memo.get(g, cus, [&] { return search_fp6_plan(g, cus); });
+}
+
+template <int NF>
+hipError_t start_fp6(const Fp6Plan &pl, const Fp6Params &p, unsigned blocks, hipStream_t st)
+{
+    if (pl.lds > 64 * 1024) {
+        // raise the kernel's dynamic-LDS limit once per device
+        static std::atomic<unsigned long long> raised{0};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (!(raised.load() & bit)) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bwn_fp6_kernel<NF>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+            if (e != hipSuccess) return e;
+            raised.fetch_or(bit);
+        }
+    }
+    bwn_fp6_kernel<NF><<<dim3(blocks), dim3(64 * pl.waves), pl.lds, st>>>(p);
+    return hipGetLastError();
+}
+
+hipError_t launch_fp6_plan(const Fp6Plan &pl, const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
+                           float *out, hipStream_t st)
+{
+    Fp6Params p;
+    p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out;
+    p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
+    p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW; p.Cw = g.Cw;
+    p.G = pl.G;
+    p.wgs = pl.wgs;
+    p.fgroups = ceil_div(g.F, 32 * pl.nf);
+    p.positions = pl.positions;
+    const long long units = (long long)g.N * pl.wgs, blocks = (units + 7) / 8 * 8 * p.fgroups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    p.units = (int)units;
+    const unsigned b = (unsigned)blocks;
+    switch (pl.nf) {
+        case 4: return start_fp6<4>(pl, p, b, st);
+        case 3: return start_fp6<3>(pl, p, b, st);
+        case 2: return start_fp6<2>(pl, p, b, st);
+        default: return start_fp6<1>(pl, p, b, st);
+    }
+}
+
+}  // namespace
+
+bool bwn_fp6_supports(const Geom &g) { return make_fp6_plan(g).ok; }
+
+hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out,
+                          hipStream_t st)
+{
+    const Fp6Plan &pl = make_fp6_plan(g);
+    if (!pl.ok) return hipErrorInvalidValue;
+    return launch_fp6_plan(pl, I, Wpk, alpha, g, out, st);
+}
+
+}  // namespace xnor

@@ -1,4 +1,5 @@
-// Binary-Weight-Network convolution (Sec. II-A, Eq. 1) on the bf16 matrix instruction, exact in its
+// Binary-Weight-Network convolution (Sec. II-A, Eq. 1) on the bf16 matrix instruction, for the shapes that the FP6 kernel
+// of csrc/bwn_fp6.hip leaves (rows too wide to be staged whole under two output rows, images of 2 GiB), exact in its
 // operands: every fp32 input value x is split into three bf16 terms x = hi + mid + lo (each term
 // the leading eight significand bits of what the terms before it left over: the three differences
 // are exact in fp32 and 3 x 8 bits are the whole significand), the weights are +-1 (exact in bf16),

@@ -119,6 +119,9 @@ bool bwn_split_plan(const Geom &g, int compute_units, int *tiles, int *row_segme
                     long long *workgroups);
 hipError_t launch_bwn_split(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
                             float *out, hipStream_t st);
+bool bwn_fp6_supports(const Geom &g);
+hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out,
+                          hipStream_t st);
 bool conv_fp32_mfma_supports(const Geom &g);
 hipError_t launch_conv_fp32_mfma(const float *I, const float *Wt, const Geom &g, float *out, hipStream_t st);
 size_t conv_fp32_split_workspace_bytes(const Geom &g);   // 0 if the shape is not supported
