@@ -26,8 +26,8 @@
 //   Bound by: the matrix pipe at the card's power (6.3 PFLOP/s of this pair of formats in a loop of random digits, 9.0 of
 //   zeros; an instruction takes 32 cycles), then by the digits' conversions (about 1200 cycles per 64 blocks,
 //   again for every filter group) and the wait for a chunk's loads, which other workgroups fill in part.
-//   Passes against the bf16 terms: 128x384x13x13 F=384 3x3 180 -> 112 us; loops of launches: 128x512x28x28 F=512 3x3
-//   1300 -> 735 us, 16x128x56x56 F=128 7x7 291 -> 118, 64x512x28x28 F=256 1x1 184 -> 86, 1x256x14x14 F=256 3x3 48 -> 22.
+//   Passes against the bf16 terms: 128x384x13x13 F=384 3x3 177 -> 104 us; loops of launches: 128x512x28x28 F=512 3x3
+//   1300 -> 706 us, 16x128x56x56 F=128 7x7 291 -> 116, 1x256x14x14 F=256 3x3 48 -> 23.
 //   Relative error against 64-bit sums 5.2e-7 -> 2.6e-7 (fewer roundings of the sum: five per 64 channels, not twelve).
 //   Inputs that are not finite give NaN in every window that holds them (the block's scale is NaN).
 //   Scales end at 2^-104: below, a value's error is at most 2^-126, and no digit's product leaves the normal range.
@@ -84,12 +84,21 @@ __device__ inline v32f from_fp6(const v6u &d, float scale)
     return r;
 }
 
-// The block's values, in the order of the FP4 codes of expand_word: field 2i of a digit is even[i], channel
-// 8 (i % 4) + 2 (i / 4) of the word, field 2i + 1 is odd[i], the channel behind it.
+// Sign words -> FP4 codes, four registers of eight: register j's code n is the sign of channel 4 n + 3 - j, a shift and
+// one three-input operation a register (bit 1 is +1.0 = 0x2, bit 0 is -1.0 = 0xa): 7 instructions a word where
+// expand_word takes 11, 2 to 7 % of a layer with two and more filter tiles a wave.
+__device__ inline v4i sign_codes(uint32_t w)
+{
+    auto codes = [](uint32_t v) { return (int)((~v & 0x88888888u) | 0x22222222u); };
+    return (v4i){codes(w), codes(w << 1), codes(w << 2), codes(w << 3)};
+}
+
+// The block's values in the order of those codes: field 2i of a digit is even[i], channel channel_of(i) of the word,
+// field 2i + 1 is odd[i], the channel four behind it.
 struct Block {
     v16f even, odd;
 };
-__device__ constexpr int channel_of(int i) { return 8 * (i & 3) + 2 * (i >> 2); }
+__device__ constexpr int channel_of(int i) { return 8 * (i & 3) + 3 - (i >> 2); }
 
 // `src` is the image's rows, `lane` the byte offset of the lane's block, `first` the bytes before the chunk's first
 // channel, `plane` those of a channel's plane; `nvalid` of the block's channels are there.
@@ -102,7 +111,7 @@ __device__ inline void load_block(Block &b, __amdgpu_buffer_rsrc_t src, int lane
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             b.even[i] = load(channel_of(i));
-            b.odd[i] = load(channel_of(i) + 1);
+            b.odd[i] = load(channel_of(i) + 4);
         }
     } else {                       // the last word of C % 32 channels: reads stay inside, the rest is zero
         auto load = [&](int c) __attribute__((always_inline)) {
@@ -112,7 +121,7 @@ __device__ inline void load_block(Block &b, __amdgpu_buffer_rsrc_t src, int lane
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             b.even[i] = load(channel_of(i));
-            b.odd[i] = load(channel_of(i) + 1);
+            b.odd[i] = load(channel_of(i) + 4);
         }
     }
 }
@@ -179,7 +188,8 @@ struct Fp6Wave {
         const int taps = p.kh * p.kw, nsteps = two ? taps : (taps + 1) >> 1;
         const int word_bytes = (p.positions + 1) * kPosBytes, zero = p.positions * kPosBytes;
         const int group = two && half ? word_bytes : 0;
-        // the lane's tap: its row and column in the image, its column in the window, its place
+        // The lane's tap: its row and column in the image, its column in the window, its place.  (With scalars for the two
+        // halves' walks a step of one filter tile waits for the scalar chain: 46x45x7x7 F=98 7x7 18.0 -> 20.8 us.)
         int y = iy, x = ix, kx = 0, to = ((iy - row0) * p.W + ix) * kPosBytes;
         const int y_end = iy + p.kh, back = (p.W - p.kw + 1) * kPosBytes;
         auto next_tap = [&]() __attribute__((always_inline)) {
@@ -211,10 +221,7 @@ struct Fp6Wave {
             wat += 2 * kFilters;
         };
         v4i A[NF];
-        auto expand = [&](int f) __attribute__((always_inline)) {
-            const uint4 e = expand_word(wnext[f], 32);
-            A[f] = (v4i){(int)e.x, (int)e.y, (int)e.z, (int)e.w};
-        };
+        auto expand = [&](int f) __attribute__((always_inline)) { A[f] = sign_codes(wnext[f]); };
         const char *at = place();
 #pragma unroll
         for (int t = 0; t < kDigits; ++t) read_digit(t, at);
@@ -386,13 +393,13 @@ long long fp6_positions(const Geom &g, int waves)
 // that a unit holds.  A batch is through when its matrix instructions and conversions are, on the SIMD that
 // has most of its waves, or when one workgroup's chain is: load, convert, barrier, multiply.  The constants are
 // a fit to 2700 timed launches of 45 layers (1 to 128 images, 32 to 512 channels and filters, 1x1 to 7x7, 7 to 64
-// wide); the shape taken is 2 % slower than the best of the up to 64 on average, 17 % at most.
+// wide); the shape taken is 2 % slower than the best of the up to 64 on average, 20 % at most.
 double fp6_cost(const Geom &g, int nf, int G, int waves, int positions, size_t lds, long long wgs, int cus)
 {
     constexpr double kContended = 1.3;                    // matrix instructions beside others', at the card's power
     constexpr double kConvert = 1850, kLoad = 2100;       // a round of blocks: the conversions; the wait for its loads
-    constexpr double kChunk = 3300, kWords = 260;         // barriers and the first operands; an instruction of filter words
-    constexpr double kSteps = 430, kStores = 840;         // into the steps, per chunk; outputs of a filter tile
+    constexpr double kChunk = 3300, kWords = 320;         // barriers and the first operands; an instruction of filter words
+    constexpr double kSteps = 430, kStores = 1900;         // into the steps, per chunk; outputs of a filter tile
     const int taps = g.kh * g.kw, nt = 64 * waves;
     double mfma = 0, convert = 0, wait = 0;
     auto chunks = [&](int n, int words) {
@@ -404,8 +411,10 @@ double fp6_cost(const Geom &g, int nf, int G, int waves, int positions, size_t l
     chunks(g.Cw / G, G);
     if (g.Cw % G) chunks(1, 1);
     const double alone = mfma + convert + wait + kStores * nf;
-    // registers hold three waves on a SIMD, four with one filter tile
-    const int held = std::max(1, std::min((int)(kLds / lds), (nf == 1 ? 16 : 12) / waves));
+    // registers hold three waves on a SIMD, four with one filter tile; of workgroups of five to eight waves, which
+    // put two on some SIMD, one or two
+    const int per_simd = nf == 1 ? 4 : 3;
+    const int held = std::max(1, std::min((int)(kLds / lds), waves > 4 ? per_simd / 2 : 4 * per_simd / waves));
     auto batch = [&](long long n) {
         return std::max(alone, ceil_div(n * waves, 4) * (mfma * kContended + convert) + wait / n);
     };

@@ -376,7 +376,7 @@ int xnor_bwn_conv2d_fwd_algo(const float *I, const uint32_t *Wpk, const float *a
         case XNOR_ALGO_MFMA_SPLIT:
             if (!xnor::bwn_split_supports(g)) return XNOR_E_UNSUPPORTED;
             // The FP6 form wherever it takes the shape: 45 layers over the range of the benchmark's, 1.2 to 3.1 times as
-            // fast as the bf16 form, at half its error (128x384x13x13 F=384 3x3: 215 -> 108 us in a loop of launches).
+            // fast as the bf16 form, at half its error (128x384x13x13 F=384 3x3, a pass: 177 -> 104 us).
             // What it leaves are rows too wide for its whole-row staging (large strides) and images of 2 GiB.
             if (xnor::bwn_fp6_supports(g))
                 return hip_status(xnor::launch_bwn_fp6(I, Wpk, alpha, g, out, (hipStream_t)stream));
