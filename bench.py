@@ -490,25 +490,25 @@ def run_bwn(args, xb, torch, layer, make_input, make_weights):
                 for i, n in enumerate(["filter_prepare", "conv"])}
     macs = layer.binary_macs
     conv_ms = stage_ms["conv"]
-    # the three-term form executes three bf16 multiply-accumulates per fp32 one and is priced against
-    # the bf16 peak with what it executes; the other kernels against the fp32 peak
-    terms = 3 if kernel == "split" else 1
-    peak = PEAK_BF16_MFMA_TFLOPS if kernel == "split" else PEAK_FP32_MFMA_TFLOPS
+    # the split form executes five FP6 multiply-accumulates per fp32 one and is priced against the peak of the
+    # 6- and 4-bit formats with what it executes; the other kernels against the fp32 peak
+    terms = 5 if kernel == "split" else 1
+    peak = PEAK_FP4_MFMA_TFLOPS if kernel == "split" else PEAK_FP32_MFMA_TFLOPS
     achieved = terms * 2.0 * macs / (conv_ms * 1e-3) / 1e12
     rec = {
         "metric": "GMAC/s (real input x binary weight), Binary-Weight-Network layer (sign + alpha of the filters, add/subtract convolution, rescale)",
         "value": macs / (ms_per_step * 1e-3) / 1e9, "unit": "GMAC/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "fp32 input as three bf16 terms (exact), 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x16_bf16)"
-                 if kernel == "split" else "fp32 input, 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x2_f32)",
+        "dtype": "fp32 input as five FP6 digits under a scale per position and 32 channels, 1-bit weights as FP4, fp32 accumulate "
+                 "(v_mfma_scale_f32_32x32x64_f8f6f4)" if kernel == "split" else "fp32 input, 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x2_f32)",
         "data": "synthetic (seeded; shapes and value distributions of the benchmark layer)",
         "config": {"workload": f"{layer.name} as a BWN layer: N={layer.N} C={layer.C} {layer.H}x{layer.W} F={layer.F} "
                                f"{layer.kh}x{layer.kw} stride {layer.sh} pad {layer.ph}", "macs": macs},
         "stage_ms": stage_ms,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": {"split": "bwn_split_kernel", "mfma": "bwn_mfma_kernel", "direct": "bwn_direct_kernel"}[kernel]
+                     "kernel": {"split": "bwn_fp6_kernel", "mfma": "bwn_mfma_kernel", "direct": "bwn_direct_kernel"}[kernel]
                                + " (xnor_bwn_conv2d_fwd)",
                      "executed_flops_per_mac": 2 * terms, "kernel_ms": conv_ms},
     }
