@@ -80,7 +80,7 @@ def parse():
     ap.add_argument("--warmup", type=int, default=1000)
     ap.add_argument("--layer", default="c5", help="workload name (see paper_2007_14178_amd/workloads.py)")
     ap.add_argument("--algo", default="auto", choices=["auto", "direct", "tiled", "mfma", "split"],
-                    help="the convolution kernel (split: --bwn only, the three-term bf16 form)")
+                    help="the convolution kernel (split: --bwn only, the input split into FP6 digits)")
     ap.add_argument("--unfused", action="store_true", help="run the four pre-stage calls separately")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--separate-prepare", action="store_true",
