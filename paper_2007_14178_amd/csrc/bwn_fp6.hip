@@ -30,7 +30,8 @@
 //   1300 -> 706 us, 16x128x56x56 F=128 7x7 291 -> 116, 1x256x14x14 F=256 3x3 48 -> 23.
 //   Relative error against 64-bit sums 5.2e-7 -> 2.6e-7 (fewer roundings of the sum: five per 64 channels, not twelve).
 //   Inputs that are not finite give NaN in every window that holds them (the block's scale is NaN).
-//   Scales end at 2^-104: below, a value's error is at most 2^-126, and no digit's product leaves the normal range.
+//   Scales end at 2^-103: below, a value's error is at most 2^-125, and no digit's product leaves the normal range.  Sums
+// are of half the products, so that the first digit of a value in fp32's top 1/32, which rounds to 2^128, is inside it.
 #include <algorithm>
 #include <atomic>
 
@@ -50,7 +51,7 @@ constexpr int kPosBytes = 136;     // five digits, the scale, four bytes so that
                                    // consecutive positions touch every bank once (17 bank pairs apart)
 constexpr int kDigits = 5;
 constexpr int kMaxWaves = 8;
-constexpr int kMinScale = 23;      // exponent field of the smallest scale, 2^-104
+constexpr int kMinScale = 24;      // exponent field of the smallest scale, 2^-103
 constexpr size_t kLds = 160 * 1024;
 
 struct Fp6Params {
@@ -138,9 +139,21 @@ __device__ inline void split_block(Block &b, char *at, bool keep)
     const uint32_t scale = (bits & 0x7fffffffu) >= 0x7f800000u ? 255u
                            : (uint32_t)max((int)((bits + (1u << 19)) >> 23) - 2, kMinScale);
     if (keep) *reinterpret_cast<uint32_t *>(at + 120) = scale;
+    // From 1.9375 * 2^127 up the first digit is 4.0 * 2^126, which is no float: such a block's digits are those of its halves.
+    // (The test costs up to 1 % of a layer: 128x384x13x13 F=384 3x3 111.3 -> 112.4 us.)
+    uint32_t down = 0;
+    if (__any(scale == 253)) {
+        down = scale == 253 ? 1u : 0u;
+        const float f = down ? 0.5f : 1.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            b.even[i] *= f;
+            b.odd[i] *= f;
+        }
+    }
 #pragma unroll
     for (int t = 0; t < kDigits; ++t) {
-        const float s = __uint_as_float((scale + digit_exp(t)) << 23);
+        const float s = __uint_as_float((scale - down + digit_exp(t)) << 23);
         const v6u d = to_fp6(b.even, b.odd, s);
         if (keep) {
             v2u *o = reinterpret_cast<v2u *>(at + 24 * t);
@@ -163,12 +176,12 @@ template <int NF>
 struct Fp6Wave {
     static constexpr int kFilters = 32 * NF;
 
-    // Digit T of the pixels' blocks against one filter tile.  The digits' powers are the bytes of two registers.
+    // Half of digit T of the pixels' blocks against one filter tile.  The digits' powers are the bytes of two registers.
     template <int T>
     static __device__ __attribute__((always_inline)) inline void product(v16f &acc, const v4i &a, const v6u &d, int scale)
     {
-        constexpr int powers = T < 4 ? (127 + digit_exp(0)) | (127 + digit_exp(1)) << 8 | (127 + digit_exp(2)) << 16 | (127 + digit_exp(3)) << 24
-                                     : 127 + digit_exp(4);
+        constexpr int powers = T < 4 ? (126 + digit_exp(0)) | (126 + digit_exp(1)) << 8 | (126 + digit_exp(2)) << 16 | (126 + digit_exp(3)) << 24
+                                     : 126 + digit_exp(4);
         const v8i b = {(int)d[0], (int)d[1], (int)d[2], (int)d[3], (int)d[4], (int)d[5], 0, 0};
         acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1), b, acc, 4, 2,
                                                               T & 3, powers, 0, scale);
@@ -356,7 +369,7 @@ struct Fp6Wave {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int row = 32 * f + 8 * (r >> 2) + 4 * half + (r & 3);
-                    if (row < nfil) dst[(size_t)row * OHW] = acc[f][r] * p.alpha[f0 + row];
+                    if (row < nfil) dst[(size_t)row * OHW] = (acc[f][r] + acc[f][r]) * p.alpha[f0 + row];
                 }
         }
     }

@@ -88,7 +88,7 @@ def test_every_sum_of_24_bit_integers_is_exact(xb):
 
 @pytest.mark.parametrize("top", [1.9374999, 1.9375, 1.9375001, 1.9999999, 1.0, 1.5])
 def test_scales_around_the_largest_digit(xb, top):
-    """The block's largest value on either side of where the scale steps, over fp32's whole range of exponents."""
+    """The block's largest value on either side of where the scale steps, over fp32's exponents from the smallest up to 2^121."""
     shape = (1, 64, 9, 28, 36, 1, 1, 1, 1, 0, 0)
     g = torch.Generator().manual_seed(5)
     I = (torch.rand(shape[:4], generator=g) * 2 - 1).numpy().astype(np.float32)
@@ -99,6 +99,21 @@ def test_scales_around_the_largest_digit(xb, top):
     got, alpha, ref, S, s = run(xb, shape, torch.from_numpy(I), 5)
     err = (got - alpha * ref).abs()
     assert bool((err <= alpha * (1e-5 * S + s.C * 2.0 ** -125) + 2.0 ** -149).all())
+
+
+@pytest.mark.parametrize("top", [1.875, 1.9374999, 1.9375, 1.96875, float(np.finfo(np.float32).max) / 2.0 ** 127], ids=lambda v: f"{v:.7f}")
+@pytest.mark.parametrize("shape", [(1, 1, 9, 28, 36, 1, 1, 1, 1, 0, 0), (2, 70, 12, 12, 40, 1, 1, 1, 1, 0, 0), (1, 40, 9, 12, 100, 3, 3, 1, 1, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_values_at_the_top_of_the_range(xb, shape, top):
+    """One value of up to the largest float under a window, of either sign, others of its block small or zero: the sums are
+    inside fp32's range, so they are finite and inside the bar (filters of 0.05 keep the outputs in range too)."""
+    g = torch.Generator().manual_seed(7)
+    I = torch.randn(shape[:4], generator=g) * 2.0 ** torch.randint(-20, 100, (shape[0], 1, *shape[2:4]), generator=g)
+    I[:, :, ::2] = 0
+    for k, (y, x) in enumerate(((1, 1), (1, 5), (4, 1), (4, 9), (7, 4))):
+        I[:, :, y - 1:y + 2, x - 1:x + 2] *= 2.0 ** -60
+        I[:, (17 * k) % shape[1], y, x] = float(np.float32(top)) * 2.0 ** 127 * (-1) ** k
+    check(xb, shape, I, 7)
 
 
 def test_small_values_beside_large_ones(xb):
