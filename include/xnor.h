@@ -353,10 +353,11 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
 /*
  * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
  * both operands split exactly into three bf16 terms whose products are summed in fp32 by the bf16 and f16
- * matrix instructions (the smallest ones, together at most 2^-16 of the whole, from terms rounded to 11 bits).  Results are
+ * matrix instructions (the smallest ones, together at most 2^-16 of the whole, from terms rounded to 11 bits, or by
+ * the bf16 instruction alone beside values that f16 would not hold so).  Results are
  * closer to the exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32
- * arithmetic gives them, and an output so small that bits of a value could matter to it that is small beside the
- * largest of its image or filters is formed by the plain fp32 sum.
+ * arithmetic gives them, and an output so small that bits of a value below 2^-133 (or 2^-133 of what lies beside it)
+ * could matter to it is formed by the plain fp32 sum.
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes

@@ -5,9 +5,19 @@
 //   hi*hi + hi*mid + hi*lo + mid*hi + lo*hi + r*r,
 // the first five on the bf16 instruction and the last one, at most 2^-16 of the whole, on the f16 one with r
 // rounded to f16's 11 bits (2^-29 of the whole lost on average, of either sign; 2^-26 at most): six matrix instructions per 16
-// channels where bf16 alone takes eight (mid*mid, mid*lo and lo*mid in place of r*r; 3.2 against 2.6 ms below).
-//   f16's range is kept by powers of two: an image is multiplied by the one that brings its largest magnitude to
-// 2^23 .. 2^24, a filter tile's chunk of 16 channels by its own, and a chain's sum is divided by both where it joins the output's.
+// channels where bf16 alone takes eight (mid*mid, mid*lo and lo*mid in place of r*r).
+//   f16's range is kept by powers of two: a filter tile's chunk of 16 channels is multiplied by the one that brings its largest
+// magnitude to 2^23 .. 2^24, a workgroup's input by the one that brings the largest of its first chunk to 2^18 .. 2^19, and a
+// chain's sum is divided by both where it joins the output's.  Scaled values of 2^-6 to 2^24 and zeros are held.  A wave that
+// meets others (a filter decayed to 2^-30 of its neighbours, an input value 2^-25 or 2^5 of the first chunk's largest) takes the eight
+// products from that chunk on, which need no range: such a layer is as fast as with eight products everywhere, where forming the
+// outputs that could matter by the plain sum took three times as long (us, eight products in chains of one tap / this with six
+// products only and such outputs by the plain sum, the images' magnitudes read beforehand / this):
+//                                          ordinary values       one filter of 1e-11     the lower half zero, one value of 1e-12
+//   128 x 512 x 28 x 28 F=512 3x3     3285 / 2690 / 2510      3360 / 8820 / 2620 to 2810      2800 / 6990 / 2200
+//   16 x 128 x 56 x 56 F=128 5x5       327 / 251 / 245         326 / 790 / 273                 291 / 949 / 227
+//   32 x 512 x 56 x 56 F=64 1x1        103 / 122 / 90
+//   32 x 256 x 56 x 56 F=16 2x2        131 / 161 / 118
 //
 // What the sum loses.  The products of two taps x 16 channels form a chain of their own that starts at zero,
 // small products first, and joins the output's sum in one addition: the large sum is rounded once per 32
@@ -15,14 +25,13 @@
 // no better).  The instructions shift what they add to the exponent of the largest and drop the rest towards
 // minus infinity, which left every output the same amount too low (0.27e-6 of their root mean square for 7 x 7 x 416
 // terms): the weights of every other chain are therefore stored negated and its sum is subtracted.  Measured
-// against 64-bit sums over layers of 32 to 512 channels, 1 x 1 to 7 x 7, normal, positive, constant and
-// log-normal values and channels of very different sizes: at the median 0.83 of the error of chains of one tap
-// with eight products (0.74 with many terms), which had 0.17 to 0.57 of that of the kernels without a workspace.
+// against 64-bit sums over layers of 32 to 384 channels, 1 x 1 to 5 x 5, normal, positive, constant, log-normal values and values,
+// channels and filters of very different sizes: 0.65 to 0.94 of the error of chains of one tap with eight products
+// (1 x 1, where a chain has one tap: the same), which had 0.17 to 0.57 of that of the kernels without a workspace.
 //
-//   split_operands_kernel: filters -> the A operands of the convolution in its order, into the
+//   split_filters_kernel: filters -> the A operands of the convolution in its order, into the
 //   caller's workspace, 8 bytes per weight: [filter tile of 32][chunk of 16 channels][tap][hi, mid, lo, r]
-//   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7); beside it the largest and
-//   smallest magnitudes of the images' parts (the read of the input that this takes is 1.5 % of the whole).
+//   [lane] of 16 bytes (lane = filter lane % 32, channels 8 * (lane / 32) .. + 7).
 //   conv_fp32_split_kernel: workgroup = 4 waves = 128 filters x up to 4 tiles of 32 output pixels of
 //   one image (64 filters x up to 8 tiles for layers of at most 64 filters); wave = 64 filters x up
 //   to two tiles (a third one's accumulators would leave no registers for the chains).  Per chunk of 16 channels
@@ -32,11 +41,10 @@
 //   lane and feeds three matrix instructions on average, an A operand is one 16-byte load per lane from the L2
 //   and feeds as many; each is fetched again into its registers behind its last use, 7 (LDS) and 15 (L2) matrix
 //   instructions ahead of its next one.
-//   128 x 512 x 28 x 28 F=512 3x3: 3.19 -> 2.64 ms against eight products in chains of one tap, 16 x 128 x 56 x 56 F=128
-//   5x5 308 -> 233 us.  Bound by power as much as by time: the chip runs at 1.77 GHz, the matrix pipe is busy for
-//   59 % of the cycles (a register-only loop of the bf16 instruction on random operands keeps 1.74 GHz).  Timing-only builds of
-//   the first layer: without the filter loads 2.21 ms, without the split and staging 2.32, without the additions of
-//   chains to sums 2.36, without all three 1.91.  One wave per SIMD with four tiles (half the filter loads): 2.94 ms.
+//   Nothing in a chunk's steps branches: the fetch past the last chunk reads from an empty buffer.  (A branch around it let the
+//   compiler move the additions of chains and the magnitudes' maxima behind it; it spilled 25 to 280 registers then.)
+//   Bound by power as much as by time: a register-only loop of the bf16 instruction on random operands keeps 1.74 GHz, this
+//   1.77.  One wave per SIMD with four tiles (half the filter loads) was slower.
 //
 // FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
 // chains, that is still the less exact of the two.  This form keeps two accumulators per output: the
@@ -45,10 +53,10 @@
 // registers for a fourth term: three, unscaled, and eight products (all but lo*lo, below 2^-32 of the whole).
 //
 // What the split cannot hold goes by the fp32 matrix instruction instead (plain_tiles), a wave's outputs at
-// a time: outputs that came out infinite or NaN, and outputs so small that bits of a value that is small beside
-// the largest of its image (filter tile) could matter to them, only where such values were seen (`doubtful`); with
-// FLUSH also all outputs of a workgroup that stages an infinity, a NaN or a value whose first term overflows (it
-// leaves the loop at the chunk that has one).  The instructions themselves keep subnormals.
+// a time: all outputs of a workgroup that stages an infinity, a NaN or a value too large for bf16 or the scale (it leaves
+// the loop at the chunk that has one), outputs that came out infinite or NaN, and outputs so small that bits of a value
+// below 2^-133, bf16's last one, could matter to them (only where a (scaled) input or weight below 2^-110 was seen, see
+// `doubtful`).  The instructions themselves keep subnormals.
 // A launch whose every output goes that way: see plain_tiles.
 #include <algorithm>
 #include <atomic>
@@ -92,9 +100,7 @@ struct Fp32SplitParams {
     const float *Wt;
     const unsigned char *Wx;       // split filters
     const uint32_t *wstat;         // one word per (filter tile, 8 channels): kTinyBit | largest magnitude
-    const int *wexp;               // per (filter tile, chunk): the power of two its weights are stored times
-    const uint32_t *xstat;         // per (image, part of it): largest and smallest non-zero magnitude
-    int xparts;
+    const int *wexp;               // per (filter tile, chunk): kUnheld | the power of two its weights are stored times + kExpBias
     float *out;
     int N, C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW;
     int nchunks, ftiles;
@@ -115,11 +121,12 @@ constexpr float kDoubt = 0x1p-104f;
 constexpr uint32_t kHuge = 0x7f7f8000u << 1;              // (doubled bits) from here on bf16 rounds to infinity
 constexpr uint32_t kInfBits = 0x7f800000u;
 
-// The power of two that brings a largest magnitude (its bits) to 2^23 .. 2^24 (see above), as far as two factors and
-// their product stay in fp32's range.
-constexpr int kTop = 23, kMostX = 90, kMostW = 59;
-__device__ inline int scale_of(uint32_t top, int most) { return top == 0 ? 0 : min(most, kTop + 127 - (int)(top >> 23)); }
-constexpr int kHeldExp = -6;                              // scaled values from 2^-6 on: see `doubtful`
+// The power of two that brings a largest magnitude (its bits) to 2^23 .. 2^24 for weights, to 2^18 .. 2^19 for inputs (see
+// above), as far as two factors and their product stay in fp32's range with values of ordinary size behind tiny ones.
+constexpr int kTopW = 23, kMostW = 59, kTopX = 18, kMostX = 40;
+constexpr int kExpBias = 256, kUnheld = 1024;
+__device__ inline int scale_of(uint32_t top, int to, int most) { return top == 0 ? 0 : min(most, to + 127 - (int)(top >> 23)); }
+constexpr float kHeldLow = 0x1p-6f, kHeldTop = 0x1p24f;   // scaled values whose mid + lo f16 holds to 11 bits
 // 2^e for e >= -149, infinite from 2^128 on
 __device__ inline uint32_t power_bits(int e)
 {
@@ -145,63 +152,26 @@ __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
     b -= __uint_as_float(t & 0xffff0000u);
 }
 
-// Filters: 32 of them x 8 channels x all taps per workgroup: a read in runs (a filter's channels are one run in
+// 32 filters x 8 channels x all taps per workgroup: a read in runs (a filter's channels are one run in
 // memory) into LDS, then per (tap, filter) eight values from LDS, split, and 16-byte writes of 32 lanes side by
-// side.  4 bytes read and 8 (6) written per weight.  The chunk's other eight channels are read for their largest
-// magnitude alone: the chunk has one power of two.
-//   Images (not with FLUSH): the workgroups past those find the magnitudes of a part of an image each.
-struct Fp32StatParams {
-    const float *I;
-    uint32_t *xstat;
-    int per_image, parts, per_part;     // values
-};
-
+// side.  4 bytes read and 8 (6) written per weight.  The chunk's other eight channels are read for their
+// magnitudes alone: the chunk has one power of two.
 template <bool FLUSH>
-__global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *__restrict__ Wt, int F, int C, int taps, int nchunks, int ftiles,
-                                                                  uint32_t inv_run, Fp32StatParams x, unsigned char *__restrict__ Wx)
+__global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__restrict__ Wt, int F, int C, int taps, int nchunks, int ftiles,
+                                                                 uint32_t inv_run, unsigned char *__restrict__ Wx)
 {
     extern __shared__ float wl[];
-    __shared__ uint32_t stat[3];
-    const int octs = 2 * nchunks, fblocks = ftiles * octs;
-    if (threadIdx.x < 3) stat[threadIdx.x] = threadIdx.x == 1 ? 0xffffffffu : 0u;
+    __shared__ uint32_t stat[4];
+    const int octs = 2 * nchunks;
+    if (threadIdx.x < 4) stat[threadIdx.x] = threadIdx.x & 1 ? 0xffffffffu : 0u;
     __syncthreads();
     uint32_t top = 0, low = 0xffffffffu;         // of the magnitudes' bits; low: less one (0 - 1 wraps to the top)
     constexpr int kBatch = 8;                    // loads of a thread in flight
-    if (!FLUSH && (int)blockIdx.x >= fblocks) {
-        const int b = (int)blockIdx.x - fblocks, n = b / x.parts, first = (b - n * x.parts) * x.per_part;
-        const float *src = x.I + (size_t)n * x.per_image;
-        const int end = min(first + x.per_part, x.per_image);
-        for (int i = first + (int)threadIdx.x; i < end; i += kBatch * kThreads) {
-            uint32_t u[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) u[k] = __float_as_uint(src[min(i + k * kThreads, end - 1)]) & ~kTinyBit;
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                top = max(top, u[k] < kInfBits ? u[k] : 0u);
-                low = min(low, u[k] - 1u);
-            }
-        }
-#pragma unroll
-        for (int m = 1; m < 64; m *= 2) {
-            top = max(top, (uint32_t)__shfl_xor((int)top, m));
-            low = min(low, (uint32_t)__shfl_xor((int)low, m));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            atomicMax(&stat[0], top);
-            atomicMin(&stat[1], low);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            x.xstat[2 * b] = stat[0];
-            x.xstat[2 * b + 1] = stat[1];
-        }
-        return;
-    }
     const int ft = blockIdx.x / octs, oc = blockIdx.x - ft * octs;
     const int run = 8 * taps, pitch = run | 1;                     // (odd: filters fall into distinct banks)
     // values of the run that exist, in this half of the chunk and in the other
     const int live = max(0, min(8, C - 8 * oc)) * taps, live2 = FLUSH ? 0 : max(0, min(8, C - 8 * (oc ^ 1))) * taps;
-    uint32_t finite = 0;
+    uint32_t finite = 0, low2 = 0xffffffffu;     // of both halves: the largest that is finite, the smallest
     for (int i0 = threadIdx.x; i0 < 32 * run; i0 += kBatch * kThreads) {
         float v[kBatch], o[kBatch];
         int at[kBatch];
@@ -228,6 +198,7 @@ __global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *_
             if constexpr (!FLUSH) {
                 const uint32_t u2 = __float_as_uint(o[k]) & ~kTinyBit;
                 finite = max(finite, max(u < kInfBits ? u : 0u, u2 < kInfBits ? u2 : 0u));
+                low2 = min(low2, min(u - 1u, u2 - 1u));
             }
         }
     }
@@ -235,15 +206,21 @@ __global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *_
     for (int m = 1; m < 64; m *= 2) {
         top = max(top, (uint32_t)__shfl_xor((int)top, m));
         low = min(low, (uint32_t)__shfl_xor((int)low, m));
-        if constexpr (!FLUSH) finite = max(finite, (uint32_t)__shfl_xor((int)finite, m));
+        if constexpr (!FLUSH) {
+            finite = max(finite, (uint32_t)__shfl_xor((int)finite, m));
+            low2 = min(low2, (uint32_t)__shfl_xor((int)low2, m));
+        }
     }
     if ((threadIdx.x & 63) == 0) {
         atomicMax(&stat[0], top);
         atomicMin(&stat[1], low);
-        if constexpr (!FLUSH) atomicMax(&stat[2], finite);
+        if constexpr (!FLUSH) {
+            atomicMax(&stat[2], finite);
+            atomicMin(&stat[3], low2);
+        }
     }
     __syncthreads();
-    const int e = FLUSH ? 0 : scale_of(stat[2], kMostW);
+    const int e = FLUSH ? 0 : scale_of(stat[2], kTopW, kMostW);
     unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * operand_bytes(FLUSH) + (oc & 1) * 512;
     for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
         const int f = i & 31, t = i >> 5;
@@ -268,9 +245,10 @@ __global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *_
     }
     if (threadIdx.x == 0) {
         uint32_t *stats = reinterpret_cast<uint32_t *>(Wx + (size_t)ftiles * nchunks * taps * operand_bytes(FLUSH));
-        const float tiny = FLUSH ? kTiny : ldexpf(1.f, kHeldExp - e);
-        stats[blockIdx.x] = stat[0] | (stat[1] < __float_as_uint(tiny) - 1u ? kTinyBit : 0u);
-        if (!FLUSH && (oc & 1) == 0) reinterpret_cast<int *>(stats + fblocks)[ft * nchunks + (oc >> 1)] = e;
+        stats[blockIdx.x] = stat[0] | (stat[1] < __float_as_uint(ldexpf(kTiny, -e)) - 1u ? kTinyBit : 0u);
+        if (!FLUSH && (oc & 1) == 0)
+            reinterpret_cast<int *>(stats + ftiles * octs)[ft * nchunks + (oc >> 1)] =
+                (e + kExpBias) | (stat[3] < __float_as_uint(ldexpf(kHeldLow, -e)) - 1u ? kUnheld : 0);
     }
 }
 
@@ -279,8 +257,8 @@ __global__ __launch_bounds__(kThreads) void split_operands_kernel(const float *_
 // nothing).  `put(i, j, r, v)` takes the value of accumulator register r of filter tile i and pixel tile j.
 //   The filters come from the workspace, hi + mid + lo, which is the weight again; a lane whose weights are not
 //   all held there (infinite, NaN, too large for bf16 or so small that bits are missing) reads its own from the
-//   layer's filters.  32 x 256 x 28 x 28 F=256 3x3 takes 0.25 ms, with one NaN in the input 0.41, all NaN 0.57, with
-//   filters of 1e-36 among the others 0.89 (0.45 for any without a workspace; 15 to 36 ms where lanes formed
+//   layer's filters.  32 x 256 x 28 x 28 F=256 3x3 takes 0.19 ms, with one NaN in the input 0.42, all NaN 0.58, with a third
+//   of the filters at 1e-36 0.60, below 1e-44 0.87 (0.45 for any without a workspace; 15 to 36 ms where lanes formed
 //   such outputs one by one).  The operands of a (tap, chunk) step are loaded a step ahead: a lane of half h holds channels
 //   8 h .. 8 h + 7 of the chunk, and a matrix instruction takes one of either half.
 template <int NT, bool FLUSH, class Pixel, class Put>
@@ -341,7 +319,7 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             bool held = true;
-            const float back = FLUSH ? sgn : sgn * ldexpf(1.f, -p.wexp[ft[i] * p.nchunks + ch]);
+            const float back = FLUSH ? sgn : sgn * ldexpf(1.f, kExpBias - (p.wexp[ft[i] * p.nchunks + ch] & ~kUnheld));
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const auto term = [&](int q) {
@@ -399,14 +377,29 @@ __device__ __attribute__((always_inline)) void plain_tiles(const Fp32SplitParams
             for (int r = 0; r < 16; ++r) put(i, j, r, total[i][j][r]);
 }
 
-// f(0) .. f(23), each number a constant
+// f(0) .. f(31), each number a constant
 template <class F, int... M>
 __device__ __attribute__((always_inline)) inline void for_each_of(F f, std::integer_sequence<int, M...>)
 {
     (f(std::integral_constant<int, M>{}), ...);
 }
 template <class F>
-__device__ __attribute__((always_inline)) inline void for_units(F f) { for_each_of(f, std::make_integer_sequence<int, 24>{}); }
+__device__ __attribute__((always_inline)) inline void for_units(F f) { for_each_of(f, std::make_integer_sequence<int, 32>{}); }
+
+// The products of a (tap, 16 channels) step in their order, small ones first: the terms of filters and input (0 .. 3: hi, mid, lo,
+// r = mid + lo), and which term's registers are free behind each.
+template <int PRODUCTS>
+struct Order;
+template <>
+struct Order<6> {      // r*r, hi*lo, hi*mid, lo*hi, mid*hi, hi*hi
+    int a[6] = {3, 0, 0, 2, 1, 0}, b[6] = {3, 2, 1, 0, 0, 0};
+    int load_a[6] = {3, -1, -1, 2, 1, 0}, read_b[6] = {3, 2, 1, -1, -1, 0};
+};
+template <>
+struct Order<8> {      // mid*lo, lo*mid, lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
+    int a[8] = {1, 2, 2, 0, 1, 1, 0, 0}, b[8] = {2, 1, 0, 2, 1, 0, 1, 0};
+    int load_a[8] = {3, -1, 2, -1, -1, 1, -1, 0}, read_b[8] = {3, -1, -1, 2, -1, -1, 1, 0};
+};
 
 // The work of one wave with NT pixel tiles (0: it only takes part in the staging).  X0, Y0: the output
 // pixel of the workgroup's first tile (tw > 0); ix0, iy0: the input position of the staged block's corner.
@@ -483,26 +476,11 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
 #pragma unroll
         for (int r = 4 * quarter; r < 4 * quarter + 4; ++r) acc[i][j][r] = fmaf(__uint_as_float(factor), tapsum[i][r], acc[i][j][r]);
     };
-    // The image's power of two
-    uint32_t xtop = 0, xlow = 0xffffffffu;       // largest and smallest non-zero magnitude (FLUSH: of what was staged, doubled bits; low: less one)
-    int xexp = 0;
-    if constexpr (!FLUSH) {
-        if (lane < p.xparts) {
-            const uint2 v = reinterpret_cast<const uint2 *>(p.xstat)[n * p.xparts + lane];
-            xtop = v.x;
-            xlow = v.y;
-        }
-#pragma unroll
-        for (int m = 1; m < 64; m *= 2) {
-            xtop = max(xtop, (uint32_t)__shfl_xor((int)xtop, m));
-            xlow = min(xlow, (uint32_t)__shfl_xor((int)xlow, m));
-        }
-        xtop = __builtin_amdgcn_readfirstlane((int)xtop);
-        xlow = __builtin_amdgcn_readfirstlane((int)xlow);
-        xexp = scale_of(xtop, kMostX);
-    }
-    const float xscale = __uint_as_float(power_bits(xexp));
-
+    // Largest and smallest non-zero magnitude of what is staged, less one (FLUSH: of all, doubled bits; else: of a chunk, scaled)
+    uint32_t xtop = 0, xlow = 0xffffffffu;
+    float xmax = 0.f;
+    int xexp = 0;                                // else: the power of two that the workgroup's input is staged times
+    float xscale = 1.f;
 
     const float *img = p.I + (size_t)n * p.C * HW;
 
@@ -510,7 +488,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     // q * 128 + t % 128 (q < kGran) of channel octet t / 128, the same for a whole wave, so the address
     // of a value is a scalar base (the channel's plane) plus a lane offset kept in registers.  A
     // position past the last one repeats the last one (the same bytes to the same place), one outside
-    // the image loads offset 0 and becomes zero at the commit: no branch, and nothing waits for a
+    // the image loads from past the buffer's end, which gives zero: no branch, and nothing waits for a
     // load before the next is issued.
     const int tl = threadIdx.x & 127;
     const int oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);
@@ -545,7 +523,10 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     constexpr int kPieces = 2 * kGran + 1;
     float pv[4];
     uint32_t ph[2], pm[2], pl[2], pr[2];
-    uint32_t *const huge_seen = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);   // (FLUSH) by the chunks, in turn
+    // Words behind the input buffers.  By the chunks, in turn: FLUSH: has a value been too large?  Else: number + 1 of the last
+    // chunk with a value whose mid + lo f16 does not hold (kTinyBit: with one that is not finite); then the largest and the
+    // smallest of such values and the waves' largest of the first chunk.
+    uint32_t *const words = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);
     auto commit_unit = [&](auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
         constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
         if constexpr (S < 2 * kGran) {
@@ -561,6 +542,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 } else {
                     pv[k] *= xscale;
                     pv[k + 1] *= xscale;
+                    xmax = __builtin_elementwise_maximum(__builtin_elementwise_maximum(xmax, fabsf(pv[k])), fabsf(pv[k + 1]));   // (keeps NaN)
+                    xlow = min(xlow, min((__float_as_uint(pv[k]) << 1) - 1u, (__float_as_uint(pv[k + 1]) << 1) - 1u));
                 }
             } else if constexpr (U == 1 || U == 4) {
                 constexpr int e = U == 4;
@@ -580,7 +563,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 if constexpr (!FLUSH) dst[12] = make_uint2(pr[0], pr[1]);
             }
         } else if constexpr (U == 0) {
-            if (ch + 1 < p.nchunks) prefetch(ch + 1);
+            prefetch(ch + 1);      // (past the last chunk: no channel, every load is 0 without a read)
         }
     };
     auto commit_piece = [&](auto piece_c, int ch) __attribute__((always_inline)) {
@@ -652,15 +635,49 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 for (int k = 0; k < 4; ++k) load_a(k >> 1, k & 1, t);
         }
     }
-    if (FLUSH && threadIdx.x < 2) huge_seen[threadIdx.x] = 0;
-    __syncthreads();
+    // else: does what was committed for chunk `ch` have a value that f16 does not hold?
+    auto check_held = [&](int ch) __attribute__((always_inline)) {
+        if (!(xmax < kHeldTop) || xlow < (__float_as_uint(kHeldLow) << 1) - 1u) {
+            atomicMax(&words[ch & 1], ((uint32_t)ch + 1u) | (xmax < INFINITY ? 0u : kTinyBit));
+            atomicMax(&words[2], __float_as_uint(xmax));
+            atomicMin(&words[3], xlow);
+        }
+        xmax = 0.f;
+        xlow = 0xffffffffu;
+    };
+    if constexpr (FLUSH) {
+        if (threadIdx.x < 2) words[threadIdx.x] = 0;
+        __syncthreads();
+    } else {
+        uint32_t top = 0;
+#pragma unroll
+        for (int q = 0; q < kGran; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t u = __float_as_uint(nxt[q][k]) & ~kTinyBit;
+                top = max(top, u < kInfBits ? u : 0u);
+            }
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) top = max(top, (uint32_t)__shfl_xor((int)top, m));
+        if (threadIdx.x < 4) words[threadIdx.x] = threadIdx.x == 3 ? 0xffffffffu : 0u;
+        if (lane == 0) words[4 + (threadIdx.x >> 6)] = top;
+        __syncthreads();
+        top = __builtin_amdgcn_readfirstlane((int)max(max(words[4], words[5]), max(words[6], words[7])));
+        xexp = top == 0 ? kTopX : scale_of(top, kTopX, kMostX);
+        xscale = __uint_as_float(power_bits(xexp));
+    }
     commit_rest(0, 0);
-    if (FLUSH && xtop >= kHuge) huge_seen[0] = 1;
+    if constexpr (FLUSH) {
+        if (xtop >= kHuge) words[0] = 1;
+    } else {
+        check_held(0);
+    }
     __syncthreads();
     bool by_plain_sum = false;                 // (uniform over the workgroup)
-    for (int ch = 0; ch < p.nchunks; ++ch) {
+    int ch = 0;
+    auto one_chunk = [&](auto products_c) __attribute__((always_inline)) {
         // (written before the barrier behind which it is read, and again only behind the next one)
-        const uint32_t huge = FLUSH ? huge_seen[ch & 1] : 0;
+        const uint32_t flag = FLUSH ? words[ch & 1] : words[ch & 1] & kTinyBit;
         const bool more = ch + 1 < p.nchunks;
         int pc = more ? 0 : kPieces;                     // the next piece of chunk ch + 1 to commit
         if constexpr (NT > 0 && FLUSH) {
@@ -743,11 +760,12 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             }
             for (; tap < taps; ++tap) tap_body(std::integral_constant<int, -1>{}, tap);
         } else if constexpr (NT > 0) {
-            // The sequence of (chain, pixel tile) steps, twelve matrix instructions a tap; a step's B operands
+            // The sequence of (chain, pixel tile) steps, twelve or sixteen matrix instructions a tap; a step's B operands
             // are read during the step before, each behind the last use of its register, and the chunk's first
             // steps carry the pieces of the next chunk's commit.
-#pragma unroll
-            for (int i = 0; i < 2; ++i) factor[i] = power_bits(-(xexp + p.wexp[(i ? ft1 : ft0) * p.nchunks + ch]));
+            const int we0 = p.wexp[ft0 * p.nchunks + ch], we1 = p.wexp[ft1 * p.nchunks + ch];
+            factor[0] = power_bits(kExpBias - xexp - (we0 & ~kUnheld));
+            factor[1] = power_bits(kExpBias - xexp - (we1 & ~kUnheld));
             const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
             auto read_b = [&](uint4 &to, int term, int byte_off) __attribute__((always_inline)) {
                 to = *reinterpret_cast<const uint4 *>(tile_r + byte_off + 32 * term);
@@ -775,32 +793,32 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 auto unit = [&](auto m_c) __attribute__((always_inline)) {
                     // filter tile, product and tap of the M-th instruction: one tile's chain after the other's, so that
                     // a chain's sum is settled under the instructions of the next one, four values to each
-                    constexpr int M = decltype(m_c)::value, LEN = 6 * TAPS;
+                    constexpr int M = decltype(m_c)::value, PRODUCTS = decltype(products_c)::value, LEN = PRODUCTS * TAPS;
                     if constexpr (M < 2 * LEN) {
                         constexpr int i = M / LEN, at = M % LEN, P = at / TAPS, tap = at % TAPS;
-                        // r*r, hi*lo, hi*mid, lo*hi, mid*hi, hi*hi with r = mid + lo
-                        constexpr int ta = P == 0 ? 3 : P == 3 ? 2 : P == 4 ? 1 : 0;
-                        constexpr int tb = P == 0 ? 3 : P == 1 ? 2 : P == 2 ? 1 : 0;
-                        if constexpr (P == 0) {
-                            const floatx16 none = {};
+                        constexpr Order<PRODUCTS> O{};
+                        constexpr int ta = O.a[P], tb = O.b[P];
+                        const floatx16 none = {};
+                        if constexpr (ta == 3) {
                             tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[tap][i][ta]), __builtin_bit_cast(halfx8, b[tap][tb]),
                                                                                at == 0 ? none : tapsum[i], 0, 0, 0);
                         } else {
                             tapsum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[tap][i][ta]), __builtin_bit_cast(bf16x8, b[tap][tb]),
-                                                                                tapsum[i], 0, 0, 0);
+                                                                                at == 0 ? none : tapsum[i], 0, 0, 0);
                         }
                         if constexpr (at > 0 && at < 5) {
                             if constexpr (i == 0) settle(1, j > 0 ? j - 1 : NT - 1, pending, at - 1);   // (of the step before)
                             else settle(0, j, factor[0] ^ sign, at - 1);
                         }
                         if constexpr (M == 2 * LEN - 1) pending = factor[1] ^ sign;
-                        if constexpr (j == NT - 1 && (P == 0 || P > 2)) {                               // this term's last use
-                            load_a(tap, i, ta);
-                            if constexpr (TAPS == 1) load_a(1, i, ta);
+                        if constexpr (j == NT - 1 && O.load_a[P] >= 0) {
+                            load_a(tap, i, O.load_a[P]);
+                            if constexpr (TAPS == 1) load_a(1, i, O.load_a[P]);
                         }
-                        if constexpr (i == 1 && (P < 3 || P == 5)) {
-                            read_b(b[tap][tb], tb, tap ? to1 : to0);
-                            if constexpr (TAPS == 1) read_b(b[1][tb], tb, to1);
+                        if constexpr (i == 1 && O.read_b[P] >= 0) {
+                            constexpr int term = O.read_b[P];
+                            read_b(b[tap][term], term, tap ? to1 : to0);
+                            if constexpr (TAPS == 1) read_b(b[1][term], term, to1);
                         }
                         // (behind the instructions without such values)
                         constexpr int piece = TAPS == 2 ? i : 0, unit = TAPS == 2 ? at - 5 : M - 5;
@@ -850,10 +868,25 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             if (left > 0) chain_body(one, none_left, per);
         }
         if (pc < kPieces) commit_rest(pc, ch + 1);       // what the chunk's steps did not carry
-        if (FLUSH && more && xtop >= kHuge) huge_seen[(ch + 1) & 1] = 1;
+        if constexpr (FLUSH) {
+            if (more && xtop >= kHuge) words[(ch + 1) & 1] = 1;
+        } else {
+            if (more) check_held(ch + 1);
+        }
         __syncthreads();                                 // chunk ch has been read, chunk ch + 1 is written
-        by_plain_sum = __builtin_amdgcn_readfirstlane((int)huge) != 0;
-        if (by_plain_sum) break;
+        by_plain_sum = __builtin_amdgcn_readfirstlane((int)flag) != 0;
+        ++ch;
+    };
+    if constexpr (FLUSH || NT == 0) {
+        while (ch < p.nchunks && !by_plain_sum) one_chunk(std::integral_constant<int, 8>{});
+    } else {
+        // six products up to the first chunk with a value that f16 does not hold, eight from there on
+        auto held = [&]() __attribute__((always_inline)) -> bool {
+            const int w = p.wexp[ft0 * p.nchunks + ch] | p.wexp[ft1 * p.nchunks + ch];
+            return (w & kUnheld) == 0 && (__builtin_amdgcn_readfirstlane((int)words[ch & 1]) & 0x7fffffff) != ch + 1;
+        };
+        while (ch < p.nchunks && !by_plain_sum && held()) one_chunk(std::integral_constant<int, 6>{});
+        while (ch < p.nchunks && !by_plain_sum) one_chunk(std::integral_constant<int, 8>{});
     }
 
     if constexpr (NT > 0 && !FLUSH) {
@@ -862,10 +895,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     }
 
     // Below which magnitude an output is doubtful.
-    //   FLUSH: a value of 2^-110 and above is held in full; of a smaller one up to 2^-134 is lost.  The losses add up
+    // A (scaled) value of 2^-110 and above is held in full; of a smaller one up to 2^-134 is lost.  The losses add up
     // to at most 2^-134 * Nred * (max |x| + max |w|), and an output of 2^30 times that is not touched by them.
-    //   Else: scaled values of 2^-6 and above are held in full and mid + lo to 2^-11 of itself; of a smaller one up to
-    // 2^-25 of mid + lo is lost, times at most 2^-8 of the other operand, and an output of 2^24 times that is not touched.
     if constexpr (FLUSH) {
         uint32_t *const wgstat = reinterpret_cast<uint32_t *>(lds_raw);    // (nothing staged is used past the last barrier)
 #pragma unroll
@@ -887,17 +918,22 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         wtiny |= s0 | s1;
     }
     const bool wlost = __any((wtiny & kTinyBit) != 0);
-    const bool xlost = FLUSH ? xlow < (__float_as_uint(kTiny) << 1) - 1u : xlow < power_bits(kHeldExp - xexp) - 1u;
+    if constexpr (!FLUSH) {
+        xmax = fmaxf(kHeldTop, __uint_as_float(words[2]));         // (read behind the last barrier)
+        xlow = words[3];
+    }
+    const bool xlost = xlow < (__float_as_uint(kTiny) << 1) - 1u;
     float doubtful = 0.f;
     if (xlost || wlost) {
 #pragma unroll
         for (int s = 1; s < 64; s *= 2) wtop = max(wtop, (uint32_t)__shfl_xor((int)wtop, s));
+        const float w = __uint_as_float(wtop), nred = (float)(p.C * taps);
         if constexpr (FLUSH) {
-            doubtful = kDoubt * (float)(p.C * taps) * (__uint_as_float(xtop >> 1) + __uint_as_float(wtop));
+            doubtful = kDoubt * nred * (__uint_as_float(xtop >> 1) + w);
         } else {
-            const float x = __uint_as_float(xtop), w = __uint_as_float(wtop);
-            const float by_x = xlost ? w * fmaxf(x * 0x1p-23f, ldexpf(1.f, -kMostX)) : 0.f, by_w = wlost ? x * fmaxf(w * 0x1p-23f, ldexpf(1.f, -kMostW)) : 0.f;
-            doubtful = 0x1p-9f * (float)(p.C * taps) * (by_x + by_w);
+            // (unscaled: what weights lose counts by the largest power that a chunk of the filter tiles is divided by)
+            const float by_x = xlost ? w : 0.f, by_w = wlost ? xmax * fmaxf(w * 0x1p-23f, ldexpf(1.f, -kMostW)) : 0.f;
+            doubtful = ldexpf(kDoubt * nred * (by_x + by_w), -xexp);
         }
     }
 
@@ -981,6 +1017,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitP
     }
 }
 
+constexpr int word_bytes(bool flush) { return (flush ? 2 : 8) * (int)sizeof(uint32_t); }
+
 struct Plan {
     bool ok, flush;
     int granules;
@@ -1002,7 +1040,7 @@ Plan search_plan(const Geom &g, int granules)
     const int taps = g.kh * g.kw;
     const long long OHW = (long long)g.OH * g.OW;
     if (taps > kMaxTaps || OHW > (1 << 24) || (long long)g.C * g.H * g.W >= (1LL << 29)) return pl;
-    if ((long long)g.F * g.C * taps >= (1LL << 28)) return pl;      // (32-bit sizes; 1.5 GiB of split filters)
+    if ((long long)g.F * g.C * taps >= (1LL << 28)) return pl;      // (32-bit sizes; 2 GiB of split filters where C and F are whole tiles)
     // (the fp32 matrix kernel's chains are as long as this one's; what it does not take runs one thread
     //  per output otherwise)
     pl.flush = !conv_fp32_mfma_supports(g);
@@ -1017,7 +1055,7 @@ Plan search_plan(const Geom &g, int granules)
                         int ty, int gx) {
         const long long npos = rows * cols;
         if (npos > maxpos || groups > (1 << 24)) return;
-        const size_t lds = 2 * (size_t)npos * pos_bytes(pl.flush) + 2 * sizeof(uint32_t);
+        const size_t lds = 2 * (size_t)npos * pos_bytes(pl.flush) + word_bytes(pl.flush);
         const long long wgs = (long long)g.N * fgroups * groups;
         const double whole = ceil_div(tiles, wps) + 0.5, part = ceil_div(last, wps) + 0.5;
         const double mean = whole + (part - whole) / (double)period;
@@ -1069,7 +1107,7 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
         if (!(raised.load() & bit)) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     2 * max_pos(GRAN) * pos_bytes(FLUSH) + 2 * (int)sizeof(uint32_t));
+                                                     2 * max_pos(GRAN) * pos_bytes(FLUSH) + word_bytes(FLUSH));
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }
@@ -1081,23 +1119,17 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
 }  // namespace
 
 namespace {
-// The workspace: split filters, their words, their powers of two, the words of the images' parts.
+// The workspace: split filters, their words, their powers of two.
 struct Layout {
-    size_t wstat, wexp, xstat, bytes;
-    int xparts, xper;
+    size_t wstat, wexp, bytes;
 };
 Layout layout_of(const Geom &g, bool flush)
 {
     const size_t nchunks = ceil_div(g.C, kChan), ftiles = ceil_div(g.F, 32);
-    const long long per_image = (long long)g.C * g.H * g.W;
     Layout l{};
-    // (a part is 32 values a thread or more; a wave reads an image's parts, one per lane)
-    l.xparts = flush ? 0 : (int)std::max<long long>(1, std::min<long long>(64, per_image / (32 * kThreads)));
-    l.xper = flush ? 0 : ceil_div(per_image, l.xparts);
     l.wstat = ftiles * nchunks * g.kh * g.kw * operand_bytes(flush);
     l.wexp = l.wstat + ftiles * nchunks * 2 * sizeof(uint32_t);
-    l.xstat = (l.wexp + (flush ? 0 : ftiles * nchunks * sizeof(int)) + 7) & ~(size_t)7;
-    l.bytes = l.xstat + (size_t)g.N * l.xparts * 2 * sizeof(uint32_t);
+    l.bytes = l.wexp + (flush ? 0 : ftiles * nchunks * sizeof(int));
     return l;
 }
 }  // namespace
@@ -1119,8 +1151,6 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     p.I = I; p.Wt = Wt; p.Wx = ws; p.out = out;
     p.wstat = reinterpret_cast<const uint32_t *>(ws + l.wstat);
     p.wexp = reinterpret_cast<const int *>(ws + l.wexp);
-    p.xstat = reinterpret_cast<const uint32_t *>(ws + l.xstat);
-    p.xparts = l.xparts;
     p.N = g.N; p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
     p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW;
     p.nchunks = ceil_div(g.C, kChan); p.ftiles = ceil_div(g.F, 32);
@@ -1129,12 +1159,11 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     p.pitch = pl.pitch; p.npos = pl.npos;
     p.inv_pitch = reciprocal((unsigned long long)pl.pitch);
     const long long blocks = (long long)g.N * p.groups * p.fgroups;
-    const long long first = (long long)p.ftiles * 2 * p.nchunks + (long long)g.N * l.xparts;
-    if (blocks > 0x7fffffffLL || first > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t filter_lds = (size_t)32 * ((8 * taps) | 1) * sizeof(float);
-    const Fp32StatParams x{I, reinterpret_cast<uint32_t *>(ws + l.xstat), (int)((long long)g.C * g.H * g.W), l.xparts, l.xper};
-    const auto split = pl.flush ? split_operands_kernel<true> : split_operands_kernel<false>;
-    split<<<dim3((unsigned)first), dim3(kThreads), filter_lds, st>>>(Wt, g.F, g.C, taps, p.nchunks, p.ftiles, reciprocal(8ull * taps), x, ws);
+    const auto split = pl.flush ? split_filters_kernel<true> : split_filters_kernel<false>;
+    split<<<dim3((unsigned)(p.ftiles * 2 * p.nchunks)), dim3(kThreads), filter_lds, st>>>(Wt, g.F, g.C, taps, p.nchunks, p.ftiles,
+                                                                                          reciprocal(8ull * taps), ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.flush) return launch_form<true, kGranules>(p, (unsigned)blocks, pl.lds, st);

@@ -305,6 +305,14 @@ def test_fp32_split_is_taken_where_it_is_the_faster_kernel(xb):
         assert used == ((N, C, H, W, F, k) in faster), (N, C, H, W, F, k)
 
 
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_fp32_split_workspace_holds_filters_only(xb, k):
+    """No pass over the images before the convolution: what it would leave behind grows with their number.  Terms of 32 filters x 16
+    channels, two words for them and one power of two."""
+    sizes = {xb.xnor_conv2d_fp32_workspace_bytes(xb.Shape(N, 130, 28, 28, 70, k, k, 1, 1, k // 2, k // 2)) for N in (1, 3, 200)}
+    assert sizes == {3 * 9 * (k * k * 4096 + 12)}
+
+
 def test_plans_of_a_network_of_many_shapes_are_kept(xb):
     """Forty layer shapes in turn, as a network has them: a query costs what it costs for one shape asked again
     and again (0.4 us), not a search of all plans each time (2.1 us)."""

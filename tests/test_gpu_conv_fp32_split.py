@@ -129,8 +129,8 @@ def rel64(got, I, Wt, stride, pad):
                                    (2, 8, 30, 33, 24, 7), (2, 130, 12, 13, 40, 7), (1, 400, 14, 14, 32, 7)], ids=lambda s: "x".join(map(str, s)))
 def test_split_is_no_less_exact_than_what_it_replaces(xb, shape, positive):
     """Against 64-bit sums, beside the kernel that runs without a workspace, on the same data.  The split form
-    rounds an output's sum once per 16 terms, the fp32 matrix instruction once per two: sqrt(2 / 16) = 0.35 of
-    its error where roundings are independent, 0.2 to 0.57 measured; the form with short chains 0.3 to 0.5 of
+    rounds an output's sum once per 32 terms (16 with one tap), the fp32 matrix instruction once per two: sqrt(2 / 32) = 0.25
+    (0.35) of its error where roundings are independent, 0.16 to 0.57 measured; the form with short chains 0.3 to 0.5 of
     one thread per output.  Six products in the output's own chain are at 0.9 to 1.4, short chains without
     the rounding carried over at 7, a drift in the instruction's rounding left in at 1.0 to 1.6."""
     N, C, H, W, F, k = shape
@@ -297,6 +297,63 @@ def test_split_images_channels_and_filters_of_very_different_sizes(xb, shape):
     chains = (k * k + 1) // 2 * -(-C // 16)
     bar = max(chains + 8, C * k * k / 2 + 8) * 2.0 ** -23 * S
     assert (np.abs(got - ref) <= bar + 2.0 ** -149).all()
+    assert np.sqrt(((got - ref) ** 2).sum()) <= 3e-7 * np.sqrt((S ** 2).sum())
+
+
+def sums64(I, Wt, pad):
+    d = [torch.from_numpy(a).double() for a in (I, Wt)]
+    return [torch.nn.functional.conv2d(*x, padding=pad).numpy() for x in (d, [v.abs() for v in d])]
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 5])
+def test_split_filter_far_below_the_others(xb, k):
+    """A filter 2^-40 of its neighbours is summed from the same products as at their size: its outputs are the same bits
+    but for the exponent (its tile holds another such filter in both runs, so that both take the same products)."""
+    print(f"case conv_fp32 split far below k={k}", flush=True)
+    rng = np.random.default_rng(21)
+    I, Wt = rng.standard_normal((2, 40, 11, 12)).astype(np.float32), rng.standard_normal((70, 40, k, k)).astype(np.float32)
+    Wt[[1, 40, 66]] *= np.float32(2.0 ** -45)
+    s = xb.Shape(2, 40, 11, 12, 70, k, k, 1, 1, k // 2, k // 2)
+    a = split(xb, dev(I), dev(Wt), s)
+    Wt[[5, 69]] *= np.float32(2.0 ** -40)
+    b = split(xb, dev(I), dev(Wt), s)
+    assert np.array_equal(b[:, [5, 69]] * 2.0 ** 40, a[:, [5, 69]])
+    ref, S = sums64(I, Wt, k // 2)
+    chains = (k * k + 1) // 2 * 3
+    assert (np.abs(b - ref) <= (chains + 8) * 2.0 ** -23 * S).all()
+
+
+@pytest.mark.parametrize("what", ["first_zero", "first_tiny", "first_large", "tiny_later", "large_later", "largest_later", "half_zero"])
+@pytest.mark.parametrize("shape", [(2, 40, 9, 11, 33, 1), (2, 70, 13, 12, 130, 2), (1, 100, 14, 15, 70, 3), (2, 33, 8, 9, 64, 5)], ids=lambda s: "x".join(map(str, s)))
+def test_split_inputs_far_from_the_first_chunk(xb, shape, what):
+    """The workgroup's power of two comes from its first 16 channels: nothing, values far below and far above the others
+    there, and values outside what f16 holds from some later channel on.  Bar: a sum is rounded once per chain of two taps and
+    16 channels, a chain's about six times, each by at most 2^-23 of S = sum |I * Wt|; the plain sum once per two terms."""
+    N, C, H, W, F, k = shape
+    print(f"case conv_fp32 split first chunk shape={shape} {what}", flush=True)
+    rng = np.random.default_rng(zlib.crc32((what + str(shape)).encode()))
+    I, Wt = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((F, C, k, k)).astype(np.float32)
+    if what == "first_zero":
+        I[:, :16] = 0
+    if what == "first_tiny":
+        I[:, :16] *= np.float32(1e-37)
+    if what == "first_large":
+        I[:, :16] *= np.float32(1e33)
+        I[0, :16, : H // 2] = 0
+    if what == "tiny_later":
+        I[:, C - 2, 2, 3] = 1e-20
+    if what == "large_later":
+        I[:, C - 2, 2, 3] = 1e9
+    if what == "largest_later":
+        I[:, :16] *= np.float32(1e-30)
+        I[:, C - 2, 2, 3] = 1e36
+    if what == "half_zero":
+        I[:, :, H // 2:] = 0
+        I[:, 0, 0, 0] = 1e-12
+    got = split(xb, dev(I), dev(Wt), xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2))
+    ref, S = sums64(I, Wt, k // 2)
+    chains = (k * k + 1) // 2 * -(-C // 16)
+    assert (np.abs(got - ref) <= max(chains + 8, C * k * k / 2 + 8 if what in ("first_large", "largest_later") else 0) * 2.0 ** -23 * S + 2.0 ** -149).all()
     assert np.sqrt(((got - ref) ** 2).sum()) <= 3e-7 * np.sqrt((S ** 2).sum())
 
 
