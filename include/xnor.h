@@ -74,10 +74,12 @@ typedef enum {
     XNOR_ALGO_MFMA_PERSISTENT = 6, /* ... with persistent workgroups, two wave groups each, and      */
     XNOR_ALGO_MFMA_TILE = 7,  /* ... with many small workgroups: by name, whatever XNOR_ALGO_MFMA takes
                                (the _algo calls only; tests and measurements)                     */
-    XNOR_ALGO_MFMA_SPLIT = 5 /* xnor_bwn_conv2d_fwd_algo: the fp32 input split into five FP6 digits with a
-                               scale per position and 32 channels, v_mfma_scale_f32_32x32x64_f8f6f4
-                               against +-1 weights, or, where that form does not take the shape, into three bf16
-                               terms; xnor_conv2d_fp32_fwd_ws: both operands split into bf16 terms  */
+    XNOR_ALGO_MFMA_SPLIT = 5, /* xnor_bwn_conv2d_fwd_algo: the fp32 input split into terms, one of the two below;
+                               xnor_conv2d_fp32_fwd_ws: both operands split into bf16 terms          */
+    XNOR_ALGO_MFMA_SPLIT_FP6 = 8, /* xnor_bwn_conv2d_fwd_algo: five FP6 digits with a scale per position and 32
+                               channels, v_mfma_scale_f32_32x32x64_f8f6f4 against +-1 weights, and       */
+    XNOR_ALGO_MFMA_SPLIT_BF16 = 9 /* ... three bf16 terms, v_mfma_f32_32x32x16_bf16: by name, whatever
+                               XNOR_ALGO_MFMA_SPLIT takes (tests and measurements)                    */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
@@ -299,13 +301,15 @@ int xnor_forward_image(const float *I, const uint32_t *Wpk, const float *alpha, 
  * output pixels do not fit in 128 KB of LDS, or kh*kw > 64) or XNOR_ALGO_MFMA_SPLIT (every input
  * value split into terms that the matrix instruction takes, +-1 weights, fp32 accumulation.  Terms:
  * five FP6 digits under a power of two that 32 channels of a position share, which hold every
- * value to within 2^-23.9 of the largest of the 32 and those of about its binade exactly; or, where the
- * rows under 32 output pixels are too wide for that kernel or an image has 2 GiB, three bf16 terms, which hold it
- * exactly.  An input that is not finite gives NaN, not an infinity; at the bottom of fp32's range
- * the error grows by at most alpha * 2^-125 per input value under the window;
+ * value to within 2^-23.9 of the largest of the 32 and those of about its binade exactly; or three bf16 terms,
+ * which hold it exactly: xnor_bwn_split_kernel says which.  An input that is not finite gives NaN, not an
+ * infinity; at the bottom of fp32's range the error grows by at most alpha * 2^-125 per input value under the window;
  * XNOR_E_UNSUPPORTED where the input rows under 32 output pixels are more than 512 staged
  * positions or do not fit, twice over and with two sets of filter words, in 160 KB of LDS, or
- * kh*kw > 64); other values XNOR_E_UNSUPPORTED.
+ * kh*kw > 64, whichever form would run); XNOR_ALGO_MFMA_SPLIT_FP6 and _BF16: the two forms by name
+ * (XNOR_E_UNSUPPORTED: FP6 where the rows under 32 output pixels, without padding, and the filter words of one
+ * 32-channel word do not fit in 160 KB of LDS, or kh*kw > 64, or an image has 2 GiB; BF16 as XNOR_ALGO_MFMA_SPLIT);
+ * other values XNOR_E_UNSUPPORTED.
  */
 int xnor_bwn_conv2d_fwd(const float *I, const uint32_t *Wpk, const float *alpha, const xnor_shape *s,
                         float *out, void *stream);
@@ -316,16 +320,20 @@ int xnor_bwn_conv2d_fwd_algo(const float *I, const uint32_t *Wpk, const float *a
  * xnor_algo), or a negative status.  Host only. */
 int xnor_bwn_pick_algo(const xnor_shape *s);
 
+/* The form that XNOR_ALGO_MFMA_SPLIT takes in xnor_bwn_conv2d_fwd_algo for this shape: XNOR_ALGO_MFMA_SPLIT_FP6 or
+ * _BF16, or XNOR_E_UNSUPPORTED where the call would return it.  Host only. */
+int xnor_bwn_split_kernel(const xnor_shape *s);
+
 /*
- * The launch that XNOR_ALGO_MFMA_SPLIT's bf16 form makes for this shape on a GPU of `compute_units` units (0: the
- * current device's, 256 where there is none), whichever of the two forms runs it.  Host only; for tests and for reading a timing.
+ * The launch that XNOR_ALGO_MFMA_SPLIT_BF16 makes for this shape on a GPU of `compute_units` units (0: the
+ * current device's, 256 where there is none).  Host only; for tests and for reading a timing.
  *   *tiles         32-pixel tiles of one image a workgroup takes (1..6; an image's last workgroup
  *                  the rest)
  *   *row_segments  0: a tile is 32 consecutive output pixels; k > 0: a tile is one of the k
  *                  32-pixel segments of one output row (the row's last one short)
  *   *lds_bytes     dynamic LDS per workgroup (<= 160 KB; <= 80 KB lets two share a unit)
  *   *workgroups    the grid: N x ceil(F/128) x ceil(tiles of an image / *tiles)
- * XNOR_E_UNSUPPORTED where XNOR_ALGO_MFMA_SPLIT would return it; XNOR_E_SHAPE for compute_units < 0.
+ * XNOR_E_UNSUPPORTED where XNOR_ALGO_MFMA_SPLIT_BF16 would return it; XNOR_E_SHAPE for compute_units < 0.
  */
 int xnor_bwn_split_plan(const xnor_shape *s, int compute_units, int *tiles, int *row_segments,
                         size_t *lds_bytes, long long *workgroups);

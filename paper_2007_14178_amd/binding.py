@@ -17,10 +17,11 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libxnor_hip.so")
 
 ALGO_AUTO, ALGO_DIRECT, ALGO_TILED, ALGO_MFMA, ALGO_MFMA_BANDS, ALGO_MFMA_SPLIT = 0, 1, 2, 3, 4, 5
-ALGO_MFMA_PERSISTENT, ALGO_MFMA_TILE = 6, 7
+ALGO_MFMA_PERSISTENT, ALGO_MFMA_TILE, ALGO_MFMA_SPLIT_FP6, ALGO_MFMA_SPLIT_BF16 = 6, 7, 8, 9
 ALGO_NAMES = {ALGO_AUTO: "auto", ALGO_DIRECT: "direct", ALGO_TILED: "tiled", ALGO_MFMA: "mfma",
               ALGO_MFMA_BANDS: "mfma_bands", ALGO_MFMA_SPLIT: "mfma_split",
-              ALGO_MFMA_PERSISTENT: "mfma_persistent", ALGO_MFMA_TILE: "mfma_tile"}
+              ALGO_MFMA_PERSISTENT: "mfma_persistent", ALGO_MFMA_TILE: "mfma_tile",
+              ALGO_MFMA_SPLIT_FP6: "mfma_split_fp6", ALGO_MFMA_SPLIT_BF16: "mfma_split_bf16"}
 E_NULL, E_SHAPE, E_ALIGN, E_HIP, E_UNSUPPORTED, E_WORKSPACE = -1, -2, -3, -4, -5, -6
 
 
@@ -122,6 +123,7 @@ def _load() -> ctypes.CDLL:
     L.xnor_conv2d_fp32_fwd_ws.argtypes = [vp, vp, sp, vp, vp, sz, ci, vp]
     L.xnor_conv2d_pick_algo.argtypes = [sp, sz]
     L.xnor_bwn_pick_algo.argtypes = [sp]
+    L.xnor_bwn_split_kernel.argtypes = [sp]
     L.xnor_bwn_split_plan.argtypes = [sp, ci, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(sz),
                                       ctypes.POINTER(ctypes.c_longlong)]
     L.xnor_conv2d_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
@@ -131,7 +133,7 @@ def _load() -> ctypes.CDLL:
                  "xnor_filter_expand", "xnor_conv2d_fwd_expanded", "xnor_box_filter_K",
                  "xnor_conv2d_chain_workspace_bytes", "xnor_conv2d_fwd_chain",
                  "xnor_forward_image_supported", "xnor_forward_image",
-                 "xnor_bwn_conv2d_fwd", "xnor_bwn_conv2d_fwd_algo",
+                 "xnor_bwn_conv2d_fwd", "xnor_bwn_conv2d_fwd_algo", "xnor_bwn_split_kernel",
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
                  "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
@@ -487,8 +489,16 @@ def xnor_bwn_pick_algo(s: Shape) -> int:
     return r
 
 
+def xnor_bwn_split_kernel(s: Shape) -> int:
+    """The form that ALGO_MFMA_SPLIT takes for this shape: ALGO_MFMA_SPLIT_FP6 or ALGO_MFMA_SPLIT_BF16."""
+    r = lib.xnor_bwn_split_kernel(ctypes.byref(s.c()))
+    if r < 0:
+        raise XnorError(r, "xnor_bwn_split_kernel")
+    return r
+
+
 def xnor_bwn_split_plan(s: Shape, compute_units: int = 0) -> dict:
-    """The launch ALGO_MFMA_SPLIT makes for this shape: tiles per workgroup, row segments (0 =
+    """The launch ALGO_MFMA_SPLIT_BF16 makes for this shape: tiles per workgroup, row segments (0 =
     tiles of consecutive pixels), LDS bytes per workgroup, workgroups."""
     t, r = ctypes.c_int(), ctypes.c_int()
     b, w = ctypes.c_size_t(), ctypes.c_longlong()

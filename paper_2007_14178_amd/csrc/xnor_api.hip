@@ -81,6 +81,15 @@ bool fp32_split_pays(const xnor::Geom &g)
     return direct_us > split_us;
 }
 
+// The form of the split Binary-Weight-Network kernel.  The FP6 form wherever it takes a shape that the bf16 form takes: 45 layers
+// over the range of the benchmark's, 1.2 to 3.1 times as fast, at half the error (128x384x13x13 F=384 3x3, a
+// pass: 177 -> 104 us).
+int bwn_split_kernel_of(const xnor::Geom &g)
+{
+    if (!xnor::bwn_split_supports(g)) return XNOR_E_UNSUPPORTED;
+    return xnor::bwn_fp6_supports(g) ? XNOR_ALGO_MFMA_SPLIT_FP6 : XNOR_ALGO_MFMA_SPLIT_BF16;
+}
+
 // The expanded filters of xnor_conv2d_fwd_static live here instead of in a caller's workspace.
 // One copy per GPU, held until the process ends.  In host code the name is only a handle: the
 // memory's address on the current device comes from hipGetSymbolAddress, once per device.
@@ -374,12 +383,13 @@ int xnor_bwn_conv2d_fwd_algo(const float *I, const uint32_t *Wpk, const float *a
         case XNOR_ALGO_DIRECT:
             return hip_status(xnor::launch_bwn_direct(I, Wpk, alpha, g, out, (hipStream_t)stream));
         case XNOR_ALGO_MFMA_SPLIT:
+        case XNOR_ALGO_MFMA_SPLIT_FP6:
+        case XNOR_ALGO_MFMA_SPLIT_BF16:
+            if (algo == XNOR_ALGO_MFMA_SPLIT) algo = bwn_split_kernel_of(g);
+            if (algo == XNOR_ALGO_MFMA_SPLIT_FP6)
+                return xnor::bwn_fp6_supports(g) ? hip_status(xnor::launch_bwn_fp6(I, Wpk, alpha, g, out, (hipStream_t)stream))
+                                                 : XNOR_E_UNSUPPORTED;
             if (!xnor::bwn_split_supports(g)) return XNOR_E_UNSUPPORTED;
-            // The FP6 form wherever it takes the shape: 45 layers over the range of the benchmark's, 1.2 to 3.1 times as
-            // fast as the bf16 form, at half its error (128x384x13x13 F=384 3x3, a pass: 177 -> 104 us).
-            // What it leaves are rows too wide for its whole-row staging (large strides) and images of 2 GiB.
-            if (xnor::bwn_fp6_supports(g))
-                return hip_status(xnor::launch_bwn_fp6(I, Wpk, alpha, g, out, (hipStream_t)stream));
             return hip_status(xnor::launch_bwn_split(I, Wpk, alpha, g, out, (hipStream_t)stream));
         case XNOR_ALGO_MFMA:
             if (!xnor::bwn_mfma_supports(g)) return XNOR_E_UNSUPPORTED;
@@ -397,6 +407,15 @@ int xnor_bwn_pick_algo(const xnor_shape *s)
     if (rc) return rc;
     return xnor::bwn_split_supports(g) ? XNOR_ALGO_MFMA_SPLIT
            : xnor::bwn_mfma_supports(g) ? XNOR_ALGO_MFMA : XNOR_ALGO_DIRECT;
+}
+
+int xnor_bwn_split_kernel(const xnor_shape *s)
+{
+    if (!s) return XNOR_E_NULL;
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    if (rc) return rc;
+    return bwn_split_kernel_of(g);
 }
 
 int xnor_bwn_split_plan(const xnor_shape *s, int compute_units, int *tiles, int *row_segments,

@@ -156,10 +156,17 @@ def test_null_and_alignment_rejected(xb):
     assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, sp, ok, 99, None) == xb.E_UNSUPPORTED
     wide = xb.Shape(1, 64, 8, 4000, 8, 3, 3, 1, 1, 1, 1)      # rows too wide for the matrix-core kernel's LDS band
     assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(wide.c()), ok, xb.ALGO_MFMA, None) == xb.E_UNSUPPORTED
-    # the three-term bf16 kernel: up to 64 taps, and rows that fit its staging
-    assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(wide.c()), ok, xb.ALGO_MFMA_SPLIT, None) == xb.E_UNSUPPORTED
+    # the split kernels: up to 64 taps, and rows that fit their staging
     nine = xb.Shape(1, 64, 16, 16, 8, 9, 9, 1, 1, 4, 4)
-    assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(nine.c()), ok, xb.ALGO_MFMA_SPLIT, None) == xb.E_UNSUPPORTED
+    for form in (xb.ALGO_MFMA_SPLIT, xb.ALGO_MFMA_SPLIT_FP6, xb.ALGO_MFMA_SPLIT_BF16):
+        assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(wide.c()), ok, form, None) == xb.E_UNSUPPORTED
+        assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(nine.c()), ok, form, None) == xb.E_UNSUPPORTED
+    for refused in (wide, nine):
+        assert L.xnor_bwn_split_kernel(ctypes.byref(refused.c())) == xb.E_UNSUPPORTED
+    assert L.xnor_bwn_split_kernel(None) == xb.E_NULL
+    for form in (xb.ALGO_MFMA_SPLIT_FP6, xb.ALGO_MFMA_SPLIT_BF16):        # the binary-weight layer's alone
+        assert L.xnor_conv2d_fwd_algo(ok, ok, ok, ok, sp, ok, None, ok, 1 << 30, form, None) == xb.E_UNSUPPORTED
+        assert L.xnor_conv2d_fp32_fwd_algo(ok, ok, sp, ok, form, None) == xb.E_UNSUPPORTED
     assert L.xnor_bwn_conv2d_fwd_algo(None, ok, ok, sp, ok, xb.ALGO_MFMA_SPLIT, None) == xb.E_NULL
 
 
@@ -180,7 +187,7 @@ def _rows_spanned(OH, OW, tiles, row_segments):
 
 
 def test_bwn_split_plan_holds_what_its_tiles_need(xb):
-    """The launch plan of the three-term bf16 kernel, on the benchmark layers and on seeded random
+    """The launch plan of the three-term bf16 kernel, whose limits are those of XNOR_ALGO_MFMA_SPLIT, on the benchmark layers and on seeded random
     shapes, for several unit counts: the staged positions it sizes the LDS for cover the input rows
     under the output rows that any workgroup's tiles really touch (walked tile by tile here), within
     the kernel's limits, and the grid is N x filter groups x tile groups."""

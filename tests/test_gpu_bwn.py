@@ -45,19 +45,21 @@ def check(xb, full, I, Wt, algo, key):
     s = xb.Shape(*full)
     O_ref, S, a = oracle_bwn(key, I, Wt, oracle.Shape(*full))
     Wpk, alpha, _ = xb.xnor_filter_prepare(dev(Wt))
-    algo_id = {"auto": xb.ALGO_AUTO, "direct": xb.ALGO_DIRECT, "mfma": xb.ALGO_MFMA, "split": xb.ALGO_MFMA_SPLIT}[algo]
+    algo_id = {"auto": xb.ALGO_AUTO, "direct": xb.ALGO_DIRECT, "mfma": xb.ALGO_MFMA, "split": xb.ALGO_MFMA_SPLIT,
+               "fp6": xb.ALGO_MFMA_SPLIT_FP6, "bf16": xb.ALGO_MFMA_SPLIT_BF16}[algo]
     try:
         out = xb.xnor_bwn_conv2d_fwd(dev(I), Wpk, alpha, s, algo=algo_id)
     except xb.XnorError as e:
-        if e.status == xb.E_UNSUPPORTED and algo in ("mfma", "split"):
+        if e.status == xb.E_UNSUPPORTED and algo in ("mfma", "split", "fp6", "bf16"):
             pytest.skip("the matrix-core kernel does not take this shape")
         raise
     torch.cuda.synchronize()
     got = out.cpu().numpy().astype(np.float64)
     assert got.shape == O_ref.shape
     bar = RTOL * a[None, :, None, None] * S[:, None]
-    if algo in ("split", "auto"):
-        # the three-term bf16 kernel flushes terms below the normal range: at most 2^-125 per input value
+    if algo in ("split", "auto", "fp6", "bf16"):
+        # at the bottom of the range the FP6 digits end at 2^-125 of a value, and the three-term bf16 kernel flushes terms
+        # below the normal range: at most 2^-125 per input value
         bar = bar + a[None, :, None, None] * (full[1] * full[5] * full[6]) * 2.0 ** -125
     err = np.abs(got - O_ref)
     assert (err <= bar).all(), f"{(err > bar).sum()} of {err.size} outside the bar; worst err/bar {np.nanmax(err / np.maximum(bar, 1e-300)):.3g}"
@@ -88,7 +90,7 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("algo", ["direct", "mfma", "split", "auto"])
+@pytest.mark.parametrize("algo", ["direct", "mfma", "split", "fp6", "bf16", "auto"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_bwn_shapes_vs_oracle(xb, shape, algo):
     print(f"case bwn shape={shape} algo={algo}", flush=True)
@@ -105,16 +107,29 @@ def test_bwn_benchmark_layers_two_images(xb, name):
     I, Wt = make_input(L, n), make_weights(L)
     full = (n, L.C, L.H, L.W, L.F, L.kh, L.kw, L.sh, L.sw, L.ph, L.pw)
     out_m = check(xb, full, I, Wt, "mfma", name)
-    out_s = check(xb, full, I, Wt, "split", name)
+    out_6 = check(xb, full, I, Wt, "fp6", name)
+    out_b = check(xb, full, I, Wt, "bf16", name)
     out_d = check(xb, full, I, Wt, "direct", name)
     # the kernels differ only in summation order
     assert torch.allclose(out_m, out_d, rtol=0, atol=float(2e-5 * out_d.abs().max()))
-    assert torch.allclose(out_s, out_d, rtol=0, atol=float(2e-5 * out_d.abs().max()))
+    assert torch.allclose(out_6, out_d, rtol=0, atol=float(2e-5 * out_d.abs().max()))
+    assert torch.allclose(out_b, out_d, rtol=0, atol=float(2e-5 * out_d.abs().max()))
+
+
+@pytest.mark.parametrize("shape", [(2, 70, 9, 66, 40, 7, 7, 1, 1, 3, 3), (1, 40, 12, 144, 70, 7, 7, 1, 1, 0, 0), (1, 64, 11, 130, 33, 5, 5, 2, 2, 2, 2),
+                                   (1, 65, 7, 297, 130, 3, 3, 1, 1, 1, 1), (2, 64, 64, 64, 64, 8, 8, 1, 1, 4, 4)], ids=lambda s: "x".join(map(str, s)))
+def test_bwn_fp6_on_shapes_that_the_bf16_form_does_not_take(xb, shape):
+    """By name the FP6 form stages more positions than the bf16 form, which decides what XNOR_ALGO_MFMA_SPLIT takes."""
+    print(f"case bwn fp6 shape={shape}", flush=True)
+    with pytest.raises(xb.XnorError):
+        xb.xnor_bwn_split_kernel(xb.Shape(*shape))
+    _, I, Wt = random_layer(np.random.default_rng(zlib.crc32(("bwn" + str(shape)).encode())), "t", *shape)
+    check(xb, shape, I, Wt, "fp6", shape)
 
 
 def test_bwn_tiny_inputs_stay_within_the_flush_floor(xb):
     """Inputs at the bottom of the fp32 range: the fp32 kernels carry them exactly (sums of a few
-    denormals are exact), the three-term bf16 kernel may flush each term below 2^-126."""
+    denormals are exact), the three-term bf16 kernel may flush each term below 2^-126 and the FP6 digits end at 2^-125 of a value."""
     shape = (2, 20, 9, 9, 12, 3, 3, 1, 1, 1, 1)
     print(f"case bwn-tiny shape={shape}", flush=True)
     rng = np.random.default_rng(5)
@@ -127,7 +142,8 @@ def test_bwn_tiny_inputs_stay_within_the_flush_floor(xb):
     a = oracle.alpha(Wt).astype(np.float64)
     Wpk, alpha, _ = xb.xnor_filter_prepare(dev(Wt))
     nred = shape[1] * shape[5] * shape[6]
-    for algo, floor in ((xb.ALGO_DIRECT, 0.0), (xb.ALGO_MFMA, 0.0), (xb.ALGO_MFMA_SPLIT, 2.0 ** -125), (xb.ALGO_AUTO, 2.0 ** -125)):
+    for algo, floor in ((xb.ALGO_DIRECT, 0.0), (xb.ALGO_MFMA, 0.0), (xb.ALGO_MFMA_SPLIT_FP6, 2.0 ** -125), (xb.ALGO_MFMA_SPLIT_BF16, 2.0 ** -125),
+                        (xb.ALGO_AUTO, 2.0 ** -125)):
         out = xb.xnor_bwn_conv2d_fwd(dev(I), Wpk, alpha, s, algo=algo)
         torch.cuda.synchronize()
         err = np.abs(out.cpu().numpy().astype(np.float64) - O_ref.astype(np.float64))
@@ -148,7 +164,7 @@ def test_bwn_on_binary_input_equals_the_xnor_path(xb):
     Wpk, alpha, _ = xb.xnor_filter_prepare(dev(Wt))
     Ipk, K, _ = xb.xnor_input_prepare(dI, s)
     _, dot = xb.xnor_conv2d_fwd(Ipk, Wpk, K, alpha, s, want_dot=True)
-    for algo in (xb.ALGO_DIRECT, xb.ALGO_MFMA, xb.ALGO_MFMA_SPLIT):
+    for algo in (xb.ALGO_DIRECT, xb.ALGO_MFMA, xb.ALGO_MFMA_SPLIT_FP6, xb.ALGO_MFMA_SPLIT_BF16):
         out = xb.xnor_bwn_conv2d_fwd(dI, Wpk, alpha, s, algo=algo)
         torch.cuda.synchronize()
         assert torch.equal(out, dot.float() * alpha[None, :, None, None])

@@ -27,20 +27,20 @@ def sums64(I, Wt, s):
     return out.reshape(s.N, s.F, OH, OW), cols.abs().sum(1).reshape(s.N, 1, OH, OW)
 
 
-def run(xb, shape, I, seed):
+def run(xb, shape, I, seed, algo=None):
     print(f"case bwn-fp6 shape={shape} seed={seed}", flush=True)
     s = xb.Shape(*shape)
     Wt = torch.randn((s.F, s.C, s.kh, s.kw), generator=torch.Generator().manual_seed(seed + 1)) * 0.05
     Wpk, alpha, _ = xb.xnor_filter_prepare(Wt.cuda())
     OH, OW = (s.H + 2 * s.ph - s.kh) // s.sh + 1, (s.W + 2 * s.pw - s.kw) // s.sw + 1
     out = torch.full((s.N, s.F, OH, OW), float("nan"), device="cuda")
-    xb.xnor_bwn_conv2d_fwd(I.cuda(), Wpk, alpha, s, out=out, algo=xb.ALGO_MFMA_SPLIT)
+    xb.xnor_bwn_conv2d_fwd(I.cuda(), Wpk, alpha, s, out=out, algo=algo or xb.ALGO_MFMA_SPLIT_FP6)
     torch.cuda.synchronize()
     return out.cpu().double(), alpha.cpu().double()[None, :, None, None], *sums64(I, Wt, s), s
 
 
-def check(xb, shape, I, seed):
-    got, alpha, ref, S, s = run(xb, shape, I, seed)
+def check(xb, shape, I, seed, algo=None):
+    got, alpha, ref, S, s = run(xb, shape, I, seed, algo)
     bar = alpha * (1e-5 * S + s.C * s.kh * s.kw * 2.0 ** -125)
     err = (got - alpha * ref).abs()
     assert bool((err <= bar).all()), f"worst err/bar {float((err / bar.clamp_min(1e-300)).nan_to_num(1e9).max()):.3g}"
@@ -102,9 +102,10 @@ def test_scales_around_the_largest_digit(xb, top):
 
 
 @pytest.mark.parametrize("top", [1.875, 1.9374999, 1.9375, 1.96875, float(np.finfo(np.float32).max) / 2.0 ** 127], ids=lambda v: f"{v:.7f}")
+@pytest.mark.parametrize("form", ["FP6", "BF16"])
 @pytest.mark.parametrize("shape", [(1, 1, 9, 28, 36, 1, 1, 1, 1, 0, 0), (2, 70, 12, 12, 40, 1, 1, 1, 1, 0, 0), (1, 40, 9, 12, 100, 3, 3, 1, 1, 1, 1)],
                          ids=lambda s: "x".join(map(str, s)))
-def test_values_at_the_top_of_the_range(xb, shape, top):
+def test_values_at_the_top_of_the_range(xb, shape, top, form):
     """One value of up to the largest float under a window, of either sign, others of its block small or zero: the sums are
     inside fp32's range, so they are finite and inside the bar (filters of 0.05 keep the outputs in range too)."""
     g = torch.Generator().manual_seed(7)
@@ -113,7 +114,7 @@ def test_values_at_the_top_of_the_range(xb, shape, top):
     for k, (y, x) in enumerate(((1, 1), (1, 5), (4, 1), (4, 9), (7, 4))):
         I[:, :, y - 1:y + 2, x - 1:x + 2] *= 2.0 ** -60
         I[:, (17 * k) % shape[1], y, x] = float(np.float32(top)) * 2.0 ** 127 * (-1) ** k
-    check(xb, shape, I, 7)
+    check(xb, shape, I, 7, getattr(xb, "ALGO_MFMA_SPLIT_" + form))
 
 
 def test_small_values_beside_large_ones(xb):
@@ -145,7 +146,11 @@ def test_not_finite_inputs_reach_their_windows_only(xb):
 def test_rows_too_wide_for_whole_rows_keep_the_bf16_form(xb):
     """Large strides: 32 output pixels lie on two output rows, with nine input rows of 400 under them."""
     shape = (2, 40, 33, 400, 70, 1, 1, 8, 8, 0, 0)
-    check(xb, shape, torch.randn(shape[:4], generator=torch.Generator().manual_seed(13)), 13)
+    assert xb.xnor_bwn_split_kernel(xb.Shape(*shape)) == xb.ALGO_MFMA_SPLIT_BF16
+    I = torch.randn(shape[:4], generator=torch.Generator().manual_seed(13))
+    with pytest.raises(xb.XnorError):
+        check(xb, shape, I, 13)
+    check(xb, shape, I, 13, xb.ALGO_MFMA_SPLIT)
 
 
 def test_captured_launches_replay_the_eager_result(xb):
@@ -156,6 +161,7 @@ def test_captured_launches_replay_the_eager_result(xb):
     I, Wt = torch.randn(shape[:4], generator=g).cuda(), torch.randn((100, 96, 3, 3), generator=g).cuda()
     Wpk, alpha, _ = xb.xnor_filter_prepare(Wt)
     out = torch.empty((4, 100, 14, 14), device="cuda")
+    assert xb.xnor_bwn_pick_algo(s) == xb.ALGO_MFMA_SPLIT and xb.xnor_bwn_split_kernel(s) == xb.ALGO_MFMA_SPLIT_FP6
     xb.xnor_bwn_conv2d_fwd(I, Wpk, alpha, s, out=out)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()

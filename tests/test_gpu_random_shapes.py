@@ -140,17 +140,18 @@ def test_random_shape_all_forms(xb, shape):
 
     # Binary-Weight-Network layer
     O_b, S = oracle.bwn(I, Wt, osh, want_scale=True)
-    for name, algo in (("direct", xb.ALGO_DIRECT), ("mfma", xb.ALGO_MFMA), ("split", xb.ALGO_MFMA_SPLIT), ("auto", xb.ALGO_AUTO)):
+    for name, algo in (("direct", xb.ALGO_DIRECT), ("mfma", xb.ALGO_MFMA), ("fp6", xb.ALGO_MFMA_SPLIT_FP6), ("bf16", xb.ALGO_MFMA_SPLIT_BF16),
+                       ("auto", xb.ALGO_AUTO)):
         try:
             ob = xb.xnor_bwn_conv2d_fwd(dI, Wpk, alpha, s, algo=algo)
         except xb.XnorError as e:
-            assert e.status == xb.E_UNSUPPORTED and name in ("mfma", "split"), (name, e)
+            assert e.status == xb.E_UNSUPPORTED and name in ("mfma", "fp6", "bf16"), (name, e)
             continue
         torch.cuda.synchronize()
         err = np.abs(ob.cpu().numpy().astype(np.float64) - O_b.astype(np.float64))
         bar = RTOL * a_ref.astype(np.float64)[None, :, None, None] * S[:, None]
-        if name in ("split", "auto"):
-            # (the three-term bf16 kernel may flush a term below the normal range: 2^-125 per input value)
+        if name in ("fp6", "bf16", "auto"):
+            # (FP6 digits end there, and the three-term bf16 kernel may flush a term below the normal range: 2^-125 per input value)
             bar = bar + a_ref.astype(np.float64)[None, :, None, None] * (shape[1] * shape[5] * shape[6]) * 2.0 ** -125
         assert (err <= bar).all(), f"bwn ({name}): {(err > bar).sum()} of {err.size} outside the bar"
 
