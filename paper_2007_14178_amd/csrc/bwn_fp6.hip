@@ -139,21 +139,9 @@ __device__ inline void split_block(Block &b, char *at, bool keep)
     const uint32_t scale = (bits & 0x7fffffffu) >= 0x7f800000u ? 255u
                            : (uint32_t)max((int)((bits + (1u << 19)) >> 23) - 2, kMinScale);
     if (keep) *reinterpret_cast<uint32_t *>(at + 120) = scale;
-    // From 1.9375 * 2^127 up the first digit is 4.0 * 2^126, which is no float: such a block's digits are those of its halves.
-    // (The test costs up to 1 % of a layer: 128x384x13x13 F=384 3x3 111.3 -> 112.4 us.)
-    uint32_t down = 0;
-    if (__any(scale == 253)) {
-        down = scale == 253 ? 1u : 0u;
-        const float f = down ? 0.5f : 1.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            b.even[i] *= f;
-            b.odd[i] *= f;
-        }
-    }
 #pragma unroll
     for (int t = 0; t < kDigits; ++t) {
-        const float s = __uint_as_float((scale - down + digit_exp(t)) << 23);
+        const float s = __uint_as_float((scale + digit_exp(t)) << 23);
         const v6u d = to_fp6(b.even, b.odd, s);
         if (keep) {
             v2u *o = reinterpret_cast<v2u *>(at + 24 * t);
@@ -162,11 +150,12 @@ __device__ inline void split_block(Block &b, char *at, bool keep)
             o[2] = (v2u){d[4], d[5]};
         }
         if (t + 1 < kDigits) {
-            const v32f back = from_fp6(d, s);
+            // (half of the digit, subtracted twice: from 1.9375 * 2^127 up the first one is 4.0 * 2^126, which is no float)
+            const v32f back = from_fp6(d, __uint_as_float((scale - 1 + digit_exp(t)) << 23));
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                b.even[i] -= back[2 * i];
-                b.odd[i] -= back[2 * i + 1];
+                b.even[i] = fmaf(-2.f, back[2 * i], b.even[i]);
+                b.odd[i] = fmaf(-2.f, back[2 * i + 1], b.odd[i]);
             }
         }
     }
