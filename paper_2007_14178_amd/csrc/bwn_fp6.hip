@@ -374,6 +374,7 @@ struct Fp6Plan {
     bool ok;
     int nf, G, waves, wgs, positions;
     size_t lds;
+    double cycles;                 // about what the launch takes (see kRouteCosts)
 };
 
 // LDS of a workgroup: the staged positions of G words and the zero position; the filter words of G * taps rows, up to
@@ -391,40 +392,48 @@ long long fp6_positions(const Geom &g, int waves)
     return std::min((long long)g.H, (orows - 1) * g.sh + g.kh) * g.W;
 }
 
-// About what a launch takes on its busiest compute unit, in cycles: `wgs` workgroups on `cus` units, in batches of those
+// About what a launch takes on its busiest compute unit, in cycles: `busiest` workgroups, in batches of those
 // that a unit holds.  A batch is through when its matrix instructions and conversions are, on the SIMD that
-// has most of its waves, or when one workgroup's chain is: load, convert, barrier, multiply.  The constants are
-// a fit to 2700 timed launches of 45 layers (1 to 128 images, 32 to 512 channels and filters, 1x1 to 7x7, 7 to 64
-// wide); the shape taken is 2 % slower than the best of the up to 64 on average, 20 % at most.
-double fp6_cost(const Geom &g, int nf, int G, int waves, int positions, size_t lds, long long wgs, int cus)
+// has most of its waves, or when one workgroup's chain is: load, convert, barrier, multiply.
+struct Fp6Costs {
+    double contended;              // matrix instructions beside others', at the card's power
+    double convert, load;          // a round of blocks: the conversions; the wait for its loads
+    double chunk, words;           // barriers and the first operands; an instruction of filter words
+    double stores, launch;         // outputs of a filter tile
+};
+// Between a layer's own shapes of workgroup: a fit to 2700 timed launches of 45 layers (1 to 128 images, 32 to 512 channels and
+// filters, 1x1 to 7x7, 7 to 64 wide); the shape taken is 2 % slower than the best of the up to 64 on average, 20 % at most.
+constexpr Fp6Costs kPlanCosts = {1.3, 1850, 2100, 3300, 320, 1900, 0};
+// Between the two forms, with split_cycles of csrc/bwn_split.hip: a fit to which is the faster one, over the shapes taken of 13000
+// layers (1 to 128 images, 1 to 512 channels, 4 to 512 filters, 1x1 to 7x7, 4 to 420 wide, strides 1 to 4).
+constexpr Fp6Costs kRouteCosts = {2.4, 800, 2500, 0, 0, 3500, 8800};
+
+double fp6_cost(const Fp6Costs &c, const Geom &g, int nf, int G, int waves, int positions, size_t lds, long long busiest)
 {
-    constexpr double kContended = 1.3;                    // matrix instructions beside others', at the card's power
-    constexpr double kConvert = 1850, kLoad = 2100;       // a round of blocks: the conversions; the wait for its loads
-    constexpr double kChunk = 3300, kWords = 320;         // barriers and the first operands; an instruction of filter words
-    constexpr double kSteps = 430, kStores = 1900;         // into the steps, per chunk; outputs of a filter tile
+    constexpr double kSteps = 430;                        // into the steps, per chunk
     const int taps = g.kh * g.kw, nt = 64 * waves;
     double mfma = 0, convert = 0, wait = 0;
     auto chunks = [&](int n, int words) {
         const int steps = words == 2 ? taps : (taps + 1) / 2, rounds = ceil_div((long long)positions * words, nt);
         mfma += n * (steps * nf * kDigits * 32 + kSteps);
-        convert += n * rounds * kConvert;
-        wait += n * (kChunk + rounds * kLoad + kWords * taps * words * nf * 0.5 / waves);
+        convert += n * rounds * c.convert;
+        wait += n * (c.chunk + rounds * c.load + c.words * taps * words * nf * 0.5 / waves);
     };
     chunks(g.Cw / G, G);
     if (g.Cw % G) chunks(1, 1);
-    const double alone = mfma + convert + wait + kStores * nf;
+    const double alone = mfma + convert + wait + c.stores * nf;
     // registers hold three waves on a SIMD, four with one filter tile; of workgroups of five to eight waves, which
     // put two on some SIMD, one or two
     const int per_simd = nf == 1 ? 4 : 3;
     const int held = std::max(1, std::min((int)(kLds / lds), waves > 4 ? per_simd / 2 : 4 * per_simd / waves));
     auto batch = [&](long long n) {
-        return std::max(alone, ceil_div(n * waves, 4) * (mfma * kContended + convert) + wait / n);
+        return std::max(alone, ceil_div(n * waves, 4) * (mfma * c.contended + convert) + wait / n);
     };
-    const long long busiest = (wgs + cus - 1) / cus, full = busiest / held, rest = busiest % held;
-    return full * batch(held) + (rest ? batch(rest) : 0.0);
+    const long long full = busiest / held, rest = busiest % held;
+    return c.launch + full * batch(held) + (rest ? batch(rest) : 0.0);
 }
 
-Fp6Plan search_fp6_plan(const Geom &g, int cus, int force_nf = 0, int force_G = 0, int force_waves = 0)
+Fp6Plan search_fp6_plan(const Geom &g, int cus)
 {
     Fp6Plan pl{};
     const long long OHW = (long long)g.OH * g.OW, taps = (long long)g.kh * g.kw;
@@ -436,7 +445,6 @@ Fp6Plan search_fp6_plan(const Geom &g, int cus, int force_nf = 0, int force_G = 
         if (nf > 1 && 32 * (nf - 1) >= g.F) continue;
         for (int G = std::min(2, g.Cw); G >= 1; --G)
             for (int waves = std::min(kMaxWaves, tiles); waves >= 1; --waves) {
-                if ((force_nf && nf != force_nf) || (force_G && G != force_G) || (force_waves && waves != force_waves)) continue;
                 const long long positions = fp6_positions(g, waves);
                 if (positions > (long long)(kLds / kPosBytes)) continue;
                 const size_t lds = fp6_lds(g, nf, G, (int)positions);
@@ -444,12 +452,17 @@ Fp6Plan search_fp6_plan(const Geom &g, int cus, int force_nf = 0, int force_G = 
                 const int wgs = ceil_div(tiles, waves);
                 const long long all = (long long)g.N * wgs * ceil_div(g.F, 32 * nf);
                 if (all > 0x7ffffff0LL) continue;
-                const double cost = fp6_cost(g, nf, G, waves, (int)positions, lds, all, cus);
+                const double cost = fp6_cost(kPlanCosts, g, nf, G, waves, (int)positions, lds, (all + cus - 1) / cus);
                 if (best < 0 || cost < best) {
                     best = cost;
-                    pl = {true, nf, G, waves, wgs, (int)positions, lds};
+                    pl = {true, nf, G, waves, wgs, (int)positions, lds, 0.0};
                 }
             }
+    }
+    if (pl.ok) {
+        // (a unit's filter groups run on one XCD: with 36 units and seven groups 35 workgroups on its 32 compute units)
+        const long long per_xcd = ((long long)g.N * pl.wgs + 7) / 8 * ceil_div(g.F, 32 * pl.nf);
+        pl.cycles = fp6_cost(kRouteCosts, g, pl.nf, pl.G, pl.waves, pl.positions, pl.lds, ceil_div(per_xcd, std::max(1, cus / 8)));
     }
     return pl;
 }
@@ -507,6 +520,7 @@ hipError_t launch_fp6_plan(const Fp6Plan &pl, const float *I, const uint32_t *Wp
 }  // namespace
 
 bool bwn_fp6_supports(const Geom &g) { return make_fp6_plan(g).ok; }
+double bwn_fp6_cycles(const Geom &g) { return make_fp6_plan(g).cycles; }
 
 hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out,
                           hipStream_t st)

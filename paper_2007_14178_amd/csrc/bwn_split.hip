@@ -460,9 +460,29 @@ struct SplitPlan {
     bool ok;
     int tiles, rows_max, pitch, tpr, total;
     size_t lds;
+    double cycles;                 // about what the launch takes (see split_cycles)
 };
 
-SplitPlan make_split_plan(const Geom &g, int cus = 0)
+// About what the launch takes on its busiest compute unit, in cycles, for the choice between this form and the FP6
+// one: workgroups in batches of those that a unit holds; a batch is through when its matrix instructions and splits
+// are or when one workgroup's chain of chunks is.  (Fitted together with kRouteCosts of csrc/bwn_fp6.hip.)
+double split_cycles(const Geom &g, const SplitPlan &pl, int cus)
+{
+    constexpr double kContended = 1.66;                  // matrix instructions: operands, waits, the card's power
+    constexpr double kSplit = 280;                       // a chunk's granules, per 128 positions
+    constexpr double kChunk = 4600, kEnds = 13000;       // a chunk's wait and barrier; first fetch, outputs
+    const double chunks = ceil_div(g.C, 16);
+    const double mfma = chunks * g.kh * g.kw * ((pl.tiles + 1) / 2) * 6 * 32 * kContended;
+    const double split = chunks * kSplit * ceil_div((long long)pl.rows_max * pl.pitch, 128);
+    const double wait = chunks * kChunk + kEnds;
+    const long long wgs = (long long)g.N * ceil_div(g.F, kFiltersPerWg) * ceil_div(pl.total, pl.tiles);
+    const int held = pl.lds <= kLdsBudget / 2 ? 2 : 1;
+    auto batch = [&](long long n) { return std::max(mfma + split + wait, n * (mfma + split) + wait / n); };
+    const long long busiest = (wgs + cus - 1) / cus, full = busiest / held, rest = busiest % held;
+    return full * batch(held) + (rest ? batch(rest) : 0.0);
+}
+
+SplitPlan search_split_plan(const Geom &g, int cus)
 {
     SplitPlan pl{};
     const long long OHW = (long long)g.OH * g.OW;
@@ -478,7 +498,6 @@ SplitPlan make_split_plan(const Geom &g, int cus = 0)
     // 28 outputs, 25 tiles, 6,6,6,6,1 against 5 x 5: 2 % faster; 56 x 56 with 16 images and 128
     // filters: 272 workgroups of six tiles are two rounds of one workgroup per unit, the second
     // nearly empty.)
-    if (cus <= 0) cus = compute_units();
     // Two ways to cut an image into tiles: 32 consecutive pixels (no pixel slot idle but in an image's
     // last tile; a workgroup's pixels straddle rows, which costs a staged row), or 32-pixel segments
     // of single rows (the last segment of a row short; whole rows per workgroup, which on wide rows
@@ -519,17 +538,26 @@ SplitPlan make_split_plan(const Geom &g, int cus = 0)
             }
         }
     }
+    if (pl.ok) pl.cycles = split_cycles(g, pl, cus);
     return pl;
+}
+
+const SplitPlan &make_split_plan(const Geom &g)
+{
+    static thread_local PlanMemo<SplitPlan> memo;
+    const int cus = compute_units();
+    return memo.get(g, cus, [&] { return search_split_plan(g, cus); });
 }
 
 }  // namespace
 
 bool bwn_split_supports(const Geom &g) { return make_split_plan(g).ok; }
+double bwn_split_cycles(const Geom &g) { return make_split_plan(g).cycles; }
 
 bool bwn_split_plan(const Geom &g, int compute_units, int *tiles, int *row_segments, size_t *lds_bytes,
                     long long *workgroups)
 {
-    const SplitPlan pl = make_split_plan(g, compute_units);
+    const SplitPlan pl = search_split_plan(g, compute_units > 0 ? compute_units : xnor::compute_units());
     if (!pl.ok) return false;
     *tiles = pl.tiles;
     *row_segments = pl.tpr;
@@ -541,7 +569,7 @@ bool bwn_split_plan(const Geom &g, int compute_units, int *tiles, int *row_segme
 hipError_t launch_bwn_split(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
                             float *out, hipStream_t st)
 {
-    const SplitPlan pl = make_split_plan(g);
+    const SplitPlan &pl = make_split_plan(g);
     if (!pl.ok) return hipErrorInvalidValue;
     SplitParams p;
     p.I = I; p.Wpk = Wpk; p.alpha = alpha; p.out = out;

@@ -81,13 +81,29 @@ bool fp32_split_pays(const xnor::Geom &g)
     return direct_us > split_us;
 }
 
-// The form of the split Binary-Weight-Network kernel.  The FP6 form wherever it takes a shape that the bf16 form takes: 45 layers
-// over the range of the benchmark's, 1.2 to 3.1 times as fast, at half the error (128x384x13x13 F=384 3x3, a
-// pass: 177 -> 104 us).
+// The form of the split Binary-Weight-Network kernel, by estimates of both launches.  The FP6 form stages whole input rows,
+// skipped columns of a stride included, and converts 32 channels whatever exist: with strides on wide rows most of
+// that is for nothing.  Timed both ways over 13000 layers (see kRouteCosts), more than 2.5 % faster was
+//   strides of 1 (3343 layers)       FP6 in 3236, up to 6.5 times (1.69 times at 128x384x13x13 F=384 3x3), bf16 in 61, mostly of few channels
+//   strides of 2 (7075)              FP6 in 5979, bf16 in 837
+//   strides of 3 and 4 (2582)        FP6 in 813, bf16 in 1686, up to 11 times (28x1x118x235 F=10 1x1 stride 4: 13.4 against 151 us)
+// The form taken is 0.3 % behind the better one on average, 0.02 % where strides are 1 and channels 32 or more; it is
+// more than 2.5 % slower than bf16 in 258 and than FP6 in 162 of them.
 int bwn_split_kernel_of(const xnor::Geom &g)
 {
-    if (!xnor::bwn_split_supports(g)) return XNOR_E_UNSUPPORTED;
-    return xnor::bwn_fp6_supports(g) ? XNOR_ALGO_MFMA_SPLIT_FP6 : XNOR_ALGO_MFMA_SPLIT_BF16;
+    static thread_local xnor::PlanMemo<int> memo;
+    return memo.get(g, xnor::compute_units(), [&]() -> int {
+        if (!xnor::bwn_split_supports(g)) return XNOR_E_UNSUPPORTED;
+        if (!xnor::bwn_fp6_supports(g)) return XNOR_ALGO_MFMA_SPLIT_BF16;
+        return xnor::bwn_fp6_cycles(g) > xnor::bwn_split_cycles(g) ? XNOR_ALGO_MFMA_SPLIT_BF16 : XNOR_ALGO_MFMA_SPLIT_FP6;
+    });
+}
+
+// What XNOR_ALGO_AUTO runs.
+int bwn_algo_of(const xnor::Geom &g)
+{
+    const int form = bwn_split_kernel_of(g);
+    return form > 0 ? form : xnor::bwn_mfma_supports(g) ? XNOR_ALGO_MFMA : XNOR_ALGO_DIRECT;
 }
 
 // The expanded filters of xnor_conv2d_fwd_static live here instead of in a caller's workspace.
@@ -378,14 +394,14 @@ int xnor_bwn_conv2d_fwd_algo(const float *I, const uint32_t *Wpk, const float *a
     const int rc = make_geom(s, &g);
     if (rc) return rc;
     if (!aligned(I, 4) || !aligned(Wpk, 4) || !aligned(alpha, 4) || !aligned(out, 4)) return XNOR_E_ALIGN;
-    if (algo == XNOR_ALGO_AUTO) algo = xnor_bwn_pick_algo(s);
+    if (algo == XNOR_ALGO_AUTO) algo = bwn_algo_of(g);
     switch (algo) {
         case XNOR_ALGO_DIRECT:
             return hip_status(xnor::launch_bwn_direct(I, Wpk, alpha, g, out, (hipStream_t)stream));
         case XNOR_ALGO_MFMA_SPLIT:
         case XNOR_ALGO_MFMA_SPLIT_FP6:
         case XNOR_ALGO_MFMA_SPLIT_BF16:
-            if (algo == XNOR_ALGO_MFMA_SPLIT) algo = bwn_split_kernel_of(g);
+            if (algo == XNOR_ALGO_MFMA_SPLIT && (algo = bwn_split_kernel_of(g)) < 0) return algo;
             if (algo == XNOR_ALGO_MFMA_SPLIT_FP6)
                 return xnor::bwn_fp6_supports(g) ? hip_status(xnor::launch_bwn_fp6(I, Wpk, alpha, g, out, (hipStream_t)stream))
                                                  : XNOR_E_UNSUPPORTED;
@@ -405,8 +421,8 @@ int xnor_bwn_pick_algo(const xnor_shape *s)
     xnor::Geom g;
     const int rc = make_geom(s, &g);
     if (rc) return rc;
-    return xnor::bwn_split_supports(g) ? XNOR_ALGO_MFMA_SPLIT
-           : xnor::bwn_mfma_supports(g) ? XNOR_ALGO_MFMA : XNOR_ALGO_DIRECT;
+    const int algo = bwn_algo_of(g);
+    return algo == XNOR_ALGO_MFMA_SPLIT_FP6 || algo == XNOR_ALGO_MFMA_SPLIT_BF16 ? XNOR_ALGO_MFMA_SPLIT : algo;
 }
 
 int xnor_bwn_split_kernel(const xnor_shape *s)

@@ -312,6 +312,19 @@ def test_fp32_split_is_taken_where_it_is_the_faster_kernel(xb):
         assert used == ((N, C, H, W, F, k) in faster), (N, C, H, W, F, k)
 
 
+def test_bwn_split_takes_the_faster_form(xb):
+    """Layers timed both ways that differ by more than a third: (N, C, H, W, F, k, stride, pad), us of the FP6 and the bf16 form."""
+    timed = [((128, 384, 13, 13, 384, 3, 1, 1), 111, 178), ((128, 512, 28, 28, 512, 3, 1, 1), 710, 1300), ((1, 64, 56, 56, 64, 3, 1, 1), 9.8, 20),
+             ((100, 286, 61, 61, 257, 3, 2, 1), 501, 695), ((6, 55, 179, 216, 27, 2, 1, 1), 43.7, 285), ((19, 14, 12, 411, 60, 1, 1, 0), 24.6, 91.8),
+             ((44, 170, 45, 93, 355, 1, 2, 0), 137, 297), ((7, 78, 161, 71, 98, 5, 2, 0), 48.9, 111),
+             ((28, 1, 118, 235, 10, 1, 4, 0), 151, 13.4), ((12, 131, 45, 138, 43, 3, 3, 1), 144, 33.3), ((33, 396, 13, 167, 5, 3, 4, 1), 312, 77.2),
+             ((27, 126, 29, 280, 509, 1, 3, 0), 310, 91.1), ((5, 4, 132, 316, 383, 1, 2, 0), 84.5, 31.8), ((48, 23, 89, 76, 396, 3, 4, 1), 311, 126),
+             ((10, 1, 14, 96, 347, 3, 3, 1), 22.1, 10.5), ((4, 40, 48, 48, 342, 3, 2, 1), 28.8, 16.3)]
+    for (N, C, H, W, F, k, st, p), fp6, bf16 in timed:
+        want = xb.ALGO_MFMA_SPLIT_FP6 if fp6 < bf16 else xb.ALGO_MFMA_SPLIT_BF16
+        assert xb.xnor_bwn_split_kernel(xb.Shape(N, C, H, W, F, k, k, st, st, p, p)) == want, (N, C, H, W, F, k, st, p)
+
+
 @pytest.mark.parametrize("k", [1, 3, 5])
 def test_fp32_split_workspace_holds_filters_only(xb, k):
     """No pass over the images before the convolution: what it would leave behind grows with their number.  Terms of 32 filters x 16
