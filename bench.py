@@ -80,7 +80,7 @@ def parse():
     ap.add_argument("--warmup", type=int, default=1000)
     ap.add_argument("--layer", default="c5", help="workload name (see paper_2007_14178_amd/workloads.py)")
     ap.add_argument("--algo", default="auto", choices=["auto", "direct", "tiled", "mfma", "split"],
-                    help="the convolution kernel (split: --bwn only, the input split into FP6 digits)")
+                    help="the convolution kernel (split: --bwn only, the input split into FP6 digits or bf16 terms)")
     ap.add_argument("--unfused", action="store_true", help="run the four pre-stage calls separately")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--separate-prepare", action="store_true",
@@ -454,7 +454,7 @@ def run_bwn(args, xb, torch, layer, make_input, make_weights):
     alpha = torch.empty((s.F,), dtype=torch.float32, device="cuda")
     out = torch.empty((s.N, s.F, OH, OW), dtype=torch.float32, device="cuda")
     algo = {"auto": xb.ALGO_AUTO, "direct": xb.ALGO_DIRECT, "mfma": xb.ALGO_MFMA, "split": xb.ALGO_MFMA_SPLIT}[args.algo]
-    # which kernel that is for this shape: the three-term bf16 form, else the fp32 matrix form, else direct
+    # which kernel that is for this shape: a split form, else the fp32 matrix form, else direct
     kernel = args.algo
     if kernel == "auto":
         kernel = "direct"
@@ -490,25 +490,30 @@ def run_bwn(args, xb, torch, layer, make_input, make_weights):
                 for i, n in enumerate(["filter_prepare", "conv"])}
     macs = layer.binary_macs
     conv_ms = stage_ms["conv"]
-    # the split form executes five FP6 multiply-accumulates per fp32 one and is priced against the peak of the
-    # 6- and 4-bit formats with what it executes; the other kernels against the fp32 peak
-    terms = 5 if kernel == "split" else 1
-    peak = PEAK_FP4_MFMA_TFLOPS if kernel == "split" else PEAK_FP32_MFMA_TFLOPS
+    # the split forms execute five FP6 or three bf16 multiply-accumulates per fp32 one and are priced against the peak of
+    # their formats with what they execute; the other kernels against the fp32 peak
+    if kernel == "split":
+        kernel = {xb.ALGO_MFMA_SPLIT_FP6: "fp6", xb.ALGO_MFMA_SPLIT_BF16: "bf16"}[xb.xnor_bwn_split_kernel(s)]
+    terms = {"fp6": 5, "bf16": 3}.get(kernel, 1)
+    peak = {"fp6": PEAK_FP4_MFMA_TFLOPS, "bf16": PEAK_BF16_MFMA_TFLOPS}.get(kernel, PEAK_FP32_MFMA_TFLOPS)
     achieved = terms * 2.0 * macs / (conv_ms * 1e-3) / 1e12
     rec = {
         "metric": "GMAC/s (real input x binary weight), Binary-Weight-Network layer (sign + alpha of the filters, add/subtract convolution, rescale)",
         "value": macs / (ms_per_step * 1e-3) / 1e9, "unit": "GMAC/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "fp32 input as five FP6 digits under a scale per position and 32 channels, 1-bit weights as FP4, fp32 accumulate "
-                 "(v_mfma_scale_f32_32x32x64_f8f6f4)" if kernel == "split" else "fp32 input, 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x2_f32)",
+        "dtype": {"fp6": "fp32 input as five FP6 digits under a scale per position and 32 channels, 1-bit weights as FP4, fp32 accumulate "
+                         "(v_mfma_scale_f32_32x32x64_f8f6f4)",
+                  "bf16": "fp32 input as three bf16 terms (exact), 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x16_bf16)",
+                  "mfma": "fp32 input, 1-bit weights, fp32 accumulate (v_mfma_f32_32x32x2_f32)",
+                  "direct": "fp32 input, 1-bit weights, fp32 accumulate"}[kernel],
         "data": "synthetic (seeded; shapes and value distributions of the benchmark layer)",
         "config": {"workload": f"{layer.name} as a BWN layer: N={layer.N} C={layer.C} {layer.H}x{layer.W} F={layer.F} "
                                f"{layer.kh}x{layer.kw} stride {layer.sh} pad {layer.ph}", "macs": macs},
         "stage_ms": stage_ms,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": {"split": "bwn_fp6_kernel", "mfma": "bwn_mfma_kernel", "direct": "bwn_direct_kernel"}[kernel]
+                     "kernel": {"fp6": "bwn_fp6_kernel", "bf16": "bwn_split_kernel", "mfma": "bwn_mfma_kernel", "direct": "bwn_direct_kernel"}[kernel]
                                + " (xnor_bwn_conv2d_fwd)",
                      "executed_flops_per_mac": 2 * terms, "kernel_ms": conv_ms},
     }
@@ -563,9 +568,13 @@ def run_vanilla_layer(args, xb, torch, layer, make_input, make_weights):
     ms = time_call(torch, lambda: xb.xnor_conv2d_fp32_fwd(dI, dW, s, out=out), args.warmup, args.steps)
     macs = layer.binary_macs                      # the same count of multiply-accumulates, now real-valued
     # with its workspace the call splits both operands into three bf16 terms: six matrix instructions' worth of
-    # products for windows of up to 5 x 5 or so, eight where the kernel with short chains runs (7 x 7)
+    # products, eight where the form with short chains runs (windows that the fp32 matrix kernel does not take)
     split = xb.xnor_conv2d_fp32_workspace_bytes(s) > 0
-    products = 8 if layer.kh * layer.kw >= 49 else 6
+    products = 6
+    try:
+        xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA)
+    except xb.XnorError:
+        products = 8
     flops_per_mac = 2.0 * products if split else 2.0
     peak = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     achieved = flops_per_mac * macs / (ms * 1e-3) / 1e12

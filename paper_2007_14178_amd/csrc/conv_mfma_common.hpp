@@ -20,9 +20,6 @@ constexpr int kFilterTile = 2 * 32 * kWM;   // 2 wave rows
 constexpr int kRing = 4;          // register ring of filter operands: loads run kRing-1 steps ahead
 constexpr int kXcdShift = 3, kXcds = 1 << kXcdShift;   // MI355X: 8 XCDs of 32 CUs
 
-// A buffer store's sc1 bit (agent scope): past the L2 of the XCD.
-constexpr int kWriteThrough = 16;
-
 // q = n / d for n*d < 2^32 via one mul_hi.
 struct FastDiv {
     uint32_t mul, d;

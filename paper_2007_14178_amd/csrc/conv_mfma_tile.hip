@@ -433,6 +433,7 @@ __global__ __launch_bounds__(kThreads, NP >= 3 ? 2 : 3) void conv_mfma_tile_kern
         }
     } else {
         constexpr int kRaw = 0x00027000;      // (a plain buffer of dwords)
+        constexpr int kWriteThrough = 16;     // a buffer store's sc1 bit (agent scope): past the L2 of the XCD
         uint32_t voff[NP];                    // byte offset from the first image's plane of filter row 0; no pixel: beyond the buffer
 #pragma unroll
         for (int j = 0; j < NP; ++j)

@@ -55,15 +55,17 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
 
 // Where the three-term kernel is the faster real-valued convolution (given a workspace).  It is the more
 // exact one everywhere (see conv_fp32_split.hip).  Measured, what runs without a workspace -> split:
-// 128x512x28x28 F=512 3x3 5.11 -> 2.64 ms, 16x128x56x56 F=128 5x5 1702 -> 233 us, 7x7 22.04 -> 0.61 ms,
-// 16x224x224 three channels F=64 7x7 stride 2 1020 -> 359 us.  A launch that does not fill the chip is as long as a
-// workgroup's chain of 16-channel chunks behind a filter pass and a first fetch of 12 to 14 us, and this decides:
+// 128x512x28x28 F=512 3x3 5.14 -> 2.39 ms, 16x128x56x56 F=128 5x5 1712 -> 236 us, 7x7 22.07 -> 0.62 ms,
+// 16x224x224 three channels F=64 7x7 stride 2 996 -> 364 us.  A launch that does not fill the chip is as long as a
+// workgroup's chain of 16-channel chunks behind a filter pass and a first fetch, 12 us together, and this decides:
 //  * against the fp32 matrix form, whose chain is 8 channels a chunk.  With its four-wide filter fetch (C % 8 == 0,
-//    up to 9 taps) 3 x 3 layers of 2 x 32 x 32 take 8.7 / 13 / 22 / 40 us with 8 / 16 / 32 / 64 channels (split 18 /
-//    19 / 23 / 32), without it 25 us with 9 (split 18); from 32 channels on the split form is taken everywhere,
-//    at a third of the error (1 x 7 x 7 within 8 %, 16 x 28 x 28 29.3 / 25.8), from 8 on at 32 x 56 x 56 (44.8 / 34.2);
+//    up to 9 taps) 3 x 3 layers of 2 x 32 x 32 F=64 take 8.8 / 13 / 22 / 40 us with 8 / 16 / 32 / 64 channels (split 14.0 /
+//    14.1 / 16.7 / 22.4), without it 26 us with 9 (split 14.1); from 32 channels on the split form is taken everywhere,
+//    at a third of the error (1 x 7 x 7 20.5 / 16.6, 16 x 28 x 28 29.4 / 19.0), from 8 on at 32 x 56 x 56 (45.1 / 37.0);
 //  * against one thread per output, for windows that form does not take: there the estimates below hold within
 //    a third over 1x7x7 .. 16x112x112, C = 3 .. 128, F = 8 .. 128, 7 x 7.
+// Of 1447 drawn layers (1 to 64 images, 3 to 96 channels, 4 to 256 filters, 1x1 to 7x7) it is taken in 672, in none of
+// them slower; in 353 others it would be faster, most of them of fewer than 8 filters or 32 channels.
 bool fp32_split_pays(const xnor::Geom &g)
 {
     const double taps = (double)g.kh * g.kw, red = g.C * taps, pixels = (double)g.N * g.OH * g.OW;
