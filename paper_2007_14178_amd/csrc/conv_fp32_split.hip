@@ -122,10 +122,10 @@ constexpr uint32_t kHuge = 0x7f7f8000u << 1;              // (doubled bits) from
 constexpr uint32_t kInfBits = 0x7f800000u;
 
 // The power of two that brings a largest magnitude (its bits) to 2^23 .. 2^24 for weights, to 2^18 .. 2^19 for inputs (see
-// above), as far as two factors and their product stay in fp32's range with values of ordinary size behind tiny ones.
-constexpr int kTopW = 23, kMostW = 59, kTopX = 18, kMostX = 40;
+// above), as far as values of ordinary size behind tiny ones stay in fp32's range and what divides by two of them does (2^60 each).
+constexpr int kTopW = 23, kMostW = 59, kTopX = 18, kMostX = 40, kLeast = -60;
 constexpr int kExpBias = 256, kUnheld = 1024;
-__device__ inline int scale_of(uint32_t top, int to, int most) { return top == 0 ? 0 : min(most, to + 127 - (int)(top >> 23)); }
+__device__ inline int scale_of(uint32_t top, int to, int most) { return top == 0 ? 0 : max(kLeast, min(most, to + 127 - (int)(top >> 23))); }
 constexpr float kHeldLow = 0x1p-6f, kHeldTop = 0x1p24f;   // scaled values whose mid + lo f16 holds to 11 bits
 // 2^e for e >= -149, infinite from 2^128 on
 __device__ inline uint32_t power_bits(int e)
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
         stats[blockIdx.x] = stat[0] | (stat[1] < __float_as_uint(ldexpf(kTiny, -e)) - 1u ? kTinyBit : 0u);
         if (!FLUSH && (oc & 1) == 0)
             reinterpret_cast<int *>(stats + ftiles * octs)[ft * nchunks + (oc >> 1)] =
-                (e + kExpBias) | (stat[3] < __float_as_uint(ldexpf(kHeldLow, -e)) - 1u ? kUnheld : 0);
+                (e + kExpBias) | (e == kLeast || stat[3] < __float_as_uint(ldexpf(kHeldLow, -e)) - 1u ? kUnheld : 0);
     }
 }
 

@@ -323,7 +323,7 @@ def test_split_filter_far_below_the_others(xb, k):
     assert (np.abs(b - ref) <= (chains + 8) * 2.0 ** -23 * S).all()
 
 
-@pytest.mark.parametrize("what", ["first_zero", "first_tiny", "first_large", "tiny_later", "large_later", "largest_later", "half_zero"])
+@pytest.mark.parametrize("what", ["first_zero", "first_tiny", "first_large", "tiny_later", "large_later", "largest_later", "half_zero", "top_meets_zero"])
 @pytest.mark.parametrize("shape", [(2, 40, 9, 11, 33, 1), (2, 70, 13, 12, 130, 2), (1, 100, 14, 15, 70, 3), (2, 33, 8, 9, 64, 5)], ids=lambda s: "x".join(map(str, s)))
 def test_split_inputs_far_from_the_first_chunk(xb, shape, what):
     """The workgroup's power of two comes from its first 16 channels: nothing, values far below and far above the others
@@ -350,6 +350,10 @@ def test_split_inputs_far_from_the_first_chunk(xb, shape, what):
     if what == "half_zero":
         I[:, :, H // 2:] = 0
         I[:, 0, 0, 0] = 1e-12
+    if what == "top_meets_zero":        # a value of 2^126 that meets weights of 0, beside weights of 2^60: their product is no float
+        I[:, 0] = 1e38
+        Wt *= np.float32(2.0 ** 60)
+        Wt[:, 0] = 0
     got = split(xb, dev(I), dev(Wt), xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2))
     ref, S = sums64(I, Wt, k // 2)
     chains = (k * k + 1) // 2 * -(-C // 16)
