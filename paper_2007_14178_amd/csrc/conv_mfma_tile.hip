@@ -666,20 +666,18 @@ hipError_t launch_conv_mfma_tile(const uint32_t *Ipk, const float *K, const floa
     p.wgs_per_xcd = ceil_div((long long)p.ptiles * p.fgroups, kXcds);
     p.Wp = pl.Wp; p.RHfull = pl.RHfull; p.S2 = pl.S2; p.T = pl.T; p.tile_steps = pl.tile_steps; p.pitch16 = pl.pitch16;
     // Where the planes of `out` and `dot` begin on 64-byte boundaries, their stores leave the L2 as they come (agent
-    // scope): otherwise it is written back when the kernel ends, while nothing computes.  On 16-byte boundaries only, neighbouring
-    // planes share 64-byte units, which the memory-side cache puts together for the first 40 MiB or so and memory is written
-    // twice for past it.  Planes that begin anywhere share 16-byte units.  Written back / through by time, 1x1 and 3x3, 64 and 256
-    // channels and filters, 8 / 32 / 64 / 100 / 160 MB of outputs:
-    //   64-byte boundaries, 4 x 4 to 64 x 64     1.01 / 1.14 / 1.11 / 1.08 / 1.05
-    //   16-byte boundaries, 10 x 10 to 66 x 66   1.01 / 1.06 / 1.00 / 0.96 / 0.90   (44 MB: 1.01 at 14 x 14, 1.03 at 50 x 50)
-    // us per launch, written back -> through:
-    //   64 x 256 x 28 x 28 F=512 1x1  27.6 -> 22.3   16 x 128 x 56 x 56 F=128 5x5     15.7 -> 14.0
-    //   64 x 128 x 28 x 28 F=128 3x3  10.6 -> 9.4    64 x 128 x 28 x 28 F=256 3x3 s2   8.7 -> 8.3 (196 pixels)
-    //   1 x 256 x 14 x 14 F=256 3x3    5.2 -> 5.3    16 x 128 x 54 x 54 F=128 3x3     11.0 -> 10.9
-    // and for planes of 169, 729, 12321 and 12210 (8-byte boundaries) pixels 18.8 -> 19.6, 11.1 -> 11.7, 16.8 -> 18.7, 14.0 -> 15.7.
+    // scope): otherwise it is written back when the kernel ends, while nothing computes.  Planes that begin elsewhere share 64-byte
+    // units with their neighbours, which are written twice then: while the kernel runs past 45 MB or so, and when the next one reads
+    // them before.  Written back / through by time, 1x1 and 3x3, 64 to 256 channels and filters:
+    //   MB of outputs                                       8     13     20     32     38     64    100    160
+    //   64-byte boundaries, alone                         1.01                 1.14          1.11   1.08   1.05
+    //     with a kernel that reads the outputs next       1.00   1.01   1.01   1.01   1.03   1.06
+    //   16-byte boundaries, alone                         1.01                 1.06          1.00   0.96   0.90
+    //     with a kernel that reads the outputs next       0.99   0.92   0.87   0.81   0.78
+    // us per launch, written back -> through: 64 x 256 x 28 x 28 F=512 1x1 27.6 -> 22.3, 16 x 128 x 56 x 56 F=128 5x5 15.7 -> 14.0,
+    // 64 x 128 x 28 x 28 F=128 3x3 10.6 -> 9.4.
     const uintptr_t at = reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(dot) | (uintptr_t)g.OH * g.OW * 4;
-    const long long stored = (long long)g.N * g.F * g.OH * g.OW * (dot ? 8 : 4);
-    p.write_through = (at & 63) == 0 || ((at & 15) == 0 && stored <= 40LL << 20);
+    p.write_through = (at & 63) == 0;
     p.tab16 = pl.slots_max * pl.pitch16;
     p.al16 = p.tab16 + (pl.T + kTabTail + 3) / 4;
     p.a16 = p.al16 + ft / 4;
