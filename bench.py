@@ -567,10 +567,10 @@ def run_vanilla_layer(args, xb, torch, layer, make_input, make_weights):
     out = torch.empty((s.N, s.F, OH, OW), dtype=torch.float32, device="cuda")
     ms = time_call(torch, lambda: xb.xnor_conv2d_fp32_fwd(dI, dW, s, out=out), args.warmup, args.steps)
     macs = layer.binary_macs                      # the same count of multiply-accumulates, now real-valued
-    # with its workspace the call splits both operands into three bf16 terms: six matrix instructions' worth of
-    # products, eight where the form with short chains runs (windows that the fp32 matrix kernel does not take)
+    # with its workspace the call splits both operands: into two f16 terms (three products) in layers of many terms, else into
+    # three, whose six products are eight where the form with short chains runs (windows that the fp32 matrix kernel does not take)
     split = xb.xnor_conv2d_fp32_workspace_bytes(s) > 0
-    products = 6
+    products = 3 if xb.xnor_conv2d_fp32_pairs_workspace_bytes(s) else 6
     try:
         xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA)
     except xb.XnorError:
@@ -583,7 +583,8 @@ def run_vanilla_layer(args, xb, torch, layer, make_input, make_weights):
         "value": macs / (ms * 1e-3) / 1e9, "unit": "GMAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "fp32 input and weights, fp32 accumulate " +
-                 (f"(each operand split into three bf16 terms, {products} products, v_mfma_f32_32x32x16_bf16/f16)" if split
+                 (f"(each operand split into {'two f16' if products == 3 else 'three bf16'} terms, {products} products, "
+                  f"v_mfma_f32_32x32x16_{'f16' if products == 3 else 'bf16/f16'})" if split
                   else "(v_mfma_f32_32x32x2_f32)"),
         "data": "synthetic (seeded; shapes and value distributions of the benchmark layer)",
         "config": {"workload": f"{layer.name} as a real-valued layer: N={layer.N} C={layer.C} {layer.H}x{layer.W} "

@@ -75,7 +75,7 @@ typedef enum {
     XNOR_ALGO_MFMA_TILE = 7,  /* ... with many small workgroups: by name, whatever XNOR_ALGO_MFMA takes
                                (the _algo calls only; tests and measurements)                     */
     XNOR_ALGO_MFMA_SPLIT = 5, /* xnor_bwn_conv2d_fwd_algo: the fp32 input split into terms, one of the two below;
-                               xnor_conv2d_fp32_fwd_ws: both operands split into bf16 terms          */
+                               xnor_conv2d_fp32_fwd_ws: both operands split into terms               */
     XNOR_ALGO_MFMA_SPLIT_FP6 = 8, /* xnor_bwn_conv2d_fwd_algo: five FP6 digits with a scale per position and 32
                                channels, v_mfma_scale_f32_32x32x64_f8f6f4 against +-1 weights, and       */
     XNOR_ALGO_MFMA_SPLIT_BF16 = 9 /* ... three bf16 terms, v_mfma_f32_32x32x16_bf16: by name, whatever
@@ -360,16 +360,19 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
 
 /*
  * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
- * both operands split exactly into three bf16 terms whose products are summed in fp32 by the bf16 and f16
- * matrix instructions (the smallest ones, together at most 2^-16 of the whole, from terms rounded to 11 bits, or by
- * the bf16 instruction alone beside values that f16 would not hold so).  Results are
+ * both operands split into terms whose products are summed in fp32 by the bf16 and f16 matrix instructions: exactly, into
+ * three bf16 terms (the smallest products, together at most 2^-16 of the whole, from terms rounded to 11 bits, or by
+ * the bf16 instruction alone beside values that f16 would not hold so), or, in layers of at least 2560 terms, into two f16
+ * terms that hold a value to within 2^-23 (of values below 2^-20 of the largest beside them 2^-40 of that one is lost; where
+ * that could be more than 1e-5 of an output it is formed from three terms or in 64 bits).  Results are
  * closer to the exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32
  * arithmetic gives them, and an output so small that bits of a value below 2^-133 (or 2^-133 of what lies beside it)
  * could matter to it is formed by the plain fp32 sum.
  *   workspace  caller-owned device scratch of `workspace_bytes` bytes, 16-byte aligned, or NULL; the
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes
- * bytes are given, else what xnor_conv2d_fp32_fwd takes.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_WORKSPACE for a
+ * bytes are given, else what xnor_conv2d_fp32_fwd takes.  Two terms take xnor_conv2d_fp32_pairs_workspace_bytes bytes;
+ * with fewer the split kernel works on three.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_WORKSPACE for a
  * workspace that is missing or too small; XNOR_E_UNSUPPORTED for kh*kw > 49, OH*OW > 2^24, C*H*W >= 2^29,
  * F*C*kh*kw >= 2^28, or where the input under 32 output pixels exceeds 512 staged positions (384 for shapes that
  * XNOR_ALGO_MFMA does not take).  Other values as in xnor_conv2d_fp32_fwd_algo.
@@ -377,7 +380,10 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
  *   xnor_conv2d_fp32_algo_workspace_bytes   host only; the same for the kernel that `algo` asks for:
  *                                           XNOR_E_UNSUPPORTED where the call would return it, 0 for kernels
  *                                           that use none.
+ *   xnor_conv2d_fp32_pairs_workspace_bytes  host only; 0 for layers that are not split into two terms, whatever the
+ *                                           workspace.
  */
+int xnor_conv2d_fp32_pairs_workspace_bytes(const xnor_shape *s, size_t *bytes);
 int xnor_conv2d_fp32_workspace_bytes(const xnor_shape *s, size_t *bytes);
 int xnor_conv2d_fp32_algo_workspace_bytes(const xnor_shape *s, int algo, size_t *bytes);
 int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,

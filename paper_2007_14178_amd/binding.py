@@ -114,6 +114,7 @@ def _load() -> ctypes.CDLL:
     L.xnor_conv2d_fp32_fwd.argtypes = [vp, vp, sp, vp, vp]
     L.xnor_conv2d_fp32_fwd_algo.argtypes = [vp, vp, sp, vp, ci, vp]
     L.xnor_conv2d_fp32_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
+    L.xnor_conv2d_fp32_pairs_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
     L.xnor_conv2d_mfma_kernel.argtypes = [sp]
     L.xnor_conv2d_algo_workspace_bytes.argtypes = [sp, ci, ci, ctypes.POINTER(sz)]
     L.xnor_filter_expand_algo.argtypes = [vp, sp, vp, sz, ci, vp]
@@ -137,7 +138,7 @@ def _load() -> ctypes.CDLL:
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
                  "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
-                 "xnor_conv2d_fp32_workspace_bytes", "xnor_conv2d_fp32_algo_workspace_bytes",
+                 "xnor_conv2d_fp32_workspace_bytes", "xnor_conv2d_fp32_algo_workspace_bytes", "xnor_conv2d_fp32_pairs_workspace_bytes",
                  "xnor_conv2d_mfma_kernel", "xnor_conv2d_algo_workspace_bytes", "xnor_filter_expand_algo",
                  "xnor_conv2d_fwd_expanded_algo", "xnor_conv2d_fwd_chain_algo"):
         getattr(L, name).restype = ci
@@ -534,24 +535,37 @@ def xnor_conv2d_fp32_workspace_bytes(s: Shape, algo: int = ALGO_AUTO) -> int:
     return nbytes
 
 
+def xnor_conv2d_fp32_pairs_workspace_bytes(s: Shape) -> int:
+    """Workspace with which xnor_conv2d_fp32_fwd splits both operands into two terms, not three; 0 if it never does."""
+    nbytes = s.__dict__.get("_fp32_pairs_ws")
+    if nbytes is None:
+        n = ctypes.c_size_t()
+        _ok(lib.xnor_conv2d_fp32_pairs_workspace_bytes(ctypes.byref(s.c()), ctypes.byref(n)), "xnor_conv2d_fp32_pairs_workspace_bytes")
+        nbytes = n.value
+        object.__setattr__(s, "_fp32_pairs_ws", nbytes)
+    return nbytes
+
+
 def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch.Tensor | None = None,
                          algo: int = ALGO_AUTO, workspace: torch.Tensor | None | str = "auto") -> torch.Tensor:
     """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out.
 
     ``workspace``: a uint8 GPU tensor, None (run a kernel that needs none), or "auto" (allocate what
-    xnor_conv2d_fp32_workspace_bytes asks for)."""
+    xnor_conv2d_fp32_pairs_workspace_bytes or else xnor_conv2d_fp32_workspace_bytes asks for)."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
         out = I.new_empty(oshape, dtype=torch.float32)
     if isinstance(workspace, str):
         nbytes = xnor_conv2d_fp32_workspace_bytes(s, algo) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
-        try:
-            workspace = I.new_empty((nbytes,), dtype=torch.uint8) if nbytes else None
-        except torch.OutOfMemoryError:
-            if algo != ALGO_AUTO:
-                raise
-            workspace = None            # (a kernel that needs none)
+        sizes = [n for n in (xnor_conv2d_fp32_pairs_workspace_bytes(s), nbytes) if n] if nbytes else []
+        workspace = None
+        while sizes and workspace is None:
+            try:
+                workspace = I.new_empty((sizes.pop(0),), dtype=torch.uint8)
+            except torch.OutOfMemoryError:
+                if not sizes and algo != ALGO_AUTO:     # (else three terms, or a kernel that needs none)
+                    raise
     _ok(lib.xnor_conv2d_fp32_fwd_ws(
         _dev(I, torch.float32, (s.N, s.C, s.H, s.W), "I"), _dev(Wt, torch.float32, (s.F, s.C, s.kh, s.kw), "Wt"),
         ctypes.byref(s.c()), _dev(out, torch.float32, oshape, "out"),

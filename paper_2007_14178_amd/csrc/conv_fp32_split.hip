@@ -46,6 +46,31 @@
 //   Bound by power as much as by time: a register-only loop of the bf16 instruction on random operands keeps 1.74 GHz, this
 //   1.77.  One wave per SIMD with four tiles (half the filter loads) was slower.
 //
+// Pairs (layers of many terms, see takes_pairs): both operands as two f16 terms, x = h + l, each the nearest f16 to what is
+// left, and three products of them on the f16 instruction, l * h + h * l + h * h: half the matrix instructions.  A pair holds
+// 22 significant bits and a sign, all of x in three values of four and all but its last bit in the others; with l * l left
+// out a product is off by 8e-8 of itself on average.  The sums make up for it: a chain takes all taps of a chunk up to nine or ten,
+// where the six products' takes two (the rounding of the outputs' sums is the larger part of a long sum's error).  Against
+// 64-bit sums, normal values, six products / pairs:
+//   3 x 3, 128, 256, 512 channels: 1.23e-7 1.67e-7 2.30e-7 / 1.59e-7 1.67e-7 1.82e-7;  5 x 5, 64, 128, 512: 1.36e-7 1.86e-7
+//   3.59e-7 / 1.63e-7 1.74e-7 2.30e-7;  positive values 0.95e-7 to 3.0e-7 / 0.63e-7 to 1.5e-7.
+// us: 128 x 512 x 28 x 28 F=512 3x3 2360 -> 1280, 16 x 128 x 56 x 56 F=128 5x5 247 -> 144, 4 x 512 x 20 x 20 F=128 3x3 102 -> 78.
+//   Powers of two for f16's range: a filter tile's chunk has its own, and so has a workgroup's chunk of the input: its largest
+// magnitude is found when its values arrive, a chunk ahead of their commit.  Values of 2^-20 of their chunk's largest and more keep
+// 2^-19 of themselves, smaller ones 2^-40 of the largest.  What all of those can do to an output is bounded by their number
+// (one or two in 10^7 of normal values); a wave forms the few outputs below 2^17 times that one by one, in 64 bits (one workgroup
+// of some thousand has any).  Where there are more of them, or a value without a power of two (infinite, NaN, of 2^-46 or
+// 2^74), or an output that came out infinite, NaN or below 2^-120, the workgroup's outputs are formed from three terms as in
+// the layers without pairs: log-normal values (sigma 4), one filter of 1e-11 (both stop at once: 1.02 to 1.1 times that form's
+// time), half an image of zeros but for one 1e-12 (after the whole sum: 1.5 times).
+//   conv_fp32_split_kernel<.., PAIR> has the tiles and the staging of the other forms, 80 bytes a position.  The A operands
+// are a ring of three taps (two where the window's taps are no multiple of three) in registers, an operand fetched again behind
+// its last use, 26 (14) matrix instructions ahead.  What it measured at the first layer: pairs with the six products' loop
+// 1435 us, with one buffer descriptor for an image in place of one a plane and without a load at the head of a chunk 1355, with the
+// ring, and granules for the positions that there are (240; 384 had been handled), 1275.  Matrix pipe busy 63 % of the cycles at 1.72 GHz;
+// a loop of the matrix instructions alone takes 895 us, at the card's power.  Timing-only builds: without A loads
+// 12 % shorter, without B reads 9, without commits 15.
+//
 // FLUSH: where the layer would otherwise run one thread per output, whose sums are formed from short
 // chains, that is still the less exact of the two.  This form keeps two accumulators per output: the
 // matrix instructions sum two taps of a chunk, then that sum is added to the other accumulator and what the
@@ -101,6 +126,9 @@ struct Fp32SplitParams {
     const unsigned char *Wx;       // split filters
     const uint32_t *wstat;         // one word per (filter tile, 8 channels): kTinyBit | largest magnitude
     const int *wexp;               // per (filter tile, chunk): kUnheld | the power of two its weights are stored times + kExpBias
+    const unsigned char *Wp;       // pairs: split filters, the power of two of each (filter tile, chunk), and per (filter tile,
+    const int *pexp;               //   8 channels) the weights that a pair holds in part, kNotHeld and more where none do
+    const uint32_t *plow;
     float *out;
     int N, C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW;
     int nchunks, ftiles;
@@ -133,6 +161,29 @@ __device__ inline uint32_t power_bits(int e)
     return e > 127 ? kInfBits : e > -127 ? (uint32_t)(e + 127) << 23 : 1u << max(0, e + 149);
 }
 
+// Pairs: a chunk's largest magnitude is brought to 2^14 .. 2^15, by at most 2^kPairMost or 2^-kPairMost; a scaled value below
+// kPairLow that is not zero counts as held in part.
+constexpr int kPairTop = 14, kPairMost = 60;
+constexpr float kPairLow = 0x1p-6f;
+constexpr uint32_t kNotHeld = 1u << 20, kPairMostLow = 1024;
+constexpr int kPairFew = 4;             // doubtful outputs that a wave forms one by one
+constexpr float kPairLeast = 0x1p-120f;
+constexpr int kPairPosBytes = 2 * 32 + 16, kPairOperandBytes = 2 * 1024;
+// Taps of a chunk in a chain.
+__host__ __device__ constexpr int pair_chain_taps(int taps) { return taps % 3 == 0 ? 9 : 10; }
+__device__ inline int pair_chains(int taps) { return (taps + pair_chain_taps(taps) - 1) / pair_chain_taps(taps); }
+__device__ inline bool pair_chain_negated(int chunk, int tap, int taps)
+{
+    return (chunk * pair_chains(taps) + tap / pair_chain_taps(taps)) & 1;
+}
+// the power of two for a largest magnitude (its bits), `held`: there is one
+__device__ inline int pair_exp(uint32_t top, bool &held)
+{
+    const int e = kPairTop + 127 - (int)(top >> 23);
+    held = top == 0 || (e >= -kPairMost && e <= kPairMost);
+    return top == 0 ? kPairMost : e;
+}
+
 // two fp32 -> two bf16 in one dword, to nearest even (one v_cvt_pk_bf16_f32)
 __device__ inline uint32_t pack_bf16(float a, float b)
 {
@@ -145,6 +196,13 @@ __device__ inline uint32_t pack_f16(float a, float b)
     const floatx2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
 }
+// what the f16 pair `t` leaves of (a, b); exact
+__device__ inline void subtract_pair_f16(float &a, float &b, uint32_t t)
+{
+    const halfx2 h = __builtin_bit_cast(halfx2, t);
+    a = fmaf(-1.f, (float)h.x, a);
+    b = fmaf(-1.f, (float)h.y, b);
+}
 // what the bf16 pair `t` leaves of (a, b); exact
 __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
 {
@@ -156,14 +214,14 @@ __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
 // memory) into LDS, then per (tap, filter) eight values from LDS, split, and 16-byte writes of 32 lanes side by
 // side.  4 bytes read and 8 (6) written per weight.  The chunk's other eight channels are read for their
 // magnitudes alone: the chunk has one power of two.
-template <bool FLUSH>
+template <bool FLUSH, bool PAIR>
 __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__restrict__ Wt, int F, int C, int taps, int nchunks, int ftiles,
-                                                                 uint32_t inv_run, unsigned char *__restrict__ Wx)
+                                                                 uint32_t inv_run, unsigned char *__restrict__ Wx, unsigned char *__restrict__ Wp)
 {
     extern __shared__ float wl[];
-    __shared__ uint32_t stat[4];
+    __shared__ uint32_t stat[5];
     const int octs = 2 * nchunks;
-    if (threadIdx.x < 4) stat[threadIdx.x] = threadIdx.x & 1 ? 0xffffffffu : 0u;
+    if (threadIdx.x < 5) stat[threadIdx.x] = threadIdx.x == 1 || threadIdx.x == 3 ? 0xffffffffu : 0u;
     __syncthreads();
     uint32_t top = 0, low = 0xffffffffu;         // of the magnitudes' bits; low: less one (0 - 1 wraps to the top)
     constexpr int kBatch = 8;                    // loads of a thread in flight
@@ -222,6 +280,10 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
     __syncthreads();
     const int e = FLUSH ? 0 : scale_of(stat[2], kTopW, kMostW);
     unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * operand_bytes(FLUSH) + (oc & 1) * 512;
+    bool pair_held = false;
+    const int pe = PAIR ? pair_exp(stat[2], pair_held) : 0;
+    unsigned char *const pdst = Wp + ((size_t)ft * nchunks + (oc >> 1)) * taps * kPairOperandBytes + (oc & 1) * 512;
+    uint32_t lows = 0;
     for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
         const int f = i & 31, t = i >> 5;
         const bool negated = chain_negated(FLUSH, oc >> 1, t, taps);               // (every other chain: see above)
@@ -242,6 +304,30 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
         o[64] = make_uint4(m[0], m[1], m[2], m[3]);
         o[128] = make_uint4(l[0], l[1], l[2], l[3]);
         if constexpr (!FLUSH) o[192] = make_uint4(r[0], r[1], r[2], r[3]);
+        if constexpr (PAIR) {
+            const float by = pair_chain_negated(oc >> 1, t, taps) ? -ldexpf(1.f, pe) : ldexpf(1.f, pe);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float a = by * wl[f * pitch + (2 * k) * taps + t], b = by * wl[f * pitch + (2 * k + 1) * taps + t];
+                lows += (wl[f * pitch + (2 * k) * taps + t] != 0.f && fabsf(a) < kPairLow) + (wl[f * pitch + (2 * k + 1) * taps + t] != 0.f && fabsf(b) < kPairLow);
+                h[k] = pack_f16(a, b);
+                subtract_pair_f16(a, b, h[k]);
+                l[k] = pack_f16(a, b);
+            }
+            uint4 *q = reinterpret_cast<uint4 *>(pdst + (size_t)t * kPairOperandBytes + f * 16);
+            q[0] = make_uint4(h[0], h[1], h[2], h[3]);
+            q[64] = make_uint4(l[0], l[1], l[2], l[3]);
+        }
+    }
+    if constexpr (PAIR) {
+        if (lows) atomicAdd(&stat[4], lows);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            // (stat[0], unlike stat[2], has the infinities and the NaN of this half)
+            int *const pexps = reinterpret_cast<int *>(Wp + (size_t)ftiles * nchunks * taps * kPairOperandBytes);
+            if ((oc & 1) == 0) pexps[ft * nchunks + (oc >> 1)] = pe;
+            reinterpret_cast<uint32_t *>(pexps + ftiles * nchunks)[blockIdx.x] = pair_held && stat[0] < kInfBits ? min(stat[4], kNotHeld) : kNotHeld;
+        }
     }
     if (threadIdx.x == 0) {
         uint32_t *stats = reinterpret_cast<uint32_t *>(Wx + (size_t)ftiles * nchunks * taps * operand_bytes(FLUSH));
@@ -401,6 +487,431 @@ struct Order<8> {      // mid*lo, lo*mid, lo*hi, hi*lo, mid*mid, mid*hi, hi*mid,
     int load_a[8] = {3, -1, 2, -1, -1, 1, -1, 0}, read_b[8] = {3, -1, -1, 2, -1, -1, 1, 0};
 };
 
+// The output pixel of lane column `col` in tile j of the workgroup, clamped to the image for the reads, and whether it exists.
+__device__ __attribute__((always_inline)) inline bool tile_pixel(const Fp32SplitParams &p, int t0, int X0, int Y0, int tw_shift, int j, int col, int &oy, int &ox)
+{
+    if (p.tw == 0) {
+        const int OHW = p.OH * p.OW, px = (t0 + j) * 32 + col, pxc = min(px, OHW - 1);
+        oy = pxc / p.OW;
+        ox = pxc - oy * p.OW;
+        return px < OHW;
+    }
+    const int jy = j / p.tx, jx = j - jy * p.tx;
+    oy = Y0 + jy * (32 >> tw_shift) + (col >> tw_shift);
+    ox = X0 + jx * p.tw + (col & (p.tw - 1));
+    const bool in = oy < p.OH && ox < p.OW;
+    oy = min(oy, p.OH - 1);
+    ox = min(ox, p.OW - 1);
+    return in;
+}
+
+// Largest of a wave's values, in every lane.
+__device__ inline uint32_t wave_max(uint32_t v)
+{
+    auto step = [&](auto ctrl) __attribute__((always_inline)) {
+        v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    step(std::integral_constant<int, 0x111>{});      // within a row of 16: 1, 2, 4 and 8 lanes on
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});      // a row's last lane to the next row, then to the upper half
+    step(std::integral_constant<int, 0x143>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// A wave's work in the form with pairs: false where the workgroup's outputs are to be formed from three terms after all (the
+// same for all its waves).  Arguments as for split_wave; fw0: the workgroup's first filter.
+template <int NT, int GRAN, int RING>
+__device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &p, int n, int f0, int fw0, int t0, int X0, int Y0,
+                                                         int oy0, int iy0, int ix0, int rows, int tile0)
+{
+    // LDS: two input buffers, taken in turn by the chunks, each [npos][high, low][16 channels]
+    extern __shared__ unsigned char lds_raw[];
+    constexpr int kGran = GRAN, kTiles = NT > 0 ? NT : 1;
+    const int tile_bytes = p.npos * kPairPosBytes;
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int OHW = p.OH * p.OW, taps = p.kh * p.kw, HW = p.H * p.W;
+    const int tw_shift = p.tw ? 31 - __builtin_clz((unsigned)p.tw) : 5;
+    auto pixel_of = [&](int j, int &oy, int &ox) -> bool { return tile_pixel(p, t0, X0, Y0, tw_shift, j, col, oy, ox); };
+    int base[kTiles];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int oy, ox;
+        pixel_of(tile0 + j, oy, ox);
+        base[j] = ((oy - oy0) * p.sh * p.pitch + (ox * p.sw - p.pw - ix0)) * kPairPosBytes + half * 16;
+    }
+    // Words behind the buffers: the waves' largest magnitudes of a chunk, by its parity; how many values of even and of odd chunks
+    // are held in part; is there an output to be formed again?
+    uint32_t *const words = reinterpret_cast<uint32_t *>(lds_raw + 2 * tile_bytes);
+
+    // Staging, granules and the places of values as in split_wave.
+    const float *img = p.I + (size_t)n * p.C * HW;
+    const int tl = threadIdx.x & 127;
+    const int oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7);
+    uint32_t voff[kGran];
+    int wr_off[kGran];
+#pragma unroll
+    for (int q = 0; q < kGran; ++q) {
+        const int pos = min(q * 128 + tl, p.npos - 1);
+        wr_off[q] = pos * kPairPosBytes + oct * 16;
+        const uint32_t r = quot((uint32_t)pos, p.inv_pitch);
+        const int xw = (int)((uint32_t)pos - r * (uint32_t)p.pitch);
+        const int iy = iy0 + (int)r, ix = ix0 + xw;
+        const bool ok = (int)r < rows && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
+        voff[q] = ok ? (uint32_t)(iy * p.W + ix) * 4u : kOutside;
+    }
+    float first[kGran][8], nxt[kGran][8];
+    // (a channel past the last one reads that one again: its weights are zeros, and its largest magnitude is counted already)
+    const auto image = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(img), 0, p.C * HW * 4, kRaw);
+    auto prefetch = [&](float (&to)[kGran][8], int ch) __attribute__((always_inline)) {
+        const int c0 = ch * kChan + 8 * oct;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int at = min(c0 + k, p.C - 1) * (HW * 4);
+#pragma unroll
+            for (int q = 0; q < kGran; ++q) to[q][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(image, (int)voff[q], at, 0));
+        }
+    };
+    // a chunk's largest magnitude, this wave's part, for the scale of its commit
+    auto put_top = [&](float (&of)[kGran][8], int ch) __attribute__((always_inline)) {
+        float m = 0.f;                           // (propagates NaN)
+#pragma unroll
+        for (int q = 0; q < kGran; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; k += 2)
+                m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(of[q][k])), fabsf(of[q][k + 1]));
+        const uint32_t top = wave_max(__float_as_uint(m) & ~kTinyBit);
+        if (lane == 0) words[4 * (ch & 1) + (threadIdx.x >> 6)] = top;
+    };
+    // The power of two of the chunk to be committed next, of the one being multiplied, the smallest so far; of the first, in bits.
+    int xexp = 0, xexp_now = 0, xleast = kPairMost;
+    float xscale = 1.f;
+    uint32_t xlow = 0;                           // below it a (doubled) value is held in part
+    auto take_scale = [&](const uint4 &t) __attribute__((always_inline)) -> bool {
+        const uint32_t top = __builtin_amdgcn_readfirstlane((int)max(max(t.x, t.y), max(t.z, t.w)));
+        bool held;
+        xexp = pair_exp(top, held);
+        held = held && top < kInfBits;
+        xleast = min(xleast, xexp);
+        xscale = __uint_as_float((uint32_t)(127 + xexp) << 23);
+        xlow = (__float_as_uint(kPairLow) - ((uint32_t)xexp << 23)) << 1;
+        return held;
+    };
+    auto tops_of = [&](int ch) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(words + 4 * (ch & 1)); };
+    constexpr int kPieces = 2 * kGran + 1, kUnits = 5;
+    float pv[4];
+    uint32_t ph[2], lows = 0;
+    auto commit_unit = [&](float (&from)[kGran][8], auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
+        constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
+        if constexpr (S < 2 * kGran) {
+            constexpr int q = S >> 1, hf = S & 1;
+            if constexpr (U == 0) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) pv[k] = from[q][4 * hf + k] * xscale;
+            } else if constexpr (U == 1) {       // (0 less one wraps to the top)
+                uint32_t u = 0xffffffffu;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u = min(u, (__float_as_uint(from[q][4 * hf + k]) << 1) - 1u);
+                lows += u < xlow - 1u;           // (four at most)
+            } else if constexpr (U == 2) {
+                ph[0] = pack_f16(pv[0], pv[1]);
+                ph[1] = pack_f16(pv[2], pv[3]);
+            } else if constexpr (U == 3) {
+                subtract_pair_f16(pv[0], pv[1], ph[0]);
+                subtract_pair_f16(pv[2], pv[3], ph[1]);
+            } else if constexpr (U == 4) {
+                uint2 *dst = reinterpret_cast<uint2 *>(lds_raw + (ch & 1) * tile_bytes + wr_off[q] + hf * 8);
+                dst[0] = make_uint2(ph[0], ph[1]);
+                dst[4] = make_uint2(pack_f16(pv[0], pv[1]), pack_f16(pv[2], pv[3]));
+            }
+        } else if constexpr (U == 0) {
+            prefetch(nxt, ch + 1);
+        }
+    };
+    auto commit_piece = [&](float (&from)[kGran][8], auto piece_c, int ch) __attribute__((always_inline)) {
+        commit_unit(from, piece_c, std::integral_constant<int, 0>{}, ch);
+        commit_unit(from, piece_c, std::integral_constant<int, 1>{}, ch);
+        commit_unit(from, piece_c, std::integral_constant<int, 2>{}, ch);
+        commit_unit(from, piece_c, std::integral_constant<int, 3>{}, ch);
+        commit_unit(from, piece_c, std::integral_constant<int, 4>{}, ch);
+    };
+    auto commit_rest = [&](float (&of)[kGran][8], int from, int ch) __attribute__((always_inline)) {
+        if (from <= 0) commit_piece(of, std::integral_constant<int, 0>{}, ch);
+        if (from <= 1) commit_piece(of, std::integral_constant<int, 1>{}, ch);
+        if constexpr (kGran > 1) {
+            if (from <= 2 && p.npos > 128) commit_piece(of, std::integral_constant<int, 2>{}, ch);
+            if (from <= 3 && p.npos > 128) commit_piece(of, std::integral_constant<int, 3>{}, ch);
+        }
+        if constexpr (kGran > 2) {
+            if (from <= 4 && p.npos > 256) commit_piece(of, std::integral_constant<int, 4>{}, ch);
+            if (from <= 5 && p.npos > 256) commit_piece(of, std::integral_constant<int, 5>{}, ch);
+        }
+        static_assert(kGran <= 3, "two lines per granule");
+    };
+
+    // The A operands of both filter tiles walk linearly through the workspace: a ring of RING taps, an operand fetched again behind
+    // its last use.
+    const int ft0 = f0 >> 5, ft1 = min(ft0 + 1, p.ftiles - 1);
+    const int per_tile = p.nchunks * taps * kPairOperandBytes;      // (all of them less than 2 GiB)
+    const auto operands = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(p.Wp), 0, p.ftiles * per_tile, kRaw);
+    int wx = ft0 * per_tile;                     // of the next tap to be fetched (past the last one: that one again, unused)
+    const int wx_last = wx + per_tile - kPairOperandBytes, to_second = (ft1 - ft0) * per_tile, lane16 = lane * 16;
+    uint4 a[RING][2][2];                         // [tap][filter tile][high, low]
+    auto load_a = [&](int slot, int i, int term) __attribute__((always_inline)) {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(operands, lane16 + term * 1024, wx + (i ? to_second : 0), 0);
+        a[slot][i][term] = make_uint4(v.x, v.y, v.z, v.w);
+    };
+    auto next_a = [&]() __attribute__((always_inline)) { wx = min(wx + kPairOperandBytes, wx_last); };
+
+    // the powers of two of both filter tiles in 64 chunks, a lane each
+    uint32_t wexps = 0;
+    auto load_exps = [&](int ch) __attribute__((always_inline)) {
+        const int c = min(ch + lane, p.nchunks - 1);
+        wexps = (uint32_t)(p.pexp[ft0 * p.nchunks + c] + kExpBias) | (uint32_t)(p.pexp[ft1 * p.nchunks + c] + kExpBias) << 16;
+    };
+
+    prefetch(first, 0);
+    prefetch(nxt, 1);
+    load_exps(0);
+    if constexpr (NT > 0) {
+#pragma unroll
+        for (int slot = 0; slot < RING; ++slot) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) load_a(slot, k & 1, 1 - (k >> 1));
+            next_a();
+        }
+    }
+    // the workgroup's filters: weights held in part, the smallest power of two
+    uint32_t partly = 0;
+    int wleast = kPairMost;
+    {
+        const int fa = fw0 >> 5, fb = min(fa + 2 * p.fwaves, p.ftiles);
+        for (int i = fa * 2 * p.nchunks + lane; i < fb * 2 * p.nchunks; i += 64) partly = min(partly + p.plow[i], kNotHeld);
+        for (int i = fa * p.nchunks + lane; i < fb * p.nchunks; i += 64) wleast = min(wleast, p.pexp[i]);
+        wleast = 512 - (int)wave_max((uint32_t)(512 - wleast));
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) partly = min(partly + (uint32_t)__shfl_xor((int)partly, m), kNotHeld);
+        partly = __builtin_amdgcn_readfirstlane((int)partly);
+    }
+    put_top(first, 0);
+    if (threadIdx.x < 3) words[8 + threadIdx.x] = 0;
+    __syncthreads();
+    bool stop = partly >= kPairMostLow;          // (uniform over the workgroup)
+    stop |= !take_scale(tops_of(0));
+    xexp_now = xexp;
+    commit_rest(first, 0, 0);
+    put_top(nxt, 1);
+    if (lows) atomicAdd(&words[8], 4 * lows);
+    lows = 0;
+    __syncthreads();
+
+    floatx16 acc[2][kTiles], chain[2][kTiles];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0.f; chain[i][j][r] = 0.f; }
+    uint32_t counts[2] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)words[8]), 0};
+    uint32_t sign = 0;                           // that the current chain's weights are stored with
+    for (int ch = 0; ch < p.nchunks && !stop; ++ch) {
+        const bool more = ch + 1 < p.nchunks;
+        int pc = more ? 0 : kPieces;             // the next piece of chunk ch + 1 to commit
+        if constexpr (NT > 0) {
+            const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
+            auto read_b = [&](uint4 &to, int term, int byte_off) __attribute__((always_inline)) {
+                to = *reinterpret_cast<const uint4 *>(tile_r + byte_off + 32 * term);
+            };
+            uint4 bh[kTiles], bl[kTiles];        // of the current tap
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                read_b(bh[j], 0, base[j]);
+                read_b(bl[j], 1, base[j]);
+            }
+            if (more) stop |= !take_scale(tops_of(ch + 1));
+            if ((ch & 63) == 0 && ch > 0) load_exps(ch);
+            const uint32_t exps = (uint32_t)__builtin_amdgcn_readlane((int)wexps, ch & 63);
+            const uint32_t e0 = (uint32_t)(127 + kExpBias - xexp_now - (int)(exps & 0xffffu)) << 23, e1 = (uint32_t)(127 + kExpBias - xexp_now - (int)(exps >> 16)) << 23;
+            // a chain joins the output's sum, without the scales and the sign of its operands
+            auto settle = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float by = __uint_as_float((i ? e1 : e0) ^ sign);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            acc[i][j][r] = fmaf(by, chain[i][j][r], acc[i][j][r]);
+                            chain[i][j][r] = 0.f;
+                        }
+                }
+                sign ^= 0x80000000u;
+            };
+            const int row_step = (p.pitch - p.kw + 1) * kPairPosBytes;
+            int kx = 0, off = 0, left = taps, in_chain = pair_chain_taps(taps);
+            // A tap, its operands in slot `slot` of the ring, with pieces FIRST .. FIRST + COUNT - 1 of the commit: low * high, high * low,
+            // high * high of each tile, an operand fetched again behind its last use, the next tap's place found between.
+            auto tap_body = [&](auto slot_c, auto first_c, auto count_c) __attribute__((always_inline)) {
+                constexpr int slot = decltype(slot_c)::value, FIRST = decltype(first_c)::value, COUNT = decltype(count_c)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                auto unit = [&](auto m_c) __attribute__((always_inline)) {
+                    constexpr int M = decltype(m_c)::value;
+                    if constexpr (M < 6 * NT) {
+                        constexpr int j = M / 6, P = M % 6 / 2, i = M & 1, ta = P == 0 ? 1 : 0;
+                        chain[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[slot][i][ta]), __builtin_bit_cast(halfx8, P == 1 ? bl[j] : bh[j]),
+                                                                             chain[i][j], 0, 0, 0);
+                        if constexpr (M == 1) {
+                            const bool wrap = kx + 1 == p.kw;
+                            --left;
+                            kx = wrap ? 0 : kx + 1;
+                            off = left > 0 ? off + (wrap ? row_step : kPairPosBytes) : 0;
+                        }
+                        if constexpr (j == NT - 1 && P != 1) load_a(slot, i, ta);
+                        if constexpr (i == 1 && P == 1) read_b(bl[j], 1, base[j] + off);
+                        if constexpr (i == 1 && P == 2) read_b(bh[j], 0, base[j] + off);
+                        constexpr int piece = (M - 1) / kUnits, u = (M - 1) % kUnits;
+                        if constexpr (M >= 1 && piece < COUNT) commit_unit(nxt, std::integral_constant<int, FIRST + piece>{}, std::integral_constant<int, u>{}, ch + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                for_units(unit);
+                next_a();
+            };
+            // RING taps, with the pieces from FIRST on, NT to a tap
+            auto body = [&](auto first_c) __attribute__((always_inline)) {
+                constexpr int FIRST = decltype(first_c)::value;
+                using std::integral_constant;
+                tap_body(integral_constant<int, 0>{}, integral_constant<int, FIRST>{}, integral_constant<int, std::max(0, std::min(NT, kPieces - FIRST))>{});
+                tap_body(integral_constant<int, 1>{}, integral_constant<int, FIRST + NT>{}, integral_constant<int, std::max(0, std::min(NT, kPieces - FIRST - NT))>{});
+                if constexpr (RING == 3)
+                    tap_body(integral_constant<int, 2>{}, integral_constant<int, FIRST + 2 * NT>{}, integral_constant<int, std::max(0, std::min(NT, kPieces - FIRST - 2 * NT))>{});
+                in_chain -= RING;
+                if (in_chain == 0 && left > 0) { settle(); in_chain = pair_chain_taps(taps); }
+            };
+            constexpr int kPer = RING * NT;
+            if (more) {
+                if (left >= RING) { body(std::integral_constant<int, 0>{}); pc = std::min(kPer, kPieces); }
+                if constexpr (kPer < kPieces) if (left >= RING) { body(std::integral_constant<int, kPer>{}); pc = std::min(2 * kPer, kPieces); }
+                if constexpr (2 * kPer < kPieces) if (left >= RING) { body(std::integral_constant<int, 2 * kPer>{}); pc = std::min(3 * kPer, kPieces); }
+                if constexpr (3 * kPer < kPieces) if (left >= RING) { body(std::integral_constant<int, 3 * kPer>{}); pc = std::min(4 * kPer, kPieces); }
+            }
+            while (left >= RING) body(std::integral_constant<int, kPieces>{});
+            if constexpr (RING == 2) {
+                if (left > 0) {                  // one tap: the ring turns by one
+                    tap_body(std::integral_constant<int, 0>{}, std::integral_constant<int, kPieces>{}, std::integral_constant<int, 0>{});
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint4 t = a[0][k >> 1][k & 1];
+                        a[0][k >> 1][k & 1] = a[1][k >> 1][k & 1];
+                        a[1][k >> 1][k & 1] = t;
+                    }
+                }
+            }
+            settle();
+        } else {
+            if (more) stop |= !take_scale(tops_of(ch + 1));
+        }
+        if (pc < kPieces) {                      // what the chunk's steps did not carry
+            commit_rest(nxt, pc, ch + 1);
+            prefetch(nxt, ch + 2);
+        }
+        xexp_now = xexp;
+        if (lows) { atomicAdd(&words[8 + ((ch + 1) & 1)], 4 * lows); lows = 0; }
+        if (more) put_top(nxt, ch + 2);
+        __syncthreads();                         // chunk ch has been read, chunk ch + 1 is written
+        // (written before the barrier, and again only behind the next one)
+        counts[(ch + 1) & 1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[8 + ((ch + 1) & 1)]);
+        stop |= counts[0] + counts[1] >= kPairMostLow;
+    }
+    // What values held in part (at most 2^-25, scaled, of each is lost) can do to an output, times 2^17: the bar of 1e-5.
+    const uint32_t count = partly + counts[0] + counts[1];
+    const float doubtful = (float)count * ldexpf(1.f, 17 - 25 + kPairTop + 1 - xleast - wleast);
+    bool again = stop;
+    uint32_t few[kTiles];
+    int number = 0;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int oy, ox;
+        few[j] = 0;
+        if (pixel_of(tile0 + j, oy, ox)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float v = fabsf(acc[i][j][r]);
+                    const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                    if (f < p.F) {
+                        again |= !(v <= 3.402823466e38f) || (v < kPairLeast && v > 0.f);
+                        few[j] |= v < doubtful ? 1u << (16 * i + r) : 0u;
+                    }
+                }
+        }
+        number += __builtin_popcount(few[j]);
+    }
+    if (__any(number != 0)) {
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) number += __shfl_xor(number, m);
+        again |= number > kPairFew;
+    }
+    if (__any(again) && lane == 0) words[10] = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane((int)words[10]) != 0) return false;
+    float *dst = p.out + (size_t)n * p.F * OHW;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        int oy, ox;
+        if (pixel_of(tile0 + j, oy, ox)) {
+            const int px = oy * p.OW + ox;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int f = f0 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                    if (f < p.F) dst[(size_t)f * OHW + px] = acc[i][j][r];
+                }
+        }
+    }
+    // (none of them but by chance where values are of one size)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        for (unsigned long long who; (who = __ballot(few[j] != 0)) != 0;) {
+            const int l = __builtin_ctzll(who);
+            const int bit = __builtin_ctz(__builtin_amdgcn_readlane((int)few[j], l));
+            int oy, ox;
+            pixel_of(tile0 + j, oy, ox);
+            oy = __builtin_amdgcn_readlane(oy, l);
+            ox = __builtin_amdgcn_readlane(ox, l);
+            const int r = bit & 15, f = f0 + (bit >> 4) * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+            const float *w = p.Wt + (size_t)f * p.C * taps;
+            double sum = 0.;                     // (a lane a channel, loads of four channels in flight)
+            for (int t = 0; t < taps; ++t) {
+                const int ky = t / p.kw, iy = oy * p.sh - p.ph + ky, ix = ox * p.sw - p.pw + t - ky * p.kw;
+                if ((unsigned)iy >= (unsigned)p.H || (unsigned)ix >= (unsigned)p.W) continue;
+                for (int c = lane; c < p.C; c += 256) {
+                    float x[4], y[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int ck = min(c + 64 * k, p.C - 1);
+                        x[k] = img[(size_t)ck * HW + iy * p.W + ix];
+                        y[k] = w[(size_t)ck * taps + t];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) sum = fma(c + 64 * k < p.C ? (double)x[k] : 0., (double)y[k], sum);
+                }
+            }
+#pragma unroll
+            for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
+            if (lane == l) {
+                dst[(size_t)f * OHW + oy * p.OW + ox] = (float)sum;
+                few[j] &= few[j] - 1;
+            }
+        }
+    }
+    return true;
+}
+
 // The work of one wave with NT pixel tiles (0: it only takes part in the staging).  X0, Y0: the output
 // pixel of the workgroup's first tile (tw > 0); ix0, iy0: the input position of the staged block's corner.
 template <int NT, bool FLUSH, int GRAN>
@@ -416,24 +927,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     const int OHW = p.OH * p.OW;
     const int taps = p.kh * p.kw;
     const int HW = p.H * p.W;
-    // the pixel of lane `col` in tile j of the workgroup (clamped to the image for the reads) and
-    // whether it exists
     const int tw_shift = p.tw ? 31 - __builtin_clz((unsigned)p.tw) : 5;
-    auto pixel_of = [&](int j, int &oy, int &ox) -> bool {
-        if (p.tw == 0) {
-            const int px = (t0 + j) * 32 + col, pxc = min(px, OHW - 1);
-            oy = pxc / p.OW;
-            ox = pxc - oy * p.OW;
-            return px < OHW;
-        }
-        const int jy = j / p.tx, jx = j - jy * p.tx;
-        oy = Y0 + jy * (32 >> tw_shift) + (col >> tw_shift);
-        ox = X0 + jx * p.tw + (col & (p.tw - 1));
-        const bool in = oy < p.OH && ox < p.OW;
-        oy = min(oy, p.OH - 1);
-        ox = min(ox, p.OW - 1);
-        return in;
-    };
+    auto pixel_of = [&](int j, int &oy, int &ox) -> bool { return tile_pixel(p, t0, X0, Y0, tw_shift, j, col, oy, ox); };
     int base[NT > 0 ? NT : 1];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -973,7 +1468,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     }
 }
 
-template <bool FLUSH, int GRAN>
+template <bool FLUSH, int GRAN, int PAIR, int RING>
 __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitParams p)
 {
     int b = blockIdx.x;
@@ -1010,6 +1505,16 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitP
     int my_nt = (wp + 1) * nt / wps - tile0;
     const int f0 = (h * p.fwaves + wf) * 64;
     if (f0 >= p.F) my_nt = 0;                             // no filters for this wave: staging only
+    if constexpr (PAIR > 0) {
+        const int fw0 = h * p.fwaves * 64;
+        bool done;
+        switch (my_nt) {
+            case 0: done = pair_wave<0, PAIR, RING>(p, n, 0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+            case 1: done = pair_wave<1, PAIR, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+            default: done = pair_wave<2, PAIR, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+        }
+        if (done) return;
+    }
     switch (my_nt) {
         case 0: split_wave<0, FLUSH, GRAN>(p, n, 0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
         case 1: split_wave<1, FLUSH, GRAN>(p, n, f0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
@@ -1095,7 +1600,8 @@ const Plan &make_plan(const Geom &g)
     });
 }
 
-template <bool FLUSH, int GRAN>
+// PAIR: granules of a thread in the form with pairs, 0 in the others
+template <bool FLUSH, int GRAN, int PAIR = 0, int RING = 0>
 hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
 {
     if (lds > 64 * 1024) {
@@ -1105,23 +1611,33 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
         if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
         const unsigned long long bit = 1ull << (dev & 63);
         if (!(raised.load() & bit)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN, PAIR, RING>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                                      2 * max_pos(GRAN) * pos_bytes(FLUSH) + word_bytes(FLUSH));
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }
     }
-    conv_fp32_split_kernel<FLUSH, GRAN><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
+    conv_fp32_split_kernel<FLUSH, GRAN, PAIR, RING><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
     return hipGetLastError();
 }
 
 }  // namespace
 
 namespace {
-// The workspace: split filters, their words, their powers of two.
+// Layers whose sums are long enough that pairs are no less exact than six products: 160 (tap, chunk) steps, 2560 terms.  The
+// errors are equal at 144 (3 x 3 on 256 channels 1.67e-7 both, 5 x 5 on 96 1.68e-7 against 1.63e-7) and 1.70e-7 against
+// 1.76e-7 at 162; below, six products, at 1.1 to 1.3 times the time of pairs.
+bool takes_pairs(const Geom &g, const Plan &pl)
+{
+    const long long taps = g.kh * g.kw, nchunks = ceil_div(g.C, kChan);
+    return pl.ok && !pl.flush && pl.granules == kGranules && taps >= 4 && taps * nchunks >= 160 &&
+           ceil_div(g.F, 32) * nchunks * taps * kPairOperandBytes < (1LL << 31);     // (32-bit offsets)
+}
+
+// The workspace: split filters, their words, their powers of two; of layers that take them the pairs, their powers and words.
 struct Layout {
-    size_t wstat, wexp, bytes;
+    size_t wstat, wexp, bytes, pairs, pexp, plow, pair_bytes;
 };
 Layout layout_of(const Geom &g, bool flush)
 {
@@ -1130,6 +1646,10 @@ Layout layout_of(const Geom &g, bool flush)
     l.wstat = ftiles * nchunks * g.kh * g.kw * operand_bytes(flush);
     l.wexp = l.wstat + ftiles * nchunks * 2 * sizeof(uint32_t);
     l.bytes = l.wexp + (flush ? 0 : ftiles * nchunks * sizeof(int));
+    l.pairs = (l.bytes + 255) / 256 * 256;
+    l.pexp = l.pairs + ftiles * nchunks * g.kh * g.kw * kPairOperandBytes;
+    l.plow = l.pexp + ftiles * nchunks * sizeof(int);
+    l.pair_bytes = l.plow + ftiles * nchunks * 2 * sizeof(uint32_t);
     return l;
 }
 }  // namespace
@@ -1140,7 +1660,14 @@ size_t conv_fp32_split_workspace_bytes(const Geom &g)
     return pl.ok ? layout_of(g, pl.flush).bytes : 0;
 }
 
-hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace, hipStream_t st)
+size_t conv_fp32_pairs_workspace_bytes(const Geom &g)
+{
+    const Plan &pl = make_plan(g);
+    return takes_pairs(g, pl) ? layout_of(g, false).pair_bytes : 0;
+}
+
+hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace, size_t workspace_bytes,
+                                  hipStream_t st)
 {
     const Plan &pl = make_plan(g);
     if (!pl.ok) return hipErrorInvalidValue;
@@ -1151,6 +1678,10 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     p.I = I; p.Wt = Wt; p.Wx = ws; p.out = out;
     p.wstat = reinterpret_cast<const uint32_t *>(ws + l.wstat);
     p.wexp = reinterpret_cast<const int *>(ws + l.wexp);
+    const bool pairs = takes_pairs(g, pl) && workspace_bytes >= l.pair_bytes;
+    p.Wp = ws + l.pairs;
+    p.pexp = reinterpret_cast<const int *>(ws + l.pexp);
+    p.plow = reinterpret_cast<const uint32_t *>(ws + l.plow);
     p.N = g.N; p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
     p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW;
     p.nchunks = ceil_div(g.C, kChan); p.ftiles = ceil_div(g.F, 32);
@@ -1161,11 +1692,18 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
     const long long blocks = (long long)g.N * p.groups * p.fgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t filter_lds = (size_t)32 * ((8 * taps) | 1) * sizeof(float);
-    const auto split = pl.flush ? split_filters_kernel<true> : split_filters_kernel<false>;
+    const auto split = pl.flush ? split_filters_kernel<true, false> : pairs ? split_filters_kernel<false, true> : split_filters_kernel<false, false>;
     split<<<dim3((unsigned)(p.ftiles * 2 * p.nchunks)), dim3(kThreads), filter_lds, st>>>(Wt, g.F, g.C, taps, p.nchunks, p.ftiles,
-                                                                                          reciprocal(8ull * taps), ws);
+                                                                                          reciprocal(8ull * taps), ws, ws + l.pairs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (pairs) {
+        const bool three = taps % 3 == 0;
+        const unsigned b = (unsigned)blocks;
+        if (pl.npos <= 128) return three ? launch_form<false, kGranules, 1, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 1, 2>(p, b, pl.lds, st);
+        if (pl.npos <= 256) return three ? launch_form<false, kGranules, 2, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 2, 2>(p, b, pl.lds, st);
+        return three ? launch_form<false, kGranules, 3, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 3, 2>(p, b, pl.lds, st);
+    }
     if (pl.flush) return launch_form<true, kGranules>(p, (unsigned)blocks, pl.lds, st);
     return pl.granules == kGranules ? launch_form<false, kGranules>(p, (unsigned)blocks, pl.lds, st)
                                     : launch_form<false, kMostGranules>(p, (unsigned)blocks, pl.lds, st);

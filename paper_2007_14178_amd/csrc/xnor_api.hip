@@ -483,6 +483,16 @@ int xnor_conv2d_fp32_algo_workspace_bytes(const xnor_shape *s, int algo, size_t 
     }
 }
 
+int xnor_conv2d_fp32_pairs_workspace_bytes(const xnor_shape *s, size_t *bytes)
+{
+    if (!s || !bytes) return XNOR_E_NULL;
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    if (rc) return rc;
+    *bytes = xnor::conv_fp32_pairs_workspace_bytes(g);
+    return XNOR_OK;
+}
+
 int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s, float *out, void *workspace,
                             size_t workspace_bytes, int algo, void *stream)
 {
@@ -510,7 +520,7 @@ int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s
             const size_t need = xnor::conv_fp32_split_workspace_bytes(g);
             if (need == 0) return XNOR_E_UNSUPPORTED;
             if (!workspace || workspace_bytes < need) return XNOR_E_WORKSPACE;
-            return hip_status(xnor::launch_conv_fp32_split(I, Wt, g, out, workspace, (hipStream_t)stream));
+            return hip_status(xnor::launch_conv_fp32_split(I, Wt, g, out, workspace, workspace_bytes, (hipStream_t)stream));
         }
         default:
             return XNOR_E_UNSUPPORTED;

@@ -127,8 +127,9 @@ hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alph
 bool conv_fp32_mfma_supports(const Geom &g);
 hipError_t launch_conv_fp32_mfma(const float *I, const float *Wt, const Geom &g, float *out, hipStream_t st);
 size_t conv_fp32_split_workspace_bytes(const Geom &g);   // 0 if the shape is not supported
+size_t conv_fp32_pairs_workspace_bytes(const Geom &g);   // with which it works on pairs; 0 if it never does
 hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g, float *out, void *workspace,
-                                  hipStream_t st);
+                                  size_t workspace_bytes, hipStream_t st);
 hipError_t launch_conv_fp32_direct(const float *I, const float *Wt, const Geom &g, float *out, hipStream_t st);
 hipError_t launch_bwn_mfma(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
                            float *out, hipStream_t st);
