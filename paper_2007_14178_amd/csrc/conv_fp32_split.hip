@@ -1074,10 +1074,14 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     auto commit_rest = [&](int from, int ch) __attribute__((always_inline)) {
         if (from <= 0) commit_piece(std::integral_constant<int, 0>{}, ch);
         if (from <= 1) commit_piece(std::integral_constant<int, 1>{}, ch);
-        if (from <= 2 && p.npos > 128) commit_piece(std::integral_constant<int, 2>{}, ch);
-        if (from <= 3 && p.npos > 128) commit_piece(std::integral_constant<int, 3>{}, ch);
-        if (from <= 4 && p.npos > 256) commit_piece(std::integral_constant<int, 4>{}, ch);
-        if (from <= 5 && p.npos > 256) commit_piece(std::integral_constant<int, 5>{}, ch);
+        if constexpr (kGran > 1) {
+            if (from <= 2 && p.npos > 128) commit_piece(std::integral_constant<int, 2>{}, ch);
+            if (from <= 3 && p.npos > 128) commit_piece(std::integral_constant<int, 3>{}, ch);
+        }
+        if constexpr (kGran > 2) {
+            if (from <= 4 && p.npos > 256) commit_piece(std::integral_constant<int, 4>{}, ch);
+            if (from <= 5 && p.npos > 256) commit_piece(std::integral_constant<int, 5>{}, ch);
+        }
         if constexpr (kGran > 3) {
             if (from <= 6 && p.npos > 384) commit_piece(std::integral_constant<int, 6>{}, ch);
             if (from <= 7 && p.npos > 384) commit_piece(std::integral_constant<int, 7>{}, ch);
@@ -1170,6 +1174,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     __syncthreads();
     bool by_plain_sum = false;                 // (uniform over the workgroup)
     int ch = 0;
+    int wexp0 = 0, wexp1 = 0;                    // else: the present chunk's words of both filter tiles
     auto one_chunk = [&](auto products_c) __attribute__((always_inline)) {
         // (written before the barrier behind which it is read, and again only behind the next one)
         const uint32_t flag = FLUSH ? words[ch & 1] : words[ch & 1] & kTinyBit;
@@ -1250,7 +1255,7 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
                 if constexpr (4 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 4 * NT>{}, tap); ++tap; }
                 if constexpr (5 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 5 * NT>{}, tap); ++tap; }
                 if constexpr (6 * NT < kPieces) if (tap < taps) { tap_body(std::integral_constant<int, 6 * NT>{}, tap); ++tap; }
-                static_assert(kPieces == 7, "one line per tap that carries pieces");
+                static_assert(kPieces <= 7, "one line per tap that carries pieces");
                 pc = min(tap * NT, kPieces);
             }
             for (; tap < taps; ++tap) tap_body(std::integral_constant<int, -1>{}, tap);
@@ -1258,9 +1263,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
             // The sequence of (chain, pixel tile) steps, twelve or sixteen matrix instructions a tap; a step's B operands
             // are read during the step before, each behind the last use of its register, and the chunk's first
             // steps carry the pieces of the next chunk's commit.
-            const int we0 = p.wexp[ft0 * p.nchunks + ch], we1 = p.wexp[ft1 * p.nchunks + ch];
-            factor[0] = power_bits(kExpBias - xexp - (we0 & ~kUnheld));
-            factor[1] = power_bits(kExpBias - xexp - (we1 & ~kUnheld));
+            factor[0] = power_bits(kExpBias - xexp - (wexp0 & ~kUnheld));
+            factor[1] = power_bits(kExpBias - xexp - (wexp1 & ~kUnheld));
             const unsigned char *tile_r = lds_raw + (ch & 1) * tile_bytes;
             auto read_b = [&](uint4 &to, int term, int byte_off) __attribute__((always_inline)) {
                 to = *reinterpret_cast<const uint4 *>(tile_r + byte_off + 32 * term);
@@ -1376,12 +1380,22 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
         while (ch < p.nchunks && !by_plain_sum) one_chunk(std::integral_constant<int, 8>{});
     } else {
         // six products up to the first chunk with a value that f16 does not hold, eight from there on
+        // (scalar loads: vector loads at the head of a chunk wait for all loads before them)
+        typedef const __attribute__((address_space(4))) int *Words;
+        const Words w0 = (Words)(uintptr_t)(p.wexp + ft0 * p.nchunks), w1 = (Words)(uintptr_t)(p.wexp + ft1 * p.nchunks);
+        auto take_exps = [&]() __attribute__((always_inline)) {
+            wexp0 = w0[ch];
+            wexp1 = w1[ch];
+        };
         auto held = [&]() __attribute__((always_inline)) -> bool {
-            const int w = p.wexp[ft0 * p.nchunks + ch] | p.wexp[ft1 * p.nchunks + ch];
-            return (w & kUnheld) == 0 && (__builtin_amdgcn_readfirstlane((int)words[ch & 1]) & 0x7fffffff) != ch + 1;
+            take_exps();
+            return ((wexp0 | wexp1) & kUnheld) == 0 && (__builtin_amdgcn_readfirstlane((int)words[ch & 1]) & 0x7fffffff) != ch + 1;
         };
         while (ch < p.nchunks && !by_plain_sum && held()) one_chunk(std::integral_constant<int, 6>{});
-        while (ch < p.nchunks && !by_plain_sum) one_chunk(std::integral_constant<int, 8>{});
+        while (ch < p.nchunks && !by_plain_sum) {
+            take_exps();
+            one_chunk(std::integral_constant<int, 8>{});
+        }
     }
 
     if constexpr (NT > 0 && !FLUSH) {
@@ -1468,7 +1482,8 @@ __device__ __attribute__((always_inline)) void split_wave(const Fp32SplitParams 
     }
 }
 
-template <bool FLUSH, int GRAN, int PAIR, int RING>
+// RING: of the form with pairs, 0 for the others
+template <bool FLUSH, int GRAN, int RING>
 __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitParams p)
 {
     int b = blockIdx.x;
@@ -1505,13 +1520,13 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fp32_split_kernel(Fp32SplitP
     int my_nt = (wp + 1) * nt / wps - tile0;
     const int f0 = (h * p.fwaves + wf) * 64;
     if (f0 >= p.F) my_nt = 0;                             // no filters for this wave: staging only
-    if constexpr (PAIR > 0) {
+    if constexpr (RING > 0) {
         const int fw0 = h * p.fwaves * 64;
         bool done;
         switch (my_nt) {
-            case 0: done = pair_wave<0, PAIR, RING>(p, n, 0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-            case 1: done = pair_wave<1, PAIR, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
-            default: done = pair_wave<2, PAIR, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+            case 0: done = pair_wave<0, GRAN, RING>(p, n, 0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+            case 1: done = pair_wave<1, GRAN, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
+            default: done = pair_wave<2, GRAN, RING>(p, n, f0, fw0, t0, X0, Y0, oy0, iy0, ix0, rows, tile0); break;
         }
         if (done) return;
     }
@@ -1600,8 +1615,7 @@ const Plan &make_plan(const Geom &g)
     });
 }
 
-// PAIR: granules of a thread in the form with pairs, 0 in the others
-template <bool FLUSH, int GRAN, int PAIR = 0, int RING = 0>
+template <bool FLUSH, int GRAN, int RING>
 hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
 {
     if (lds > 64 * 1024) {
@@ -1611,15 +1625,28 @@ hipError_t launch_form(const Fp32SplitParams &p, unsigned blocks, size_t lds, hi
         if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
         const unsigned long long bit = 1ull << (dev & 63);
         if (!(raised.load() & bit)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN, PAIR, RING>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_fp32_split_kernel<FLUSH, GRAN, RING>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                                      2 * max_pos(GRAN) * pos_bytes(FLUSH) + word_bytes(FLUSH));
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }
     }
-    conv_fp32_split_kernel<FLUSH, GRAN, PAIR, RING><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
+    conv_fp32_split_kernel<FLUSH, GRAN, RING><<<dim3(blocks), dim3(kThreads), lds, st>>>(p);
     return hipGetLastError();
+}
+
+// With three granules a thread whatever the positions, a launch loads and commits the last position again and again, and a
+// chunk's head waited for all its loads where the powers of two came by vector loads.  Six products, us before and after both:
+// 32 x 512 x 14 x 14 F=512 1x1 71 / 62, 36 x 224 x 19 x 19 F=64 3x3 58.6 / 55.0, 16 x 128 x 56 x 56 F=128 7x7 (short chains) 585 both.
+template <bool FLUSH, int RING>
+hipError_t launch_granules(int granules, const Fp32SplitParams &p, unsigned blocks, size_t lds, hipStream_t st)
+{
+    static_assert(kGranules == 3, "one line per number of granules");
+    if (granules == 1) return launch_form<FLUSH, 1, RING>(p, blocks, lds, st);
+    if constexpr (!FLUSH)                        // (with short chains 63 registers of it are spilled)
+        if (granules == 2) return launch_form<FLUSH, 2, RING>(p, blocks, lds, st);
+    return launch_form<FLUSH, 3, RING>(p, blocks, lds, st);
 }
 
 }  // namespace
@@ -1697,16 +1724,11 @@ hipError_t launch_conv_fp32_split(const float *I, const float *Wt, const Geom &g
                                                                                           reciprocal(8ull * taps), ws, ws + l.pairs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (pairs) {
-        const bool three = taps % 3 == 0;
-        const unsigned b = (unsigned)blocks;
-        if (pl.npos <= 128) return three ? launch_form<false, kGranules, 1, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 1, 2>(p, b, pl.lds, st);
-        if (pl.npos <= 256) return three ? launch_form<false, kGranules, 2, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 2, 2>(p, b, pl.lds, st);
-        return three ? launch_form<false, kGranules, 3, 3>(p, b, pl.lds, st) : launch_form<false, kGranules, 3, 2>(p, b, pl.lds, st);
-    }
-    if (pl.flush) return launch_form<true, kGranules>(p, (unsigned)blocks, pl.lds, st);
-    return pl.granules == kGranules ? launch_form<false, kGranules>(p, (unsigned)blocks, pl.lds, st)
-                                    : launch_form<false, kMostGranules>(p, (unsigned)blocks, pl.lds, st);
+    const unsigned b = (unsigned)blocks;
+    const int granules = ceil_div(pl.npos, 128);
+    if (pl.flush) return launch_granules<true, 0>(granules, p, b, pl.lds, st);
+    if (!pairs) return granules > kGranules ? launch_form<false, kMostGranules, 0>(p, b, pl.lds, st) : launch_granules<false, 0>(granules, p, b, pl.lds, st);
+    return taps % 3 == 0 ? launch_granules<false, 3>(granules, p, b, pl.lds, st) : launch_granules<false, 2>(granules, p, b, pl.lds, st);
 }
 
 }  // namespace xnor
