@@ -23,8 +23,14 @@
 //   of the next step become FP4 codes between them.  The chunk's staging stands between two barriers; the two or
 //   more workgroups on a compute unit fill each other's.
 //
+//   Two shapes of workgroup more, where estimates of all say so (search_fp6_plan).  Splits: the waves of a pixel tile have filters
+//   of their own and share the tile's digits, so that a block is cut for more filters (128x384x13x13 F=384 3x3 107 -> 96 us).
+//   Stagers: three or four waves that only stage, into two buffers, a chunk ahead of the others, the next round's loads in
+//   flight while a round is cut: layers that leave units with one workgroup, whose chunk's chain nothing else hides
+//   (32x512x7x7 F=512 3x3 41 -> 29 us, 1x256x14x14 F=256 3x3 19 -> 13.5; 200 drawn layers with both 1.17 times as fast).
+//
 //   Bound by: the matrix pipe at the card's power (6.3 PFLOP/s of this pair of formats in a loop of random digits, 9.0 of
-//   zeros; an instruction takes 32 cycles), then by the digits' conversions (about 1200 cycles per 64 blocks,
+//   zeros; an instruction takes 32 cycles; the first layer above with nothing but its matrix instructions and stores takes 83 us), then by the digits' conversions (about 1200 cycles per 64 blocks,
 //   again for every filter group) and the wait for a chunk's loads, which other workgroups fill in part.
 //   Passes against the bf16 terms: 128x384x13x13 F=384 3x3 177 -> 104 us; loops of launches: 128x512x28x28 F=512 3x3
 //   1300 -> 706 us, 16x128x56x56 F=128 7x7 291 -> 116, 1x256x14x14 F=256 3x3 48 -> 23.
@@ -64,8 +70,13 @@ struct Fp6Params {
     float *out;
     int C, H, W, F, kh, kw, sh, sw, ph, pw, OH, OW, Cw;
     int G;                         // words per chunk (the last chunk of an odd number of words has one)
+    int splits, tiles;             // waves that share a pixel tile, each with filters of its own; pixel tiles of a workgroup
+    uint32_t inv_splits;
+    int stagers;                   // STAGERS: waves that only stage
     int wgs;                       // workgroups of an image (per filter group)
-    int fgroups, units;            // filter groups; N * wgs
+    int fgroups, units;            // filter groups, of splits * 32 * NF filters; N * wgs
+    uint32_t inv_row;              // of a row's words in LDS, splits * 32 * NF
+    int words_bytes;               // of a chunk's filter words in LDS
     int positions;                 // staged positions there is room for; the zero position is the next one
 };
 
@@ -164,7 +175,8 @@ __device__ inline void split_block(Block &b, char *at, bool keep)
     }
 }
 
-template <int NF>
+// SPLITS: more than one split, or stagers.
+template <int NF, bool SPLITS, bool STAGERS>
 struct Fp6Wave {
     static constexpr int kFilters = 32 * NF;
 
@@ -188,7 +200,7 @@ struct Fp6Wave {
     // One chunk's steps: two (tap, word) blocks each.  With two words in the chunk lane half h takes word h of the
     // step's tap, with one the word of tap 2 * step + h.
     static __device__ __attribute__((always_inline)) inline void steps(v16f (&acc)[NF], const Fp6Params &p, const char *dig, const uint32_t *words,
-                                                                       bool two, int iy, int ix, int row0, int half, int col)
+                                                                       int row, bool two, int iy, int ix, int row0, int half, int col)
     {
         const int taps = p.kh * p.kw, nsteps = two ? taps : (taps + 1) >> 1;
         const int word_bytes = (p.positions + 1) * kPosBytes, zero = p.positions * kPosBytes;
@@ -218,12 +230,12 @@ struct Fp6Wave {
             const v2u a = o[0], b = o[1], c = o[2];
             B[t] = (v6u){a.x, a.y, b.x, b.y, c.x, c.y};
         };
-        const uint32_t *wat = words + half * kFilters + col;
+        const uint32_t *wat = words + half * row + col;
         uint32_t wnext[NF];
         auto read_words = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int f = 0; f < NF; ++f) wnext[f] = wat[32 * f];
-            wat += 2 * kFilters;
+            wat += 2 * row;
         };
         v4i A[NF];
         auto expand = [&](int f) __attribute__((always_inline)) { A[f] = sign_codes(wnext[f]); };
@@ -271,21 +283,26 @@ struct Fp6Wave {
         const int taps = p.kh * p.kw;
         const int word_bytes = (p.positions + 1) * kPosBytes;
         const int G = p.G;
-        char *dig = smem;
-        uint32_t *words = reinterpret_cast<uint32_t *>(smem + G * word_bytes);
+        // one buffer for a chunk, or two taken in turn: digits, filter words
+        const int dig_bytes = G * word_bytes;
+        const int buffer = dig_bytes + p.words_bytes;
 
         // a unit's filter groups run one behind the other on one XCD (workgroup ids go round the eight)
         const int k = blockIdx.x >> 3, fg = k % p.fgroups, unit = (k / p.fgroups) * 8 + (blockIdx.x & 7);
         if (unit >= p.units) return;
-        const int n = unit / p.wgs, waves = nt >> 6;
+        const int n = unit / p.wgs, all_waves = nt >> 6, waves = STAGERS ? all_waves - p.stagers : all_waves;
+        const int tiles = SPLITS ? p.tiles : waves, tile = SPLITS ? (int)quot((uint32_t)wave, p.inv_splits) : wave;
+        const bool stager = STAGERS && wave >= waves;
         const int OHW = p.OH * p.OW, HW = p.H * p.W;
-        const int px0 = (unit - n * p.wgs) * waves * 32, px1 = min(OHW, px0 + waves * 32) - 1;
+        const int px0 = (unit - n * p.wgs) * tiles * 32, px1 = min(OHW, px0 + tiles * 32) - 1;
         const int row0 = max(0, px0 / p.OW * p.sh - p.ph);
         const int row1 = min(p.H - 1, px1 / p.OW * p.sh - p.ph + p.kh - 1);
         const int npos = max(0, row1 - row0 + 1) * p.W;       // <= p.positions
-        const int f0 = fg * kFilters, nfil = min(kFilters, p.F - f0);
+        // the workgroup's filters; the wave's (none of them may exist)
+        const int row_words = SPLITS ? p.splits * kFilters : kFilters, f_wg = fg * row_words;
+        const int f0 = SPLITS ? f_wg + (wave - tile * p.splits) * kFilters : f_wg, nfil = min(kFilters, p.F - f0);
 
-        const int px = px0 + wave * 32 + col;
+        const int px = px0 + tile * 32 + col;
         const int oy = px / p.OW, ox = px - oy * p.OW;
         const int iy = px < OHW ? oy * p.sh - p.ph : -128, ix = ox * p.sw - p.pw;
 
@@ -294,20 +311,23 @@ struct Fp6Wave {
             const_cast<float *>(p.I + (size_t)n * p.C * HW + (size_t)row0 * p.W), 0, 0x7fffffff, 0x00027000);
         const int plane = HW * 4;
         const int nchunks = (p.Cw + G - 1) / G;
-        for (int i = tid; i < G * (kPosBytes / 4); i += nt)
-            reinterpret_cast<uint32_t *>(dig + (i / (kPosBytes / 4)) * word_bytes + p.positions * kPosBytes)[i % (kPosBytes / 4)] = 0;
+        for (int i = tid; i < G * (kPosBytes / 4); i += nt) {
+            const int at = (i / (kPosBytes / 4)) * word_bytes + p.positions * kPosBytes;
+            reinterpret_cast<uint32_t *>(smem + at)[i % (kPosBytes / 4)] = 0;
+            if constexpr (STAGERS) reinterpret_cast<uint32_t *>(smem + buffer + at)[i % (kPosBytes / 4)] = 0;
+        }
 
-        // staging rounds of a chunk: nt blocks each, the positions of its first word and then those of its second
+        // staging rounds of a chunk by `count` waves from `first` on: 64 * count blocks each, the positions of its first word and then
+        // those of its second
         auto words_in = [&](int ch) { return min(G, p.Cw - ch * G); };
-        auto place_of = [&](int r, int &g, int &pos) __attribute__((always_inline)) {
-            const int i = r * nt + tid;
+        auto place_of = [&](int i, int &g, int &pos) __attribute__((always_inline)) {
             g = i >= npos ? 1 : 0;
             pos = i - (g ? npos : 0);
-            return i;
         };
-        auto load_round = [&](Block &b, int ch, int r) __attribute__((always_inline)) {
+        auto load_round = [&](Block &b, int ch, int i) __attribute__((always_inline)) {
             int g, pos;
-            if (place_of(r, g, pos) < npos * words_in(ch))
+            place_of(i, g, pos);
+            if (i < npos * words_in(ch))
                 load_block(b, in, pos * 4 + g * 32 * plane, ch * G * 32 * plane, plane, (ch + 1) * G * 32 <= p.C, p.C - 32 * (ch * G + g));
         };
         // Filter words go from memory into LDS without a register, 64 lanes' words side by side, in rows of the filters'
@@ -316,18 +336,33 @@ struct Fp6Wave {
         // lines and not one each, cost the loop an address per tile and were slower: 114 for 102 us at
         // 128x384x13x13 F=384 3x3.)
         const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint32_t *>(p.Wpk + (size_t)f0 * taps * p.Cw), 0, 0x7fffffff, 0x00027000);
-        auto load_words = [&](int ch) __attribute__((always_inline)) {
+            const_cast<uint32_t *>(p.Wpk + (size_t)f_wg * taps * p.Cw), 0, 0x7fffffff, 0x00027000);
+        const int f_last = min(row_words, p.F - f_wg) - 1;
+        auto load_words = [&](int ch, char *words, int first, int count) __attribute__((always_inline)) {
             const bool two = words_in(ch) == 2;
             const int rows = two ? 2 * taps : taps;
             auto *to = (__attribute__((address_space(3))) char *)words;
-            for (int item = wave; item * 64 < rows * kFilters; item += waves) {
-                const int i = item * 64 + lane, f = i % kFilters, row = min(i / kFilters, rows - 1);
+            for (int item = first; item * 64 < rows * row_words; item += count) {
+                const int i = item * 64 + lane, r = SPLITS ? (int)quot((uint32_t)i, p.inv_row) : i / kFilters, f = i - r * row_words, row = min(r, rows - 1);
                 const int tap = two ? row >> 1 : row, g = two ? row & 1 : 0;
-                const int at = (min(f, nfil - 1) * taps + tap) * (p.Cw * 4) + g * 4;
+                const int at = (min(f, f_last) * taps + tap) * (p.Cw * 4) + g * 4;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(wsrc, (__attribute__((address_space(3))) void *)(to + item * 256), 4, at,
                                                          ch * G * 4, 0, 0);
             }
+        };
+        auto stage = [&](int ch, int first, int count) __attribute__((always_inline)) {
+            char *const to = smem + (STAGERS ? (ch & 1) * buffer : 0);
+            load_words(ch, to + dig_bytes, first, count);
+            const int blocks = npos * words_in(ch);
+            for (int r = 0; r < blocks; r += 64 * count) {
+                const int i = r + 64 * first + lane;
+                int g, pos;
+                place_of(i, g, pos);
+                Block cur;
+                load_round(cur, ch, i);
+                split_block(cur, to + g * word_bytes + pos * kPosBytes, i < blocks);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the words are in LDS
         };
 
         v16f acc[NF];
@@ -335,26 +370,61 @@ struct Fp6Wave {
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[f][r] = 0.f;
+        auto multiply = [&](int ch) __attribute__((always_inline)) {
+            const char *const dig = smem + (STAGERS ? (ch & 1) * buffer : 0);
+            if (px0 + tile * 32 < OHW && nfil > 0)
+                steps(acc, p, dig, reinterpret_cast<const uint32_t *>(dig + dig_bytes) + (f0 - f_wg), row_words, words_in(ch) == 2, iy, ix, row0, half, col);
+        };
 
-        for (int ch = 0; ch < nchunks; ++ch) {
-            const int blocks = npos * words_in(ch);
-            __syncthreads();                             // the chunk before has been read
-            load_words(ch);
-            for (int r = 0; r * nt < blocks; ++r) {
-                int g, pos;
-                const bool keep = place_of(r, g, pos) < blocks;
-                Block cur;
-                load_round(cur, ch, r);
-                split_block(cur, dig + g * word_bytes + pos * kPosBytes, keep);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the words are in LDS
+        if constexpr (STAGERS) {
+            stage(0, wave, all_waves);
             __syncthreads();
-            if (px0 + wave * 32 < OHW)
-                steps(acc, p, dig, words, words_in(ch) == 2, iy, ix, row0, half, col);
+            if (stager) {
+                // a round's loads are in flight while the round before is cut into digits; lanes past the last block load that one
+                const int first = wave - waves, round = 64 * p.stagers;
+                auto load_ahead = [&](Block &b, int ch, int r) __attribute__((always_inline)) {
+                    const int i = min(r + 64 * first + lane, npos * words_in(ch) - 1);
+                    load_round(b, ch, i);
+                };
+                Block next;
+                if (nchunks > 1 && npos > 0) load_ahead(next, 1, 0);
+                for (int ch = 1; ch < nchunks; ++ch) {
+                    char *const to = smem + (ch & 1) * buffer;
+                    load_words(ch, to + dig_bytes, first, p.stagers);
+                    const int blocks = npos * words_in(ch);
+                    for (int r = 0; r < blocks; r += round) {
+                        Block cur = next;
+                        const bool last = r + round >= blocks;
+                        if (!last || ch + 1 < nchunks) load_ahead(next, last ? ch + 1 : ch, last ? 0 : r + round);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int i = r + 64 * first + lane;
+                        int g, pos;
+                        place_of(i, g, pos);
+                        split_block(cur, to + g * word_bytes + pos * kPosBytes, i < blocks);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // the words are in LDS: behind them there are the 32 loads of the next round, if there is one
+                    if (blocks > 0 && ch + 1 < nchunks) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __syncthreads();                     // chunk ch is there, chunk ch - 1 has been read
+                }
+                return;
+            }
+            for (int ch = 0; ch < nchunks; ++ch) {
+                multiply(ch);
+                if (ch + 1 < nchunks) __syncthreads();
+            }
+        } else {
+            for (int ch = 0; ch < nchunks; ++ch) {
+                __syncthreads();                         // the chunk before has been read
+                stage(ch, wave, all_waves);
+                __syncthreads();
+                multiply(ch);
+            }
         }
 
         // accumulator register r of a lane: filter row 8*(r/4) + 4*half + r%4 of the tile, pixel column `col`
-        if (px < OHW) {
+        if (px < OHW && nfil > 0) {
             float *dst = p.out + ((size_t)n * p.F + f0) * OHW + px;
 #pragma unroll
             for (int f = 0; f < NF; ++f)
@@ -367,31 +437,35 @@ struct Fp6Wave {
     }
 };
 
-template <int NF>
-__global__ __launch_bounds__(64 * kMaxWaves, 3) void bwn_fp6_kernel(Fp6Params p)
+template <int NF, bool SPLITS, bool STAGERS>
+__global__ __launch_bounds__(64 * kMaxWaves, STAGERS ? 4 : 3) void bwn_fp6_kernel(Fp6Params p)
 {
-    Fp6Wave<NF>::run(p);
+    Fp6Wave<NF, SPLITS, STAGERS>::run(p);
 }
 
 struct Fp6Plan {
     bool ok;
-    int nf, G, waves, wgs, positions;
+    int nf, G, splits, stagers, waves, wgs, positions;
     size_t lds;
     double cycles;                 // about what the launch takes (see kRouteCosts)
 };
 
 // LDS of a workgroup: the staged positions of G words and the zero position; the filter words of G * taps rows, up to
 // whole steps, and of two steps that are read ahead of use (the rows' last 64 words may reach into these).
-size_t fp6_lds(const Geom &g, int nf, int G, int positions)
+size_t fp6_words_bytes(const Geom &g, int filters, int G)
 {
     const int taps = g.kh * g.kw, steps = G == 2 ? taps : (taps + 1) / 2;
-    return (size_t)G * (positions + 1) * kPosBytes + (size_t)(steps + 2) * 8 * (32 * nf);
+    return (size_t)(steps + 2) * 8 * filters;
+}
+size_t fp6_lds(const Geom &g, int filters, int G, int positions, int buffers)
+{
+    return buffers * ((size_t)G * (positions + 1) * kPosBytes + fp6_words_bytes(g, filters, G));
 }
 
-// Most positions that a workgroup of `waves` tiles stages: whole rows under the output rows it can touch.
-long long fp6_positions(const Geom &g, int waves)
+// Most positions that a workgroup of `tiles` tiles stages: whole rows under the output rows it can touch.
+long long fp6_positions(const Geom &g, int tiles)
 {
-    const long long orows = std::min(g.OH, (32 * waves + g.OW - 2) / g.OW + 1);
+    const long long orows = std::min(g.OH, (32 * tiles + g.OW - 2) / g.OW + 1);
     return std::min((long long)g.H, (orows - 1) * g.sh + g.kh) * g.W;
 }
 
@@ -436,6 +510,51 @@ double fp6_cost(const Fp6Costs &c, const Geom &g, int nf, int G, int waves, int 
     return c.launch + full * batch(held) + (rest ? batch(rest) : 0.0);
 }
 
+// The same of a workgroup of `splits` x `t` multiplying waves and `stagers` that only stage.  A fit to 257000 timed launches of 1269 layers
+// (every shape of each: 1 to 128 images, 32 to 512 channels and filters, 1x1 to 7x7, 7 to 70 wide, strides 1 and 2), for the
+// time of the shape taken.  Against the shapes above alone it is 0.83 of the time on average (the best shapes of all 0.79); a shape
+// that it takes is more than 3 % slower in 1.3 % of the layers and more than 10 % in 0.3 %; without the margin, or with stagers beside
+// more filters a wave, more pixel tiles or more workgroups than units, where their waves and LDS cost what they save, in 3 % and 1.3 %.
+constexpr int kMaxSplits = 4;
+constexpr double kSplitMargin = 0.75;
+double fp6_split_cost(const Geom &g, int nf, int G, int splits, int t, int stagers, int positions, size_t lds, long long busiest)
+{
+    constexpr double kContended = 1.06, kConvert = 2520, kLoad = 1210, kChunk = 9520, kWords = 324, kStores = 2245, kSteps = 194;
+    constexpr double kStage = 0.81 * kConvert + 35, kStaged = 2330, kHandOver = 4510, kFirst = 1077, kMixed = 0.87;
+    const int taps = g.kh * g.kw, waves = splits * t, all = waves + stagers;
+    double mfma = 0, convert = 0, wait = 0, alone = kStores * nf;
+    auto chunks = [&](int n, int words) {
+        const double steps = (words == 2 ? taps : (taps + 1) / 2) * nf * kDigits * 32 + kSteps;
+        const double filter_words = kWords * taps * words * nf * splits * 0.5;
+        const int rounds = ceil_div((long long)positions * words, 64 * (stagers ? stagers : waves));
+        mfma += n * steps;
+        convert += (double)n * rounds * kConvert * (stagers ? stagers : waves);
+        if (stagers) {
+            alone += n * std::max(steps + kHandOver, rounds * kStage + filter_words / stagers + kStaged);
+            wait += n * 30;
+        } else {
+            const double w = kChunk + rounds * kLoad + filter_words / waves;
+            alone += n * (steps + rounds * kConvert + w);
+            wait += n * w;
+        }
+    };
+    chunks(g.Cw / G, G);
+    if (g.Cw % G) chunks(1, 1);
+    double less = 1.0;
+    if (stagers) {
+        const int rounds = ceil_div((long long)positions * G, 64 * all);
+        alone += rounds * (kConvert + kLoad) + kFirst;
+        wait += rounds * kLoad + kFirst;
+        less += 0.033 * std::max(0, ceil_div((long long)positions * G, 64 * stagers) - 1) + 0.26 * std::max(0LL, busiest - 1);
+    }
+    const int per_simd = nf <= (stagers ? 3 : 2) ? 4 : 3;
+    const long long held = std::max<long long>(1, std::min<long long>((long long)(kLds / lds), all > 4 ? per_simd / 2 : 4 * per_simd / all));
+    auto batch = [&](long long n) {
+        return n == 0 ? 0.0 : std::max(alone, n * waves / 4.0 * mfma * kContended + n * convert / 4 * (stagers ? kMixed : 1.0) + wait / n);
+    };
+    return less * ((busiest / held) * batch(held) + batch(busiest % held));
+}
+
 Fp6Plan search_fp6_plan(const Geom &g, int cus)
 {
     Fp6Plan pl{};
@@ -443,29 +562,54 @@ Fp6Plan search_fp6_plan(const Geom &g, int cus)
     if (taps > 64 || OHW > (1 << 24) || (long long)g.C * g.H * g.W >= (1LL << 29)) return pl;     // (32-bit byte offsets)
     if ((long long)g.F * taps * g.Cw >= (1LL << 29)) return pl;
     const int tiles = ceil_div(OHW, 32);
+    auto consider = [&](double &best, Fp6Plan &to, int nf, int G, int splits, int t, int stagers) {
+        const long long positions = fp6_positions(g, t);
+        if (positions > (long long)(kLds / kPosBytes)) return;
+        const size_t lds = fp6_lds(g, 32 * nf * splits, G, (int)positions, stagers ? 2 : 1);
+        if (lds > kLds) return;
+        const int wgs = ceil_div(tiles, t);
+        const long long all = (long long)g.N * wgs * ceil_div(g.F, 32 * nf * splits);
+        if (all > 0x7ffffff0LL) return;
+        if (stagers && all > cus) return;                 // (only in launches of at most a workgroup a unit)
+        const bool one = &to == &pl;
+        const double cost = one ? fp6_cost(kPlanCosts, g, nf, G, t, (int)positions, lds, (all + cus - 1) / cus)
+                                : fp6_split_cost(g, nf, G, splits, t, stagers, (int)positions, lds, (all + cus - 1) / cus);
+        if (best >= 0 && cost >= best) return;
+        best = cost;
+        to = {true, nf, G, splits, stagers, splits * t, wgs, (int)positions, lds, 0.0};
+    };
+    auto shapes = [&](auto with) {
+        for (int nf = 4; nf >= 1; --nf)
+            if (nf == 1 || 32 * (nf - 1) < g.F)
+                for (int G = std::min(2, g.Cw); G >= 1; --G) with(nf, G);
+    };
     double best = -1.0;
-    for (int nf = 4; nf >= 1; --nf) {
-        if (nf > 1 && 32 * (nf - 1) >= g.F) continue;
-        for (int G = std::min(2, g.Cw); G >= 1; --G)
-            for (int waves = std::min(kMaxWaves, tiles); waves >= 1; --waves) {
-                const long long positions = fp6_positions(g, waves);
-                if (positions > (long long)(kLds / kPosBytes)) continue;
-                const size_t lds = fp6_lds(g, nf, G, (int)positions);
-                if (lds > kLds) continue;
-                const int wgs = ceil_div(tiles, waves);
-                const long long all = (long long)g.N * wgs * ceil_div(g.F, 32 * nf);
-                if (all > 0x7ffffff0LL) continue;
-                const double cost = fp6_cost(kPlanCosts, g, nf, G, waves, (int)positions, lds, (all + cus - 1) / cus);
-                if (best < 0 || cost < best) {
-                    best = cost;
-                    pl = {true, nf, G, waves, wgs, (int)positions, lds, 0.0};
-                }
-            }
-    }
+    shapes([&](int nf, int G) {
+        for (int t = std::min(kMaxWaves, tiles); t >= 1; --t) consider(best, pl, nf, G, 1, t, 0);
+    });
     if (pl.ok) {
         // (a unit's filter groups run on one XCD: with 36 units and seven groups 35 workgroups on its 32 compute units)
         const long long per_xcd = ((long long)g.N * pl.wgs + 7) / 8 * ceil_div(g.F, 32 * pl.nf);
         pl.cycles = fp6_cost(kRouteCosts, g, pl.nf, pl.G, pl.waves, pl.positions, pl.lds, ceil_div(per_xcd, std::max(1, cus / 8)));
+        // a shape with splits or stagers, where it is the better one by a margin
+        Fp6Plan other{};
+        double least = -1.0;
+        shapes([&](int nf, int G) {
+            for (int splits = 1; splits <= kMaxSplits && (splits == 1 || 32 * nf * (splits - 1) < g.F); ++splits)
+                for (int t = std::min(kMaxWaves / splits, tiles); t >= 1; --t) {
+                    const int waves = splits * t;
+                                        if (splits == 2 && (waves == 2 || waves == 4 || waves == 8)) consider(least, other, nf, G, splits, t, 0);
+                    if (waves <= 4 && (nf == 1 || (nf == 2 && t <= 2)))
+                        for (int stagers = 3; stagers <= 4; ++stagers) consider(least, other, nf, G, splits, t, stagers);
+                }
+        });
+        const double one = fp6_split_cost(g, pl.nf, pl.G, 1, pl.waves, 0, pl.positions, pl.lds,
+                                          ((long long)g.N * pl.wgs * ceil_div(g.F, 32 * pl.nf) + cus - 1) / cus);
+        // (of one word all is staged at once: half a microsecond slower)
+        if (other.ok && g.Cw > 1 && least < kSplitMargin * one) {
+            other.cycles = pl.cycles;
+            return other;
+        }
     }
     return pl;
 }
@@ -477,7 +621,7 @@ const Fp6Plan &make_fp6_plan(const Geom &g)
     return memo.get(g, cus, [&] { return search_fp6_plan(g, cus); });
 }
 
-template <int NF>
+template <int NF, bool SPLITS, bool STAGERS>
 hipError_t start_fp6(const Fp6Plan &pl, const Fp6Params &p, unsigned blocks, hipStream_t st)
 {
     if (pl.lds > 64 * 1024) {
@@ -487,14 +631,25 @@ hipError_t start_fp6(const Fp6Plan &pl, const Fp6Params &p, unsigned blocks, hip
         if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
         const unsigned long long bit = 1ull << (dev & 63);
         if (!(raised.load() & bit)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bwn_fp6_kernel<NF>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bwn_fp6_kernel<NF, SPLITS, STAGERS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
             if (e != hipSuccess) return e;
             raised.fetch_or(bit);
         }
     }
-    bwn_fp6_kernel<NF><<<dim3(blocks), dim3(64 * pl.waves), pl.lds, st>>>(p);
+    bwn_fp6_kernel<NF, SPLITS, STAGERS><<<dim3(blocks), dim3(64 * (pl.waves + pl.stagers)), pl.lds, st>>>(p);
     return hipGetLastError();
+}
+
+template <bool SPLITS>
+hipError_t start_shape(const Fp6Plan &pl, const Fp6Params &p, unsigned blocks, hipStream_t st)
+{
+    switch (pl.nf) {
+        case 4: return start_fp6<4, SPLITS, false>(pl, p, blocks, st);
+        case 3: return start_fp6<3, SPLITS, false>(pl, p, blocks, st);
+        case 2: return start_fp6<2, SPLITS, false>(pl, p, blocks, st);
+        default: return start_fp6<1, SPLITS, false>(pl, p, blocks, st);
+    }
 }
 
 hipError_t launch_fp6_plan(const Fp6Plan &pl, const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g,
@@ -505,19 +660,21 @@ hipError_t launch_fp6_plan(const Fp6Plan &pl, const float *I, const uint32_t *Wp
     p.C = g.C; p.H = g.H; p.W = g.W; p.F = g.F; p.kh = g.kh; p.kw = g.kw;
     p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.OH = g.OH; p.OW = g.OW; p.Cw = g.Cw;
     p.G = pl.G;
+    p.splits = pl.splits;
+    p.tiles = pl.waves / pl.splits;
+    p.inv_splits = reciprocal((unsigned long long)pl.splits);
     p.wgs = pl.wgs;
-    p.fgroups = ceil_div(g.F, 32 * pl.nf);
+    p.fgroups = ceil_div(g.F, 32 * pl.nf * pl.splits);
+    p.inv_row = reciprocal(32ull * pl.nf * pl.splits);
     p.positions = pl.positions;
     const long long units = (long long)g.N * pl.wgs, blocks = (units + 7) / 8 * 8 * p.fgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     p.units = (int)units;
     const unsigned b = (unsigned)blocks;
-    switch (pl.nf) {
-        case 4: return start_fp6<4>(pl, p, b, st);
-        case 3: return start_fp6<3>(pl, p, b, st);
-        case 2: return start_fp6<2>(pl, p, b, st);
-        default: return start_fp6<1>(pl, p, b, st);
-    }
+    p.stagers = pl.stagers;
+    p.words_bytes = (int)fp6_words_bytes(g, 32 * pl.nf * pl.splits, pl.G);
+    if (pl.stagers) return pl.nf == 1 ? start_fp6<1, true, true>(pl, p, b, st) : start_fp6<2, true, true>(pl, p, b, st);
+    return pl.splits > 1 ? start_shape<true>(pl, p, b, st) : start_shape<false>(pl, p, b, st);
 }
 
 }  // namespace

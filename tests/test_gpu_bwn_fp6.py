@@ -174,3 +174,64 @@ def test_captured_launches_replay_the_eager_result(xb):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+#        N   C   H   W    F  kh kw sh sw ph pw: workgroups with splits and with stagers, and layers beside them that have none
+SPLIT_SHAPES = [
+    (1, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1),     # stagers, one filter tile a wave
+    (2, 271, 13, 14, 250, 3, 3, 1, 1, 1, 1),     # ... a last word of 15 channels, an odd number of chunks, a short last tile
+    (32, 512, 7, 7, 505, 3, 3, 1, 1, 1, 1),      # ... two splits, the last one's filters short
+    (3, 97, 12, 12, 33, 3, 3, 1, 1, 1, 1),       # ... a split of one filter, a last chunk of one word of one channel
+    (2, 448, 5, 6, 32, 3, 3, 1, 1, 1, 1),        # ... fewer pixels than the tiles have
+    (8, 192, 27, 27, 256, 5, 5, 1, 1, 2, 2),     # ... several rounds a chunk
+    (76, 448, 10, 10, 32, 3, 3, 2, 2, 1, 1),     # ... strides
+    (2, 64, 9, 9, 70, 1, 1, 1, 1, 0, 0),         # ... two chunks of a word, one tap
+    (4, 320, 9, 70, 64, 1, 1, 2, 2, 0, 0),
+    (1, 96, 8, 8, 40, 3, 3, 1, 1, 6, 6),         # ... windows, and workgroups, that are all padding
+    (1, 160, 3, 40, 20, 2, 5, 3, 1, 4, 0),
+    (128, 384, 13, 13, 384, 3, 3, 1, 1, 1, 1),   # two splits without stagers
+    (120, 390, 13, 13, 300, 3, 3, 1, 1, 1, 1),   # ... the second split's filters short
+]
+
+
+@pytest.mark.parametrize("shape", SPLIT_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_splits_and_stagers(xb, shape):
+    """Sums in a chain of their own per wave, in the order of the chunks' words, whatever the workgroup's shape: the same bars."""
+    big = shape[0] > 64
+    if big:                                      # (64-bit sums of the first and the last images)
+        n = shape[0]
+        I = torch.randn(shape[:4], generator=torch.Generator().manual_seed(1))
+        I[2:n - 2] = I[:1]
+        print(f"case bwn-fp6 splits shape={shape}", flush=True)
+        s, one = xb.Shape(*shape), xb.Shape(4, *shape[1:])
+        Wt = torch.randn((s.F, s.C, s.kh, s.kw), generator=torch.Generator().manual_seed(2)) * 0.05
+        Wpk, alpha, _ = xb.xnor_filter_prepare(Wt.cuda())
+        got = xb.xnor_bwn_conv2d_fwd(I.cuda(), Wpk, alpha, s, algo=xb.ALGO_MFMA_SPLIT_FP6).cpu().double()
+        at = [0, 1, n - 2, n - 1]
+        ref, S = sums64(I[at], Wt, one)
+        a = alpha.cpu().double()[None, :, None, None]
+        assert torch.equal(got[2:n - 2], got[:1].expand(n - 4, -1, -1, -1))
+        assert bool(((got[at] - a * ref).abs() <= a * 1e-5 * S).all())
+    else:
+        check(xb, shape, torch.randn(shape[:4], generator=torch.Generator().manual_seed(sum(shape))), sum(shape))
+
+
+@pytest.mark.parametrize("shape", [(1, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1), (128, 384, 13, 13, 384, 3, 3, 1, 1, 1, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_splits_and_stagers_in_a_graph(xb, shape):
+    """Captured and replayed on new inputs in the same buffers: the eager results each time."""
+    print(f"case bwn-fp6 graph shape={shape}", flush=True)
+    s = xb.Shape(*shape)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    I, Wt = torch.randn(shape[:4], generator=g, device="cuda"), torch.randn((s.F, s.C, s.kh, s.kw), generator=g, device="cuda")
+    Wpk, alpha, _ = xb.xnor_filter_prepare(Wt)
+    out = xb.xnor_bwn_conv2d_fwd(I, Wpk, alpha, s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        xb.xnor_bwn_conv2d_fwd(I, Wpk, alpha, s, out)
+    for _ in range(3):
+        I.copy_(torch.randn(shape[:4], generator=g, device="cuda"))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, xb.xnor_bwn_conv2d_fwd(I, Wpk, alpha, s))
