@@ -6,6 +6,7 @@
 // 256-byte wavefront reads along the image's fastest axis with many loads in flight per lane.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "xnor_internal.hpp"
 
@@ -720,6 +721,136 @@ hipError_t launch_box_filter_K(const float *A, const Geom &g, float *K, hipStrea
     const long long total = (long long)g.N * g.OH * g.OW;
     box_filter_K_kernel<<<ceil_div(total, 256), 256, 0, st>>>(A, g, total, K);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Eq. 10 as a whole for small inputs, in one launch: a block forms A for the rows under a band of output rows (and for the band's own
+// share of the image's rows, which it writes), keeps them in LDS and forms K from there.  The rows that bands share are read
+// once for each of them, which at these sizes costs less than the second launch: xnor_scale_K of 1 x 64 x 32 x 32 takes the host
+// 10.3 us with two launches.  Sums in the order of channel_mean_abs_kernel and box_filter_K_kernel: the same bits.
+// ------------------------------------------------------------------------------------------------
+constexpr size_t kBandLds = 60 * 1024;
+struct BandShape {
+    int S, G, rows, bands, most;       // channel slices, groups of 64 pixels side by side; output rows of a band, bands, most input rows
+    size_t smem;
+};
+// The rows that band b forms A for: those under its windows, if there are any, and its own.
+__host__ __device__ inline void band_rows(const Geom &g, const BandShape &s, int b, int *r0, int *r1)
+{
+    const int oy0 = b * s.rows, oy1 = oy0 + s.rows < g.OH ? oy0 + s.rows : g.OH;
+    const int own0 = (int)((long long)b * g.H / s.bands), own1 = (int)((long long)(b + 1) * g.H / s.bands);
+    const int top = oy0 * g.sh - g.ph, end = (oy1 - 1) * g.sh - g.ph + g.kh;
+    const int w0 = top > 0 ? top : 0, w1 = end < g.H ? end : g.H;
+    *r0 = w0 < w1 && w0 < own0 ? w0 : own0;
+    *r1 = w0 < w1 && w1 > own1 ? w1 : own1;
+}
+
+__global__ __launch_bounds__(1024) void scale_K_band_kernel(const float *__restrict__ I, Geom g, BandShape s, int chunk,
+                                                            float *__restrict__ A, float *__restrict__ K)
+{
+    extern __shared__ double band_lds[];
+    const int lane = threadIdx.x, slice = threadIdx.y, group = threadIdx.z, HW = g.H * g.W;
+    double *const part = band_lds + group * s.S * 128;
+    float *const a = reinterpret_cast<float *>(band_lds + s.G * s.S * 128);
+    const int n = blockIdx.x / s.bands, b = blockIdx.x - n * s.bands;
+    const int oy0 = b * s.rows, oy1 = min(g.OH, oy0 + s.rows);
+    const int own0 = (int)((long long)b * g.H / s.bands), own1 = (int)((long long)(b + 1) * g.H / s.bands);
+    int r0, r1;
+    band_rows(g, s, b, &r0, &r1);
+    const int pixels = (r1 - r0) * g.W;
+    const float *const src = I + (size_t)n * g.C * HW + (size_t)r0 * g.W;
+    const int c0 = slice * chunk, c1 = min(g.C, c0 + chunk);
+    // two pixels of a thread at a time, their loads in flight together
+    for (int base = 0; base < pixels; base += 128 * s.G) {
+        const int q = base + 128 * group + lane;
+        const float *const at[2] = {src + min(q, pixels - 1), src + min(q + 64, pixels - 1)};
+        double acc[2] = {0.0, 0.0};
+        auto sum_of = [&](auto count) __attribute__((always_inline)) {
+            constexpr int N = decltype(count)::value;
+            int c = c0;
+            for (; c + 8 <= c1; c += 8) {
+                float v[N][8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int u = 0; u < N; ++u) v[u][j] = at[u][(size_t)(c + j) * HW];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int u = 0; u < N; ++u) acc[u] += (double)fabsf(v[u][j]);
+            }
+            for (; c < c1; ++c)
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] += (double)fabsf(at[u][(size_t)c * HW]);
+        };
+        if (base + 128 * group + 64 < pixels) sum_of(std::integral_constant<int, 2>{});
+        else if (base + 128 * group < pixels) sum_of(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int u = 0; u < 2; ++u) part[slice * 128 + 64 * u + lane] = acc[u];
+        __syncthreads();
+        // (slice u sums the u-th pixels; of one slice that does both)
+        for (int u = slice; u < 2; u += s.S) {
+            const int p = q + 64 * u;
+            if (p >= pixels) continue;
+            double sum = part[64 * u + lane];
+            for (int k = 1; k < s.S; ++k) sum += part[k * 128 + 64 * u + lane];
+            const float mean = (float)(sum / (double)g.C);
+            const int row = r0 + p / g.W;
+            a[p] = mean;
+            if (row >= own0 && row < own1) A[(size_t)n * HW + (size_t)r0 * g.W + p] = mean;
+        }
+        __syncthreads();
+    }
+    const int tid = (group * s.S + slice) * 64 + lane;
+    for (int o = tid; o < (oy1 - oy0) * g.OW; o += 64 * s.S * s.G) {
+        const int r = o / g.OW, ox = o - r * g.OW, oy = oy0 + r;
+        const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
+        double sum = 0.0;
+        for (int ky = 0; ky < g.kh; ++ky)
+            for (int kx = 0; kx < g.kw; ++kx) {
+                const int iy = iy0 + ky, ix = ix0 + kx;
+                const bool in = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+                const float v = a[in ? (iy - r0) * g.W + ix : 0];
+                sum += in ? (double)v : 0.0;
+            }
+        K[((size_t)n * g.OH + oy) * g.OW + ox] = (float)(sum / (double)(g.kh * g.kw));
+    }
+}
+
+// Inputs of less than 2^20 values whose bands read a row four times at most and fit LDS.  us a call, two launches / one, eager; in a
+// graph: 1 x 64 x 32 x 32 8.1 / 5.8; 4.6 / 4.3, 5 x 100 x 37 x 53 8.3 / 5.6; 5.4 / 5.3; of 2^20 values, 1 x 64 x 128 x 128 8.1 / 6.0;
+// 4.9 / 5.7.
+static bool band_shape(const Geom &g, BandShape *s)
+{
+    const long long values = (long long)g.N * g.C * g.H * g.W;
+    if (values >= (1 << 20) || g.kh > 16) return false;
+    s->S = 1;
+    while (s->S < kMaxSlices && g.C / (2 * s->S) >= 8) s->S *= 2;      // (as in launch_channel_mean_abs)
+    s->G = std::max(1, 16 / s->S);
+    s->rows = std::max(1, ceil_div((long long)g.N * g.OH, 256));
+    s->bands = ceil_div(g.OH, s->rows);
+    long long read = 0;
+    s->most = 0;
+    for (int b = 0; b < s->bands; ++b) {             // (at most 256 / N and one of them)
+        int r0, r1;
+        band_rows(g, *s, b, &r0, &r1);
+        s->most = std::max(s->most, r1 - r0);
+        read += r1 - r0;
+    }
+    if (read > 4LL * g.H + 8) return false;
+    s->smem = (size_t)s->S * s->G * 128 * sizeof(double) + (size_t)s->most * g.W * sizeof(float);
+    return s->smem <= kBandLds;
+}
+
+hipError_t launch_scale_K(const float *I, const Geom &g, float *A, float *K, hipStream_t st)
+{
+    BandShape s;
+    if (band_shape(g, &s)) {
+        scale_K_band_kernel<<<dim3((unsigned)(g.N * s.bands)), dim3(64, s.S, s.G), s.smem, st>>>(I, g, s, (g.C + s.S - 1) / s.S, A, K);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_channel_mean_abs(I, g.N, g.C, g.H, g.W, A, st);
+    return e != hipSuccess ? e : launch_box_filter_K(A, g, K, st);
 }
 
 // ------------------------------------------------------------------------------------------------

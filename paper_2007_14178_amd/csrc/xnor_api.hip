@@ -185,10 +185,7 @@ int xnor_scale_K(const float *I, const xnor_shape *s, float *A_work, float *K, v
     const int rc = make_geom(s, &g);
     if (rc) return rc;
     if (!aligned(I, 4) || !aligned(A_work, 4) || !aligned(K, 4)) return XNOR_E_ALIGN;
-    hipStream_t st = (hipStream_t)stream;
-    hipError_t e = xnor::launch_channel_mean_abs(I, g.N, g.C, g.H, g.W, A_work, st);
-    if (e != hipSuccess || !K) return hip_status(e);
-    return hip_status(xnor::launch_box_filter_K(A_work, g, K, st));
+    return hip_status(xnor::launch_scale_K(I, g, A_work, K, (hipStream_t)stream));
 }
 
 int xnor_alpha(const float *Wt, int F, int C, int kh, int kw, float *alpha, void *stream)

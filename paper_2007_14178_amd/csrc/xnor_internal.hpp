@@ -85,6 +85,7 @@ hipError_t launch_binarize_pack(const float *x, int N, int C, int H, int W, uint
                                 hipStream_t st);
 hipError_t launch_channel_mean_abs(const float *I, int N, int C, int H, int W, float *A,
                                    hipStream_t st);
+hipError_t launch_scale_K(const float *I, const Geom &g, float *A, float *K, hipStream_t st);
 bool pack_and_mean_supports(int C);
 hipError_t launch_pack_and_mean(const float *x, int N, int C, int H, int W, uint32_t *packed,
                                 float *A, hipStream_t st);
