@@ -362,9 +362,11 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
  * The same convolution with a workspace, with which its fastest kernel can run: XNOR_ALGO_MFMA_SPLIT,
  * both operands split into terms whose products are summed in fp32 by the bf16 and f16 matrix instructions: exactly, into
  * three bf16 terms (the smallest products, together at most 2^-16 of the whole, from terms rounded to 11 bits, or by
- * the bf16 instruction alone beside values that f16 would not hold so), or, in layers of at least 2560 terms, into two f16
- * terms that hold a value to within 2^-23 (of values below 2^-20 of the largest beside them 2^-40 of that one is lost; where
- * that could be more than 1e-5 of an output it is formed from three terms or in 64 bits).  Results are
+ * the bf16 instruction alone beside values that f16 would not hold so), or, in layers of at least four taps and 160 (tap, 16
+ * channels, the last ones in part) steps, into two f16 terms that hold a value within 2^-23 of itself, of whose products the smallest
+ * (at most 2^-22 of the whole) is left out.  (Values below 2^-21 of the largest beside them are within 2^-45 of that one; where
+ * that could be more than 2^-22 of an output it is formed from three terms or in 64 bits.  Sums of so many terms are no further off
+ * than with three terms; those that most of the terms are zero in can be, a product alone within 2^-21.)  Results are
  * closer to the exact sum than those of the fp32 matrix instruction; infinities and NaN come out as fp32
  * arithmetic gives them, and an output so small that bits of a value below 2^-133 (or 2^-133 of what lies beside it)
  * could matter to it is formed by the plain fp32 sum.

@@ -54,20 +54,30 @@
 // 64-bit sums, normal values, six products / pairs:
 //   3 x 3, 128, 256, 512 channels: 1.23e-7 1.67e-7 2.30e-7 / 1.59e-7 1.67e-7 1.82e-7;  5 x 5, 64, 128, 512: 1.36e-7 1.86e-7
 //   3.59e-7 / 1.63e-7 1.74e-7 2.30e-7;  positive values 0.95e-7 to 3.0e-7 / 0.63e-7 to 1.5e-7.
-// us: 128 x 512 x 28 x 28 F=512 3x3 2360 -> 1280, 16 x 128 x 56 x 56 F=128 5x5 247 -> 144, 4 x 512 x 20 x 20 F=128 3x3 102 -> 78.
+// us: 128 x 512 x 28 x 28 F=512 3x3 2360 -> 1320, 16 x 128 x 56 x 56 F=128 5x5 247 -> 146, 1 x 512 x 13 x 13 F=64 3x3 92 -> 74.
 //   Powers of two for f16's range: a filter tile's chunk has its own, and so has a workgroup's chunk of the input: its largest
-// magnitude is found when its values arrive, a chunk ahead of their commit.  Values of 2^-20 of their chunk's largest and more keep
-// 2^-19 of themselves, smaller ones 2^-40 of the largest.  What all of those can do to an output is bounded by their number
-// (one or two in 10^7 of normal values); a wave forms the few outputs below 2^17 times that one by one, in 64 bits (one workgroup
-// of some thousand has any).  Where there are more of them, or a value without a power of two (infinite, NaN, of 2^-46 or
-// 2^74), or an output that came out infinite, NaN or below 2^-120, the workgroup's outputs are formed from three terms as in
-// the layers without pairs: log-normal values (sigma 4), one filter of 1e-11 (both stop at once: 1.02 to 1.1 times that form's
-// time), half an image of zeros but for one 1e-12 (after the whole sum: 1.5 times).
+// magnitude is found when its values arrive, a chunk ahead of their commit.  Low terms are stored times 2^11, as large as their
+// high ones, so that values of 2^-21 of their chunk's largest are still within 2^-23 of themselves.  The sums have that factor,
+// too: h * h gets it from its operands, multiplied by 2^5 and 2^6 in their registers behind the other two products.  (Stored as
+// they are, low terms leave f16's normal range from 2^-17 of the largest on: an output that only values of 2^-20 of their
+// neighbours' size go into had 2.5 to 4.2 times the error of three terms, and has 0.79 to 0.94 of it so.  The multiplications
+// cost 4 % at the first layer above and 1 % at the second.)
+//   Smaller values are held in part, within 2^-45 of the largest.  What all of them can do to an output is bounded by their number
+// (3 in 10^7 of normal values); a wave forms the few outputs below 2^22 times that one by one, in 64 bits.  Where there are
+// more of them, or a value without a power of two (infinite, NaN, of 2^-46 or 2^68), or an output that came out infinite, NaN or
+// below 2^-120, the workgroup's outputs are formed from three terms as in the layers without pairs.  Log-normal values (sigma 4)
+// and filters of 2^-16 or 1e-11 of their neighbours stop at once, at 1.02 to 1.14 times that form's time; where it shows in
+// the outputs alone (such a value somewhere in a workgroup and filters or windows of zeros) the workgroup takes 1.6 times it.
+//   Errors against those of three terms by kind of values (3 x 3 on 288 and 512 channels, 5 x 5 on 128): normal 0.79 to 0.96, half
+// of them zeros 0.79 to 0.98, positive 0.47 to 0.52, constant 0.33 to 0.44, channels of 2^-(c % 16) 0.82 to 0.97, log-normal
+// (sigma 2) 0.82 to 0.96, 90 % zeros 0.73 to 0.87.  Larger ones are left where few terms are: 99 % zeros 1.09 to 1.24 (a
+// product alone is within 2^-21, that of three terms within 2^-23); and constant values in one window with others of 2^16 of
+// their size, whose largest error is 0.6 to 2.2 times (the chain that holds those is the longer one).
 //   conv_fp32_split_kernel<.., PAIR> has the tiles and the staging of the other forms, 80 bytes a position.  The A operands
 // are a ring of three taps (two where the window's taps are no multiple of three) in registers, an operand fetched again behind
 // its last use, 26 (14) matrix instructions ahead.  What it measured at the first layer: pairs with the six products' loop
 // 1435 us, with one buffer descriptor for an image in place of one a plane and without a load at the head of a chunk 1355, with the
-// ring, and granules for the positions that there are (240; 384 had been handled), 1275.  Matrix pipe busy 63 % of the cycles at 1.72 GHz;
+// ring, and granules for the positions that there are (240; 384 had been handled), 1275, with the high terms' multiplications 1320.  Matrix pipe busy 63 % of the cycles at 1.72 GHz;
 // a loop of the matrix instructions alone takes 895 us, at the card's power.  Timing-only builds: without A loads
 // 12 % shorter, without B reads 9, without commits 15.
 //
@@ -161,11 +171,17 @@ __device__ inline uint32_t power_bits(int e)
     return e > 127 ? kInfBits : e > -127 ? (uint32_t)(e + 127) << 23 : 1u << max(0, e + 149);
 }
 
-// Pairs: a chunk's largest magnitude is brought to 2^14 .. 2^15, by at most 2^kPairMost or 2^-kPairMost; a scaled value below
-// kPairLow that is not zero counts as held in part.
-constexpr int kPairTop = 14, kPairMost = 60;
-constexpr float kPairLow = 0x1p-6f;
-constexpr uint32_t kNotHeld = 1u << 20, kPairMostLow = 1024;
+// Pairs: a chunk's largest magnitude is brought to 2^kPairTopW (weights) or 2^kPairTopX (input) and up to twice that, by at most
+// 2^kPairMost or 2^-kPairMostDown.  The low term is stored times 2^kPairShift, and the high ones are multiplied by 2^kPairUpW and
+// 2^kPairUpX, which make 2^kPairShift, for their product.  A scaled value below kPairLow that is not zero counts as held in part: kPairLoss
+// of it may be lost.
+constexpr int kPairTopW = 9, kPairTopX = 8, kPairUpW = 14 - kPairTopW, kPairUpX = 14 - kPairTopX, kPairShift = kPairUpW + kPairUpX;
+constexpr int kPairMost = 54, kPairMostDown = 60;
+constexpr float kPairLow = 0x1p-13f;
+constexpr int kPairLossExp = -25 - kPairShift;
+constexpr uint32_t kNotHeld = 1u << 20, kPairMostLow = 1024, kPairMostLowW = 64;    // (of a workgroup's input, of its weights)
+constexpr int kPairShareExp = 22;       // an output stands where such values can change it by at most 2^-kPairShareExp of itself
+static_assert(kPairShift == 11, "a low term is as large as its high one");
 constexpr int kPairFew = 4;             // doubtful outputs that a wave forms one by one
 constexpr float kPairLeast = 0x1p-120f;
 constexpr int kPairPosBytes = 2 * 32 + 16, kPairOperandBytes = 2 * 1024;
@@ -177,10 +193,10 @@ __device__ inline bool pair_chain_negated(int chunk, int tap, int taps)
     return (chunk * pair_chains(taps) + tap / pair_chain_taps(taps)) & 1;
 }
 // the power of two for a largest magnitude (its bits), `held`: there is one
-__device__ inline int pair_exp(uint32_t top, bool &held)
+__device__ inline int pair_exp(int to, uint32_t top, bool &held)
 {
-    const int e = kPairTop + 127 - (int)(top >> 23);
-    held = top == 0 || (e >= -kPairMost && e <= kPairMost);
+    const int e = to + 127 - (int)(top >> 23);
+    held = top == 0 || (e >= -kPairMostDown && e <= kPairMost);
     return top == 0 ? kPairMost : e;
 }
 
@@ -196,12 +212,19 @@ __device__ inline uint32_t pack_f16(float a, float b)
     const floatx2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
 }
-// what the f16 pair `t` leaves of (a, b); exact
-__device__ inline void subtract_pair_f16(float &a, float &b, uint32_t t)
+// eight f16 times 2^N
+template <int N>
+__device__ inline void scale_f16(uint4 &v)
+{
+    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+    v = __builtin_bit_cast(uint4, __builtin_bit_cast(half8, v) * (half8)(_Float16)(1 << N));
+}
+// what the f16 pair `t` leaves of (a, b), times 2^kPairShift, for (a, b) given so; exact
+__device__ inline void leave_pair_f16(float &a, float &b, uint32_t t)
 {
     const halfx2 h = __builtin_bit_cast(halfx2, t);
-    a = fmaf(-1.f, (float)h.x, a);
-    b = fmaf(-1.f, (float)h.y, b);
+    a = fmaf(-(float)(1 << kPairShift), (float)h.x, a);
+    b = fmaf(-(float)(1 << kPairShift), (float)h.y, b);
 }
 // what the bf16 pair `t` leaves of (a, b); exact
 __device__ inline void subtract_pair(float &a, float &b, uint32_t t)
@@ -281,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
     const int e = FLUSH ? 0 : scale_of(stat[2], kTopW, kMostW);
     unsigned char *const dst = Wx + ((size_t)ft * nchunks + (oc >> 1)) * taps * operand_bytes(FLUSH) + (oc & 1) * 512;
     bool pair_held = false;
-    const int pe = PAIR ? pair_exp(stat[2], pair_held) : 0;
+    const int pe = PAIR ? pair_exp(kPairTopW, stat[2], pair_held) : 0;
     unsigned char *const pdst = Wp + ((size_t)ft * nchunks + (oc >> 1)) * taps * kPairOperandBytes + (oc & 1) * 512;
     uint32_t lows = 0;
     for (int i = threadIdx.x; i < 32 * taps; i += kThreads) {
@@ -311,7 +334,9 @@ __global__ __launch_bounds__(kThreads) void split_filters_kernel(const float *__
                 float a = by * wl[f * pitch + (2 * k) * taps + t], b = by * wl[f * pitch + (2 * k + 1) * taps + t];
                 lows += (wl[f * pitch + (2 * k) * taps + t] != 0.f && fabsf(a) < kPairLow) + (wl[f * pitch + (2 * k + 1) * taps + t] != 0.f && fabsf(b) < kPairLow);
                 h[k] = pack_f16(a, b);
-                subtract_pair_f16(a, b, h[k]);
+                a *= (float)(1 << kPairShift);
+                b *= (float)(1 << kPairShift);
+                leave_pair_f16(a, b, h[k]);
                 l[k] = pack_f16(a, b);
             }
             uint4 *q = reinterpret_cast<uint4 *>(pdst + (size_t)t * kPairOperandBytes + f * 16);
@@ -586,15 +611,16 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
     };
     // The power of two of the chunk to be committed next, of the one being multiplied, the smallest so far; of the first, in bits.
     int xexp = 0, xexp_now = 0, xleast = kPairMost;
-    float xscale = 1.f;
+    float xscale = 1.f, xscale_low = 1.f;
     uint32_t xlow = 0;                           // below it a (doubled) value is held in part
     auto take_scale = [&](const uint4 &t) __attribute__((always_inline)) -> bool {
         const uint32_t top = __builtin_amdgcn_readfirstlane((int)max(max(t.x, t.y), max(t.z, t.w)));
         bool held;
-        xexp = pair_exp(top, held);
+        xexp = pair_exp(kPairTopX, top, held);
         held = held && top < kInfBits;
         xleast = min(xleast, xexp);
         xscale = __uint_as_float((uint32_t)(127 + xexp) << 23);
+        xscale_low = __uint_as_float((uint32_t)(127 + kPairShift + xexp) << 23);
         xlow = (__float_as_uint(kPairLow) - ((uint32_t)xexp << 23)) << 1;
         return held;
     };
@@ -618,8 +644,10 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
                 ph[0] = pack_f16(pv[0], pv[1]);
                 ph[1] = pack_f16(pv[2], pv[3]);
             } else if constexpr (U == 3) {
-                subtract_pair_f16(pv[0], pv[1], ph[0]);
-                subtract_pair_f16(pv[2], pv[3], ph[1]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) pv[k] = from[q][4 * hf + k] * xscale_low;
+                leave_pair_f16(pv[0], pv[1], ph[0]);
+                leave_pair_f16(pv[2], pv[3], ph[1]);
             } else if constexpr (U == 4) {
                 uint2 *dst = reinterpret_cast<uint2 *>(lds_raw + (ch & 1) * tile_bytes + wr_off[q] + hf * 8);
                 dst[0] = make_uint2(ph[0], ph[1]);
@@ -698,7 +726,7 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
     put_top(first, 0);
     if (threadIdx.x < 3) words[8 + threadIdx.x] = 0;
     __syncthreads();
-    bool stop = partly >= kPairMostLow;          // (uniform over the workgroup)
+    bool stop = partly >= kPairMostLowW;         // (uniform over the workgroup)
     stop |= !take_scale(tops_of(0));
     xexp_now = xexp;
     commit_rest(first, 0, 0);
@@ -733,7 +761,7 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
             if (more) stop |= !take_scale(tops_of(ch + 1));
             if ((ch & 63) == 0 && ch > 0) load_exps(ch);
             const uint32_t exps = (uint32_t)__builtin_amdgcn_readlane((int)wexps, ch & 63);
-            const uint32_t e0 = (uint32_t)(127 + kExpBias - xexp_now - (int)(exps & 0xffffu)) << 23, e1 = (uint32_t)(127 + kExpBias - xexp_now - (int)(exps >> 16)) << 23;
+            const uint32_t e0 = (uint32_t)(127 - kPairShift + kExpBias - xexp_now - (int)(exps & 0xffffu)) << 23, e1 = (uint32_t)(127 - kPairShift + kExpBias - xexp_now - (int)(exps >> 16)) << 23;
             // a chain joins the output's sum, without the scales and the sign of its operands
             auto settle = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -751,16 +779,17 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
             };
             const int row_step = (p.pitch - p.kw + 1) * kPairPosBytes;
             int kx = 0, off = 0, left = taps, in_chain = pair_chain_taps(taps);
-            // A tap, its operands in slot `slot` of the ring, with pieces FIRST .. FIRST + COUNT - 1 of the commit: low * high, high * low,
-            // high * high of each tile, an operand fetched again behind its last use, the next tap's place found between.
+            // A tap, its operands in slot `slot` of the ring, with pieces FIRST .. FIRST + COUNT - 1 of the commit: high * low, low * high,
+            // high * high of all tiles, the high operands scaled for the last between, an operand fetched again behind its last use, the
+            // next tap's place found between.
             auto tap_body = [&](auto slot_c, auto first_c, auto count_c) __attribute__((always_inline)) {
                 constexpr int slot = decltype(slot_c)::value, FIRST = decltype(first_c)::value, COUNT = decltype(count_c)::value;
                 __builtin_amdgcn_sched_barrier(0);
                 auto unit = [&](auto m_c) __attribute__((always_inline)) {
                     constexpr int M = decltype(m_c)::value;
                     if constexpr (M < 6 * NT) {
-                        constexpr int j = M / 6, P = M % 6 / 2, i = M & 1, ta = P == 0 ? 1 : 0;
-                        chain[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[slot][i][ta]), __builtin_bit_cast(halfx8, P == 1 ? bl[j] : bh[j]),
+                        constexpr int P = M / (2 * NT), j = M % (2 * NT) / 2, i = M & 1, ta = P == 1 ? 1 : 0;
+                        chain[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[slot][i][ta]), __builtin_bit_cast(halfx8, P == 0 ? bl[j] : bh[j]),
                                                                              chain[i][j], 0, 0, 0);
                         if constexpr (M == 1) {
                             const bool wrap = kx + 1 == p.kw;
@@ -768,8 +797,10 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
                             kx = wrap ? 0 : kx + 1;
                             off = left > 0 ? off + (wrap ? row_step : kPairPosBytes) : 0;
                         }
-                        if constexpr (j == NT - 1 && P != 1) load_a(slot, i, ta);
-                        if constexpr (i == 1 && P == 1) read_b(bl[j], 1, base[j] + off);
+                        if constexpr (j == NT - 1 && P == 0) scale_f16<kPairUpW>(a[slot][i][0]);
+                        if constexpr (j == NT - 1 && P != 0) load_a(slot, i, ta);
+                        if constexpr (i == 1 && P == 0) read_b(bl[j], 1, base[j] + off);
+                        if constexpr (i == 1 && P == 1) scale_f16<kPairUpX>(bh[j]);
                         if constexpr (i == 1 && P == 2) read_b(bh[j], 0, base[j] + off);
                         constexpr int piece = (M - 1) / kUnits, u = (M - 1) % kUnits;
                         if constexpr (M >= 1 && piece < COUNT) commit_unit(nxt, std::integral_constant<int, FIRST + piece>{}, std::integral_constant<int, u>{}, ch + 1);
@@ -825,9 +856,9 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
         counts[(ch + 1) & 1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[8 + ((ch + 1) & 1)]);
         stop |= counts[0] + counts[1] >= kPairMostLow;
     }
-    // What values held in part (at most 2^-25, scaled, of each is lost) can do to an output, times 2^17: the bar of 1e-5.
+    // What values held in part can do to an output, times 2^kPairShareExp.
     const uint32_t count = partly + counts[0] + counts[1];
-    const float doubtful = (float)count * ldexpf(1.f, 17 - 25 + kPairTop + 1 - xleast - wleast);
+    const float doubtful = (float)count * ldexpf(1.f, kPairShareExp + kPairLossExp + std::max(kPairTopW, kPairTopX) + 1 - xleast - wleast);
     bool again = stop;
     uint32_t few[kTiles];
     int number = 0;
@@ -1652,9 +1683,10 @@ hipError_t launch_granules(int granules, const Fp32SplitParams &p, unsigned bloc
 }  // namespace
 
 namespace {
-// Layers whose sums are long enough that pairs are no less exact than six products: 160 (tap, chunk) steps, 2560 terms.  The
-// errors are equal at 144 (3 x 3 on 256 channels 1.67e-7 both, 5 x 5 on 96 1.68e-7 against 1.63e-7) and 1.70e-7 against
-// 1.76e-7 at 162; below, six products, at 1.1 to 1.3 times the time of pairs.
+// Layers whose sums are long enough that pairs are no less exact than six products: 160 (tap, chunk of 16 channels) steps.  The
+// errors are equal at 144 (3 x 3 on 256 channels 1.67e-7 both, 5 x 5 on 96 1.68e-7 against 1.63e-7); from there on 0.94 to 0.98 (3 x 3
+// on 273 1.71e-7 against 1.81e-7, on 288 1.70e-7 against 1.77e-7, 5 x 5 on 97 1.75e-7 against 1.86e-7, on 112 1.72e-7 against 1.76e-7,
+// 2 x 2 on 640 1.63e-7 against 1.68e-7); below, six products, at 1.1 to 1.3 times the time of pairs.
 bool takes_pairs(const Geom &g, const Plan &pl)
 {
     const long long taps = g.kh * g.kw, nchunks = ceil_div(g.C, kChan);

@@ -212,3 +212,34 @@ def test_pairs_by_the_workspace_and_the_number_of_terms(xb):
     assert np.array_equal(pair, xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s).cpu().numpy())
     ws = torch.empty((xb.xnor_conv2d_fp32_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
     assert np.array_equal(three, xb.xnor_conv2d_fp32_fwd(dev(I), dev(Wt), s, workspace=ws).cpu().numpy())
+
+
+@pytest.mark.parametrize("what", ["values", "one value", "channels", "equal"])
+@pytest.mark.parametrize("p", [12, 17, 19, 20, 22])
+@pytest.mark.parametrize("shape", [(1, 512, 13, 13, 64, 3), (1, 256, 17, 17, 70, 5)], ids=lambda s: "x".join(map(str, s)))
+def test_pairs_beside_larger_values_are_no_less_exact_than_three_terms(xb, shape, p, what):
+    """Values of 2^-p of others in their workgroup's chunk, values of different mantissas or all of one (what a pair loses of that
+    adds up).  Error over the outputs whose windows hold none of the larger ones, against what their terms' sizes make a sum's
+    rounding, of both forms on the same data: 0.76 to 0.95 of that of three terms."""
+    N, C, H, W, F, k = shape
+    print(f"case conv_fp32 pair beside larger shape={shape} p={p} {what}", flush=True)
+    rng = np.random.default_rng(zlib.crc32((what + str(p) + str(shape)).encode()))
+    I, Wt = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((F, C, k, k)).astype(np.float32)
+    far = np.zeros((N, C, H, W), bool)
+    far[:, ::16, 4::8, 4::8] = True
+    if what == "values":
+        I = np.sign(I) * (1 + rng.random(I.shape)).astype(np.float32)
+    if what == "one value":
+        I = np.where(I < 0, np.float32(-0.6663), np.float32(1.3337))
+    if what == "channels":              # of a chunk, beside the larger values too
+        I *= (np.float32(2.0) ** -(np.arange(C) % 16).astype(np.float32))[None, :, None, None]
+    if what == "equal":
+        I, Wt = np.full_like(I, 1.3337), np.broadcast_to((1 + rng.random((F, 1, 1, 1))).astype(np.float32), Wt.shape).copy()
+    I[far] = np.float32(2.0) ** p
+    s = xb.Shape(N, C, H, W, F, k, k, 1, 1, k // 2, k // 2)
+    ref, _ = sums64(I, Wt, s)
+    size = np.sqrt(sums64(I.astype(np.float64) ** 2, Wt.astype(np.float64) ** 2, s)[0])
+    clear = sums64(far.astype(np.float32), np.ones_like(Wt), s)[0] == 0
+    assert clear.any() and not clear.all()
+    pair, three = (np.sqrt((((run(xb, I, Wt, s, f) - ref) / size)[clear] ** 2).mean()) for f in (True, False))
+    assert 0 < pair <= three, (pair, three)
