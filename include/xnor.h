@@ -75,11 +75,14 @@ typedef enum {
     XNOR_ALGO_MFMA_TILE = 7,  /* ... with many small workgroups: by name, whatever XNOR_ALGO_MFMA takes
                                (the _algo calls only; tests and measurements)                     */
     XNOR_ALGO_MFMA_SPLIT = 5, /* xnor_bwn_conv2d_fwd_algo: the fp32 input split into terms, one of the two below;
-                               xnor_conv2d_fp32_fwd_ws: both operands split into terms               */
+                               xnor_conv2d_fp32_fwd_ws: both operands split into terms, two where the
+                               layer and the workspace allow, else three                             */
     XNOR_ALGO_MFMA_SPLIT_FP6 = 8, /* xnor_bwn_conv2d_fwd_algo: five FP6 digits with a scale per position and 32
                                channels, v_mfma_scale_f32_32x32x64_f8f6f4 against +-1 weights, and       */
-    XNOR_ALGO_MFMA_SPLIT_BF16 = 9 /* ... three bf16 terms, v_mfma_f32_32x32x16_bf16: by name, whatever
+    XNOR_ALGO_MFMA_SPLIT_BF16 = 9, /* ... three bf16 terms, v_mfma_f32_32x32x16_bf16: by name, whatever
                                XNOR_ALGO_MFMA_SPLIT takes (tests and measurements)                    */
+    XNOR_ALGO_MFMA_SPLIT_PAIRS = 10, /* xnor_conv2d_fp32_fwd_ws: two f16 terms, and                  */
+    XNOR_ALGO_MFMA_SPLIT_THREE = 11 /* ... three bf16 terms: by name, however large the workspace     */
 } xnor_algo;
 
 /* Host helpers (no GPU work). */
@@ -374,9 +377,10 @@ int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape 
  *              call writes the split filters into it, its contents mean nothing afterwards.
  * XNOR_ALGO_AUTO takes the split kernel where it is the faster one and xnor_conv2d_fp32_workspace_bytes
  * bytes are given, else what xnor_conv2d_fp32_fwd takes.  Two terms take xnor_conv2d_fp32_pairs_workspace_bytes bytes;
- * with fewer the split kernel works on three.  XNOR_ALGO_MFMA_SPLIT: XNOR_E_WORKSPACE for a
- * workspace that is missing or too small; XNOR_E_UNSUPPORTED for kh*kw > 49, OH*OW > 2^24, C*H*W >= 2^29,
- * F*C*kh*kw >= 2^28, or where the input under 32 output pixels exceeds 512 staged positions (384 for shapes that
+ * with fewer the split kernel works on three, and XNOR_ALGO_MFMA_SPLIT_THREE has it do so with any workspace (for results
+ * that do not depend on its size).  XNOR_ALGO_MFMA_SPLIT_PAIRS: XNOR_E_UNSUPPORTED for layers that are not split into two terms.
+ * XNOR_ALGO_MFMA_SPLIT and these two: XNOR_E_WORKSPACE for a workspace that is missing or too small; XNOR_E_UNSUPPORTED for
+ * kh*kw > 49, OH*OW > 2^24, C*H*W >= 2^29, F*C*kh*kw >= 2^28, or where the input under 32 output pixels exceeds 512 staged positions (384 for shapes that
  * XNOR_ALGO_MFMA does not take).  Other values as in xnor_conv2d_fp32_fwd_algo.
  *   xnor_conv2d_fp32_workspace_bytes        host only; 0 where no workspace would be used by XNOR_ALGO_AUTO.
  *   xnor_conv2d_fp32_algo_workspace_bytes   host only; the same for the kernel that `algo` asks for:

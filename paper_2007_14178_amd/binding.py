@@ -18,10 +18,12 @@ LIB_PATH = os.path.join(_HERE, "libxnor_hip.so")
 
 ALGO_AUTO, ALGO_DIRECT, ALGO_TILED, ALGO_MFMA, ALGO_MFMA_BANDS, ALGO_MFMA_SPLIT = 0, 1, 2, 3, 4, 5
 ALGO_MFMA_PERSISTENT, ALGO_MFMA_TILE, ALGO_MFMA_SPLIT_FP6, ALGO_MFMA_SPLIT_BF16 = 6, 7, 8, 9
+ALGO_MFMA_SPLIT_PAIRS, ALGO_MFMA_SPLIT_THREE = 10, 11
 ALGO_NAMES = {ALGO_AUTO: "auto", ALGO_DIRECT: "direct", ALGO_TILED: "tiled", ALGO_MFMA: "mfma",
               ALGO_MFMA_BANDS: "mfma_bands", ALGO_MFMA_SPLIT: "mfma_split",
               ALGO_MFMA_PERSISTENT: "mfma_persistent", ALGO_MFMA_TILE: "mfma_tile",
-              ALGO_MFMA_SPLIT_FP6: "mfma_split_fp6", ALGO_MFMA_SPLIT_BF16: "mfma_split_bf16"}
+              ALGO_MFMA_SPLIT_FP6: "mfma_split_fp6", ALGO_MFMA_SPLIT_BF16: "mfma_split_bf16",
+              ALGO_MFMA_SPLIT_PAIRS: "mfma_split_pairs", ALGO_MFMA_SPLIT_THREE: "mfma_split_three"}
 E_NULL, E_SHAPE, E_ALIGN, E_HIP, E_UNSUPPORTED, E_WORKSPACE = -1, -2, -3, -4, -5, -6
 
 
@@ -554,14 +556,18 @@ def xnor_conv2d_fp32_fwd(I: torch.Tensor, Wt: torch.Tensor, s: Shape, out: torch
     """Real-valued convolution (the float comparison of Table I): fp32 input and weights. Returns out.
 
     ``workspace``: a uint8 GPU tensor, None (run a kernel that needs none), or "auto" (allocate what
-    xnor_conv2d_fp32_pairs_workspace_bytes or else xnor_conv2d_fp32_workspace_bytes asks for)."""
+    xnor_conv2d_fp32_pairs_workspace_bytes or, where there is no memory for that, xnor_conv2d_fp32_workspace_bytes asks
+    for).  ALGO_AUTO and ALGO_MFMA_SPLIT split both operands into two terms where the layer and the workspace allow and else
+    into three; ALGO_MFMA_SPLIT_PAIRS and ALGO_MFMA_SPLIT_THREE are the two by name."""
     OH, OW = xnor_out_dim(s)
     oshape = (s.N, s.F, OH, OW)
     if out is None:
         out = I.new_empty(oshape, dtype=torch.float32)
     if isinstance(workspace, str):
-        nbytes = xnor_conv2d_fp32_workspace_bytes(s, algo) if algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) else 0
-        sizes = [n for n in (xnor_conv2d_fp32_pairs_workspace_bytes(s), nbytes) if n] if nbytes else []
+        takes = algo in (ALGO_AUTO, ALGO_MFMA_SPLIT, ALGO_MFMA_SPLIT_PAIRS, ALGO_MFMA_SPLIT_THREE)
+        nbytes = xnor_conv2d_fp32_workspace_bytes(s, algo) if takes else 0
+        either = algo in (ALGO_AUTO, ALGO_MFMA_SPLIT) and nbytes
+        sizes = [n for n in (xnor_conv2d_fp32_pairs_workspace_bytes(s) if either else 0, nbytes) if n]
         workspace = None
         while sizes and workspace is None:
             try:

@@ -473,7 +473,11 @@ int xnor_conv2d_fp32_algo_workspace_bytes(const xnor_shape *s, int algo, size_t 
             *bytes = 0;
             return xnor::conv_fp32_mfma_supports(g) ? XNOR_OK : XNOR_E_UNSUPPORTED;
         case XNOR_ALGO_MFMA_SPLIT:
+        case XNOR_ALGO_MFMA_SPLIT_THREE:
             *bytes = xnor::conv_fp32_split_workspace_bytes(g);
+            return *bytes > 0 ? XNOR_OK : XNOR_E_UNSUPPORTED;
+        case XNOR_ALGO_MFMA_SPLIT_PAIRS:
+            *bytes = xnor::conv_fp32_pairs_workspace_bytes(g);
             return *bytes > 0 ? XNOR_OK : XNOR_E_UNSUPPORTED;
         default:
             return XNOR_E_UNSUPPORTED;
@@ -513,10 +517,13 @@ int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s
         case XNOR_ALGO_MFMA:
             if (!xnor::conv_fp32_mfma_supports(g)) return XNOR_E_UNSUPPORTED;
             return hip_status(xnor::launch_conv_fp32_mfma(I, Wt, g, out, (hipStream_t)stream));
-        case XNOR_ALGO_MFMA_SPLIT: {
-            const size_t need = xnor::conv_fp32_split_workspace_bytes(g);
+        case XNOR_ALGO_MFMA_SPLIT:
+        case XNOR_ALGO_MFMA_SPLIT_PAIRS:
+        case XNOR_ALGO_MFMA_SPLIT_THREE: {
+            const size_t need = algo == XNOR_ALGO_MFMA_SPLIT_PAIRS ? xnor::conv_fp32_pairs_workspace_bytes(g) : xnor::conv_fp32_split_workspace_bytes(g);
             if (need == 0) return XNOR_E_UNSUPPORTED;
             if (!workspace || workspace_bytes < need) return XNOR_E_WORKSPACE;
+            if (algo == XNOR_ALGO_MFMA_SPLIT_THREE) workspace_bytes = need;
             return hip_status(xnor::launch_conv_fp32_split(I, Wt, g, out, workspace, workspace_bytes, (hipStream_t)stream));
         }
         default:
@@ -527,7 +534,7 @@ int xnor_conv2d_fp32_fwd_ws(const float *I, const float *Wt, const xnor_shape *s
 int xnor_conv2d_fp32_fwd_algo(const float *I, const float *Wt, const xnor_shape *s, float *out, int algo,
                               void *stream)
 {
-    if (algo == XNOR_ALGO_MFMA_SPLIT) algo = -1;       // needs a workspace: not this call's
+    if (algo == XNOR_ALGO_MFMA_SPLIT || algo == XNOR_ALGO_MFMA_SPLIT_PAIRS || algo == XNOR_ALGO_MFMA_SPLIT_THREE) algo = -1;   // need a workspace: not this call's
     return xnor_conv2d_fp32_fwd_ws(I, Wt, s, out, nullptr, 0, algo, stream);
 }
 

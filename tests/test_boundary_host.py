@@ -388,3 +388,26 @@ def test_a_saved_shape_asks_the_library_that_loads_it(xb):
     for t in (pickle.loads(pickle.dumps(s)), copy.copy(s), copy.deepcopy(s)):
         assert t == s and not [k for k in t.__dict__ if k.startswith("_")]
         assert (xb.xnor_conv2d_workspace_bytes(t), xb.xnor_conv2d_fp32_workspace_bytes(t)) == sizes
+
+
+def test_fp32_split_forms_by_name(xb):
+    """Two and three terms by name: what they ask for, where they are refused, and a workspace that is too small."""
+    L, ok = xb.lib, ctypes.c_void_p(4096)
+    pairs, short = xb.Shape(1, 288, 12, 12, 40, 3, 3, 1, 1, 1, 1), xb.Shape(1, 272, 12, 12, 40, 3, 3, 1, 1, 1, 1)
+    nine = xb.Shape(1, 288, 16, 16, 8, 9, 9, 1, 1, 4, 4)
+    assert xb.xnor_conv2d_fp32_workspace_bytes(pairs, xb.ALGO_MFMA_SPLIT_PAIRS) == xb.xnor_conv2d_fp32_pairs_workspace_bytes(pairs)
+    for s in (pairs, short):
+        assert xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT_THREE) == xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT)
+    refused = [(short, xb.ALGO_MFMA_SPLIT_PAIRS), (nine, xb.ALGO_MFMA_SPLIT_PAIRS), (nine, xb.ALGO_MFMA_SPLIT_THREE)]
+    for s, algo in refused:
+        with pytest.raises(xb.XnorError) as e:
+            xb.xnor_conv2d_fp32_workspace_bytes(s, algo)
+        assert e.value.status == xb.E_UNSUPPORTED
+        assert L.xnor_conv2d_fp32_fwd_ws(ok, ok, ctypes.byref(s.c()), ok, ok, 1 << 40, algo, None) == xb.E_UNSUPPORTED
+    for algo in (xb.ALGO_MFMA_SPLIT_PAIRS, xb.ALGO_MFMA_SPLIT_THREE):
+        need = xb.xnor_conv2d_fp32_workspace_bytes(pairs, algo)
+        assert L.xnor_conv2d_fp32_fwd_ws(ok, ok, ctypes.byref(pairs.c()), ok, ok, need - 1, algo, None) == xb.E_WORKSPACE
+        assert L.xnor_conv2d_fp32_fwd_ws(ok, ok, ctypes.byref(pairs.c()), ok, None, need, algo, None) == xb.E_WORKSPACE
+        assert L.xnor_conv2d_fp32_fwd_algo(ok, ok, ctypes.byref(pairs.c()), ok, algo, None) == xb.E_UNSUPPORTED
+        assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(pairs.c()), ok, algo, None) == xb.E_UNSUPPORTED
+        assert L.xnor_conv2d_fwd_algo(ok, ok, ok, ok, ctypes.byref(pairs.c()), ok, None, ok, 1 << 30, algo, None) == xb.E_UNSUPPORTED

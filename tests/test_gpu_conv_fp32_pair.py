@@ -243,3 +243,29 @@ def test_pairs_beside_larger_values_are_no_less_exact_than_three_terms(xb, shape
     assert clear.any() and not clear.all()
     pair, three = (np.sqrt((((run(xb, I, Wt, s, f) - ref) / size)[clear] ** 2).mean()) for f in (True, False))
     assert 0 < pair <= three, (pair, three)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_pairs_run_by_name_and_by_workspace(xb, shape):
+    """Values of one size are summed from pairs in every workgroup (another form would give that form's bits), and either form has
+    a name under which the size of the workspace makes no difference."""
+    print(f"case conv_fp32 pair forms shape={shape}", flush=True)
+    rng = np.random.default_rng(zlib.crc32(("forms" + str(shape)).encode()))
+    s = xb.Shape(*shape)
+    I, Wt = ((1 + rng.random(d)) * rng.choice([-1, 1], d) for d in ((s.N, s.C, s.H, s.W), (s.F, s.C, s.kh, s.kw)))
+    I, Wt = dev(I.astype(np.float32)), dev(Wt.astype(np.float32))
+    small, large = xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT_THREE), xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT_PAIRS)
+    assert large == xb.xnor_conv2d_fp32_pairs_workspace_bytes(s) > small == xb.xnor_conv2d_fp32_workspace_bytes(s, xb.ALGO_MFMA_SPLIT)
+
+    def form(algo, nbytes):
+        return xb.xnor_conv2d_fp32_fwd(I, Wt, s, algo=algo, workspace=torch.full((nbytes,), 0xff, dtype=torch.uint8, device="cuda"))
+
+    pairs, three = form(xb.ALGO_MFMA_SPLIT_PAIRS, large), form(xb.ALGO_MFMA_SPLIT_THREE, small)
+    ref, S = sums64(I.cpu().numpy(), Wt.cpu().numpy(), s)
+    # (an output of a few terms, at a corner, can have the same bits either way; most of a 32 x 32 tile's can not)
+    differ = (pairs != three).cpu().numpy()[S > 0]
+    assert differ.mean() > 0.25
+    assert torch.equal(form(xb.ALGO_MFMA_SPLIT_THREE, 2 * large), three) and torch.equal(form(xb.ALGO_MFMA_SPLIT, large - 1), three)
+    assert torch.equal(form(xb.ALGO_MFMA_SPLIT_PAIRS, 2 * large), pairs) and torch.equal(form(xb.ALGO_MFMA_SPLIT, large), pairs)
+    for algo, want in ((xb.ALGO_MFMA_SPLIT_PAIRS, pairs), (xb.ALGO_MFMA_SPLIT_THREE, three)):
+        assert torch.equal(xb.xnor_conv2d_fp32_fwd(I, Wt, s, algo=algo), want)
