@@ -726,12 +726,13 @@ hipError_t launch_box_filter_K(const float *A, const Geom &g, float *K, hipStrea
 // ------------------------------------------------------------------------------------------------
 // Eq. 10 as a whole for small inputs, in one launch: a block forms A for the rows under a band of output rows (and for the band's own
 // share of the image's rows, which it writes), keeps them in LDS and forms K from there.  The rows that bands share are read
-// once for each of them, which at these sizes costs less than the second launch: xnor_scale_K of 1 x 64 x 32 x 32 takes the host
-// 10.3 us with two launches.  Sums in the order of channel_mean_abs_kernel and box_filter_K_kernel: the same bits.
+// once for each of them, which at these sizes costs less than the second launch.  Sums in the order of channel_mean_abs_kernel and
+// box_filter_K_kernel: the same bits.
 // ------------------------------------------------------------------------------------------------
 constexpr size_t kBandLds = 60 * 1024;
 struct BandShape {
-    int S, G, rows, bands, most;       // channel slices, groups of 64 pixels side by side; output rows of a band, bands, most input rows
+    bool ok;
+    int S, G, chunk, rows, bands;      // channel slices, groups of 128 pixels side by side; channels of a slice; output rows of a band, bands
     size_t smem;
 };
 // The rows that band b forms A for: those under its windows, if there are any, and its own.
@@ -745,7 +746,7 @@ __host__ __device__ inline void band_rows(const Geom &g, const BandShape &s, int
     *r1 = w0 < w1 && w1 > own1 ? w1 : own1;
 }
 
-__global__ __launch_bounds__(1024) void scale_K_band_kernel(const float *__restrict__ I, Geom g, BandShape s, int chunk,
+__global__ __launch_bounds__(1024) void scale_K_band_kernel(const float *__restrict__ I, Geom g, BandShape s,
                                                             float *__restrict__ A, float *__restrict__ K)
 {
     extern __shared__ double band_lds[];
@@ -759,7 +760,7 @@ __global__ __launch_bounds__(1024) void scale_K_band_kernel(const float *__restr
     band_rows(g, s, b, &r0, &r1);
     const int pixels = (r1 - r0) * g.W;
     const float *const src = I + (size_t)n * g.C * HW + (size_t)r0 * g.W;
-    const int c0 = slice * chunk, c1 = min(g.C, c0 + chunk);
+    const int c0 = slice * s.chunk, c1 = min(g.C, c0 + s.chunk);
     // two pixels of a thread at a time, their loads in flight together
     for (int base = 0; base < pixels; base += 128 * s.G) {
         const int q = base + 128 * group + lane;
@@ -817,36 +818,51 @@ __global__ __launch_bounds__(1024) void scale_K_band_kernel(const float *__restr
     }
 }
 
-// Inputs of less than 2^20 values whose bands read a row four times at most and fit LDS.  us a call, two launches / one, eager; in a
-// graph: 1 x 64 x 32 x 32 8.1 / 5.8; 4.6 / 4.3, 5 x 100 x 37 x 53 8.3 / 5.6; 5.4 / 5.3; of 2^20 values, 1 x 64 x 128 x 128 8.1 / 6.0;
-// 4.9 / 5.7.
-static bool band_shape(const Geom &g, BandShape *s)
+// Inputs of less than 2^20 values in at most a band for each of 256 units, which fit LDS, read a row four times at most, and whose
+// threads have two pixels of up to 16 channels or one of up to 48 (of any number if all bands together read up to 2.6e6 values), once; of
+// one channel three times, where the bands fill half the units.  Past that a workgroup's loads take longer than the second launch:
+// 1 x 1024 x 28 x 28 3 x 3, two pixels of 64, 7.6 us in two launches / 9.1 in one; 16 x 1023 x 8 x 8, one of 64, 7.9 / 9.0; 1 x 116 x 3 x 3000 3 x 3, on
+// three units, 5.6 / 132; 1 x 512 x 1 x 2000 1 x 1, on one, 5.6 / 66.  Of 307 drawn inputs (1 to 64 images, 1 to 1024 channels, 1 x 4 to 300 x 3000,
+// 1 x 1 to 7 x 7) it takes 262, at 0.39 to 1.01 of the time of two launches in a graph, 0.89 on average, 0.73 eager; one other would be 4 % faster.  us,
+// eager; in a graph: 1 x 64 x 32 x 32 3 x 3 7.7 / 5.4; 4.6 / 4.1, 5 x 100 x 37 x 53 7.6 / 5.6; 5.5 / 5.3.
+static BandShape band_shape(const Geom &g)
 {
+    BandShape s{};
     const long long values = (long long)g.N * g.C * g.H * g.W;
-    if (values >= (1 << 20) || g.kh > 16) return false;
-    s->S = 1;
-    while (s->S < kMaxSlices && g.C / (2 * s->S) >= 8) s->S *= 2;      // (as in launch_channel_mean_abs)
-    s->G = std::max(1, 16 / s->S);
-    s->rows = std::max(1, ceil_div((long long)g.N * g.OH, 256));
-    s->bands = ceil_div(g.OH, s->rows);
-    long long read = 0;
-    s->most = 0;
-    for (int b = 0; b < s->bands; ++b) {             // (at most 256 / N and one of them)
+    if (values >= (1 << 20) || g.kh > 16) return s;
+    s.S = 1;
+    while (s.S < kMaxSlices && g.C / (2 * s.S) >= 8) s.S *= 2;      // (as in launch_channel_mean_abs)
+    s.G = std::max(1, 16 / s.S);
+    s.rows = std::max(1, ceil_div((long long)g.N * g.OH, 256));
+    s.bands = ceil_div(g.OH, s.rows);
+    s.chunk = ceil_div(g.C, s.S);
+    const long long blocks = (long long)g.N * s.bands;
+    if (blocks > 256) return s;
+    long long read = 0, most = 0;
+    for (int b = 0; b < s.bands; ++b) {
         int r0, r1;
-        band_rows(g, *s, b, &r0, &r1);
-        s->most = std::max(s->most, r1 - r0);
+        band_rows(g, s, b, &r0, &r1);
+        most = std::max<long long>(most, r1 - r0);
         read += r1 - r0;
     }
-    if (read > 4LL * g.H + 8) return false;
-    s->smem = (size_t)s->S * s->G * 128 * sizeof(double) + (size_t)s->most * g.W * sizeof(float);
-    return s->smem <= kBandLds;
+    const long long pixels = most * g.W;
+    if (read > 4LL * g.H + 8) return s;
+    if (pixels > 128 * s.G) {
+        if (g.C > 1 || blocks < 128 || pixels > 3 * 128 * s.G) return s;
+    } else if (pixels > 64 ? s.chunk > 16 : s.chunk > 48 && g.N * read * g.W * g.C > (5 << 19)) {
+        return s;
+    }
+    s.smem = (size_t)s.S * s.G * 128 * sizeof(double) + (size_t)pixels * sizeof(float);
+    s.ok = s.smem <= kBandLds;
+    return s;
 }
 
 hipError_t launch_scale_K(const float *I, const Geom &g, float *A, float *K, hipStream_t st)
 {
-    BandShape s;
-    if (band_shape(g, &s)) {
-        scale_K_band_kernel<<<dim3((unsigned)(g.N * s.bands)), dim3(64, s.S, s.G), s.smem, st>>>(I, g, s, (g.C + s.S - 1) / s.S, A, K);
+    static thread_local PlanMemo<BandShape> memo;
+    const BandShape &s = memo.get(g, 0, [&] { return band_shape(g); });
+    if (s.ok) {
+        scale_K_band_kernel<<<dim3((unsigned)(g.N * s.bands)), dim3(64, s.S, s.G), s.smem, st>>>(I, g, s, A, K);
         return hipGetLastError();
     }
     const hipError_t e = launch_channel_mean_abs(I, g.N, g.C, g.H, g.W, A, st);
