@@ -380,7 +380,8 @@ struct Fp6Wave {
             stage(0, wave, all_waves);
             __syncthreads();
             if (stager) {
-                // a round's loads are in flight while the round before is cut into digits; lanes past the last block load that one
+                // a round's loads are in flight while the round before is cut into digits, up to the chunk's end; lanes past the last block
+                // load that one
                 const int first = wave - waves, round = 64 * p.stagers;
                 auto load_ahead = [&](Block &b, int ch, int r) __attribute__((always_inline)) {
                     const int i = min(r + 64 * first + lane, npos * words_in(ch) - 1);
@@ -403,9 +404,7 @@ struct Fp6Wave {
                         split_block(cur, to + g * word_bytes + pos * kPosBytes, i < blocks);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    // the words are in LDS: behind them there are the 32 loads of the next round, if there is one
-                    if (blocks > 0 && ch + 1 < nchunks) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
-                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the words are in LDS (and the next round's values in registers)
                     __syncthreads();                     // chunk ch is there, chunk ch - 1 has been read
                 }
                 return;
