@@ -342,6 +342,19 @@ int xnor_bwn_split_plan(const xnor_shape *s, int compute_units, int *tiles, int 
                         size_t *lds_bytes, long long *workgroups);
 
 /*
+ * The same of XNOR_ALGO_MFMA_SPLIT_FP6.
+ *   *filter_tiles  tiles of 32 filters a wave takes (1..4)
+ *   *words         words of 32 channels staged at a time (1, 2)
+ *   *splits        waves that share a pixel tile's digits, each with filters of its own (1..4)
+ *   *tiles         32-pixel tiles a workgroup takes
+ *   *stagers       its waves that only stage (0, 3, 4)
+ *   *lds_bytes     dynamic LDS per workgroup (<= 160 KB)
+ *   *workgroups    N x ceil(tiles of an image / *tiles) x ceil(F / (32 * *filter_tiles * *splits))
+ */
+int xnor_bwn_fp6_plan(const xnor_shape *s, int compute_units, int *filter_tiles, int *words, int *splits, int *tiles, int *stagers,
+                      size_t *lds_bytes, long long *workgroups);
+
+/*
  * Real-valued ("vanilla") convolution: the float comparison that the paper's timings set the XNOR
  * convolution against (Sec. IV, Table I).  Nothing is binarised and there are no scaling factors:
  *     out[n][f][oy][ox] = sum over in-image taps and channels of I * Wt

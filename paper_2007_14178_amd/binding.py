@@ -127,6 +127,7 @@ def _load() -> ctypes.CDLL:
     L.xnor_conv2d_pick_algo.argtypes = [sp, sz]
     L.xnor_bwn_pick_algo.argtypes = [sp]
     L.xnor_bwn_split_kernel.argtypes = [sp]
+    L.xnor_bwn_fp6_plan.argtypes = [sp, ci] + [ctypes.POINTER(ci)] * 5 + [ctypes.POINTER(sz), ctypes.POINTER(ctypes.c_longlong)]
     L.xnor_bwn_split_plan.argtypes = [sp, ci, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(sz),
                                       ctypes.POINTER(ctypes.c_longlong)]
     L.xnor_conv2d_workspace_bytes.argtypes = [sp, ctypes.POINTER(sz)]
@@ -136,7 +137,7 @@ def _load() -> ctypes.CDLL:
                  "xnor_filter_expand", "xnor_conv2d_fwd_expanded", "xnor_box_filter_K",
                  "xnor_conv2d_chain_workspace_bytes", "xnor_conv2d_fwd_chain",
                  "xnor_forward_image_supported", "xnor_forward_image",
-                 "xnor_bwn_conv2d_fwd", "xnor_bwn_conv2d_fwd_algo", "xnor_bwn_split_kernel",
+                 "xnor_bwn_conv2d_fwd", "xnor_bwn_conv2d_fwd_algo", "xnor_bwn_split_kernel", "xnor_bwn_fp6_plan",
                  "xnor_prepare", "xnor_conv2d_fwd_static",
                  "xnor_probe_mfma_fp4", "xnor_probe_mfma_bf16", "xnor_probe_xor_popcount", "xnor_probe_copy", "xnor_probe_read",
                  "xnor_conv2d_fp32_fwd", "xnor_conv2d_fp32_fwd_algo", "xnor_conv2d_fp32_fwd_ws",
@@ -511,6 +512,15 @@ def xnor_bwn_split_plan(s: Shape, compute_units: int = 0) -> dict:
     _ok(lib.xnor_bwn_split_plan(ctypes.byref(s.c()), compute_units, ctypes.byref(t), ctypes.byref(r),
                                 ctypes.byref(b), ctypes.byref(w)), "xnor_bwn_split_plan")
     return {"tiles": t.value, "row_segments": r.value, "lds_bytes": b.value, "workgroups": w.value}
+
+
+def xnor_bwn_fp6_plan(s: Shape, compute_units: int = 0) -> dict:
+    """The launch ALGO_MFMA_SPLIT_FP6 makes for this shape: filter tiles a wave, words a chunk, splits, pixel tiles, stagers, LDS
+    bytes per workgroup, workgroups."""
+    v = [ctypes.c_int() for _ in range(5)]
+    b, w = ctypes.c_size_t(), ctypes.c_longlong()
+    _ok(lib.xnor_bwn_fp6_plan(ctypes.byref(s.c()), compute_units, *map(ctypes.byref, v), ctypes.byref(b), ctypes.byref(w)), "xnor_bwn_fp6_plan")
+    return dict(zip(("filter_tiles", "words", "splits", "tiles", "stagers"), (x.value for x in v)), lds_bytes=b.value, workgroups=w.value)
 
 
 def xnor_bwn_conv2d_fwd(I: torch.Tensor, Wpk: torch.Tensor, alpha: torch.Tensor, s: Shape,

@@ -597,7 +597,7 @@ Fp6Plan search_fp6_plan(const Geom &g, int cus)
             for (int splits = 1; splits <= kMaxSplits && (splits == 1 || 32 * nf * (splits - 1) < g.F); ++splits)
                 for (int t = std::min(kMaxWaves / splits, tiles); t >= 1; --t) {
                     const int waves = splits * t;
-                                        if (splits == 2 && (waves == 2 || waves == 4 || waves == 8)) consider(least, other, nf, G, splits, t, 0);
+                    if (splits == 2 && (waves == 2 || waves == 4 || waves == 8)) consider(least, other, nf, G, splits, t, 0);
                     if (waves <= 4 && (nf == 1 || (nf == 2 && t <= 2)))
                         for (int stagers = 3; stagers <= 4; ++stagers) consider(least, other, nf, G, splits, t, stagers);
                 }
@@ -680,6 +680,13 @@ hipError_t launch_fp6_plan(const Fp6Plan &pl, const float *I, const uint32_t *Wp
 
 bool bwn_fp6_supports(const Geom &g) { return make_fp6_plan(g).ok; }
 double bwn_fp6_cycles(const Geom &g) { return make_fp6_plan(g).cycles; }
+bool bwn_fp6_plan(const Geom &g, int cus, Fp6Shape *out)
+{
+    const Fp6Plan pl = search_fp6_plan(g, cus > 0 ? cus : compute_units());
+    if (!pl.ok) return false;
+    *out = {pl.nf, pl.G, pl.splits, pl.waves / pl.splits, pl.stagers, pl.lds, (long long)g.N * pl.wgs * ceil_div(g.F, 32 * pl.nf * pl.splits)};
+    return true;
+}
 
 hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out,
                           hipStream_t st)

@@ -445,6 +445,21 @@ int xnor_bwn_split_plan(const xnor_shape *s, int compute_units, int *tiles, int 
                ? XNOR_OK : XNOR_E_UNSUPPORTED;
 }
 
+int xnor_bwn_fp6_plan(const xnor_shape *s, int compute_units, int *filter_tiles, int *words, int *splits, int *tiles, int *stagers,
+                      size_t *lds_bytes, long long *workgroups)
+{
+    if (!s || !filter_tiles || !words || !splits || !tiles || !stagers || !lds_bytes || !workgroups) return XNOR_E_NULL;
+    if (compute_units < 0) return XNOR_E_SHAPE;
+    xnor::Geom g;
+    const int rc = make_geom(s, &g);
+    if (rc) return rc;
+    xnor::Fp6Shape f;
+    if (!xnor::bwn_fp6_plan(g, compute_units, &f)) return XNOR_E_UNSUPPORTED;
+    *filter_tiles = f.filter_tiles; *words = f.words; *splits = f.splits; *tiles = f.tiles; *stagers = f.stagers;
+    *lds_bytes = f.lds_bytes; *workgroups = f.workgroups;
+    return XNOR_OK;
+}
+
 int xnor_bwn_conv2d_fwd(const float *I, const uint32_t *Wpk, const float *alpha, const xnor_shape *s,
                         float *out, void *stream)
 {

@@ -123,6 +123,12 @@ hipError_t launch_bwn_split(const float *I, const uint32_t *Wpk, const float *al
                             float *out, hipStream_t st);
 bool bwn_fp6_supports(const Geom &g);
 double bwn_fp6_cycles(const Geom &g);
+struct Fp6Shape {
+    int filter_tiles, words, splits, tiles, stagers;
+    size_t lds_bytes;
+    long long workgroups;
+};
+bool bwn_fp6_plan(const Geom &g, int compute_units, Fp6Shape *out);
 hipError_t launch_bwn_fp6(const float *I, const uint32_t *Wpk, const float *alpha, const Geom &g, float *out,
                           hipStream_t st);
 bool conv_fp32_mfma_supports(const Geom &g);

@@ -181,16 +181,16 @@ SPLIT_SHAPES = [
     (1, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1),     # stagers, one filter tile a wave
     (2, 271, 13, 14, 250, 3, 3, 1, 1, 1, 1),     # ... a last word of 15 channels, an odd number of chunks, a short last tile
     (32, 512, 7, 7, 505, 3, 3, 1, 1, 1, 1),      # ... two splits, the last one's filters short
-    (3, 97, 12, 12, 33, 3, 3, 1, 1, 1, 1),       # ... a split of one filter, a last chunk of one word of one channel
+    (3, 97, 12, 12, 33, 3, 3, 1, 1, 1, 1),       # ... a last filter tile of one filter, a last chunk of one word of one channel
     (2, 448, 5, 6, 32, 3, 3, 1, 1, 1, 1),        # ... fewer pixels than the tiles have
     (8, 192, 27, 27, 256, 5, 5, 1, 1, 2, 2),     # ... several rounds a chunk
     (76, 448, 10, 10, 32, 3, 3, 2, 2, 1, 1),     # ... strides
-    (2, 64, 9, 9, 70, 1, 1, 1, 1, 0, 0),         # ... two chunks of a word, one tap
+    (2, 64, 9, 9, 70, 1, 1, 1, 1, 0, 0),         # ... one chunk, one tap
     (4, 320, 9, 70, 64, 1, 1, 2, 2, 0, 0),
     (1, 96, 8, 8, 40, 3, 3, 1, 1, 6, 6),         # ... windows, and workgroups, that are all padding
     (1, 160, 3, 40, 20, 2, 5, 3, 1, 4, 0),
     (128, 384, 13, 13, 384, 3, 3, 1, 1, 1, 1),   # two splits without stagers
-    (120, 390, 13, 13, 300, 3, 3, 1, 1, 1, 1),   # ... the second split's filters short
+    (120, 390, 13, 13, 300, 3, 3, 1, 1, 1, 1),   # neither, beside it: more filters than the splits' estimate takes
 ]
 
 
@@ -235,3 +235,38 @@ def test_splits_and_stagers_in_a_graph(xb, shape):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, xb.xnor_bwn_conv2d_fwd(I, Wpk, alpha, s))
+
+
+#    N   C   H   W    F  k  s, what the workgroups are: filter tiles a wave, words a chunk, splits, pixel tiles, stagers
+FORMS = [
+    ((1, 68, 16, 16, 29, 3, 2), (1, 1, 1, 2, 4)),       # three chunks of a word
+    ((5, 71, 34, 26, 26, 1, 2), (1, 1, 1, 1, 3)),
+    ((1, 100, 5, 5, 32, 1, 1), (1, 2, 1, 1, 3)),
+    ((2, 109, 37, 50, 100, 3, 2), (1, 1, 2, 2, 4)),     # several rounds a chunk
+    ((14, 61, 36, 36, 90, 7, 2), (1, 1, 3, 1, 4)),      # three splits, the last one's filters short
+    ((3, 90, 25, 23, 33, 1, 2), (1, 2, 2, 1, 4)),       # a split of one filter
+    ((13, 102, 28, 23, 34, 1, 1), (1, 2, 2, 2, 3)),     # ... of two, two pixel tiles
+    ((3, 76, 19, 18, 73, 3, 2), (1, 2, 3, 1, 4)),
+    ((1, 43, 16, 22, 297, 3, 2), (1, 2, 3, 1, 4)),      # ... two splits of the last group without filters
+    ((2, 51, 25, 25, 112, 3, 2), (1, 2, 4, 1, 4)),      # four splits
+    ((10, 190, 27, 27, 486, 3, 2), (2, 1, 3, 1, 4)),    # two filter tiles a wave
+    ((28, 62, 33, 26, 213, 3, 2), (2, 1, 4, 1, 4)),     # ... the last split's second tile empty
+    ((17, 35, 27, 31, 68, 1, 1), (2, 2, 2, 2, 4)),
+    ((21, 52, 17, 17, 205, 1, 1), (2, 2, 2, 2, 3)),
+    ((18, 226, 15, 14, 450, 3, 1), (2, 2, 4, 1, 4)),
+    ((24, 53, 28, 29, 131, 1, 1), (1, 2, 2, 2, 0)),     # splits without stagers
+    ((14, 104, 38, 29, 484, 1, 1), (2, 2, 2, 2, 0)),
+    ((19, 126, 35, 48, 137, 3, 1), (3, 1, 2, 2, 0)),    # ... the second split's filters short
+    ((24, 74, 36, 36, 134, 3, 1), (3, 2, 2, 2, 0)),
+]
+
+
+@pytest.mark.parametrize("layer, form", FORMS, ids=lambda v: "x".join(map(str, v)))
+def test_workgroups_of_every_form(xb, layer, form):
+    """The form is what the plan for 256 units says that it is, and the device's plan is that one."""
+    N, C, H, W, F, k, st = layer
+    shape = (N, C, H, W, F, k, k, st, st, k // 2, k // 2)
+    plan = xb.xnor_bwn_fp6_plan(xb.Shape(*shape), 256)
+    assert tuple(plan[n] for n in ("filter_tiles", "words", "splits", "tiles", "stagers")) == form
+    assert xb.xnor_bwn_fp6_plan(xb.Shape(*shape)) == plan
+    check(xb, shape, torch.randn(shape[:4], generator=torch.Generator().manual_seed(sum(shape))), sum(shape))
