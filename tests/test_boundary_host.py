@@ -411,3 +411,25 @@ def test_fp32_split_forms_by_name(xb):
         assert L.xnor_conv2d_fp32_fwd_algo(ok, ok, ctypes.byref(pairs.c()), ok, algo, None) == xb.E_UNSUPPORTED
         assert L.xnor_bwn_conv2d_fwd_algo(ok, ok, ok, ctypes.byref(pairs.c()), ok, algo, None) == xb.E_UNSUPPORTED
         assert L.xnor_conv2d_fwd_algo(ok, ok, ok, ok, ctypes.byref(pairs.c()), ok, None, ok, 1 << 30, algo, None) == xb.E_UNSUPPORTED
+
+
+def test_bwn_stagers_have_a_unit_to_themselves(xb):
+    """Workgroups with waves that only stage are for launches of at most one a compute unit, counted where a pixel block's filter
+    groups run: on one of the eight XCDs.  (N, C, H, W, F, k, stride, pad): on some of these 33 to 36 would run on the 32 units of one."""
+    layers = [(21, 197, 32, 32, 300, 1, 2, 0), (9, 91, 23, 23, 367, 7, 1, 3), (3, 256, 28, 28, 352, 7, 1, 3), (6, 256, 17, 17, 384, 7, 2, 3),
+              (5, 130, 27, 18, 328, 7, 1, 0), (1, 64, 42, 39, 192, 5, 1, 0), (1, 256, 14, 14, 256, 3, 1, 1), (32, 512, 7, 7, 512, 3, 1, 1),
+              (8, 192, 27, 27, 256, 5, 1, 2), (64, 256, 14, 14, 256, 3, 1, 1)]
+    staged = 0
+    for N, C, H, W, F, k, st, p in layers:
+        plan = xb.xnor_bwn_fp6_plan(xb.Shape(N, C, H, W, F, k, k, st, st, p, p), 256)
+        groups = -(-F // (32 * plan["filter_tiles"] * plan["splits"]))
+        blocks = plan["workgroups"] // groups
+        assert plan["lds_bytes"] <= 160 * 1024 and plan["splits"] * plan["tiles"] + plan["stagers"] <= 8
+        if plan["stagers"]:
+            staged += 1
+            assert -(-blocks // 8) * groups <= 32, (N, C, H, W, F, k, st, p)
+    assert staged >= 5
+    with pytest.raises(xb.XnorError) as e:
+        xb.xnor_bwn_fp6_plan(xb.Shape(1, 64, 8, 4000, 8, 3, 3, 1, 1, 1, 1), 256)
+    assert e.value.status == xb.E_UNSUPPORTED
+    assert xb.lib.xnor_bwn_fp6_plan(None, 0, *[None] * 7) == xb.E_NULL
