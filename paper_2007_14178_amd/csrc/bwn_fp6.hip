@@ -24,14 +24,14 @@
 //   more workgroups on a compute unit fill each other's.
 //
 //   Two shapes of workgroup more, where estimates of all say so (search_fp6_plan).  Splits: the waves of a pixel tile have filters
-//   of their own and share the tile's digits, so that a block is cut for more filters (128x384x13x13 F=384 3x3 107 -> 96 us).
+//   of their own and share the tile's digits, so that a block is cut for more filters (128x384x13x13 F=384 3x3 105 -> 91 us).
 //   Stagers: three or four waves that only stage, into two buffers, a chunk ahead of the others, the next round's loads in
 //   flight while a round is cut: layers that leave units with one workgroup, whose chunk's chain nothing else hides
 //   (32x512x7x7 F=512 3x3 41 -> 29 us, 1x256x14x14 F=256 3x3 19 -> 13.5; 200 drawn layers with both 1.17 times as fast).
 //
 //   Bound by: the matrix pipe at the card's power (6.3 PFLOP/s of this pair of formats in a loop of random digits, 9.0 of
-//   zeros; an instruction takes 32 cycles; the first layer above with nothing but its matrix instructions and stores takes 83 us), then by the digits' conversions (about 1200 cycles per 64 blocks,
-//   again for every filter group) and the wait for a chunk's loads, which other workgroups fill in part.
+//   zeros; an instruction takes 32 cycles; the first layer above with nothing but its matrix instructions and stores takes 83 us),
+//   then by the digits' conversions (about 1200 cycles per 64 blocks, again for every filter group) and the wait for a chunk's loads, which other workgroups fill in part.
 //   Passes against the bf16 terms: 128x384x13x13 F=384 3x3 177 -> 104 us; loops of launches: 128x512x28x28 F=512 3x3
 //   1300 -> 706 us, 16x128x56x56 F=128 7x7 291 -> 116, 1x256x14x14 F=256 3x3 48 -> 23.
 //   Relative error against 64-bit sums 5.2e-7 -> 2.6e-7 (fewer roundings of the sum: five per 64 channels, not twelve).
@@ -498,8 +498,8 @@ double fp6_cost(const Fp6Costs &c, const Geom &g, int nf, int G, int waves, int 
     chunks(g.Cw / G, G);
     if (g.Cw % G) chunks(1, 1);
     const double alone = mfma + convert + wait + c.stores * nf;
-    // registers hold three waves on a SIMD, four with one filter tile; of workgroups of five to eight waves, which
-    // put two on some SIMD, one or two
+    // registers hold three waves on a SIMD, four with one filter tile (with two filter tiles four as well, as the other estimate below
+    // has it; this one's constants were fitted with three); of workgroups of five to eight waves, which put two on some SIMD, one or two
     const int per_simd = nf == 1 ? 4 : 3;
     const int held = std::max(1, std::min((int)(kLds / lds), waves > 4 ? per_simd / 2 : 4 * per_simd / waves));
     auto batch = [&](long long n) {
@@ -596,7 +596,9 @@ Fp6Plan search_fp6_plan(const Geom &g, int cus)
     });
     if (pl.ok) {
         pl.cycles = fp6_cost(kRouteCosts, g, pl.nf, pl.G, pl.waves, pl.positions, pl.lds, busiest_of(pl.wgs, 32 * pl.nf));
-        // a shape with splits or stagers, where it is the better one by a margin
+        // A shape with splits or stagers, where it is the better one by a margin.  Without stagers two splits in 2, 4 or 8 waves, as the estimate
+        // was fitted for: with the other numbers of both it would choose differently in 2 % of 7800 drawn layers, 0.91 of the time on
+        // average and up to 1.35 times.  The route to this form or the other keeps the estimate of the shape without.
         Fp6Plan other{};
         double least = -1.0;
         shapes([&](int nf, int G) {

@@ -75,9 +75,10 @@
 // their size, whose largest error is 0.6 to 2.2 times (the chain that holds those is the longer one).
 //   conv_fp32_split_kernel<.., PAIR> has the tiles and the staging of the other forms, 80 bytes a position.  The A operands
 // are a ring of three taps (two where the window's taps are no multiple of three) in registers, an operand fetched again behind
-// its last use, 26 (14) matrix instructions ahead.  What it measured at the first layer: pairs with the six products' loop
+// its last use, 26 (14) matrix instructions ahead; those fetched in a chunk's last tap are waited for at its end, with the values of the chunk
+// after the next, for their magnitudes.  What it measured at the first layer: pairs with the six products' loop
 // 1435 us, with one buffer descriptor for an image in place of one a plane and without a load at the head of a chunk 1355, with the
-// ring, and granules for the positions that there are (240; 384 had been handled), 1275, with the high terms' multiplications 1320.  Matrix pipe busy 63 % of the cycles at 1.72 GHz;
+// ring, and granules for the positions that there are (240; 384 had been handled), 1275 (matrix pipe busy 63 % of the cycles at 1.72 GHz), with the high terms' multiplications 1320;
 // a loop of the matrix instructions alone takes 895 us, at the card's power.  Timing-only builds: without A loads
 // 12 % shorter, without B reads 9, without commits 15.
 //
@@ -609,7 +610,8 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
         const uint32_t top = wave_max(__float_as_uint(m) & ~kTinyBit);
         if (lane == 0) words[4 * (ch & 1) + (threadIdx.x >> 6)] = top;
     };
-    // The power of two of the chunk to be committed next, of the one being multiplied, the smallest so far; of the first, in bits.
+    // The power of two of the chunk to be committed next, of the one being multiplied, the smallest so far; the first as a factor, with and
+    // without that of the low terms.
     int xexp = 0, xexp_now = 0, xleast = kPairMost;
     float xscale = 1.f, xscale_low = 1.f;
     uint32_t xlow = 0;                           // below it a (doubled) value is held in part

@@ -53,10 +53,11 @@ int pick_algo(const xnor::Geom &g, size_t workspace_bytes)
     return XNOR_ALGO_DIRECT;
 }
 
-// Where the three-term kernel is the faster real-valued convolution (given a workspace).  It is the more
-// exact one everywhere (see conv_fp32_split.hip).  Measured, what runs without a workspace -> split:
-// 128x512x28x28 F=512 3x3 5.14 -> 2.39 ms, 16x128x56x56 F=128 5x5 1712 -> 236 us, 7x7 22.07 -> 0.62 ms,
-// 16x224x224 three channels F=64 7x7 stride 2 996 -> 364 us.  A launch that does not fill the chip is as long as a
+// Where the split kernel is the faster real-valued convolution (given a workspace).  It is more exact than the kernels
+// that need none.  Measured, what runs without a workspace -> split, in two terms (the first two; three terms 2.36 ms, 245 us) and in three:
+// 128x512x28x28 F=512 3x3 5.14 -> 1.33 ms, 16x128x56x56 F=128 5x5 1712 -> 141 us; 7x7 22.07 -> 0.62 ms,
+// 16x224x224 three channels F=64 7x7 stride 2 996 -> 364 us.  (All layers of two terms are far inside the lines below, which are those
+// of three.)  A launch that does not fill the chip is as long as a
 // workgroup's chain of 16-channel chunks behind a filter pass and a first fetch, 12 us together, and this decides:
 //  * against the fp32 matrix form, whose chain is 8 channels a chunk.  With its four-wide filter fetch (C % 8 == 0,
 //    up to 9 taps) 3 x 3 layers of 2 x 32 x 32 F=64 take 8.8 / 13 / 22 / 40 us with 8 / 16 / 32 / 64 channels (split 14.0 /
