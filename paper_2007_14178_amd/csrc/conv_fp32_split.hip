@@ -61,7 +61,7 @@
 // too: h * h gets it from its operands, multiplied by 2^5 and 2^6 in their registers behind the other two products.  (Stored as
 // they are, low terms leave f16's normal range from 2^-17 of the largest on: an output that only values of 2^-20 of their
 // neighbours' size go into had 2.5 to 4.2 times the error of three terms, and has 0.79 to 0.94 of it so.  The multiplications
-// cost 4 % at the first layer above and 1 % at the second.)
+// cost 4 % at the first layer above, 2 % at the second, and 2.4 % on average over 100 drawn layers.)
 //   Smaller values are held in part, within 2^-45 of the largest.  What all of them can do to an output is bounded by their number
 // (3 in 10^7 of normal values); a wave forms the few outputs below 2^22 times that one by one, in 64 bits.  Where there are
 // more of them, or a value without a power of two (infinite, NaN, of 2^-46 or 2^68), or an output that came out infinite, NaN or
@@ -213,12 +213,16 @@ __device__ inline uint32_t pack_f16(float a, float b)
     const floatx2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halfx2));
 }
-// eight f16 times 2^N
-template <int N>
+// half of eight f16 (0: the first four) times 2^N
+template <int N, int HALF>
 __device__ inline void scale_f16(uint4 &v)
 {
-    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-    v = __builtin_bit_cast(uint4, __builtin_bit_cast(half8, v) * (half8)(_Float16)(1 << N));
+    auto times = [](uint32_t t) __attribute__((always_inline)) {
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(halfx2, t) * (halfx2)(_Float16)(1 << N));
+    };
+    uint32_t &x = HALF ? v.z : v.x, &y = HALF ? v.w : v.y;
+    x = times(x);
+    y = times(y);
 }
 // what the f16 pair `t` leaves of (a, b), times 2^kPairShift, for (a, b) given so; exact
 __device__ inline void leave_pair_f16(float &a, float &b, uint32_t t)
@@ -627,9 +631,9 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
         return held;
     };
     auto tops_of = [&](int ch) __attribute__((always_inline)) { return *reinterpret_cast<const uint4 *>(words + 4 * (ch & 1)); };
-    constexpr int kPieces = 2 * kGran + 1, kUnits = 5;
+    constexpr int kPieces = 2 * kGran + 1, kUnits = 6;
     float pv[4];
-    uint32_t ph[2], lows = 0;
+    uint32_t ph[2], pu[4], lows = 0;
     auto commit_unit = [&](float (&from)[kGran][8], auto piece_c, auto unit_c, int ch) __attribute__((always_inline)) {
         constexpr int S = decltype(piece_c)::value, U = decltype(unit_c)::value;
         if constexpr (S < 2 * kGran) {
@@ -638,19 +642,19 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
 #pragma unroll
                 for (int k = 0; k < 4; ++k) pv[k] = from[q][4 * hf + k] * xscale;
             } else if constexpr (U == 1) {       // (0 less one wraps to the top)
-                uint32_t u = 0xffffffffu;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) u = min(u, (__float_as_uint(from[q][4 * hf + k]) << 1) - 1u);
-                lows += u < xlow - 1u;           // (four at most)
+                for (int k = 0; k < 4; ++k) pu[k] = (__float_as_uint(from[q][4 * hf + k]) << 1) - 1u;
             } else if constexpr (U == 2) {
+                lows += min(min(pu[0], pu[1]), min(pu[2], pu[3])) < xlow - 1u;       // (four at most)
                 ph[0] = pack_f16(pv[0], pv[1]);
                 ph[1] = pack_f16(pv[2], pv[3]);
             } else if constexpr (U == 3) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) pv[k] = from[q][4 * hf + k] * xscale_low;
+            } else if constexpr (U == 4) {
                 leave_pair_f16(pv[0], pv[1], ph[0]);
                 leave_pair_f16(pv[2], pv[3], ph[1]);
-            } else if constexpr (U == 4) {
+            } else if constexpr (U == 5) {
                 uint2 *dst = reinterpret_cast<uint2 *>(lds_raw + (ch & 1) * tile_bytes + wr_off[q] + hf * 8);
                 dst[0] = make_uint2(ph[0], ph[1]);
                 dst[4] = make_uint2(pack_f16(pv[0], pv[1]), pack_f16(pv[2], pv[3]));
@@ -665,6 +669,7 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
         commit_unit(from, piece_c, std::integral_constant<int, 2>{}, ch);
         commit_unit(from, piece_c, std::integral_constant<int, 3>{}, ch);
         commit_unit(from, piece_c, std::integral_constant<int, 4>{}, ch);
+        commit_unit(from, piece_c, std::integral_constant<int, 5>{}, ch);
     };
     auto commit_rest = [&](float (&of)[kGran][8], int from, int ch) __attribute__((always_inline)) {
         if (from <= 0) commit_piece(of, std::integral_constant<int, 0>{}, ch);
@@ -737,6 +742,7 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
     lows = 0;
     __syncthreads();
 
+    static_assert(NT <= 2, "where the operands are scaled");
     floatx16 acc[2][kTiles], chain[2][kTiles];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -781,17 +787,21 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
             };
             const int row_step = (p.pitch - p.kw + 1) * kPairPosBytes;
             int kx = 0, off = 0, left = taps, in_chain = pair_chain_taps(taps);
-            // A tap, its operands in slot `slot` of the ring, with pieces FIRST .. FIRST + COUNT - 1 of the commit: high * low, low * high,
-            // high * high of all tiles, the high operands scaled for the last between, an operand fetched again behind its last use, the
-            // next tap's place found between.
+            // A tap, its operands in slot `slot` of the ring, with pieces FIRST .. FIRST + COUNT - 1 of the commit: high * low, low * high (in
+            // the order that leaves the fetches more time: the first first, for B's, or last, for A's in the shorter ring), high * high of all
+            // tiles, the high operands scaled for the last behind their other product, no more vector instructions to a unit than issue under a
+            // matrix instruction, an operand fetched again behind its last use, the next tap's place found between.  (100 drawn layers 2.2 %
+            // faster than with all of an operand's scaling in one unit, commits in five units and the first order alone; with either order for both
+            // rings the other one's layers are 2 % slower.)
+            constexpr int kHighLow = RING == 2 ? 1 : 0, kLowHigh = 1 - kHighLow;
             auto tap_body = [&](auto slot_c, auto first_c, auto count_c) __attribute__((always_inline)) {
                 constexpr int slot = decltype(slot_c)::value, FIRST = decltype(first_c)::value, COUNT = decltype(count_c)::value;
                 __builtin_amdgcn_sched_barrier(0);
                 auto unit = [&](auto m_c) __attribute__((always_inline)) {
                     constexpr int M = decltype(m_c)::value;
                     if constexpr (M < 6 * NT) {
-                        constexpr int P = M / (2 * NT), j = M % (2 * NT) / 2, i = M & 1, ta = P == 1 ? 1 : 0;
-                        chain[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[slot][i][ta]), __builtin_bit_cast(halfx8, P == 0 ? bl[j] : bh[j]),
+                        constexpr int P = M / (2 * NT), j = M % (2 * NT) / 2, i = M & 1, ta = P == kLowHigh ? 1 : 0;
+                        chain[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a[slot][i][ta]), __builtin_bit_cast(halfx8, P == kHighLow ? bl[j] : bh[j]),
                                                                              chain[i][j], 0, 0, 0);
                         if constexpr (M == 1) {
                             const bool wrap = kx + 1 == p.kw;
@@ -799,13 +809,24 @@ __device__ __attribute__((always_inline)) bool pair_wave(const Fp32SplitParams &
                             kx = wrap ? 0 : kx + 1;
                             off = left > 0 ? off + (wrap ? row_step : kPairPosBytes) : 0;
                         }
-                        if constexpr (j == NT - 1 && P == 0) scale_f16<kPairUpW>(a[slot][i][0]);
-                        if constexpr (j == NT - 1 && P != 0) load_a(slot, i, ta);
-                        if constexpr (i == 1 && P == 0) read_b(bl[j], 1, base[j] + off);
-                        if constexpr (i == 1 && P == 1) scale_f16<kPairUpX>(bh[j]);
+                        if constexpr (j == NT - 1 && P != kHighLow) load_a(slot, i, ta);
+                        if constexpr (i == 1 && P == kHighLow) read_b(bl[j], 1, base[j] + off);
                         if constexpr (i == 1 && P == 2) read_b(bh[j], 0, base[j] + off);
-                        constexpr int piece = (M - 1) / kUnits, u = (M - 1) % kUnits;
-                        if constexpr (M >= 1 && piece < COUNT) commit_unit(nxt, std::integral_constant<int, FIRST + piece>{}, std::integral_constant<int, u>{}, ch + 1);
+                        // (x, y: the unit behind a high operand's other product; halves in units of their own where those come before its third)
+                        constexpr int x = M - (2 * NT * kHighLow + 2 * (NT - 1)), y = M - (2 * NT * kLowHigh + 1);
+                        constexpr bool a_halves = 2 * NT * kHighLow + 2 * NT < 4 * NT, b_halves = 2 * NT * kLowHigh + 3 < 4 * NT;
+                        if constexpr (x == 0 || x == 1) {
+                            scale_f16<kPairUpW, 0>(a[slot][x][0]);
+                            if constexpr (!a_halves) scale_f16<kPairUpW, 1>(a[slot][x][0]);
+                        }
+                        if constexpr (a_halves && (x == 2 || x == 3)) scale_f16<kPairUpW, 1>(a[slot][x - 2][0]);
+                        if constexpr (b_halves && y >= 1 && y <= 2 * NT) scale_f16<kPairUpX, (y - 1) & 1>(bh[(y - 1) / 2]);
+                        if constexpr (!b_halves && y >= 0 && y % 2 == 0 && y / 2 < NT) {
+                            scale_f16<kPairUpX, 0>(bh[y / 2]);
+                            scale_f16<kPairUpX, 1>(bh[y / 2]);
+                        }
+                        constexpr int piece = M / kUnits, u = M % kUnits;
+                        if constexpr (piece < COUNT) commit_unit(nxt, std::integral_constant<int, FIRST + piece>{}, std::integral_constant<int, u>{}, ch + 1);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 };
